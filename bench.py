@@ -56,7 +56,7 @@ def kernel_source_hash() -> str:
     import hashlib
     h = hashlib.sha256()
     csrc = os.path.join(ROOT, "paper_2307_14995_amd", "csrc")
-    for name in ("ltn_pass_bf16.hip", "ltn_pass_f32_mfma.hip", "ltn_bf16_tiles.h", "ltn_kernels.h", "ltn_api.hip"):
+    for name in ("ltn_pass_bf16.hip", "ltn_pass_f32.hip", "ltn_bf16_tiles.h", "ltn_kernels.h", "ltn_api.hip"):
         with open(os.path.join(csrc, name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()[:16]
@@ -112,13 +112,13 @@ def write_traffic_profile(workload: str, fetch_csv: str, write_csv: str) -> int:
     out["scale"] = {"FETCH_SIZE": round(sf, 4), "WRITE_SIZE": round(sw, 4)}
     for name in fetch:
         m = re.search(r"pass_bf16_kernel<(\d+), (\d+), (\d+)", name)
-        mf = re.search(r"pass_f32_mfma_kernel<(\d+), (\d+), (\d+)", name)
+        mf = re.search(r"pass_f32_kernel<(\d+), (\d+), (\d+)", name)
         if not (m or mf) or name not in write:
             continue
         if m:
             key = f"pass_bf16_kernel<{m.group(1)},{m.group(2)}>" + ("" if m.group(3) == "0" else f" mode {m.group(3)}")
         else:
-            key = f"pass_f32_mfma_kernel<{mf.group(1)},{mf.group(2)},{mf.group(3)}>"
+            key = f"pass_f32_kernel<{mf.group(1)},{mf.group(2)},{mf.group(3)}>"
         rd = sum(fetch[name]) / len(fetch[name]) * 1024.0 * sf
         wr = sum(write[name]) / len(write[name]) * 1024.0 * sw
         out["kernels"][key] = {"launches": len(fetch[name]), "read_bytes_per_launch": round(rd),
@@ -245,7 +245,7 @@ def main() -> int:
     tflops = {n: f * token_heads / (ms_per_step * 1e-3) / 1e12 for n, f in fl.items()}
 
     # Dominant kernel: the backward launch (all three gradients in one kernel).
-    bwd_kernel = f"pass_bf16_kernel<{w.D},{plan_b[0]}>" if w.dtype == torch.bfloat16 else f"pass_f32_mfma_kernel<{w.D},{plan_b[0]},{block}>"
+    bwd_kernel = f"pass_bf16_kernel<{w.D},{plan_b[0]}>" if w.dtype == torch.bfloat16 else f"pass_f32_kernel<{w.D},{plan_b[0]},{block}>"
     bwd_bytes = ab["bwd"] * token_heads
     achieved = bwd_bytes / (bwd_ms * 1e-3) / 1e9
     if w.dtype == torch.float32:

@@ -32,8 +32,7 @@
  *     before anything is launched.  Bt == 0 or H == 0 is a successful no-op; when
  *     Bt * H * N == 0 the token tensors are not touched and may be NULL.
  *   - Arithmetic: bf16 tensors use bf16 MFMA with fp32 accumulation and an fp32
- *     running state; fp32 tensors use fp32 arithmetic throughout (fp32 MFMA for plain
- *     passes with D in {64, 128}, fp32 multiply-adds elsewhere).  Only
+ *     running state; fp32 tensors use fp32 arithmetic throughout (fp32 MFMA).  Only
  *     non-negative powers of lambda are ever formed, so lambda = 0 and
  *     lambda = 1 are exact and strong decays cannot overflow (the failure mode
  *     Sec. 3.3 describes for the factorised form of Algorithm 1).
@@ -44,8 +43,8 @@
  *     is handled on chip; the paper's listings assume block | N).
  *     `block` is the intra-block tile length: 0 lets the library choose
  *     (ltn_attn_pick_block); bf16 supports 64; fp32 supports 16, 32 and 64
- *     with D * block <= 4096 (D = 96 counts as 128 there: its tiles are 128 wide
- *     on chip, the last columns zero).
+ *     with D * block <= 4096 (D = 96 counts as 128 there); a block of 64 fp32 tokens
+ *     is two tiles of 32 on chip.
  *   - Results are bitwise reproducible run to run for fixed arguments (no
  *     floating-point atomics).
  */

@@ -31,7 +31,7 @@ HIPCC_FLAGS = [
 # Kernels whose inline-assembly loads land in registers asynchronously (issued blocks ahead,
 # waited for with explicit vmcnt counts): a spill or a stack copy between issue and wait would
 # read stale data without any diagnostic, so such a build is refused.
-NO_SPILL = re.compile(r"pass_bf16_kernel|pass_f32_kernel|tiled_(fwd|bwd)_bf16_kernel")
+NO_SPILL = re.compile(r"pass_bf16_kernel|tiled_(fwd|bwd)_bf16_kernel")
 
 
 def sources():

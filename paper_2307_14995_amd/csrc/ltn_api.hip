@@ -51,9 +51,8 @@ size_t esize_of(ltn_dtype dtype) { return dtype == LTN_BF16 ? 2 : 4; }
 // full width 0.110 ms).  Measured on MI355X for 8..256 chains, forward and backward.
 // ltn_attn_set_debug_plan (test only) overrides the choice.
 // chain_passes = chains (x segments) x count; count = passes per chain in the launch.
-int pick_dv(long long chain_passes, int D, ltn_dtype dtype, int blk, int count = 1) {
+int pick_dv(long long chain_passes, int D, int count = 1) {
     if (D == 96) {                         // three 32-column slices, or all 96 columns in one workgroup
-        if (dtype != LTN_BF16) return 32;
         if (const int v = g_debug_dv.load(std::memory_order_relaxed)) {
             if (v == 32 || v == 96) return v;
         }
@@ -61,26 +60,17 @@ int pick_dv(long long chain_passes, int D, ltn_dtype dtype, int blk, int count =
         return (chain_passes * 3 <= 256 && ltn::xcd_ids_fit(chain_passes / count, count * 3)) ? 32 : 96;
     }
     // D = 256: the state copies of more than 64 columns do not fit the LDS
-    const int hi = (D == 256) ? 64 : D;
-    int lo = (dtype == LTN_BF16) ? 32 : (D == 256 ? 64 : D / 2);
-    // fp32 on the matrix cores: a quarter of the columns too where its kernel has them
-    if (dtype == LTN_F32 && ((D == 128 && blk == 32) || (D == 64 && blk == 64))) lo = D / 4;
+    const int lo = 32, hi = (D == 256) ? 64 : D;
     if (const int v = g_debug_dv.load(std::memory_order_relaxed)) {
         if ((v == D || v == D / 2 || v == D / 4 || v == D / 8) && v >= lo && v <= hi) return v;
     }
     int fits = 0;
     for (int dv = lo; dv <= hi; dv *= 2) {
         if (chain_passes * (D / dv) > 256) continue;
-        if (dtype != LTN_BF16 || count * (D / dv) == 1 || ltn::xcd_ids_fit(chain_passes / count, count * (D / dv))) return dv;
+        if (count * (D / dv) == 1 || ltn::xcd_ids_fit(chain_passes / count, count * (D / dv))) return dv;
         if (!fits) fits = dv;
     }
-    if (fits) return fits;
-    // More than one round even at full width.  The fp32 matrix-core kernel is bound by its MFMA
-    // and LDS latencies, and two of its half-width workgroups fit one compute unit (76 KB of LDS
-    // each), so half width runs 5-7 % faster there (measured: 1B and 7B shapes, backward); the
-    // memory-bound bf16 kernel keeps full width (fewest re-reads).
-    if (dtype == LTN_F32 && D == 128 && blk == 32) return D / 2;
-    return hi;
+    return fits ? fits : hi;               // more than one round even at full width: fewest re-reads
 }
 
 // The same rule for a pass whose value side has DC columns and whose kernels exist for
@@ -89,6 +79,97 @@ int pick_dv_range(long long chain_passes, int DC, int lo, int hi) {
     for (int dv = lo; dv <= hi; dv *= 2)
         if (chain_passes * (DC / dv) <= 256) return dv;
     return hi;
+}
+
+// Launch plan of the fp32 kernel: value columns per workgroup and segments per chain, the pair
+// with the least estimated time.  The kernel is bound by the fp32 matrix rate, so the estimate
+// counts the MFMAs a SIMD issues per block (its slots), times blocks, times rounds of 256 units:
+// a slice of dv columns costs its share of the state products plus the whole score tiles (a
+// narrower slice repeats those); a cut into segments adds the state-only sweep at full width
+// and two more launches.  kF32Launch and kF32Block are a launch and the latencies of a block in
+// units of one MFMA (32 cycles), fitted to forced plans (128 features, 64 chains x 2048 tokens:
+// 32 / 64 / 128 columns 1.9 / 3.0 / 5.0 us a block; the choice was the fastest plan, or within 8 %
+// of it, at 30 shapes of 2 .. 256 chains x 100 .. 2048 tokens, 64 .. 256 features).
+struct F32Plan { int dv, segs; long long seg_len; double t; };
+constexpr double kF32Launch = 250.0, kF32Block = 30.0;
+
+F32Plan pick_f32(long long chains, int count, long long N, int D, int DC, int blk, bool gated) {
+    if (blk > 32) blk = 32;
+    const int forced_dv = g_debug_dv.load(std::memory_order_relaxed), forced_segs = g_debug_segs.load(std::memory_order_relaxed);
+    const int ts = blk / 16;
+    const double scores = ts * (ts + 1) / 2 * (D / 4) / 4.0;                 // per SIMD, whatever the slice
+    auto slice_cost = [&](int dv) {
+        const double c = scores + dv / 16 / 4.0 * (2.0 * ts * (D / 4) + 2.0 * ts * (ts + 1)) + kF32Block;
+        return D == 96 && dv == 32 ? c + 40.0 : c;                           // four waves, one per SIMD: latencies exposed
+    };
+    const int full = DC == 256 ? 128 : DC;                                   // columns of a sweep's workgroup
+    const double sweep_cost = full / 16 / 4.0 * ts * (D / 4) + kF32Block;
+    F32Plan best = {0, 1, 0, 0.0};
+    auto consider = [&](int dv, int segs, long long len) {
+        const long long pieces = chains * count * segs, wgs = pieces * (DC / dv), blocks = ((segs > 1 ? len : N) + blk - 1) / blk;
+        double t = (double)((wgs + 255) / 256) * blocks * slice_cost(dv);
+        if (segs > 1) t += (double)((pieces * (DC / full) + 255) / 256) * blocks * sweep_cost + 2 * kF32Launch;
+        if (!best.dv || t < best.t) best = F32Plan{dv, segs, len, t};
+    };
+    int dvs[5], n_dv = 0;
+    if (gated) dvs[n_dv++] = DC;
+    else {
+        for (const int dv : {128, 96, 64, 32})
+            if (ltn::f32_has_slice(D, DC, dv, blk)) {
+                if (dv == forced_dv) {
+                    n_dv = 0;
+                    dvs[n_dv++] = dv;
+                    break;
+                }
+                dvs[n_dv++] = dv;
+            }
+    }
+    // the sweep exists for the library's own block length of each shape
+    const bool can_cut = forced_segs != 1 && N >= 2 * D && blk == (D == 256 || DC == 256 ? 16 : 32);
+    for (int i = 0; i < n_dv; ++i) {
+        if (!(forced_segs > 1 && can_cut)) consider(dvs[i], 1, 0);
+        if (!can_cut) continue;
+        const long long at_least = N / 256 > D ? 256 : D;
+        for (long long want = 2; want <= 64 && N / want >= at_least; want += want < 8 ? 1 : want / 4) {
+            long long w = forced_segs > 1 ? forced_segs : want;
+            // every segment holds a whole state in its rows: at least D tokens, the last one too
+            for (; w > 1; --w) {
+                const long long len = ((N + w - 1) / w + 63) / 64 * 64, segs = (N + len - 1) / len;
+                if (segs > 1 && len >= D && N - (segs - 1) * len >= D) {
+                    if (chains * count * segs * (DC / full) <= 1024 || forced_segs > 1) consider(dvs[i], (int)segs, len);
+                    break;
+                }
+            }
+            if (forced_segs > 1) break;
+        }
+        if (forced_segs > 1 && !best.dv) consider(dvs[i], 1, 0);
+    }
+    return best;
+}
+
+// One launch of fp32 passes of one shape, cut into segments (state-only sweep, scan, per-segment
+// pass) when the plan says so; the segments' states live in the output's rows.
+ltn_status run_f32(ltn::PassBatch& pb, int D, int DC, int blk, hipStream_t stream, bool gated = false) {
+    if (blk > 32) blk = 32;               // a block of 64 tokens is two tiles of 32 on chip
+    const F32Plan plan = pick_f32(pb.chains, pb.count, pb.N, D, DC, blk, gated);
+    if (!plan.dv) return LTN_ERR_UNSUPPORTED;
+    pb.segs = plan.segs;
+    pb.seg_len = plan.seg_len;
+    if (plan.segs > 1) {
+        float* const kv_out = pb.p[0].state_out;
+        for (int i = 0; i < pb.count; ++i) pb.p[i].seg_rows = static_cast<float*>(pb.p[i].out ? pb.p[i].out : pb.p[i].gated_out);
+        ltn::PassBatch sweep = pb;
+        sweep.state_only = 1;
+        sweep.need_last = kv_out != nullptr;
+        for (int i = 0; i < pb.count; ++i) {
+            sweep.p[i].gate = nullptr;
+            sweep.p[i].state_in = nullptr;
+        }
+        if (ltn::launch_pass_f32(sweep, D, DC == 256 ? 128 : DC, blk, stream, DC) != hipSuccess) return LTN_ERR_LAUNCH;
+        if (ltn::launch_segment_scan_rows(pb, pb.p[0].state_in, kv_out, D, stream, DC) != hipSuccess) return LTN_ERR_LAUNCH;
+        pb.p[0].state_out = nullptr;
+    }
+    return ltn::launch_pass_f32(pb, D, plan.dv, blk, stream, DC) == hipSuccess ? LTN_OK : LTN_ERR_LAUNCH;
 }
 
 ltn_status check_common(int Bt, int H, long long N, int D, int block, ltn_dtype dtype, int* blk_out) {
@@ -214,15 +295,14 @@ SegPlan pick_segments(long long chain_passes, long long N, int D, ltn_dtype dtyp
 // workgroup (slices of all D value columns).
 ltn_status run_passes(ltn::PassBatch& pb, int D, int blk, ltn_dtype dtype, void* workspace, hipStream_t stream,
                       bool full_width = false) {
+    if (dtype != LTN_BF16) return run_f32(pb, D, D, blk, stream, full_width);
     const long long chain_passes = (long long)pb.chains * pb.count;
     const SegPlan plan = pick_segments(chain_passes, pb.N, D, dtype, full_width,
                                        (pb.pairs_first && pb.count == 3) ? pb.chains : 0);
     pb.segs = 1;
     if (plan.segs == 1) {
-        const int dv = full_width ? D : pick_dv(chain_passes, D, dtype, blk, pb.count);
-        const hipError_t e = (dtype == LTN_BF16) ? ltn::launch_pass_bf16(pb, D, dv, stream)
-                                                 : ltn::launch_pass_f32(pb, D, dv, blk, stream);
-        return e == hipSuccess ? LTN_OK : LTN_ERR_LAUNCH;
+        const int dv = full_width ? D : pick_dv(chain_passes, D, pb.count);
+        return ltn::launch_pass_bf16(pb, D, dv, stream) == hipSuccess ? LTN_OK : LTN_ERR_LAUNCH;
     }
     // three launches: segment end states from zero, scan, then the pass proper per segment
     if (!workspace) return LTN_ERR_NULL;
@@ -253,7 +333,7 @@ ltn_status run_passes(ltn::PassBatch& pb, int D, int blk, ltn_dtype dtype, void*
         main.p[i].state_in = states + i * per_pass;
         main.p[i].state_out = nullptr;
     }
-    const int dv = full_width ? D : pick_dv(chain_passes * plan.segs, D, dtype, blk, pb.count);
+    const int dv = full_width ? D : pick_dv(chain_passes * plan.segs, D, pb.count);
     return ltn::launch_pass_bf16(main, D, dv, stream) == hipSuccess ? LTN_OK : LTN_ERR_LAUNCH;
 }
 
@@ -300,10 +380,16 @@ ltn_status ltn_attn_query_plan(int Bt, int H, long long N, int D, ltn_dtype dtyp
     if (Bt <= 0 || H <= 0 || N <= 0 || call < 0 || call > 2) return LTN_ERR_SHAPE;
     if (dtype != LTN_F32 && dtype != LTN_BF16) return LTN_ERR_UNSUPPORTED;
     if (D != 64 && D != 96 && D != 128 && D != 256) return LTN_ERR_UNSUPPORTED;
+    if (dtype == LTN_F32) {
+        const F32Plan f = pick_f32((long long)Bt * H, call == 1 ? 3 : 1, N, D, D, ltn_attn_pick_block(D, dtype), call == 2);
+        *segs_out = f.segs;
+        *dv_out = f.dv;
+        return LTN_OK;
+    }
     const long long chain_passes = (long long)Bt * H * (call == 1 ? 3 : 1);
     const SegPlan plan = pick_segments(chain_passes, N, D, dtype, call == 2, call == 1 ? (long long)Bt * H : 0);
     *segs_out = plan.segs;
-    *dv_out = (call == 2) ? D : pick_dv(chain_passes * plan.segs, D, dtype, ltn_attn_pick_block(D, dtype), call == 1 ? 3 : 1);
+    *dv_out = (call == 2) ? D : pick_dv(chain_passes * plan.segs, D, call == 1 ? 3 : 1);
     return LTN_OK;
 }
 
@@ -416,14 +502,25 @@ static ltn_status fwd_common(const void* q, const void* k, const void* v, const 
     // (one workgroup per chain, or per chain segment).  With few chains that can leave
     // compute units idle; when the caller wants the attention output stored anyway
     // (training), the plain forward at its usual split followed by the gate kernel on the
-    // stored output is then the faster way to the same result (measured on MI355X: below
-    // about 192 chains).
-    if (o && dtype == LTN_BF16 && chains < 192) {
+    // stored output is then the faster way to the same result (bf16, measured on MI355X: below
+    // about 192 chains).  fp32 loses nothing by storing o, so there y's own memory can hold it on
+    // the way, and whichever form is estimated faster is taken whether o is wanted or not (the
+    // gate kernel's three tensors at about 5 TB/s; 32 chains x 2048 tokens, 128 features:
+    // 86 us fused, 70 us in two steps; 8 chains x 300 tokens 58 and 28 us).
+    bool two_steps = o && chains < 192;
+    if (dtype == LTN_F32) {
+        const double slots_per_value = 3 * 4 / 5e12 * 2.4e9 / 32;
+        two_steps = pick_f32(chains, 1, N, D, D, blk, false).t + kF32Launch + (double)chains * N * D * slots_per_value <
+                    pick_f32(chains, 1, N, D, D, blk, true).t;
+    }
+    if (two_steps) {
+        void* const dst = o ? o : y;
+        pb.p[0].out = dst;
         pb.p[0].gate = nullptr;
         pb.p[0].gated_out = nullptr;
         const ltn_status s1 = run_passes(pb, D, blk, dtype, workspace, st);
         if (s1 != LTN_OK) return s1;
-        return ltn::launch_gate(o, u, nullptr, y, nullptr, eps, chains * N, D, 1, 0, st) == hipSuccess
+        return ltn::launch_gate(dst, u, nullptr, y, nullptr, eps, chains * N, D, dtype == LTN_BF16, 0, st) == hipSuccess
                    ? LTN_OK : LTN_ERR_LAUNCH;
     }
     return run_passes(pb, D, blk, dtype, workspace, st, true);
@@ -655,11 +752,7 @@ static ltn_status run_dkdv(ltn::PassBatch& pb, int DA, int DC, int blk, ltn_dtyp
     const long long chain_passes = (long long)pb.chains * pb.count;
     pb.segs = 1;
     hipError_t e;
-    if (dtype != LTN_BF16) {
-        const int lo = 64, hi = (DA == 256) ? 64 : (DC < 128 ? DC : 128);
-        e = ltn::launch_pass_f32(pb, DA, pick_dv_range(chain_passes, DC, lo, hi), blk, st, DC);
-        return e == hipSuccess ? LTN_OK : LTN_ERR_LAUNCH;
-    }
+    if (dtype != LTN_BF16) return run_f32(pb, DA, DC, blk, st);
     const int hi = dkdv_hi(DA, DC);
     const SegPlan plan = pick_segments_dkdv(chain_passes, pb.N, DA, DC, dtype);
     if (plan.segs == 1) {

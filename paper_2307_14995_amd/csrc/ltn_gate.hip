@@ -6,6 +6,7 @@
 // and its derivative.  The forward of this map is normally fused into the attention
 // forward (the gated epilogue of the pass kernels); these stand-alone kernels serve the
 // backward (which needs the stored attention output x) and callers that hold x already.
+// The forward may run in place (y = x's memory: a lane reads its piece before it writes it).
 // Streaming kernels, HBM-bound: every lane owns 16 bytes of one row, a row's lanes are
 // neighbours in one wave and reduce with cross-lane shuffles (rows of 96 features take 16 or 32
 // lanes of which 12 or 24 hold data); fp32 arithmetic.
@@ -59,8 +60,8 @@ constexpr int kThreads = 256;
 
 template <int D, bool BF16, bool BWD>
 __global__ __launch_bounds__(kThreads)
-void gate_kernel(const char* __restrict__ x, const char* __restrict__ u, const char* __restrict__ dy,
-                 char* __restrict__ o0, char* __restrict__ o1, float eps, long long rows) {
+void gate_kernel(const char* x, const char* __restrict__ u, const char* __restrict__ dy,
+                 char* o0, char* __restrict__ o1, float eps, long long rows) {
     using V = Vec<BF16>;
     constexpr int ACT = D / V::N;                 // lanes that hold a piece of the row
     constexpr int LPR = ACT <= 8 ? 8 : (ACT <= 16 ? 16 : (ACT <= 32 ? 32 : 64));   // lanes given to a row (96 features: 12 of 16, 24 of 32)

@@ -29,6 +29,9 @@ struct PassArgs {
     const void* gate;     // [chains, N, D] or nullptr
     void* gated_out;      // [chains, N, D]
     float eps;
+    // fp32 kernel, sequence-parallel form: [chains, N, DC] buffer (the output) in the first D
+    // rows of whose segments the segments' states live between the launches; nullptr otherwise
+    float* seg_rows;
 };
 
 struct PassBatch {
@@ -67,14 +70,13 @@ hipError_t launch_tiled_fwd_bf16(const void* q, const void* k, const void* v, vo
 hipError_t launch_tiled_bwd_bf16(const void* q, const void* k, const void* v, const void* d_o, void* dq, void* dk,
                                  void* dv, const float* decay, int chains, int H, long long N, int D,
                                  hipStream_t stream);
-// fp32 kernel.  D in {64,96,128,256}, block in {16,32,64}, D*block <= 4096 (D = 256: dv = 64;
-// D = 96: dv = 32, block 16 or 32).
+// fp32 MFMA kernel.  D in {64,96,128,256}, block in {16,32,64}, D*block <= 4096 (96 counts as 128),
+// the (dv, block) combinations f32_has_slice() accepts; gated: dv = D in {64,128}.  (D, DC) as for bf16.
+bool f32_has_slice(int D, int DC, int dv, int block);
 hipError_t launch_pass_f32(const PassBatch& pb, int D, int dv, int block, hipStream_t stream, int DC = 0);
-// fp32 MFMA kernel (v_mfma_f32_16x16x4_f32) for plain passes with D in {64,128}: the
-// (D, dv, block) combinations pass_f32_mfma_supports() accepts; launch_pass_f32 routes those
-// here and keeps its plain-FMA kernel for the rest (gated epilogue, unequal widths, 96, 256).
-bool pass_f32_mfma_supports(int D, int dv, int block);
-hipError_t launch_pass_f32_mfma(const PassBatch& pb, int D, int dv, int block, hipStream_t stream);
+// The scan below for fp32 passes, whose segment states live in PassArgs::seg_rows.
+hipError_t launch_segment_scan_rows(const PassBatch& pb, const float* kv_in, float* kv_out, int D, hipStream_t stream,
+                                    int DC = 0);
 // Turns the segment-local end states L[pass][chain][g] in `states` (as written by a
 // state_only launch) into the states at each segment's start, in place:
 //   S[0] = kv_in (pass 0 only) or 0,   S[g+1] = lambda^len(g) S[g] + L[g],
