@@ -159,12 +159,27 @@ def _dev(t: torch.Tensor, what: str) -> torch.Tensor:
     return t
 
 
+def _devs(names: str, *tensors) -> None:
+    """_dev for several tensors; `names` (one word each) are looked at only when one is refused."""
+    for t in tensors:
+        if not t.is_cuda or not t.is_contiguous():
+            for u, n in zip(tensors, names.split()):
+                _dev(u, n)
+
+
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
-def _stream(device) -> ctypes.c_void_p:
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+def _call(fn, device, *args) -> int:
+    """fn(*args, current stream of `device`) with `device` current.  A small call (one decode step) is
+    bound by the host: a device guard and a Stream object for every call were a quarter of its 11.5 us (8.4 without), so
+    the guard is taken only where another device is current and the stream handle is read as it is."""
+    index = device.index
+    if torch.cuda.current_device() == index:
+        return fn(*args, torch._C._cuda_getCurrentRawStream(index))
+    with torch.cuda.device(index):
+        return fn(*args, torch._C._cuda_getCurrentRawStream(index))
 
 
 def _workspace(nbytes: int, device):
@@ -174,8 +189,7 @@ def _workspace(nbytes: int, device):
 def ltn_attn_fwd(q, k, v, decay, kv_in=None, return_state=False, block=0, out=None, kv_out=None):
     """O[Bt,H,N,D] = ((Q K^T) (.) M) V, optionally continuing from / returning the fp32 state."""
     lib = load_library()
-    for t, n in ((q, "q"), (k, "k"), (v, "v"), (decay, "decay")):
-        _dev(t, n)
+    _devs("q k v decay", q, k, v, decay)
     if q.shape != k.shape or q.shape != v.shape or q.dim() != 4 or k.dtype != q.dtype or v.dtype != q.dtype:
         raise ValueError("q, k, v must be [Bt,H,N,D] tensors of one shape and dtype")
     Bt, H, N, D = q.shape
@@ -191,9 +205,8 @@ def ltn_attn_fwd(q, k, v, decay, kv_in=None, return_state=False, block=0, out=No
     code = _dtype_code(q.dtype)
     ws_bytes = int(lib.ltn_attn_workspace_bytes(Bt, H, N, D, block, code, 0))
     ws = _workspace(ws_bytes, q.device)
-    with torch.cuda.device(q.device):
-        rc = lib.ltn_attn_fwd(_ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(decay), _ptr(kv_in), _ptr(kv_out),
-                              Bt, H, N, D, int(block), code, _ptr(ws), ws_bytes, _stream(q.device))
+    rc = _call(lib.ltn_attn_fwd, q.device, _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(decay), _ptr(kv_in),
+               _ptr(kv_out), Bt, H, N, D, int(block), code, _ptr(ws), ws_bytes)
     if rc != 0:
         raise LtnError(rc, "ltn_attn_fwd")
     return (o, kv_out) if (return_state or kv_out is not None) else o
@@ -203,8 +216,7 @@ def ltn_attn_fwd_static(q, k, v, decay, out, kv_in=None, kv_out=None, block=0):
     """ltn_attn_fwd through the library's static scratch: every buffer comes from the caller,
     nothing is allocated here or in the library.  Returns `out`."""
     lib = load_library()
-    for t, n in ((q, "q"), (k, "k"), (v, "v"), (decay, "decay"), (out, "out")):
-        _dev(t, n)
+    _devs("q k v decay out", q, k, v, decay, out)
     if q.shape != k.shape or q.shape != v.shape or q.shape != out.shape or q.dim() != 4:
         raise ValueError("q, k, v, out must be [Bt,H,N,D] tensors of one shape")
     if not (q.dtype == k.dtype == v.dtype == out.dtype):
@@ -217,9 +229,8 @@ def ltn_attn_fwd_static(q, k, v, decay, out, kv_in=None, kv_out=None, block=0):
             _dev(t, n)
             if t.dtype != torch.float32 or tuple(t.shape) != (Bt, H, D, D):
                 raise ValueError(f"{n} must be fp32 [Bt,H,D,D]")
-    with torch.cuda.device(q.device):
-        rc = lib.ltn_attn_fwd_static(_ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(decay), _ptr(kv_in), _ptr(kv_out),
-                                     Bt, H, N, D, int(block), _dtype_code(q.dtype), _stream(q.device))
+    rc = _call(lib.ltn_attn_fwd_static, q.device, _ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(decay), _ptr(kv_in),
+               _ptr(kv_out), Bt, H, N, D, int(block), _dtype_code(q.dtype))
     if rc != 0:
         raise LtnError(rc, "ltn_attn_fwd_static")
     return out
@@ -229,8 +240,7 @@ def ltn_attn_fwd_gated(q, k, v, u, decay, eps=0.0, kv_in=None, return_state=Fals
                        out=None, y_out=None, kv_out=None):
     """Forward with the fused epilogue y = SRMSNorm_D(o) (.) u.  Returns (o or None, y[, kv_out])."""
     lib = load_library()
-    for t, n in ((q, "q"), (k, "k"), (v, "v"), (u, "u"), (decay, "decay")):
-        _dev(t, n)
+    _devs("q k v u decay", q, k, v, u, decay)
     if not (q.shape == k.shape == v.shape == u.shape) or q.dim() != 4:
         raise ValueError("q, k, v, u must be [Bt,H,N,D] tensors of one shape")
     if not (q.dtype == k.dtype == v.dtype == u.dtype):
@@ -249,10 +259,8 @@ def ltn_attn_fwd_gated(q, k, v, u, decay, eps=0.0, kv_in=None, return_state=Fals
     code = _dtype_code(q.dtype)
     ws_bytes = int(lib.ltn_attn_workspace_bytes(Bt, H, N, D, block, code, 2))
     ws = _workspace(ws_bytes, q.device)
-    with torch.cuda.device(q.device):
-        rc = lib.ltn_attn_fwd_gated(_ptr(q), _ptr(k), _ptr(v), _ptr(u), _ptr(o), _ptr(y), _ptr(decay),
-                                    _ptr(kv_in), _ptr(kv_out), float(eps), Bt, H, N, D, int(block), code,
-                                    _ptr(ws), ws_bytes, _stream(q.device))
+    rc = _call(lib.ltn_attn_fwd_gated, q.device, _ptr(q), _ptr(k), _ptr(v), _ptr(u), _ptr(o), _ptr(y), _ptr(decay),
+               _ptr(kv_in), _ptr(kv_out), float(eps), Bt, H, N, D, int(block), code, _ptr(ws), ws_bytes)
     if rc != 0:
         raise LtnError(rc, "ltn_attn_fwd_gated")
     return (o, y, kv_out) if (return_state or kv_out is not None) else (o, y)
@@ -273,8 +281,7 @@ def ltn_gate_fwd(x, u, eps=0.0, out=None):
     if u.shape != x.shape or u.dtype != x.dtype:
         raise ValueError("x and u must share shape and dtype")
     y = torch.empty_like(x) if out is None else _dev(out, "out")
-    with torch.cuda.device(x.device):
-        rc = lib.ltn_gate_fwd(_ptr(x), _ptr(u), _ptr(y), float(eps), rows, D, _dtype_code(x.dtype), _stream(x.device))
+    rc = _call(lib.ltn_gate_fwd, x.device, _ptr(x), _ptr(u), _ptr(y), float(eps), rows, D, _dtype_code(x.dtype))
     if rc != 0:
         raise LtnError(rc, "ltn_gate_fwd")
     return y
@@ -284,17 +291,15 @@ def ltn_gate_bwd(x, u, d_y, eps=0.0, out=None):
     """(d_x, d_u) of ltn_gate_fwd."""
     lib = load_library()
     rows, D = _rows(x, "x")
-    for t, n in ((u, "u"), (d_y, "d_y")):
-        _dev(t, n)
-        if t.shape != x.shape or t.dtype != x.dtype:
-            raise ValueError("x, u and d_y must share shape and dtype")
+    _devs("u d_y", u, d_y)
+    if not (x.shape == u.shape == d_y.shape) or not (x.dtype == u.dtype == d_y.dtype):
+        raise ValueError("x, u and d_y must share shape and dtype")
     if out is None:
         dx, du = torch.empty_like(x), torch.empty_like(x)
     else:
         dx, du = (_dev(t, "out") for t in out)
-    with torch.cuda.device(x.device):
-        rc = lib.ltn_gate_bwd(_ptr(x), _ptr(u), _ptr(d_y), _ptr(dx), _ptr(du), float(eps), rows, D,
-                              _dtype_code(x.dtype), _stream(x.device))
+    rc = _call(lib.ltn_gate_bwd, x.device, _ptr(x), _ptr(u), _ptr(d_y), _ptr(dx), _ptr(du), float(eps), rows, D,
+               _dtype_code(x.dtype))
     if rc != 0:
         raise LtnError(rc, "ltn_gate_bwd")
     return dx, du
@@ -303,8 +308,7 @@ def ltn_gate_bwd(x, u, d_y, eps=0.0, out=None):
 def ltn_attn_bwd(q, k, v, d_o, decay, block=0, out=None):
     """(dQ, dK, dV) of the forward definition; needs q, k, v, dO only."""
     lib = load_library()
-    for t, n in ((q, "q"), (k, "k"), (v, "v"), (d_o, "d_o"), (decay, "decay")):
-        _dev(t, n)
+    _devs("q k v d_o decay", q, k, v, d_o, decay)
     if not (q.shape == k.shape == v.shape == d_o.shape) or q.dim() != 4:
         raise ValueError("q, k, v, d_o must be [Bt,H,N,D] tensors of one shape")
     if not (q.dtype == k.dtype == v.dtype == d_o.dtype):
@@ -319,9 +323,8 @@ def ltn_attn_bwd(q, k, v, d_o, decay, block=0, out=None):
     code = _dtype_code(q.dtype)
     ws_bytes = int(lib.ltn_attn_workspace_bytes(Bt, H, N, D, block, code, 1))
     ws = _workspace(ws_bytes, q.device)
-    with torch.cuda.device(q.device):
-        rc = lib.ltn_attn_bwd(_ptr(q), _ptr(k), _ptr(v), _ptr(d_o), _ptr(dq), _ptr(dk), _ptr(dv), _ptr(decay),
-                              Bt, H, N, D, int(block), code, _ptr(ws), ws_bytes, _stream(q.device))
+    rc = _call(lib.ltn_attn_bwd, q.device, _ptr(q), _ptr(k), _ptr(v), _ptr(d_o), _ptr(dq), _ptr(dk), _ptr(dv),
+               _ptr(decay), Bt, H, N, D, int(block), code, _ptr(ws), ws_bytes)
     if rc != 0:
         raise LtnError(rc, "ltn_attn_bwd")
     return dq, dk, dv
@@ -330,8 +333,7 @@ def ltn_attn_bwd(q, k, v, d_o, decay, block=0, out=None):
 def ltn_attn_decode_step(q, k, v, kv, decay, out=None):
     """kv <- lambda kv + k^T v (in place); returns o = q kv.  q, k, v: [Bt,H,D]; kv: fp32 [Bt,H,D,D]."""
     lib = load_library()
-    for t, n in ((q, "q"), (k, "k"), (v, "v"), (kv, "kv"), (decay, "decay")):
-        _dev(t, n)
+    _devs("q k v kv decay", q, k, v, kv, decay)
     if not (q.shape == k.shape == v.shape) or q.dim() != 3 or not (q.dtype == k.dtype == v.dtype):
         raise ValueError("q, k, v must be [Bt,H,D] tensors of one shape and dtype")
     Bt, H, D = q.shape
@@ -340,9 +342,8 @@ def ltn_attn_decode_step(q, k, v, kv, decay, out=None):
     if decay.dtype != torch.float32 or decay.numel() != H:
         raise ValueError("decay must be fp32 [H]")
     o = torch.empty_like(q) if out is None else _dev(out, "out")
-    with torch.cuda.device(q.device):
-        rc = lib.ltn_attn_decode_step(_ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(kv), _ptr(decay),
-                                      Bt, H, D, _dtype_code(q.dtype), _stream(q.device))
+    rc = _call(lib.ltn_attn_decode_step, q.device, _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(kv), _ptr(decay), Bt, H,
+               D, _dtype_code(q.dtype))
     if rc != 0:
         raise LtnError(rc, "ltn_attn_decode_step")
     return o
@@ -351,8 +352,7 @@ def ltn_attn_decode_step(q, k, v, kv, decay, out=None):
 def ltn_attn_decode_steps(q, k, v, kv, decay, out=None):
     """S decode steps in one call: q, k, v: [Bt,H,S,D]; kv: fp32 [Bt,H,D,D] updated in place; returns o."""
     lib = load_library()
-    for t, n in ((q, "q"), (k, "k"), (v, "v"), (kv, "kv"), (decay, "decay")):
-        _dev(t, n)
+    _devs("q k v kv decay", q, k, v, kv, decay)
     if not (q.shape == k.shape == v.shape) or q.dim() != 4 or not (q.dtype == k.dtype == v.dtype):
         raise ValueError("q, k, v must be [Bt,H,S,D] tensors of one shape and dtype")
     Bt, H, S, D = q.shape
@@ -361,9 +361,8 @@ def ltn_attn_decode_steps(q, k, v, kv, decay, out=None):
     if decay.dtype != torch.float32 or decay.numel() != H:
         raise ValueError("decay must be fp32 [H]")
     o = torch.empty_like(q) if out is None else _dev(out, "out")
-    with torch.cuda.device(q.device):
-        rc = lib.ltn_attn_decode_steps(_ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(kv), _ptr(decay),
-                                       Bt, H, S, D, _dtype_code(q.dtype), _stream(q.device))
+    rc = _call(lib.ltn_attn_decode_steps, q.device, _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(kv), _ptr(decay), Bt, H,
+               S, D, _dtype_code(q.dtype))
     if rc != 0:
         raise LtnError(rc, "ltn_attn_decode_steps")
     return o
@@ -372,17 +371,15 @@ def ltn_attn_decode_steps(q, k, v, kv, decay, out=None):
 def ltn_attn_fwd_tiled(q, k, v, decay, out=None):
     """The forward output by the quadratic tile loop of App. B Algorithm 3 (comparison kernel, bf16)."""
     lib = load_library()
-    for t, n in ((q, "q"), (k, "k"), (v, "v"), (decay, "decay")):
-        _dev(t, n)
+    _devs("q k v decay", q, k, v, decay)
     if q.shape != k.shape or q.shape != v.shape or q.dim() != 4 or k.dtype != q.dtype or v.dtype != q.dtype:
         raise ValueError("q, k, v must be [Bt,H,N,D] tensors of one shape and dtype")
     Bt, H, N, D = q.shape
     if decay.dtype != torch.float32 or decay.numel() != H:
         raise ValueError("decay must be fp32 [H]")
     o = torch.empty_like(q) if out is None else _dev(out, "out")
-    with torch.cuda.device(q.device):
-        rc = lib.ltn_attn_fwd_tiled(_ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(decay), Bt, H, N, D,
-                                    _dtype_code(q.dtype), _stream(q.device))
+    rc = _call(lib.ltn_attn_fwd_tiled, q.device, _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(decay), Bt, H, N, D,
+               _dtype_code(q.dtype))
     if rc != 0:
         raise LtnError(rc, "ltn_attn_fwd_tiled")
     return o
@@ -391,8 +388,7 @@ def ltn_attn_fwd_tiled(q, k, v, decay, out=None):
 def ltn_attn_bwd_tiled(q, k, v, d_o, decay, out=None):
     """(dQ, dK, dV) by the quadratic tile loops of App. B Algorithm 4 (comparison kernel, bf16)."""
     lib = load_library()
-    for t, n in ((q, "q"), (k, "k"), (v, "v"), (d_o, "d_o"), (decay, "decay")):
-        _dev(t, n)
+    _devs("q k v d_o decay", q, k, v, d_o, decay)
     if not (q.shape == k.shape == v.shape == d_o.shape) or q.dim() != 4:
         raise ValueError("q, k, v, d_o must be [Bt,H,N,D] tensors of one shape")
     if not (q.dtype == k.dtype == v.dtype == d_o.dtype):
@@ -404,9 +400,8 @@ def ltn_attn_bwd_tiled(q, k, v, d_o, decay, out=None):
         dq, dk, dv = torch.empty_like(q), torch.empty_like(q), torch.empty_like(q)
     else:
         dq, dk, dv = (_dev(t, "out") for t in out)
-    with torch.cuda.device(q.device):
-        rc = lib.ltn_attn_bwd_tiled(_ptr(q), _ptr(k), _ptr(v), _ptr(d_o), _ptr(dq), _ptr(dk), _ptr(dv), _ptr(decay),
-                                    Bt, H, N, D, _dtype_code(q.dtype), _stream(q.device))
+    rc = _call(lib.ltn_attn_bwd_tiled, q.device, _ptr(q), _ptr(k), _ptr(v), _ptr(d_o), _ptr(dq), _ptr(dk), _ptr(dv),
+               _ptr(decay), Bt, H, N, D, _dtype_code(q.dtype))
     if rc != 0:
         raise LtnError(rc, "ltn_attn_bwd_tiled")
     return dq, dk, dv
@@ -418,9 +413,8 @@ def ltn_probe_stream_read(buf, bytes_per_workgroup, workgroups, iters, to_regist
     _dev(buf, "buf")
     if sink is None:
         sink = torch.zeros(1, dtype=torch.int32, device=buf.device)
-    with torch.cuda.device(buf.device):
-        rc = lib.ltn_probe_stream_read(_ptr(buf), buf.numel() * buf.element_size(), int(bytes_per_workgroup), int(workgroups),
-                                       int(iters), int(bool(to_registers)), _ptr(sink), _stream(buf.device))
+    rc = _call(lib.ltn_probe_stream_read, buf.device, _ptr(buf), buf.numel() * buf.element_size(),
+               int(bytes_per_workgroup), int(workgroups), int(iters), int(bool(to_registers)), _ptr(sink))
     if rc != 0:
         raise LtnError(rc, "ltn_probe_stream_read")
     return sink
@@ -450,9 +444,8 @@ def ltn_prologue_fwd(x, theta=None, act=True, pos0=0, out=None):
     y = torch.empty((Bt, H, N, W), dtype=x.dtype, device=x.device) if out is None else _dev(out, "out")
     if tuple(y.shape) != (Bt, H, N, W) or y.dtype != x.dtype:
         raise ValueError("out must be [Bt,H,N,2D] (or [Bt,H,N,D] without theta) in x's dtype")
-    with torch.cuda.device(x.device):
-        rc = lib.ltn_prologue_fwd(_ptr(x), _ptr(theta), _ptr(y), int(bool(act)), Bt, H, N, D, int(pos0),
-                                  _dtype_code(x.dtype), _stream(x.device))
+    rc = _call(lib.ltn_prologue_fwd, x.device, _ptr(x), _ptr(theta), _ptr(y), int(bool(act)), Bt, H, N, D, int(pos0),
+               _dtype_code(x.dtype))
     if rc != 0:
         raise LtnError(rc, "ltn_prologue_fwd")
     return y
@@ -474,17 +467,15 @@ def ltn_prologue_bwd(x, d_y, theta=None, act=True, pos0=0, want_dtheta=True):
     dth = torch.empty((H, D), dtype=torch.float32, device=x.device) if (theta is not None and want_dtheta) else None
     ws_bytes = int(lib.ltn_prologue_workspace_bytes(Bt, H, N, D)) if dth is not None else 0
     ws = _workspace(ws_bytes, x.device)
-    with torch.cuda.device(x.device):
-        rc = lib.ltn_prologue_bwd(_ptr(x), _ptr(theta), _ptr(d_y), _ptr(dx), _ptr(dth), int(bool(act)),
-                                  Bt, H, N, D, int(pos0), _dtype_code(x.dtype), _ptr(ws), ws_bytes, _stream(x.device))
+    rc = _call(lib.ltn_prologue_bwd, x.device, _ptr(x), _ptr(theta), _ptr(d_y), _ptr(dx), _ptr(dth), int(bool(act)),
+               Bt, H, N, D, int(pos0), _dtype_code(x.dtype), _ptr(ws), ws_bytes)
     if rc != 0:
         raise LtnError(rc, "ltn_prologue_bwd")
     return dx, dth
 
 
 def _check_dkdv(q, k, v, decay):
-    for t, n in ((q, "q"), (k, "k"), (v, "v"), (decay, "decay")):
-        _dev(t, n)
+    _devs("q k v decay", q, k, v, decay)
     if q.dim() != 4 or q.shape != k.shape or v.dim() != 4 or v.shape[:3] != q.shape[:3]:
         raise ValueError("q, k must be [Bt,H,N,Dk] and v [Bt,H,N,Dv]")
     if not (q.dtype == k.dtype == v.dtype):
@@ -509,9 +500,8 @@ def ltn_attn_fwd_dkdv(q, k, v, decay, kv_in=None, return_state=False, block=0, o
     code = _dtype_code(q.dtype)
     ws_bytes = int(lib.ltn_attn_workspace_bytes_dkdv(Bt, H, N, Dk, Dv, code, 0))
     ws = _workspace(ws_bytes, q.device)
-    with torch.cuda.device(q.device):
-        rc = lib.ltn_attn_fwd_dkdv(_ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(decay), _ptr(kv_in), _ptr(kv_out),
-                                   Bt, H, N, Dk, Dv, int(block), code, _ptr(ws), ws_bytes, _stream(q.device))
+    rc = _call(lib.ltn_attn_fwd_dkdv, q.device, _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(decay), _ptr(kv_in),
+               _ptr(kv_out), Bt, H, N, Dk, Dv, int(block), code, _ptr(ws), ws_bytes)
     if rc != 0:
         raise LtnError(rc, "ltn_attn_fwd_dkdv")
     return (o, kv_out) if (return_state or kv_out is not None) else o
@@ -528,9 +518,8 @@ def ltn_attn_bwd_dkdv(q, k, v, d_o, decay, block=0):
     code = _dtype_code(q.dtype)
     ws_bytes = int(lib.ltn_attn_workspace_bytes_dkdv(Bt, H, N, Dk, Dv, code, 1))
     ws = _workspace(ws_bytes, q.device)
-    with torch.cuda.device(q.device):
-        rc = lib.ltn_attn_bwd_dkdv(_ptr(q), _ptr(k), _ptr(v), _ptr(d_o), _ptr(dq), _ptr(dk), _ptr(dv), _ptr(decay),
-                                   Bt, H, N, Dk, Dv, int(block), code, _ptr(ws), ws_bytes, _stream(q.device))
+    rc = _call(lib.ltn_attn_bwd_dkdv, q.device, _ptr(q), _ptr(k), _ptr(v), _ptr(d_o), _ptr(dq), _ptr(dk), _ptr(dv),
+               _ptr(decay), Bt, H, N, Dk, Dv, int(block), code, _ptr(ws), ws_bytes)
     if rc != 0:
         raise LtnError(rc, "ltn_attn_bwd_dkdv")
     return dq, dk, dv
@@ -544,9 +533,8 @@ def ltn_attn_decode_steps_dkdv(q, k, v, kv, decay, out=None):
     if kv.dtype != torch.float32 or tuple(kv.shape) != (Bt, H, Dk, Dv):
         raise ValueError("kv must be fp32 [Bt,H,Dk,Dv]")
     o = torch.empty_like(v) if out is None else _dev(out, "out")
-    with torch.cuda.device(q.device):
-        rc = lib.ltn_attn_decode_steps_dkdv(_ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(kv), _ptr(decay),
-                                            Bt, H, S, Dk, Dv, _dtype_code(q.dtype), _stream(q.device))
+    rc = _call(lib.ltn_attn_decode_steps_dkdv, q.device, _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(kv), _ptr(decay),
+               Bt, H, S, Dk, Dv, _dtype_code(q.dtype))
     if rc != 0:
         raise LtnError(rc, "ltn_attn_decode_steps_dkdv")
     return o
