@@ -220,6 +220,26 @@ SegPlan cut_chain(long long N, long long want) {
     return plan;
 }
 
+// Heads of 64 and 128 features, before those rules and where segments of 512 tokens would be
+// fewer than 8: segments down to 256 tokens (about 160 in the gated pass) when the cut pays for
+// its sweep, scan and two launches.  The gated pass takes
+// it from 5 segments on: it has one full-width workgroup per chain otherwise (measured, 128
+// features: 24 chains x 2000 tokens 61.7 -> 32.0 us, 4 x 1000 31.8 -> 19.9, 32 x 3001 45.2 -> 43;
+// 32 x 512, 3 or 4 segments, would lose: 19.1 against 23.6).  The plain passes have the column
+// split to compare with, so their times are estimated, in us, from forced plans of 4 .. 40 chains x
+// 1000 .. 8000 tokens: uncut `whole` per block of 64 tokens, cut `fixed` more, `block` per block of
+// a segment and `state` per segment (its state is written, scanned and read).  128 features:
+// 8 x 4000 forward 45.5 -> 24.5 us, 24 x 4000 49.8 -> 38.3, 4 x 4000 backward 47.2 -> 28.3; 32 x 3001
+// stays whole (37.4 against 39.5); 64 features: 4 x 2000 20.0 -> 14.3.
+struct CutCost { double whole, fixed, block, state; long long least; };
+bool cut_pays(long long chain_passes, long long N, long long want, int D, bool bwd) {
+    const CutCost c = D == 128 ? CutCost{0.66, 10.5, bwd ? 1.7 : 1.3, 0.05, bwd ? 6 : 7}
+                               : CutCost{0.48, bwd ? 6.5 : 7.5, bwd ? 1.0 : 0.8, 0.02, 6};
+    if (want < c.least) return false;
+    const long long blocks = (N + 63) / 64, seg_blocks = (N / want + 63) / 64;
+    return c.whole * blocks > c.fixed + c.block * seg_blocks + c.state * chain_passes * want;
+}
+
 // paired_chains: the number of chains when the passes are the three of a backward (whose
 // (dV, dK) workgroups sit side by side on one XCD at full width), else 0.
 SegPlan pick_segments(long long chain_passes, long long N, int D, ltn_dtype dtype, bool full_width = false,
@@ -230,9 +250,13 @@ SegPlan pick_segments(long long chain_passes, long long N, int D, ltn_dtype dtyp
     const long long per_seg = (D == 256) ? 4 : ((D == 96 && !full_width) ? 3 : 1);
     long long want = 256 / (per_seg * chain_passes);
     bool whole_rows = per_seg == 1;        // one workgroup per chain, pass and segment
+    const long long finer = N / (full_width ? 160 : 256) < want ? N / (full_width ? 160 : 256) : want;
     // a pass that must keep full-width slices has no column split to fall back on
     if (want > N / 512) want = N / 512;       // segments of at least 512 tokens
-    if (full_width) {
+    if ((D == 64 || D == 128) && want < 8 && finer > want &&
+        (full_width ? finer >= 5 : cut_pays(chain_passes, N, finer, D, paired_chains > 0))) {
+        want = finer;
+    } else if (full_width) {
         // from 4 ways on; 2 or 3 ways when the segments stay at least 2048 tokens long (not for 96
         // features, whose state-only sweep runs three workgroups per segment; for 128 features
         // only when that leaves an eighth of the compute units free: at 128 chains the second
