@@ -264,6 +264,11 @@ SegPlan pick_segments(long long chain_passes, long long N, int D, ltn_dtype dtyp
         const bool few_ok = D != 96 && want >= 2 && N / want >= 2048 && (D == 64 || chain_passes * want <= 224);
         if (want < kMinSegsFullWidth && !few_ok) want = 1;
     } else if (per_seg > 1) {
+        // from 5 segments of at least 256 tokens on where 512-token ones would be fewer than 8
+        // (measured, 2 .. 16 chains x 1000 .. 4000 tokens: 256 features forward 4 x 2000 39.3 -> 31.3
+        // us, backward 2 x 2000 42.2 -> 34.6; 96 features 8 x 2000 27.2 -> 20.2 and 2 x 2000
+        // 25.4 -> 19.6; at 1000 tokens, 3 segments, the cut loses)
+        if (want < 8 && finer >= 5 && finer > want) want = finer;
         if (want < 3) want = 1;
         if (D == 96) {
             // Workgroup ids deal (chain, segment) pairs to the 8 XCDs of 32 compute units and keep
@@ -757,7 +762,13 @@ static SegPlan pick_segments_dkdv(long long chain_passes, long long N, int DA, i
     if (dtype != LTN_BF16 || chain_passes <= 0 || N <= 64) return plan;
     const long long per_seg = DC / dkdv_hi(DA, DC);
     long long want = 256 / (per_seg * chain_passes);
+    const long long finer = N / 256 < want ? N / 256 : want;
     if (want > N / 512) want = N / 512;       // segments of at least 512 tokens (measured: 2 .. 32 chains, N = 2048 .. 16384)
+    // where those are fewer than 8, segments of at least 256 tokens from 5 on, or 4 from 1536 tokens on
+    // (measured, 2 .. 32 chains x 500 .. 4000 tokens: (256, 128) forward 4 x 2000 46.9 -> 26.5 us,
+    // 32 x 2000 52.9 -> 45.9, backward 8 x 2000 76.8 -> 60; (128, 64) forward 16 x 2000 25.5 -> 20,
+    // backward 4 x 2000 46.4 -> 32.5; 16 x 1000, 3 or 4 segments, loses)
+    if (want < 8 && finer > want && (finer >= 5 || (finer == 4 && N >= 1536))) want = finer;
     if (want < kMinSegsFullWidth) want = 1;
     if (const int v = g_debug_segs.load(std::memory_order_relaxed)) want = v;
     if (want <= 1) return plan;

@@ -14,7 +14,7 @@ BF = torch.bfloat16
 
 
 def test_short_segment_plans_fit_one_round_and_the_scratch():
-    for D in (64, 128):
+    for D in (64, 96, 128, 256):
         for call, passes in ((0, 1), (1, 3), (2, 1)):
             for chains in (1, 2, 3, 5, 8, 12, 20, 31, 40, 51, 64):
                 for N in (65, 319, 640, 799, 800, 1000, 1537, 2000, 3001, 4097, 9999, 32768):
@@ -26,7 +26,7 @@ def test_short_segment_plans_fit_one_round_and_the_scratch():
 
 
 CASES = [("gated", 1, 3, 800, 128), ("gated", 1, 4, 1001, 64), ("gated", 2, 3, 1087, 128), ("fwd", 1, 4, 1999, 128),
-         ("fwd", 2, 4, 2049, 64), ("bwd", 1, 4, 2050, 64), ("bwd", 1, 3, 3011, 128)]
+         ("fwd", 2, 4, 2049, 64), ("bwd", 1, 4, 2050, 64), ("bwd", 1, 3, 3011, 128), ("fwd", 1, 2, 1345, 256), ("bwd", 1, 2, 1999, 96)]
 
 
 @pytest.mark.gpu
@@ -54,3 +54,33 @@ def test_short_segments_match_the_oracle(call, Bt, H, N, D):
         ref = ref / torch.sqrt((ref * ref).mean(-1, keepdim=True) + 1e-6) * g.double()
         check("y", y, ref.numpy(), TOL[BF])
     check("kv", kv, kv_ref, TOL[BF])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("Dk,N", [(256, 1537), (256, 1290), (128, 2001)])
+def test_short_segments_of_unequal_widths(Dk, N):
+    Bt, H, Dv = 1, 3, Dk // 2
+    assert ltn.ltn_attn_workspace_bytes_dkdv(Bt, H, N, Dk, Dv, BF, 0) > 0
+    q, k, v = synth.make_qkv_dkdv(Bt, H, N, Dk, Dv, BF, 950 + N)
+    g = synth.make_do(Bt, H, N, Dv, BF, 950 + N)
+    decay = mixed_decay(H)
+    o, kv = ltn.ltn_attn_fwd_dkdv(*gpu(q, k, v, decay), return_state=True)
+    o_ref, kv_ref = orc.fwd_recurrent_dkdv(q, k, v, decay, return_state=True)
+    check("O", o, o_ref, TOL[BF])
+    check("kv", kv, kv_ref, TOL[BF])
+    for n, x, r in zip(("dQ", "dK", "dV"), ltn.ltn_attn_bwd_dkdv(*gpu(q, k, v, g, decay)),
+                       orc.bwd_recurrent_dkdv(q, k, v, g, decay)):
+        check(n, x, r, TOL[BF])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("H,N", [(3, 1), (3, 512), (70, 511), (3, 1000)])
+def test_fused_gated_forward_that_stores_o(H, N):
+    # heads of 64 features: short, or cut into segments
+    q, k, v = synth.make_qkv(1, H, N, 64, BF, 970 + N)
+    u = synth.make_gate(1, H, N, 64, BF, 970 + N)
+    decay = mixed_decay(H)
+    o_ref, y_ref = orc.fwd_gated(q, k, v, u, decay, eps=1e-6)
+    o, y = ltn.ltn_attn_fwd_gated(*gpu(q, k, v, u, decay), eps=1e-6)
+    check("O", o, o_ref, TOL[BF])
+    check("Y", y, y_ref, TOL[BF])
