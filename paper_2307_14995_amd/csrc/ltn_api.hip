@@ -536,7 +536,13 @@ static ltn_status fwd_common(const void* q, const void* k, const void* v, const 
     // the way, and whichever form is estimated faster is taken whether o is wanted or not (the
     // gate kernel's three tensors at about 5 TB/s; 32 chains x 2048 tokens, 128 features:
     // 86 us fused, 70 us in two steps; 8 chains x 300 tokens 58 and 28 us).
+    // (64 features: a full-width workgroup is a quarter of the work, and the fused form is the faster
+    // one where it is cut into 3 or more segments -- 32 x 2048 tokens 26.5 us in two steps, 21.5
+    // fused; 64 x 8192 123 and 104 -- or at most 512 tokens long, where the second launch counts:
+    // 15.5 and 13; uncut and longer the split pays again, 80 x 2048 36 and 48.)
     bool two_steps = o && chains < 192;
+    if (two_steps && D == 64 && dtype == LTN_BF16)
+        two_steps = N > 512 && pick_segments(chains, N, D, dtype, true).segs < 3;
     if (dtype == LTN_F32) {
         const double slots_per_value = 3 * 4 / 5e12 * 2.4e9 / 32;
         two_steps = pick_f32(chains, 1, N, D, D, blk, false).t + kF32Launch + (double)chains * N * D * slots_per_value <
