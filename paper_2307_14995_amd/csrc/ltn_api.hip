@@ -351,10 +351,11 @@ ltn_status run_passes(ltn::PassBatch& pb, int D, int blk, ltn_dtype dtype, void*
         sweep.p[i].state_in = nullptr;
         sweep.p[i].state_out = states + i * per_pass;
     }
-    // one full-width workgroup per segment; two of 64 columns while those fit one round of compute
-    // units (forward of 8 chains x 8000 tokens 32.5 -> 29.5 us, 2 x 8192 24.9 -> 22.3, gated 4 x 2000
-    // 21.7 -> 20.4; same values)
-    const int sweep_dv = D == 256 ? 64 : D == 96 ? 32 : D == 128 && chain_passes * plan.segs * 2 <= 256 ? 64 : D;
+    // one full-width workgroup per segment; narrower slices while those fit one round of compute
+    // units (128 features, full width, 64 and 32 columns: forward of 2 chains x 8192 tokens 24.9, 22.4
+    // and 21.9 us, 8 x 8000 32.5 and 29.7; 64 features, 64 and 32 columns: 17.7 and 17.1; same values)
+    int sweep_dv = D == 256 ? 64 : D == 96 ? 32 : D;
+    while ((D == 64 || D == 128) && sweep_dv > 32 && chain_passes * plan.segs * (2 * D / sweep_dv) <= 256) sweep_dv /= 2;
     if (ltn::launch_pass_bf16(sweep, D, sweep_dv, stream) != hipSuccess) return LTN_ERR_LAUNCH;
     if (ltn::launch_segment_scan(states, kv_in, kv_out, pb.decay, pb.count, pb.chains, pb.H, plan.segs,
                                  plan.seg_len, pb.N, D, stream) != hipSuccess)
