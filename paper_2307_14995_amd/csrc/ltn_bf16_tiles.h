@@ -78,14 +78,21 @@ __device__ __forceinline__ void static_for(const F& f) { static_for_impl(f, std:
 
 // Unpadded row-major LDS tile of COLS bf16 columns whose 16-byte chunks are XOR-swizzled
 // with the row: chunk c of row r lives at chunk position c ^ key(r).  The key is built for the
-// lanes that meet in one LDS cycle: (i) 8 consecutive rows put a given 32-byte chunk pair on 8
-// different bank groups (what 32 lanes of a transpose read touch); (ii) a 16-byte row read (lane
-// 16 g + i: row i, chunk c + g) is served 16 lanes at a time as lanes {0-3, 12-15, 20-23, 24-27}
-// and {4-11, 16-19, 28-31} of each half wave, so rows {0-3, 12-15} of a chunk meet rows 4-11 of its
-// neighbour, and the key's lowest bit has to differ between those two sets.  Measured on all
-// units: row reads 243 bytes per cycle, transpose reads 217; with the lowest bit taken from row
-// bit 3 (distinct positions for lanes 0-15, which do not meet) row reads ran at 128.  Adding a
-// multiple of 16 rows does not change the key, so row-block offsets stay compile-time immediates.
+// lanes that meet in one LDS cycle (conditions checked at compile time below):
+//   (i)   a transpose read's 32 lanes: 8 consecutive rows (from a multiple of 8) of one 32-byte
+//         chunk pair on different banks;
+//   (ii)  a 16-byte row read (lane 16 g + i: row i, chunk c + g) is served 16 lanes at a time as
+//         lanes {0-3, 12-15, 20-23, 24-27} and {4-11, 16-19, 28-31} of each half wave: rows
+//         {0-3, 12-15} of a chunk and rows 4-11 of its neighbour on different banks;
+//   (iii) an 8-byte state-copy write's 32 lanes: all 16 rows of one chunk on different banks.
+// (i) fixes the chunk pair within 8 rows, (iii) gives the two rows that share a pair different
+// halves, and (ii) then wants those two rows on the same side of its split: row r + 8 of the 256
+// bytes takes the pair of row r ^ 4.  Row reads run at 243 bytes per cycle and unit, transpose
+// reads at 217; without (ii), pairs in the same order for rows 8-15, row reads ran at 128, and
+// without (iii), the half from row bit 2, heads of 64 features lost 3-5 % (forward of 48 chains x
+// 2000 tokens 21.8 us against 20.7, backward of 64 x 3500 44.7 against 43.3; wider heads the same
+// either way).  Adding a multiple of 16 rows does not change the key,
+// so row-block offsets stay compile-time immediates.
 template <int COLS>
 struct Swz {
     static constexpr int RB = COLS * 2;        // bytes per row
@@ -96,11 +103,34 @@ struct Swz {
     static constexpr int NI = BYTES / 1024;    // wave-wide direct loads per tile
     static_assert(COLS == 256 || COLS == 128 || COLS == 64 || COLS == 32, "tile widths");
     __host__ __device__ static constexpr int key(int r) {
-        // q: index of the row's 256-byte group member
-        return (((r / RPB) % (KC / 2)) << 1) | (((r / RPB) / (KC / 4)) & 1);
+        const int q = r / RPB;                 // index of the row's 256-byte group
+        const int half = (q / (KC / 2)) & 1;
+        return (((q % (KC / 2)) ^ (half * (KC / 4))) << 1) | half;
     }
     __device__ static __forceinline__ int off(int r, int c) { return r * RB + ((c ^ key(r)) << 4); }
+    // the 16-byte bank group of chunk c of row r, as one of 16 bits
+    static constexpr unsigned bank(int r, int c) { return 1u << ((r * CPR + (c ^ key(r))) & 15); }
+    static constexpr bool spreads() {
+        for (int c = 0; c < CPR; c += 2) {
+            unsigned row_read[2] = {0, 0}, write[2] = {0, 0};
+            for (int r = 0; r < 16; ++r) {
+                const bool outer = r < 4 || r >= 12;
+                row_read[!outer] |= bank(r, c);
+                row_read[outer] |= bank(r, c + 1);
+                write[0] |= bank(r, c);
+                write[1] |= bank(r, c + 1);
+            }
+            for (int r0 = 0; r0 < 16; r0 += 8) {
+                unsigned pair = 0;
+                for (int r = r0; r < r0 + 8; ++r) pair |= bank(r, c) | bank(r, c + 1);
+                if (pair != 0xffff) return false;
+            }
+            if (row_read[0] != 0xffff || row_read[1] != 0xffff || write[0] != 0xffff || write[1] != 0xffff) return false;
+        }
+        return true;
+    }
 };
+static_assert(Swz<32>::spreads() && Swz<64>::spreads() && Swz<128>::spreads() && Swz<256>::spreads(), "bank conflicts");
 
 // Direct global -> LDS fetch of one 64-row tile of COLS columns by four waves (u = 0..3),
 // every lane with a full 64-bit address (the quadratic comparison kernels; the pass kernel uses

@@ -42,10 +42,11 @@
 //     stores themselves.  In the register-fed layout (256 features) all four output waves
 //     share the loads; in the gated pass the gate values are loaded from assembly too, at
 //     the end of the block before the one that uses them, and counted with the tile loads.  LDS
-//     rows are unpadded; the 16-byte chunk index is XOR-swizzled with the row so that row reads
-//     and transpose reads (ds_read_b64_tr_b16, for operands needed "down the token axis") spread
-//     over the banks.  Rows past the end of a short last block are fetched from a small buffer of zeros; tile columns past the end of a tensor's rows (heads of 96
-//     features in 128-wide tiles) are cleared once and masked out of every load.
+//     rows are unpadded; the 16-byte chunk index is XOR-swizzled with the row so that row reads,
+//     transpose reads (ds_read_b64_tr_b16, for operands needed "down the token axis") and the
+//     state-copy writes spread over the banks.  Rows past the end of a short last block are
+//     fetched from a small buffer of zeros; tile columns past the end of a tensor's rows (heads
+//     of 96 features in 128-wide tiles) are cleared once and masked out of every load.
 //   * wave role and strip are compile-time constants of the code each wave runs, so
 //     causal tile skipping costs no branches inside a block.
 // Only non-negative powers of lambda are formed.
