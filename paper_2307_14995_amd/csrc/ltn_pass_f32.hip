@@ -148,7 +148,7 @@ void pass_f32_kernel(const PassBatch pb, const int nsplit, const int xcd_ids) {
     v4f ra[SO ? 1 : C::LA], rb[C::LA], rc[C::LC];
     // A block's rows are addressed from the lowest of them, a wave-uniform base, with 32-bit lane
     // offsets that are the same for every full block.  Rows past the end of a short last block
-    // re-read its last row: a masked score or a zero decay factor multiplies whatever they hold.
+    // re-read its last row (every address stays inside the segment) and are cleared in LDS.
     const int T = (int)((N + B - 1) / B), tail = (int)(N - (long long)(T - 1) * B);
     auto row_at = [&](int r, int len) { return rev ? len - 1 - r : r; };
     auto first_low = [&](int len) { return rev ? N - len : 0; };
@@ -209,6 +209,22 @@ void pass_f32_kernel(const PassBatch pb, const int nsplit, const int xcd_ids) {
             if (C::EC % C::THREADS == 0 || e < C::EC) *(v4f*)&stage[C::C_OFF + r * PC + 4 * c4] = rc[i];
         }
     };
+    // Rows past the end of a short last block, cleared by the threads that have just stored them: a
+    // zero decay factor times an infinity of the row they repeat would be NaN in the state and in
+    // that row's own output.  (Of A they reach only outputs that are not stored.)
+    auto clear_tail = [&](float* stage) {
+        const v4f z = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < C::LA; ++i) {
+            const int e = tid + i * C::THREADS, r = e / (D / 4), c4 = e % (D / 4);
+            if (e < C::EA && r >= tail) *(v4f*)&stage[C::B_OFF + r * PA + 4 * c4] = z;
+        }
+#pragma unroll
+        for (int i = 0; i < C::LC; ++i) {
+            const int e = tid + i * C::THREADS, r = e / (DV / 4), c4 = e % (DV / 4);
+            if (e < C::EC && r >= tail) *(v4f*)&stage[C::C_OFF + r * PC + 4 * c4] = z;
+        }
+    };
 
     {
         const int len0 = T == 1 ? tail : B;
@@ -219,6 +235,7 @@ void pass_f32_kernel(const PassBatch pb, const int nsplit, const int xcd_ids) {
     }
     fetch();
     commit(smem);
+    if (T == 1 && tail != B) clear_tail(smem);
     advance(1);
     __syncthreads();
 
@@ -401,7 +418,10 @@ void pass_f32_kernel(const PassBatch pb, const int nsplit, const int xcd_ids) {
                 __builtin_amdgcn_sched_group_barrier(0x008, MR, 0);
             }
         }
-        if (more) commit(smem + (odd ^ 1) * C::STAGE);
+        if (more) {
+            commit(smem + (odd ^ 1) * C::STAGE);
+            if (i + 2 == T && tail != B) clear_tail(smem + (odd ^ 1) * C::STAGE);
+        }
         __syncthreads();
     };
     for (int i = 0; i < T; i += 2) {
