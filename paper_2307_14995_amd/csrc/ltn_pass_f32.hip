@@ -257,7 +257,7 @@ void pass_f32_kernel(const PassBatch pb, const int nsplit, const int xcd_ids) {
     // score units of this wave (causal tile: key tile kt <= token strip s; feature range ks): operand
     // and result offsets, and the decay factors of the lane's four entries
     constexpr int UNITS = C::TRI * KS, UPW = (UNITS + NW - 1) / NW, KC = D / 16 / KS;
-    int ua[UPW], ub[UPW], up[UPW];
+    int ua[UPW], ub[UPW], up[UPW], ue[UPW];
     v4f um[UPW];
     float qscale[TS];
     unsigned oo[TS];                       // byte offsets of this lane's output pieces in a full block
@@ -271,12 +271,9 @@ void pass_f32_kernel(const PassBatch pb, const int nsplit, const int xcd_ids) {
             ua[n] = C::A_OFF + (16 * s + i16) * PA + 16 * KC * ks + 4 * g;
             ub[n] = C::B_OFF + (16 * kt + i16) * PA + 16 * KC * ks + 4 * g;
             up[n] = C::P_OFF + (ks * B + 16 * s + i16) * PP + 16 * kt + 4 * g;
-            const int e = 16 * (s - kt) + i16 - 4 * g;             // token - key at j = 0
+            ue[n] = 16 * (s - kt) + i16 - 4 * g;                   // token - key at j = 0
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const float v = pw[max(e - j, 0)];
-                um[n][j] = e >= j ? v : 0.0f;
-            }
+            for (int j = 0; j < 4; ++j) um[n][j] = pw[max(ue[n] - j, 0)];
         }
 #pragma unroll
         for (int s = 0; s < TS; ++s) {
@@ -367,7 +364,11 @@ void pass_f32_kernel(const PassBatch pb, const int nsplit, const int xcd_ids) {
                     p0 = mfma4(b4[2], a4[2], p0);
                     p1 = mfma4(b4[3], a4[3], p1);
                 }
-                *(v4f*)&smem[up[n] + odd * C::P_SIZE] = (p0 + p1) * um[n];
+                p0 = (p0 + p1) * um[n];
+                // a select, not a zero factor: an infinite score with a later key stays masked
+#pragma unroll
+                for (int j = 0; j < 4; ++j) p0[j] = ue[n] >= j ? p0[j] : 0.0f;
+                *(v4f*)&smem[up[n] + odd * C::P_SIZE] = p0;
             }
 #pragma unroll
             for (int s = 0; s < TS; ++s) oe[odd][s] = v4f{0.f, 0.f, 0.f, 0.f};

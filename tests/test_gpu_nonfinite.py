@@ -85,3 +85,21 @@ def test_infinite_query_in_the_first_token_of_the_reversed_pass(Dk, Dv, dv, N):
         fn = ltn.ltn_attn_bwd if Dk == Dv else ltn.ltn_attn_bwd_dkdv
         dv_got = fn(*gpu(q, k, v, g, DECAY))[2].cpu().numpy()
     assert (dv_got[..., 0, :] == np.inf * np.sign(k.numpy()[..., 0, 5, None] * g.numpy()[..., 0, :])).all()
+
+
+@pytest.mark.parametrize("Dk,Dv,dv,N", SHAPES)
+def test_infinite_key_or_query_leaves_rows_masked_from_it_alone(Dk, Dv, dv, N):
+    q, k, v, g = inputs(Dk, Dv, N)
+    o_ref, _ = oracle(Dk, Dv, q, k, v)
+    dv_ref = (orc.bwd_recurrent if Dk == Dv else orc.bwd_recurrent_dkdv)(q, k, v, g, DECAY)[2]
+    t = 10                                 # inside a 16-token tile, neither first nor last
+    ki, qi = k.clone(), q.clone()
+    ki[..., t, 5] = float("inf")
+    qi[..., t, 5] = float("inf")
+    o, _ = forward(Dk, Dv, dv, q, ki, v)
+    assert close(o[..., :t, :], o_ref[..., :t, :])
+    assert (o[..., t, :] == np.inf * np.sign(q.numpy()[..., t, 5, None] * v.numpy()[..., t, :])).all()
+    with force_plan(dv, 1):
+        fn = ltn.ltn_attn_bwd if Dk == Dv else ltn.ltn_attn_bwd_dkdv
+        dv_got = fn(*gpu(qi, k, v, g, DECAY))[2].cpu().numpy()
+    assert close(dv_got[..., t + 1:, :], dv_ref[..., t + 1:, :])
