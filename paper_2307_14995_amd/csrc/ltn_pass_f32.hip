@@ -503,14 +503,22 @@ void segment_scan_rows_kernel(const ScanArgs s, const float* __restrict__ kv_in,
 #pragma unroll
         for (int i = 0; i < 8; ++i)
             l[i] = (g0 + i + 1 < segs || (g0 + i + 1 == segs && final_state)) ? *at(g0 + i) : v4f{0.f, 0.f, 0.f, 0.f};
+        // keep_inf as in the bf16 passes' scan
+        auto walk = [&](auto keep_inf) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int g = g0 + i;
-            if (g < segs) {
-                *at(g) = run;
-                run = run * (g + 1 < segs ? lam_full : decay_pow(lam, (int)last_n)) + l[i];
+            for (int i = 0; i < 8; ++i) {
+                const int g = g0 + i;
+                if (g < segs) {
+                    *at(g) = run;
+                    const float f = g + 1 < segs ? lam_full : decay_pow(lam, (int)last_n);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        run[j] = run[j] * (decltype(keep_inf)::value && __builtin_isinf(run[j]) ? 1.f : f) + l[i][j];
+                }
             }
-        }
+        };
+        if (lam > 0.f && lam_full == 0.f) walk(std::true_type{});
+        else walk(std::false_type{});
     }
     if (final_state) *(v4f*)(kv_out + so) = run;
 }

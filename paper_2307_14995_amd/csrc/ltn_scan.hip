@@ -8,6 +8,7 @@
 //
 // The states array [count][chains][segs][D*D] is rewritten in place from L[.] to S[.] (the
 // state at each segment's start); the state after the last segment goes to kv_out.
+#include <type_traits>
 #include "ltn_kernels.h"
 
 namespace ltn {
@@ -37,6 +38,7 @@ void segment_scan_kernel(float* states, const float* __restrict__ kv_in, float* 
     const int have = kv_out ? segs : segs - 1;
     f32x4 run = (pass == 0 && kv_in) ? *(const f32x4*)(kv_in + (size_t)chain * DD + e) : f32x4{0.f, 0.f, 0.f, 0.f};
     float lam_full = 0.f, lam_last = 0.f;
+    bool flushed = false;                // lambda^len is zero although lambda is not
     for (int g0 = 0; g0 < segs; g0 += kAhead) {
         f32x4 local[kAhead];
 #pragma unroll
@@ -46,15 +48,24 @@ void segment_scan_kernel(float* states, const float* __restrict__ kv_in, float* 
             const float lam = decay[chain % H];
             lam_full = decay_pow(lam, seg_len);
             lam_last = final_state ? decay_pow(lam, (int)(N - (long long)(segs - 1) * seg_len)) : 0.f;
+            flushed = lam > 0.f && lam_full == 0.f;
         }
+        // keep_inf: an infinite entry stays infinite, as it does under the whole-chain pass's one
+        // factor per block, instead of becoming 0 x Inf.  A loop of its own: tested per segment it
+        // cost 0.5 us of an 8 us scan.
+        auto walk = [&](auto keep_inf) {
 #pragma unroll
-        for (int i = 0; i < kAhead; ++i) {
-            if (g0 + i >= segs) break;
-            *(f32x4*)(s + (size_t)(g0 + i) * DD) = run;
-            const float f = g0 + i + 1 < segs ? lam_full : lam_last;
+            for (int i = 0; i < kAhead; ++i) {
+                if (g0 + i >= segs) break;
+                *(f32x4*)(s + (size_t)(g0 + i) * DD) = run;
+                const float f = g0 + i + 1 < segs ? lam_full : lam_last;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) run[j] = fmaf(f, run[j], local[i][j]);
-        }
+                for (int j = 0; j < 4; ++j)
+                    run[j] = fmaf(decltype(keep_inf)::value && __builtin_isinf(run[j]) ? 1.f : f, run[j], local[i][j]);
+            }
+        };
+        if (flushed) walk(std::true_type{});
+        else walk(std::false_type{});
     }
     if (final_state) *(f32x4*)(kv_out + (size_t)chain * DD + e) = run;
 }

@@ -103,3 +103,25 @@ def test_infinite_key_or_query_leaves_rows_masked_from_it_alone(Dk, Dv, dv, N):
         fn = ltn.ltn_attn_bwd if Dk == Dv else ltn.ltn_attn_bwd_dkdv
         dv_got = fn(*gpu(qi, k, v, g, DECAY))[2].cpu().numpy()
     assert close(dv_got[..., t + 1:, :], dv_ref[..., t + 1:, :])
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("Dk,Dv", [(64, 64), (128, 64)])
+def test_infinite_state_survives_segments_whose_decay_underflows(Dk, Dv, dtype):
+    """0.5^256 is zero in fp32: cut or whole, a state entry that is infinite stays so."""
+    N, H1 = 3 * 256 + 40, 2
+    decay = torch.tensor([0.5, 0.0])
+    q, k, v = (synth.make_qkv(1, H1, N, Dk, dtype, 77) if Dk == Dv else synth.make_qkv_dkdv(1, H1, N, Dk, Dv, dtype, 77))
+    k[..., 3, 5] = float("inf")
+    fn = ltn.ltn_attn_fwd if Dk == Dv else ltn.ltn_attn_fwd_dkdv
+    got = {}
+    for segs in (1, 3):
+        with force_plan(0, segs):
+            got[segs] = [x.float().cpu() for x in fn(*gpu(q, k, v, decay), return_state=True)]
+    for whole, cut in zip(got[1], got[3]):
+        assert torch.equal(whole[:, 0].isnan(), cut[:, 0].isnan())
+        assert torch.equal(whole[:, 0].isinf(), cut[:, 0].isinf())
+        bad = ~whole[:, 0].isfinite()
+        assert bad.any() and torch.equal(whole[:, 0][bad].sign().nan_to_num(), cut[:, 0][bad].sign().nan_to_num())
+    # lambda = 0: the state of the last token alone, which is finite; 0 x Inf in either form before it
+    assert torch.equal(got[1][1][:, 1].isnan(), got[3][1][:, 1].isnan())
