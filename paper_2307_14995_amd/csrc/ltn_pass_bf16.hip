@@ -116,6 +116,26 @@ __device__ __forceinline__ void wait_vm8(u32x4 (&r)[8]) {
                  : "n"(N) : "memory");
 }
 
+// The same load by the lanes of `mask` only (wave-uniform, possibly none; all 64 lanes are active at
+// the call), from p + OFF: the other lanes keep what they hold.  EXEC is put back inside the statement.
+template <int OFF>
+__device__ __forceinline__ void gload16_masked(u32x4& r, const char* p, unsigned long long mask) {
+    unsigned long long saved;
+    asm volatile("s_mov_b64 %1, exec\n\ts_mov_b64 exec, %3\n\tglobal_load_dwordx4 %0, %2, off offset:%4\n\ts_mov_b64 exec, %1"
+                 : "+v"(r), "=&s"(saved) : "v"(p), "s"(mask), "n"(OFF) : "memory");
+}
+// Wait for the gate values of the gated pass: G = 2, 3 or 4 such registers.
+template <int N, int G>
+__device__ __forceinline__ void wait_gate(u32x4* r) {
+    static_assert(G >= 2 && G <= 4, "widths of the gated pass");
+    if constexpr (G == 2)
+        asm volatile("s_waitcnt vmcnt(%2)" : "+v"(r[0]), "+v"(r[1]) : "n"(N) : "memory");
+    else if constexpr (G == 3)
+        asm volatile("s_waitcnt vmcnt(%3)" : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]) : "n"(N) : "memory");
+    else
+        asm volatile("s_waitcnt vmcnt(%4)" : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]) : "n"(N) : "memory");
+}
+
 // lambda^n for 0 <= n <= 64 without one fp64 powering loop per constant: every lane powers
 // once (lambda^lane, and lambda^64), the rest are cross-lane reads.  Same values as
 // decay_pow(lam, n), bit for bit.  All 64 lanes must call get() together.
@@ -280,9 +300,7 @@ __device__ __forceinline__ void output_pass(const char* btile, const char* ctile
             ss = __uint_as_float(t[0]) + __uint_as_float(t[1]);
         }
         const float rstd = 1.0f / sqrtf(ss * (1.0f / DROW) + eps);
-        wait_dma<GWAIT>();                 // the gate values have arrived
-#pragma unroll
-        for (int p = 0; p < NT / 2; ++p) asm volatile("" : "+v"(uq[p]));
+        wait_gate<GWAIT, NT / 2>(uq);      // the gate values have arrived
 #pragma unroll
         for (int p = 0; p < NT / 2; ++p) {
             float x[8];
@@ -531,11 +549,13 @@ __device__ __forceinline__ void pass_output_wave(const Chain& ch, char* smem, un
     u32x4 uq[GATED ? G : 1];
 #pragma unroll
     for (int p = 0; p < (GATED ? G : 1); ++p) uq[p] = u32x4{0, 0, 0, 0};
-    auto load_gate = [&](int b) {          // gate values of this lane's token in block b
-        const bool ok = (16 * W + i16) < ((b + 1 == ch.T) ? ch.last_valid : kBlock);
-        const char* p0 = pu + (long long)b * step;
-#pragma unroll
-        for (int p = 0; p < G; ++p) gload16(uq[p], ok ? p0 + 64 * p : (const char*)kZeros);
+    // Gate values of this lane's token in block b (b = 0, 1, 2, ... in turn), by the lanes whose
+    // token exists: none past the last block.
+    const unsigned long long last_rows = __ballot(16 * W + i16 < ch.last_valid);
+    auto load_gate = [&](int b) {
+        const unsigned long long rows = b + 1 < ch.T ? ~0ull : (b < ch.T ? last_rows : 0ull);
+        static_for<G>([&](auto p) { gload16_masked<64 * decltype(p)::value>(uq[decltype(p)::value], pu, rows); });
+        pu += step;
     };
     if constexpr (GATED) load_gate(0);
 
@@ -559,17 +579,18 @@ __device__ __forceinline__ void pass_output_wave(const Chain& ch, char* smem, un
                                             smem + C::P_SB + (blk & 1) * C::SBYTES, Af, k, ro,
                                             po ? po + bo : nullptr, more || row_ok,
                                             uq, GATED ? py + bo : nullptr, ch.eps);
+        // The next block's gate values: a whole block ahead of their use, in the registers
+        // this block's values have just left (and, like every such load, on every path).  Issued at
+        // the start of the block that uses them they arrived after its products were done: 2.3 us
+        // a block of 128 features against 1.35 without the gate (32 chains; now 1.75).
+        if constexpr (GATED) load_gate(blk + 1);
         if (more) {
-            // The next block's gate values: a whole block ahead of their use, in the registers
-            // this block's values have just left.  Issued at the start of the block that uses
-            // them they arrived after its products were done: 2.3 us a block of 128 features
-            // against 1.35 without the gate (32 chains; now 1.75).
-            if constexpr (GATED) load_gate(blk + 1);
             wait_next(blk);
             __syncthreads();
         }
         stage = (stage + 1 == C::PST) ? 0 : stage + 1;
     }
+    if constexpr (GATED) wait_gate<0, G>(uq);   // the last prefetch was never consumed: retire it before its registers die
     if constexpr (ISSUER) wait_dma<0>();   // nothing may land in LDS after this workgroup is gone
 }
 
