@@ -220,24 +220,40 @@ SegPlan cut_chain(long long N, long long want) {
     return plan;
 }
 
-// Heads of 64 and 128 features, before those rules and where segments of 512 tokens would be
-// fewer than 8: segments down to 256 tokens (about 160 in the gated pass) when the cut pays for
-// its sweep, scan and two launches.  The gated pass takes
-// it from 5 segments on: it has one full-width workgroup per chain otherwise (measured, 128
-// features: 24 chains x 2000 tokens 61.7 -> 32.0 us, 4 x 1000 31.8 -> 19.9, 32 x 3001 45.2 -> 43;
-// 32 x 512, 3 or 4 segments, would lose: 19.1 against 23.6).  The plain passes have the column
-// split to compare with, so their times are estimated, in us, from forced plans of 4 .. 40 chains x
-// 1000 .. 8000 tokens: uncut `whole` per block of 64 tokens, cut `fixed` more, `block` per block of
-// a segment and `state` per segment (its state is written, scanned and read).  128 features:
-// 8 x 4000 forward 45.5 -> 24.5 us, 24 x 4000 49.8 -> 38.3, 4 x 4000 backward 47.2 -> 28.3; 32 x 3001
-// stays whole (37.4 against 39.5); 64 features: 4 x 2000 20.0 -> 14.3.
-struct CutCost { double whole, fixed, block, state; long long least; };
-bool cut_pays(long long chain_passes, long long N, long long want, int D, bool bwd) {
-    const CutCost c = D == 128 ? CutCost{0.66, 10.5, bwd ? 1.7 : 1.3, 0.05, bwd ? 6 : 7}
-                               : CutCost{0.48, bwd ? 6.5 : 7.5, bwd ? 1.0 : 0.8, 0.02, 6};
-    if (want < c.least) return false;
-    const long long blocks = (N + 63) / 64, seg_blocks = (N / want + 63) / 64;
-    return c.whole * blocks > c.fixed + c.block * seg_blocks + c.state * chain_passes * want;
+// Estimated time, in us, of a bf16 pass of DA query/key and DC value features under a plan, for
+// sequences that the rules above cut fewer than 8 ways.  Whole chains: a start and `whole` a block of
+// 64 tokens.  Cut: the sweep's and the scan's launches more, `block` per block of a segment (as cut_chain
+// rounds it; sweep and pass), and per segment its state, written, scanned and read, at about
+// 4 TB/s; and no less than the time in which the binding issues three launches and allocates the
+// scratch.  Fitted to forced plans, 1 .. 64 chains x 520 .. 4095 tokens, every width, forward, backward
+// and gated (mean error 2-5 % a width).
+struct BlockCost { double whole, block; };
+BlockCost block_cost(int DA, int DC, bool gated) {
+    if (gated) return DA == 64 ? BlockCost{0.91, 1.10} : BlockCost{1.69, 2.1};
+    if (DA == 64) return BlockCost{0.48, DC == 128 ? 0.96 : 0.67};
+    if (DA == 96) return BlockCost{0.70, 1.05};
+    if (DA == 128) return BlockCost{0.66, DC == 256 ? 1.55 : 1.3};
+    return BlockCost{1.38, 2.05};
+}
+double plan_time(const SegPlan& plan, long long chain_passes, long long N, int DA, int DC, bool gated, bool bwd = false) {
+    constexpr double kStart = 4.5, kCut = 7.5, kStateElement = 4.3e-6, kIssue = 16.2, kIssueBwd = 19.7;
+    const BlockCost c = block_cost(DA, DC, gated);
+    if (plan.segs == 1) return kStart + c.whole * ((N + 63) / 64);
+    const double state = kStateElement * (DA == 96 ? 128 : DA) * (DC == 96 ? 128 : DC);
+    const double t = kStart + kCut + c.block * (plan.seg_len / 64) + state * chain_passes * plan.segs;
+    const double issue = bwd ? kIssueBwd : kIssue;
+    return t < issue ? issue : t;
+}
+
+// Shorter segments than those rules allow (`finer` of them, down to 256 tokens, about 160 in the gated
+// pass): where they are estimated 3 % faster than the plan the rules give, cut or whole.  Over the
+// forced plans above (1700 shapes where the two differ) this takes 0.845 of the rules' time on
+// average; it loses more than 2 % at ten shapes, 7 % at most.  Without the state's and the issue's
+// terms it lost 5-34 % at 64 chains x 1537 .. 2000 tokens of (128, 64), at 40 .. 51 gated chains x 800 and
+// at backwards of 1 .. 4 chains x 1537 of 64 features.
+bool finer_pays(long long finer, long long want, long long chain_passes, long long N, int DA, int DC, bool gated, bool bwd = false) {
+    return plan_time(cut_chain(N, finer), chain_passes, N, DA, DC, gated, bwd) <
+           0.97 * plan_time(cut_chain(N, want), chain_passes, N, DA, DC, gated, bwd);
 }
 
 // paired_chains: the number of chains when the passes are the three of a backward (whose
@@ -250,13 +266,17 @@ SegPlan pick_segments(long long chain_passes, long long N, int D, ltn_dtype dtyp
     const long long per_seg = (D == 256) ? 4 : ((D == 96 && !full_width) ? 3 : 1);
     long long want = 256 / (per_seg * chain_passes);
     bool whole_rows = per_seg == 1;        // one workgroup per chain, pass and segment
-    const long long finer = N / (full_width ? 160 : 256) < want ? N / (full_width ? 160 : 256) : want;
+    const bool bwd = paired_chains > 0;
+    long long finer = N / (full_width ? 160 : 256) < want ? N / (full_width ? 160 : 256) : want;
+    if (D == 96 && !full_width)               // an XCD's share of three-slice segments, as below
+        while (finer > 1 && (chain_passes * finer + 7) / 8 * 3 > 32) --finer;
     // a pass that must keep full-width slices has no column split to fall back on
     if (want > N / 512) want = N / 512;       // segments of at least 512 tokens
-    if ((D == 64 || D == 128) && want < 8 && finer > want &&
-        (full_width ? finer >= 5 : cut_pays(chain_passes, N, finer, D, paired_chains > 0))) {
-        want = finer;
-    } else if (full_width) {
+    // finer cuts: from 5 segments on (6 and 7 where a whole chain splits its columns four ways), not for
+    // the gated pass of 96 features (three workgroups per segment in its sweep)
+    const long long least = full_width || per_seg > 1 ? 5 : (D == 128 && !bwd ? 7 : 6);
+    const bool try_finer = want < 8 && finer > want && finer >= least && !(D == 96 && full_width);
+    if (full_width) {
         // from 4 ways on; 2 or 3 ways when the segments stay at least 2048 tokens long (not for 96
         // features, whose state-only sweep runs three workgroups per segment; for 128 features
         // only when that leaves an eighth of the compute units free: at 128 chains the second
@@ -264,11 +284,6 @@ SegPlan pick_segments(long long chain_passes, long long N, int D, ltn_dtype dtyp
         const bool few_ok = D != 96 && want >= 2 && N / want >= 2048 && (D == 64 || chain_passes * want <= 224);
         if (want < kMinSegsFullWidth && !few_ok) want = 1;
     } else if (per_seg > 1) {
-        // from 5 segments of at least 256 tokens on where 512-token ones would be fewer than 8
-        // (measured, 2 .. 16 chains x 1000 .. 4000 tokens: 256 features forward 4 x 2000 39.3 -> 31.3
-        // us, backward 2 x 2000 42.2 -> 34.6; 96 features 8 x 2000 27.2 -> 20.2 and 2 x 2000
-        // 25.4 -> 19.6; at 1000 tokens, 3 segments, the cut loses)
-        if (want < 8 && finer >= 5 && finer > want) want = finer;
         if (want < 3) want = 1;
         if (D == 96) {
             // Workgroup ids deal (chain, segment) pairs to the 8 XCDs of 32 compute units and keep
@@ -303,6 +318,7 @@ SegPlan pick_segments(long long chain_passes, long long N, int D, ltn_dtype dtyp
         const bool four = want == 4 && paired_chains > 0 && (paired_chains * 4) % 8 == 0 && N / want >= 2 * few_len;
         if (!few && !four) want = 1;
     }
+    if (try_finer && !(D == 96 && whole_rows) && finer_pays(finer, want, chain_passes, N, D, D, full_width, bwd)) want = finer;
     if (paired_chains > 0 && want >= 6 && whole_rows) {
         // The backward's workgroup ids pair a chain's (dV, dK) passes on one XCD only when
         // chains x segments is a multiple of 8: up to a quarter fewer segments for that
@@ -775,21 +791,11 @@ static SegPlan pick_segments_dkdv(long long chain_passes, long long N, int DA, i
     long long want = 256 / (per_seg * chain_passes);
     const long long finer = N / 256 < want ? N / 256 : want;
     if (want > N / 512) want = N / 512;       // segments of at least 512 tokens (measured: 2 .. 32 chains, N = 2048 .. 16384)
-    // where those are fewer than 8, segments of at least 256 tokens from 5 on, or 4 from 1536 tokens on
-    // (measured, 2 .. 32 chains x 500 .. 4000 tokens: (256, 128) forward 4 x 2000 46.9 -> 26.5 us,
-    // 32 x 2000 52.9 -> 45.9, backward 8 x 2000 76.8 -> 60; (128, 64) forward 16 x 2000 25.5 -> 20,
-    // backward 4 x 2000 46.4 -> 32.5; 16 x 1000, 3 or 4 segments, loses)
-    if (want < 8 && finer > want && (finer >= 5 || (finer == 4 && N >= 1536))) want = finer;
+    const bool try_finer = want < 8 && finer > want && finer >= 4;
     if (want < kMinSegsFullWidth) want = 1;
+    if (try_finer && finer_pays(finer, want, chain_passes, N, DA, DC, false)) want = finer;
     if (const int v = g_debug_segs.load(std::memory_order_relaxed)) want = v;
-    if (want <= 1) return plan;
-    long long len = (N + want - 1) / want;
-    len = (len + 63) / 64 * 64;
-    const long long segs = (N + len - 1) / len;
-    if (segs <= 1 || segs > 0x7fff) return plan;
-    plan.segs = (int)segs;
-    plan.seg_len = len;
-    return plan;
+    return cut_chain(N, want);
 }
 
 // One launch of `pb` (passes of one shape): a, b with DA features, c and out with DC; cut into
