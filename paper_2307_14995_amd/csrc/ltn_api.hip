@@ -558,12 +558,20 @@ static ltn_status fwd_common(const void* q, const void* k, const void* v, const 
     // gate kernel's three tensors at about 5 TB/s; 32 chains x 2048 tokens, 128 features:
     // 86 us fused, 70 us in two steps; 8 chains x 300 tokens 58 and 28 us).
     // (64 features: a full-width workgroup is a quarter of the work, and the fused form is the faster
-    // one where it is cut into 3 or more segments -- 32 x 2048 tokens 26.5 us in two steps, 21.5
-    // fused; 64 x 8192 123 and 104 -- or at most 512 tokens long, where the second launch counts:
-    // 15.5 and 13; uncut and longer the split pays again, 80 x 2048 36 and 48.)
+    // one where it is at most 512 tokens long, where the second launch counts -- 15.5 us in two steps,
+    // 13 fused -- or cut into 3 or more segments and estimated faster: 32 x 2048 tokens 26.5 and
+    // 21.5, 64 x 8192 123 and 104, but 8 x 800 14.6 and 17.5; uncut and longer the split pays
+    // again, 80 x 2048 36 and 48.  The gate kernel streams three tensors at 5 TB/s behind 3 us; two
+    // launches and the call's allocations take 14.6 us to issue.)
     bool two_steps = o && chains < 192;
-    if (two_steps && D == 64 && dtype == LTN_BF16)
-        two_steps = N > 512 && pick_segments(chains, N, D, dtype, true).segs < 3;
+    if (two_steps && D == 64 && dtype == LTN_BF16 && N <= 512) two_steps = false;
+    else if (two_steps && D == 64 && dtype == LTN_BF16) {
+        const SegPlan fused = pick_segments(chains, N, D, dtype, true), plain = pick_segments(chains, N, D, dtype);
+        const double gate_us = 3.0 + chains * N * D * (3 * 2 / 5e6);
+        double two_us = plan_time(plain, chains, N, D, D, false) + gate_us;
+        if (two_us < 14.6) two_us = 14.6;
+        two_steps = fused.segs < 3 || plan_time(fused, chains, N, D, D, true) + 1.5 >= two_us;
+    }
     if (dtype == LTN_F32) {
         const double slots_per_value = 3 * 4 / 5e12 * 2.4e9 / 32;
         two_steps = pick_f32(chains, 1, N, D, D, blk, false).t + kF32Launch + (double)chains * N * D * slots_per_value <
