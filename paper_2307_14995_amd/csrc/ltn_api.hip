@@ -89,9 +89,13 @@ int pick_dv_range(long long chain_passes, int DC, int lo, int hi) {
 // and two more launches.  kF32Launch and kF32Block are a launch and the latencies of a block in
 // units of one MFMA (32 cycles), fitted to forced plans (128 features, 64 chains x 2048 tokens:
 // 32 / 64 / 128 columns 1.9 / 3.0 / 5.0 us a block; the choice was the fastest plan, or within 8 %
-// of it, at 30 shapes of 2 .. 256 chains x 100 .. 2048 tokens, 64 .. 256 features).
+// of it, at 30 shapes of 2 .. 256 chains x 100 .. 2048 tokens, 64 .. 256 features).  The gated pass adds
+// its epilogue, kF32Gate a block per 64 columns (6.6 us a block of 128), and, as it has only one width
+// and so is cut where plain passes take narrower slices, kF32State per element of the segments' states
+// (96 chains x 512 tokens, 64 features, cut 8 ways: 44 us, 32 in two steps; in the plain passes'
+// estimate that term chose worse: 64 x 700 forward 29 -> 33 us).
 struct F32Plan { int dv, segs; long long seg_len; double t; };
-constexpr double kF32Launch = 250.0, kF32Block = 30.0;
+constexpr double kF32Launch = 250.0, kF32Block = 30.0, kF32Gate = 40.0, kF32State = 2e-4;
 
 F32Plan pick_f32(long long chains, int count, long long N, int D, int DC, int blk, bool gated) {
     if (blk > 32) blk = 32;
@@ -99,7 +103,8 @@ F32Plan pick_f32(long long chains, int count, long long N, int D, int DC, int bl
     const int ts = blk / 16;
     const double scores = ts * (ts + 1) / 2 * (D / 4) / 4.0;                 // per SIMD, whatever the slice
     auto slice_cost = [&](int dv) {
-        const double c = scores + dv / 16 / 4.0 * (2.0 * ts * (D / 4) + 2.0 * ts * (ts + 1)) + kF32Block;
+        const double c = scores + dv / 16 / 4.0 * (2.0 * ts * (D / 4) + 2.0 * ts * (ts + 1)) + kF32Block +
+                         (gated ? kF32Gate * dv / 64 : 0.0);
         return D == 96 && dv == 32 ? c + 40.0 : c;                           // four waves, one per SIMD: latencies exposed
     };
     const int full = DC == 256 ? 128 : DC;                                   // columns of a sweep's workgroup
@@ -109,6 +114,7 @@ F32Plan pick_f32(long long chains, int count, long long N, int D, int DC, int bl
         const long long pieces = chains * count * segs, wgs = pieces * (DC / dv), blocks = ((segs > 1 ? len : N) + blk - 1) / blk;
         double t = (double)((wgs + 255) / 256) * blocks * slice_cost(dv);
         if (segs > 1) t += (double)((pieces * (DC / full) + 255) / 256) * blocks * sweep_cost + 2 * kF32Launch;
+        if (segs > 1 && gated) t += kF32State * D * DC * pieces;
         if (!best.dv || t < best.t) best = F32Plan{dv, segs, len, t};
     };
     int dvs[5], n_dv = 0;
@@ -554,9 +560,10 @@ static ltn_status fwd_common(const void* q, const void* k, const void* v, const 
     // (training), the plain forward at its usual split followed by the gate kernel on the
     // stored output is then the faster way to the same result (bf16, measured on MI355X: below
     // about 192 chains).  fp32 loses nothing by storing o, so there y's own memory can hold it on
-    // the way, and whichever form is estimated faster is taken whether o is wanted or not (the
-    // gate kernel's three tensors at about 5 TB/s; 32 chains x 2048 tokens, 128 features:
-    // 86 us fused, 70 us in two steps; 8 chains x 300 tokens 58 and 28 us).
+    // the way, and two steps are taken, whether o is wanted or not, where they are estimated 3 % faster
+    // (the gate kernel's three tensors at about 5 TB/s, two launches no faster than they are issued).
+    // Measured fused and in two steps, 128 features: 8 chains x 300 tokens 59 and 26 us, 96 x 512 82
+    // and 65, 128 x 1000 155 and 135, but 32 x 2048 86 and 96.
     // (64 features: a full-width workgroup is a quarter of the work, and the fused form is the faster
     // one where it is at most 512 tokens long, where the second launch counts -- 15.5 us in two steps,
     // 13 fused -- or cut into 3 or more segments and estimated faster: 32 x 2048 tokens 26.5 and
@@ -573,9 +580,11 @@ static ltn_status fwd_common(const void* q, const void* k, const void* v, const 
         two_steps = fused.segs < 3 || plan_time(fused, chains, N, D, D, true) + 1.5 >= two_us;
     }
     if (dtype == LTN_F32) {
-        const double slots_per_value = 3 * 4 / 5e12 * 2.4e9 / 32;
-        two_steps = pick_f32(chains, 1, N, D, D, blk, false).t + kF32Launch + (double)chains * N * D * slots_per_value <
-                    pick_f32(chains, 1, N, D, D, blk, true).t;
+        constexpr double kSlotsPerValue = 3 * 4 / 5e12 * 2.4e9 / 32;
+        const double issue = o ? 850.0 : 700.0;            // one tensor less to allocate without o
+        double two = pick_f32(chains, 1, N, D, D, blk, false).t + kF32Launch + (double)chains * N * D * kSlotsPerValue;
+        if (two < issue) two = issue;
+        two_steps = two < 0.97 * pick_f32(chains, 1, N, D, D, blk, true).t;
     }
     if (two_steps) {
         void* const dst = o ? o : y;
