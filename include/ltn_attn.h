@@ -334,8 +334,10 @@ ltn_status ltn_attn_decode_steps_dkdv(const void* q, const void* k, const void* 
 int ltn_attn_pick_block(int D, ltn_dtype dtype);
 
 /* The launch plan the library takes for these arguments (call as in
- * ltn_attn_workspace_bytes): value columns per workgroup in *dv, segments per chain in
- * *segs (1 = whole chains).  For reports that need to name the kernel variant that ran. */
+ * ltn_attn_workspace_bytes; block 0): value columns per workgroup in *dv, segments per chain in
+ * *segs (1 = whole chains).  call = 2 is the gated forward without `o` (for the widths that need
+ * `o`, with it); where it runs in two steps, the plan is that of its plain forward.  For reports
+ * that need to name the kernel variant that ran. */
 ltn_status ltn_attn_query_plan(int Bt, int H, long long N, int D, ltn_dtype dtype, int call,
                                int* dv, int* segs);
 

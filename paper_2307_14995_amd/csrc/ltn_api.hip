@@ -342,6 +342,44 @@ SegPlan pick_segments(long long chain_passes, long long N, int D, ltn_dtype dtyp
     return cut_chain(N, want);
 }
 
+// How the gated forward runs: fused, or as the plain forward followed by the gate kernel on its
+// stored output (store_o: the caller wants that output).  256 features (and 96 in fp32): no kernel
+// holds a complete output row of these widths in one workgroup.
+//
+// The fused epilogue needs complete output rows in one workgroup, i.e. full-width slices
+// (one workgroup per chain, or per chain segment).  With few chains that can leave
+// compute units idle; when the caller wants the attention output stored anyway
+// (training), the plain forward at its usual split followed by the gate kernel on the
+// stored output is then the faster way to the same result (bf16, measured on MI355X: below
+// about 192 chains).  fp32 loses nothing by storing o, so there y's own memory can hold it on
+// the way, and two steps are taken, whether o is wanted or not, where they are estimated 3 % faster
+// (the gate kernel's three tensors at about 5 TB/s, two launches no faster than they are issued).
+// Measured fused and in two steps, 128 features: 8 chains x 300 tokens 59 and 26 us, 96 x 512 82
+// and 65, 128 x 1000 155 and 135, but 32 x 2048 86 and 96.
+// (64 features: a full-width workgroup is a quarter of the work, and the fused form is the faster
+// one where it is at most 512 tokens long, where the second launch counts -- 15.5 us in two steps,
+// 13 fused -- or cut into 3 or more segments and estimated faster: 32 x 2048 tokens 26.5 and
+// 21.5, 64 x 8192 123 and 104, but 8 x 800 14.6 and 17.5; uncut and longer the split pays
+// again, 80 x 2048 36 and 48.  The gate kernel streams three tensors at 5 TB/s behind 3 us; two
+// launches and the call's allocations take 14.6 us to issue.)
+bool gated_in_two_steps(long long chains, long long N, int D, ltn_dtype dtype, int blk, bool store_o) {
+    if (D == 256 || (D == 96 && dtype != LTN_BF16)) return true;
+    if (dtype == LTN_F32) {
+        constexpr double kSlotsPerValue = 3 * 4 / 5e12 * 2.4e9 / 32;
+        const double issue = store_o ? 850.0 : 700.0;      // one tensor less to allocate without o
+        double two = pick_f32(chains, 1, N, D, D, blk, false).t + kF32Launch + (double)chains * N * D * kSlotsPerValue;
+        if (two < issue) two = issue;
+        return two < 0.97 * pick_f32(chains, 1, N, D, D, blk, true).t;
+    }
+    if (!store_o || chains >= 192) return false;
+    if (D != 64) return true;
+    if (N <= 512) return false;
+    const SegPlan fused = pick_segments(chains, N, D, dtype, true), plain = pick_segments(chains, N, D, dtype);
+    double two_us = plan_time(plain, chains, N, D, D, false) + 3.0 + chains * N * D * (3 * 2 / 5e6);
+    if (two_us < 14.6) two_us = 14.6;
+    return fused.segs < 3 || plan_time(fused, chains, N, D, D, true) + 1.5 >= two_us;
+}
+
 // full_width: the pass carries the gated epilogue, which needs complete output rows in one
 // workgroup (slices of all D value columns).
 ltn_status run_passes(ltn::PassBatch& pb, int D, int blk, ltn_dtype dtype, void* workspace, hipStream_t stream,
@@ -436,16 +474,18 @@ ltn_status ltn_attn_query_plan(int Bt, int H, long long N, int D, ltn_dtype dtyp
     if (Bt <= 0 || H <= 0 || N <= 0 || call < 0 || call > 2) return LTN_ERR_SHAPE;
     if (dtype != LTN_F32 && dtype != LTN_BF16) return LTN_ERR_UNSUPPORTED;
     if (D != 64 && D != 96 && D != 128 && D != 256) return LTN_ERR_UNSUPPORTED;
+    const long long chains = (long long)Bt * H;
+    const int count = call == 1 ? 3 : 1, blk = ltn_attn_pick_block(D, dtype);
+    const bool fused = call == 2 && !gated_in_two_steps(chains, N, D, dtype, blk, false);
     if (dtype == LTN_F32) {
-        const F32Plan f = pick_f32((long long)Bt * H, call == 1 ? 3 : 1, N, D, D, ltn_attn_pick_block(D, dtype), call == 2);
+        const F32Plan f = pick_f32(chains, count, N, D, D, blk, fused);
         *segs_out = f.segs;
         *dv_out = f.dv;
         return LTN_OK;
     }
-    const long long chain_passes = (long long)Bt * H * (call == 1 ? 3 : 1);
-    const SegPlan plan = pick_segments(chain_passes, N, D, dtype, call == 2, call == 1 ? (long long)Bt * H : 0);
+    const SegPlan plan = pick_segments(chains * count, N, D, dtype, fused, call == 1 ? chains : 0);
     *segs_out = plan.segs;
-    *dv_out = (call == 2) ? D : pick_dv(chain_passes * plan.segs, D, call == 1 ? 3 : 1);
+    *dv_out = fused ? D : pick_dv(chains * count * plan.segs, D, count);
     return LTN_OK;
 }
 
@@ -546,46 +586,7 @@ static ltn_status fwd_common(const void* q, const void* k, const void* v, const 
     pb.N = N;
     pb.p[0] = ltn::PassArgs{q, k, v, o, kv_in, kv_out, 0, gated ? u : nullptr, gated ? y : nullptr, eps};
     if (!gated) return run_passes(pb, D, blk, dtype, workspace, st);
-    if (unfused_only) {
-        pb.p[0].gate = nullptr;
-        pb.p[0].gated_out = nullptr;
-        const ltn_status s1 = run_passes(pb, D, blk, dtype, workspace, st);
-        if (s1 != LTN_OK) return s1;
-        return ltn::launch_gate(o, u, nullptr, y, nullptr, eps, chains * N, D, dtype == LTN_BF16, 0, st) == hipSuccess
-                   ? LTN_OK : LTN_ERR_LAUNCH;
-    }
-    // The fused epilogue needs complete output rows in one workgroup, i.e. full-width slices
-    // (one workgroup per chain, or per chain segment).  With few chains that can leave
-    // compute units idle; when the caller wants the attention output stored anyway
-    // (training), the plain forward at its usual split followed by the gate kernel on the
-    // stored output is then the faster way to the same result (bf16, measured on MI355X: below
-    // about 192 chains).  fp32 loses nothing by storing o, so there y's own memory can hold it on
-    // the way, and two steps are taken, whether o is wanted or not, where they are estimated 3 % faster
-    // (the gate kernel's three tensors at about 5 TB/s, two launches no faster than they are issued).
-    // Measured fused and in two steps, 128 features: 8 chains x 300 tokens 59 and 26 us, 96 x 512 82
-    // and 65, 128 x 1000 155 and 135, but 32 x 2048 86 and 96.
-    // (64 features: a full-width workgroup is a quarter of the work, and the fused form is the faster
-    // one where it is at most 512 tokens long, where the second launch counts -- 15.5 us in two steps,
-    // 13 fused -- or cut into 3 or more segments and estimated faster: 32 x 2048 tokens 26.5 and
-    // 21.5, 64 x 8192 123 and 104, but 8 x 800 14.6 and 17.5; uncut and longer the split pays
-    // again, 80 x 2048 36 and 48.  The gate kernel streams three tensors at 5 TB/s behind 3 us; two
-    // launches and the call's allocations take 14.6 us to issue.)
-    bool two_steps = o && chains < 192;
-    if (two_steps && D == 64 && dtype == LTN_BF16 && N <= 512) two_steps = false;
-    else if (two_steps && D == 64 && dtype == LTN_BF16) {
-        const SegPlan fused = pick_segments(chains, N, D, dtype, true), plain = pick_segments(chains, N, D, dtype);
-        const double gate_us = 3.0 + chains * N * D * (3 * 2 / 5e6);
-        double two_us = plan_time(plain, chains, N, D, D, false) + gate_us;
-        if (two_us < 14.6) two_us = 14.6;
-        two_steps = fused.segs < 3 || plan_time(fused, chains, N, D, D, true) + 1.5 >= two_us;
-    }
-    if (dtype == LTN_F32) {
-        constexpr double kSlotsPerValue = 3 * 4 / 5e12 * 2.4e9 / 32;
-        const double issue = o ? 850.0 : 700.0;            // one tensor less to allocate without o
-        double two = pick_f32(chains, 1, N, D, D, blk, false).t + kF32Launch + (double)chains * N * D * kSlotsPerValue;
-        if (two < issue) two = issue;
-        two_steps = two < 0.97 * pick_f32(chains, 1, N, D, D, blk, true).t;
-    }
+    const bool two_steps = gated_in_two_steps(chains, N, D, dtype, blk, o != nullptr);
     if (two_steps) {
         void* const dst = o ? o : y;
         pb.p[0].out = dst;

@@ -443,3 +443,15 @@ def test_bench_refuses_more_than_one_gpu():
                        capture_output=True, text=True, timeout=120)
     assert r.returncode == 2
     assert "one GPU" in r.stderr and r.stdout.strip() == ""
+
+
+def test_query_plan_names_the_gated_plan_that_runs():
+    import torch
+    F32, BF = torch.float32, torch.bfloat16
+    for dtype, D in ((BF, 256), (F32, 256), (F32, 96)):      # no fused form: the plain forward's plan
+        for H, N in ((2, 100), (3, 1345), (4, 4096), (96, 1999)):
+            assert ltn.ltn_attn_query_plan(1, H, N, D, dtype, 2) == ltn.ltn_attn_query_plan(1, H, N, D, dtype, 0)
+    assert ltn.ltn_attn_query_plan(1, 8, 300, 128, F32, 2) == ltn.ltn_attn_query_plan(1, 8, 300, 128, F32, 0)   # in two steps
+    assert ltn.ltn_attn_query_plan(1, 8, 300, 128, F32, 2)[0] < 128
+    assert ltn.ltn_attn_query_plan(4, 8, 2048, 128, F32, 2) == (128, 8)                                       # fused
+    assert ltn.ltn_attn_query_plan(1, 24, 1000, 128, BF, 2)[0] == 128
