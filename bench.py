@@ -45,6 +45,20 @@ def flops_per_token_head(D: int, B: int, plan_fwd=(0, 1), plan_bwd=(0, 1)):
     }
 
 
+def f32_block(block: int) -> int:
+    """Tokens of a tile of the fp32 kernel: a block of 64 is two tiles of 32 on chip."""
+    return min(block, 32)
+
+
+def f32_issued_flops_per_token_head(D: int, block: int, plan, passes: int) -> float:
+    """FLOPs the fp32 kernel issues: per pass, causal 16-token score tiles ((B/16+1)/2 of B/16 a strip,
+    recomputed per value-column slice), the same share of P C, 4 D^2 of state products, and 2 D^2 more in
+    the state-only sweep of chains cut into segments.  plan = (value columns per workgroup, segments)."""
+    dv, segs = plan
+    causal = (f32_block(block) / 16 + 1) / 2 * 16
+    return passes * (2 * causal * D * (D // dv) + 2 * causal * D + (4 if segs == 1 else 6) * D * D)
+
+
 def algorithmic_bytes_per_token_head(D: int, esize: int):
     """Ideal HBM traffic: fwd reads Q,K,V writes O; bwd reads Q,K,V,dO writes dQ,dK,dV."""
     return {"fwd": 4 * D * esize, "bwd": 7 * D * esize}
@@ -112,13 +126,15 @@ def write_traffic_profile(workload: str, fetch_csv: str, write_csv: str) -> int:
     out["scale"] = {"FETCH_SIZE": round(sf, 4), "WRITE_SIZE": round(sw, 4)}
     for name in fetch:
         m = re.search(r"pass_bf16_kernel<(\d+), (\d+), (\d+)", name)
-        mf = re.search(r"pass_f32_kernel<(\d+), (\d+), (\d+)", name)
+        mf = re.search(r"pass_f32_kernel<(\d+), (\d+), (\d+), \d+, (\d+), (\d+)>", name)   # D, DV, B, KH, DC, mode
         if not (m or mf) or name not in write:
             continue
         if m:
             key = f"pass_bf16_kernel<{m.group(1)},{m.group(2)}>" + ("" if m.group(3) == "0" else f" mode {m.group(3)}")
         else:
-            key = f"pass_f32_kernel<{mf.group(1)},{mf.group(2)},{mf.group(3)}>"
+            key = (f"pass_f32_kernel<{mf.group(1)},{mf.group(2)},{mf.group(3)}>"
+                   + ("" if mf.group(4) == mf.group(1) else f" DC {mf.group(4)}")
+                   + ("" if mf.group(5) == "0" else f" mode {mf.group(5)}"))
         rd = sum(fetch[name]) / len(fetch[name]) * 1024.0 * sf
         wr = sum(write[name]) / len(write[name]) * 1024.0 * sw
         out["kernels"][key] = {"launches": len(fetch[name]), "read_bytes_per_launch": round(rd),
@@ -245,15 +261,12 @@ def main() -> int:
     tflops = {n: f * token_heads / (ms_per_step * 1e-3) / 1e12 for n, f in fl.items()}
 
     # Dominant kernel: the backward launch (all three gradients in one kernel).
-    bwd_kernel = f"pass_bf16_kernel<{w.D},{plan_b[0]}>" if w.dtype == torch.bfloat16 else f"pass_f32_kernel<{w.D},{plan_b[0]},{block}>"
+    bwd_kernel = f"pass_bf16_kernel<{w.D},{plan_b[0]}>" if w.dtype == torch.bfloat16 else f"pass_f32_kernel<{w.D},{plan_b[0]},{f32_block(block)}>"
     bwd_bytes = ab["bwd"] * token_heads
     achieved = bwd_bytes / (bwd_ms * 1e-3) / 1e9
     if w.dtype == torch.float32:
-        # fp32 tensors: the matrix cores' fp32 rate bounds the launch, not memory.  FLOPs the backward launch
-        # issues per token-head: three passes, each with causal score tiles ((B/16+1)/2 of B/16 per 16-token
-        # strip, recomputed per value-column slice), the same share of P C, and 4 D^2 of state products.
-        causal = (block / 16 + 1) / 2 * 16
-        bwd_flops = 3 * (2 * causal * w.D * (w.D // plan_b[0]) + 2 * causal * w.D + 4 * w.D * w.D) * token_heads
+        # fp32 tensors: the matrix cores' fp32 rate bounds the launch, not memory
+        bwd_flops = f32_issued_flops_per_token_head(w.D, block, plan_b, 3) * token_heads
         ach_t = bwd_flops / (bwd_ms * 1e-3) / 1e12
         roofline = {
             "bound": "mfma", "kernel": bwd_kernel + " (the backward launch: dV, dK and dQ passes of every chain)",
@@ -480,17 +493,12 @@ def extended_report(ltn, synth, torch, dev, sections=""):
             B_ = blk or ltn.ltn_attn_pick_block(Dh, torch.float32)
             pf = ltn.ltn_attn_query_plan(Bt, H, N, Dh, torch.float32, 0)
             pb_ = ltn.ltn_attn_query_plan(Bt, H, N, Dh, torch.float32, 1)
-            # FLOPs the kernel issues per token-head and pass with 16-token strips: causal score tiles
-            # (B/16+1)/2 of B/16 per strip, recomputed per value-column slice; the same share of P C
-            def issued(passes, dv):
-                causal = (B_ / 16 + 1) / 2 * 16
-                return passes * (2 * causal * Dh * (Dh // dv) + 2 * causal * Dh + 4 * Dh * Dh)
-            print(json.dumps({"workload": name, "Bt": Bt, "H": H, "N": N, "D": Dh, "block": B_, "dv_fwd": pf[0], "dv_bwd": pb_[0],
+            print(json.dumps({"workload": name, "Bt": Bt, "H": H, "N": N, "D": Dh, "block": B_, "dv_fwd": pf[0], "segs_fwd": pf[1], "dv_bwd": pb_[0], "segs_bwd": pb_[1],
                               "fwd_ms": round(f, 4), "bwd_ms": round(b, 4), "fwd_min_ms": round(fmin, 4), "bwd_min_ms": round(bmin, 4),
                               "fwd_GBs": round(4 * Dh * 4 * th / (f * 1e-3) / 1e9, 1),
                               "bwd_GBs": round(7 * Dh * 4 * th / (b * 1e-3) / 1e9, 1),
-                              "fwd_issued_TFLOPs": round(issued(1, pf[0]) * th / (f * 1e-3) / 1e12, 1),
-                              "bwd_issued_TFLOPs": round(issued(3, pb_[0]) * th / (b * 1e-3) / 1e12, 1),
+                              "fwd_issued_TFLOPs": round(f32_issued_flops_per_token_head(Dh, B_, pf, 1) * th / (f * 1e-3) / 1e12, 1),
+                              "bwd_issued_TFLOPs": round(f32_issued_flops_per_token_head(Dh, B_, pb_, 3) * th / (b * 1e-3) / 1e12, 1),
                               "fp32_mfma_peak_TFLOPs": 157.3}), file=sys.stderr, flush=True)
             del q, k, v, g, o, gr
 

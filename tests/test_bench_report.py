@@ -1,0 +1,31 @@
+"""Host-side arithmetic of bench.py's report (CPU only): traffic records keep the kernel variants of one
+workload apart, and fp32 FLOP counts are those of the tiles and launches that run."""
+import json
+
+import bench
+
+NAME = "void ltn::(anonymous namespace)::pass_f32_kernel<{}>(ltn::PassBatch, int, int)"
+
+
+def test_traffic_record_keeps_the_fp32_variants_apart(tmp_path, monkeypatch):
+    monkeypatch.setattr(bench, "traffic_profile_path", lambda w: str(tmp_path / f"{w}.json"))
+    rows = {NAME.format("128, 128, 32, 1, 128, 0"): 30.0, NAME.format("128, 128, 32, 1, 128, 2"): 20.0,
+            NAME.format("128, 64, 32, 2, 64, 0"): 10.0, "__amd_rocclr_copyBuffer": float(1 << 20)}
+    paths = []
+    for counter in ("FETCH_SIZE", "WRITE_SIZE"):
+        paths.append(tmp_path / f"{counter}.csv")
+        paths[-1].write_text("Kernel_Name,Counter_Name,Counter_Value\n" +
+                             "".join(f'"{n}",{counter},{v}\n' for n, v in rows.items()))
+    assert bench.write_traffic_profile("w", *map(str, paths)) == 0
+    kernels = json.loads((tmp_path / "w.json").read_text())["kernels"]
+    assert {k: v["read_bytes_per_launch"] for k, v in kernels.items()} == {
+        "pass_f32_kernel<128,128,32>": 30 * 1024, "pass_f32_kernel<128,128,32> mode 2": 20 * 1024,
+        "pass_f32_kernel<128,64,32> DC 64": 10 * 1024}
+
+
+def test_fp32_flops_are_those_of_the_tiles_and_launches_that_run():
+    # a block of 64 tokens is two tiles of 32: 24 keys a token on average, whatever the block
+    whole = bench.f32_issued_flops_per_token_head(64, 64, (64, 1), 1)
+    assert whole == bench.f32_issued_flops_per_token_head(64, 32, (64, 1), 1) == 2 * 24 * 64 * 2 + 4 * 64 * 64
+    # chains cut into segments: one state update more
+    assert bench.f32_issued_flops_per_token_head(64, 64, (64, 4), 1) == whole + 2 * 64 * 64
