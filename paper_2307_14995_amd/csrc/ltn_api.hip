@@ -365,10 +365,10 @@ SegPlan pick_segments(long long chain_passes, long long N, int D, ltn_dtype dtyp
 bool gated_in_two_steps(long long chains, long long N, int D, ltn_dtype dtype, int blk, bool store_o) {
     if (D == 256 || (D == 96 && dtype != LTN_BF16)) return true;
     if (dtype == LTN_F32) {
-        constexpr double kSlotsPerValue = 3 * 4 / 5e12 * 2.4e9 / 32;
-        const double issue = store_o ? 850.0 : 700.0;      // one tensor less to allocate without o
+        // (whether o is wanted does not enter: y has the same bits with and without it)
+        constexpr double kSlotsPerValue = 3 * 4 / 5e12 * 2.4e9 / 32, kIssueTwo = 700.0;
         double two = pick_f32(chains, 1, N, D, D, blk, false).t + kF32Launch + (double)chains * N * D * kSlotsPerValue;
-        if (two < issue) two = issue;
+        if (two < kIssueTwo) two = kIssueTwo;
         return two < 0.97 * pick_f32(chains, 1, N, D, D, blk, true).t;
     }
     if (!store_o || chains >= 192) return false;
