@@ -230,36 +230,36 @@ SegPlan cut_chain(long long N, long long want) {
 // sequences that the rules above cut fewer than 8 ways.  Whole chains: a start and `whole` a block of
 // 64 tokens.  Cut: the sweep's and the scan's launches more, `block` per block of a segment (as cut_chain
 // rounds it; sweep and pass), and per segment its state, written, scanned and read, at about
-// 4 TB/s; and no less than the time in which the binding issues three launches and allocates the
-// scratch.  Fitted to forced plans, 1 .. 64 chains x 520 .. 4095 tokens, every width, forward, backward
-// and gated (mean error 2-5 % a width).
+// 4.6 TB/s; and no less than `issue`, in which the binding issues three launches and allocates the
+// scratch.  Fitted for the choice below to forced plans, 1 .. 64 chains x 520 .. 4095 tokens, every width.
 struct BlockCost { double whole, block; };
+constexpr double kIssue = 16.2, kIssueBwd = 19.1;
 BlockCost block_cost(int DA, int DC, bool gated) {
-    if (gated) return DA == 64 ? BlockCost{0.91, 1.10} : BlockCost{1.69, 2.1};
-    if (DA == 64) return BlockCost{0.48, DC == 128 ? 0.96 : 0.67};
-    if (DA == 96) return BlockCost{0.70, 1.05};
-    if (DA == 128) return BlockCost{0.66, DC == 256 ? 1.55 : 1.3};
-    return BlockCost{1.38, 2.05};
+    if (gated) return DA == 64 ? BlockCost{0.92, 1.17} : BlockCost{1.89, 1.81};
+    if (DA == 64) return BlockCost{0.47, DC == 128 ? 0.63 : 0.74};
+    if (DA == 96) return BlockCost{0.70, 0.95};
+    if (DA == 128) return BlockCost{0.69, DC == 256 ? 1.53 : DC == 128 ? 1.7 : 1.43};
+    return BlockCost{1.46, 2.23};
 }
-double plan_time(const SegPlan& plan, long long chain_passes, long long N, int DA, int DC, bool gated, bool bwd = false) {
-    constexpr double kStart = 4.5, kCut = 7.5, kStateElement = 4.3e-6, kIssue = 16.2, kIssueBwd = 19.7;
+double plan_time(const SegPlan& plan, long long chain_passes, long long N, int DA, int DC, bool gated, double issue = kIssue) {
+    constexpr double kStart = 4.2, kCut = 7.5, kStateElement = 3.5e-6;
     const BlockCost c = block_cost(DA, DC, gated);
     if (plan.segs == 1) return kStart + c.whole * ((N + 63) / 64);
     const double state = kStateElement * (DA == 96 ? 128 : DA) * (DC == 96 ? 128 : DC);
     const double t = kStart + kCut + c.block * (plan.seg_len / 64) + state * chain_passes * plan.segs;
-    const double issue = bwd ? kIssueBwd : kIssue;
     return t < issue ? issue : t;
 }
 
 // Shorter segments than those rules allow (`finer` of them, down to 256 tokens, about 160 in the gated
-// pass): where they are estimated 3 % faster than the plan the rules give, cut or whole.  Over the
-// forced plans above (1700 shapes where the two differ) this takes 0.845 of the rules' time on
-// average; it loses more than 2 % at ten shapes, 7 % at most.  Without the state's and the issue's
-// terms it lost 5-34 % at 64 chains x 1537 .. 2000 tokens of (128, 64), at 40 .. 51 gated chains x 800 and
-// at backwards of 1 .. 4 chains x 1537 of 64 features.
-bool finer_pays(long long finer, long long want, long long chain_passes, long long N, int DA, int DC, bool gated, bool bwd = false) {
-    return plan_time(cut_chain(N, finer), chain_passes, N, DA, DC, gated, bwd) <
-           0.97 * plan_time(cut_chain(N, want), chain_passes, N, DA, DC, gated, bwd);
+// pass): where they are estimated 1.5 % faster than the plan the rules give, cut or whole.  Over the
+// 1880 forced shapes where a finer cut is possible this takes 0.854 of the rules' time on average, 0.3 %
+// more than the better of each pair, and loses more than 3 % at 17 shapes.  Taking every finer cut
+// from 5 segments on (4 of 1536 tokens for unequal widths) lost that at 190: 20-34 % at 64 chains x
+// 1537 .. 2000 tokens of (128, 64), 6 % at 51 gated chains x 800, 11 % at backwards of 1 .. 4 chains x
+// 1537 of 64 features.
+bool finer_pays(long long finer, long long want, long long chain_passes, long long N, int DA, int DC, bool gated, double issue) {
+    return plan_time(cut_chain(N, finer), chain_passes, N, DA, DC, gated, issue) <
+           0.985 * plan_time(cut_chain(N, want), chain_passes, N, DA, DC, gated, issue);
 }
 
 // paired_chains: the number of chains when the passes are the three of a backward (whose
@@ -324,7 +324,8 @@ SegPlan pick_segments(long long chain_passes, long long N, int D, ltn_dtype dtyp
         const bool four = want == 4 && paired_chains > 0 && (paired_chains * 4) % 8 == 0 && N / want >= 2 * few_len;
         if (!few && !four) want = 1;
     }
-    if (try_finer && !(D == 96 && whole_rows) && finer_pays(finer, want, chain_passes, N, D, D, full_width, bwd)) want = finer;
+    if (try_finer && !(D == 96 && whole_rows) && finer_pays(finer, want, chain_passes, N, D, D, full_width, bwd ? kIssueBwd : kIssue))
+        want = finer;
     if (paired_chains > 0 && want >= 6 && whole_rows) {
         // The backward's workgroup ids pair a chain's (dV, dK) passes on one XCD only when
         // chains x segments is a multiple of 8: up to a quarter fewer segments for that
@@ -811,7 +812,8 @@ static SegPlan pick_segments_dkdv(long long chain_passes, long long N, int DA, i
     if (want > N / 512) want = N / 512;       // segments of at least 512 tokens (measured: 2 .. 32 chains, N = 2048 .. 16384)
     const bool try_finer = want < 8 && finer > want && finer >= 4;
     if (want < kMinSegsFullWidth) want = 1;
-    if (try_finer && finer_pays(finer, want, chain_passes, N, DA, DC, false)) want = finer;
+    // (DA < DC: the second launch of a backward, issued while the first one runs)
+    if (try_finer && finer_pays(finer, want, chain_passes, N, DA, DC, false, DA < DC ? 0.0 : kIssue)) want = finer;
     if (const int v = g_debug_segs.load(std::memory_order_relaxed)) want = v;
     return cut_chain(N, want);
 }

@@ -25,6 +25,28 @@ def test_short_segment_plans_fit_one_round_and_the_scratch():
                     assert need <= 16 << 20
 
 
+def test_cuts_that_do_not_pay_are_not_taken():
+    """Shapes whose forced cuts ran slower than the whole chain (5 .. 34 %), and neighbours where they pay."""
+    def segs(chains, N, D, call):
+        return ltn.ltn_attn_query_plan(1, chains, N, D, BF, call)[1]
+
+    def scratch(chains, N, Dk, call):
+        return ltn.ltn_attn_workspace_bytes_dkdv(1, chains, N, Dk, Dk // 2, BF, call)
+
+    for chains in (1, 2, 4):
+        assert segs(chains, 1537, 64, 1) == 1 and segs(chains, 1800, 64, 1) == 1 and segs(chains, 2500, 64, 1) > 4
+    for chains in (40, 51):
+        assert segs(chains, 800, 64, 2) == 1 and segs(chains, 1290, 64, 2) > 3
+    assert segs(51, 800, 128, 2) == 1 and segs(24, 800, 128, 2) == 5
+    # 1290 tokens in five segments are four of 320 and one of 10
+    for chains in (10, 12, 16):
+        assert segs(chains, 1290, 96, 0) == 1 and segs(chains, 1537, 96, 0) > 1
+    assert segs(4, 1290, 256, 1) == 1 and segs(4, 1290, 256, 0) == 5
+    for N in (1537, 1800, 2000):
+        assert scratch(64, N, 128, 0) == 0 and scratch(64, N, 128, 1) == 0 and scratch(8, N, 128, 0) > 0
+    assert scratch(48, 1290, 128, 0) == 0 and scratch(4, 1290, 256, 0) > 0
+
+
 CASES = [("gated", 1, 3, 800, 128), ("gated", 1, 4, 1001, 64), ("gated", 2, 3, 1087, 128), ("fwd", 1, 4, 1999, 128),
          ("fwd", 2, 4, 2049, 64), ("bwd", 1, 4, 2050, 64), ("bwd", 1, 3, 3011, 128), ("fwd", 1, 2, 1345, 256), ("bwd", 1, 2, 1999, 96)]
 
