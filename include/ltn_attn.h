@@ -24,7 +24,8 @@
  *     (row = key feature, column = value feature).
  *   - Work is enqueued on `stream` (a hipStream_t passed as void*; NULL = the
  *     default stream).  Calls return without synchronising.
- *   - Outputs are fully overwritten; inputs are never written.  An output whose
+ *   - Outputs are fully overwritten (fp32 passes of few chains keep their segments' states in
+ *     the outputs' rows until those rows are written); inputs are never written.  An output whose
  *     bytes overlap an input's or another output's (not only equal base
  *     pointers; the workspace counts as an output) is rejected
  *     (LTN_ERR_UNSUPPORTED).  The one exception: kv_out may be kv_in itself.
@@ -101,7 +102,7 @@ ltn_status ltn_attn_fwd(const void* q, const void* k, const void* v, void* o,
  * ltn_attn_fwd for callers that cannot allocate device memory and so have no workspace to
  * hand over: code under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc.  Same arguments, results (bit for bit) and errors as ltn_attn_fwd, without
- * the workspace pair: where ltn_attn_fwd would use a workspace (few long chains, cut into
+ * the workspace pair: where ltn_attn_fwd would use a workspace (few chains, cut into
  * segments), this entry point uses a scratch buffer of LTN_ATTN_STATIC_SCRATCH_BYTES that
  * is part of the library's device code (every GPU the library runs on holds one copy
  * until the process ends).  It calls no hipMalloc / hipFree and no allocating routine.
@@ -128,18 +129,20 @@ ltn_status ltn_attn_fwd_static(const void* q, const void* k, const void* v, void
  *   o as in ltn_attn_fwd;   y[b,h,t,:] = o[b,h,t,:] / sqrt(mean_d(o[b,h,t,:]^2) + eps) (.) u[b,h,t,:]
  *
  * The normalisation and the gate are applied to the fp32 attention output while
- * it is still on chip, so an inference caller (o == NULL) never writes or re-reads
- * the attention output; a training caller passes `o` as well, because the
+ * it is still on chip, so an inference caller (o == NULL) with bf16 tensors never writes
+ * or re-reads the attention output; a training caller passes `o` as well, because the
  * derivative of the epilogue (ltn_gate_bwd) needs it.
  *
  *   u     in : device, [Bt,H,N,D] dtype  (the gate)
  *   o     out: device, [Bt,H,N,D] dtype, or NULL
  *   y     out: device, [Bt,H,N,D] dtype
  * (With few chains and `o` requested, the library may instead run the plain forward and
- * apply the epilogue to the stored o in a second kernel; y then derives from o rounded
- * to `dtype`, so the two forms of the call agree to rounding, not bit for bit.  For D = 256,
- * and for D = 96 in fp32, that is the only form: no kernel there holds a complete output row
- * in one workgroup, so `o` must be given -- LTN_ERR_UNSUPPORTED otherwise.)
+ * apply the epilogue to the stored o in a second kernel; bf16: y then derives from o rounded
+ * to `dtype`, so the two forms of the call agree to rounding, not bit for bit.  fp32: the
+ * choice does not depend on `o`, nor does any bit of y; without `o` the attention output passes
+ * through y's memory.  For D = 256, and for D = 96 in fp32, two steps are the only form: no
+ * kernel there holds a complete output row in one workgroup, so `o` must be given --
+ * LTN_ERR_UNSUPPORTED otherwise.)
  *   eps   >= 0, added to the mean square under the root (0 is the printed formula:
  *         an all-zero output row then yields NaN, as the formula does)
  * Other arguments, layout and errors as for ltn_attn_fwd.
@@ -304,7 +307,7 @@ size_t ltn_prologue_workspace_bytes(int Bt, int H, long long N, int D);
  * Supported: (Dk, Dv) in {(256,128), (128,64)}; equal widths go through the entry points
  * above (LTN_ERR_UNSUPPORTED here).  block: 0 = library's choice; bf16 64; fp32 16, or 32
  * when Dk = 128.  workspace: device scratch of ltn_attn_workspace_bytes_dkdv(...) bytes (0
- * unless few chains meet a long sequence, as for ltn_attn_fwd / ltn_attn_bwd; call = 0 for
+ * unless few bf16 chains are some hundreds of tokens long or longer, as for ltn_attn_fwd / ltn_attn_bwd; call = 0 for
  * the forward, 1 for the backward); too small -> LTN_ERR_SHAPE, NULL when needed ->
  * LTN_ERR_NULL.
  */
@@ -352,9 +355,9 @@ ltn_status ltn_attn_set_debug_plan(int dv, int segs);
 
 /* Scratch bytes a call needs for these arguments: call = 0 for ltn_attn_fwd, 1 for
  * ltn_attn_bwd, 2 for ltn_attn_fwd_gated.  A smaller workspace makes the call fail with
- * LTN_ERR_SHAPE; a NULL one with LTN_ERR_NULL when bytes are needed.  It is 0 except
- * when few chains meet a long sequence: then every chain is cut into segments that run
- * in parallel (the recurrence of Sec. 3.3 is linear in the state, so the segments' end
+ * LTN_ERR_SHAPE; a NULL one with LTN_ERR_NULL when bytes are needed.  It is 0 except when
+ * few chains of bf16 tensors are some hundreds of tokens long or longer (which sizes, is the
+ * library's choice: ask here): then every chain is cut into segments that run in parallel (the recurrence of Sec. 3.3 is linear in the state, so the segments' end
  * states can be computed from zero and combined by a scan), and the workspace holds one
  * fp32 D x D state per (pass, chain, segment).  For ltn_attn_fwd_gated the figure covers
  * both of its forms (fused, and plain forward followed by the gate kernel).  Contents are

@@ -187,7 +187,7 @@ ltn_status check_common(int Bt, int H, long long N, int D, int block, ltn_dtype 
         if (blk != 64) return LTN_ERR_UNSUPPORTED;
     } else {
         if (blk != 16 && blk != 32 && blk != 64) return LTN_ERR_UNSUPPORTED;
-        if ((long long)(D == 96 ? 128 : D) * blk > 4096) return LTN_ERR_UNSUPPORTED;   // 96 is computed as 128
+        if ((long long)(D == 96 ? 128 : D) * blk > 4096) return LTN_ERR_UNSUPPORTED;   // 96 takes the blocks of 128
     }
     if ((long long)Bt * H > 0x3fffffffLL) return LTN_ERR_SHAPE;
     *blk_out = blk;
@@ -203,7 +203,8 @@ ltn_status check_common(int Bt, int H, long long N, int D, int block, ltn_dtype 
 // round of compute units, from 5 ways on when the segments are at least 1024 tokens long
 // (33 .. 51 passes of long chains: the forward of 36 .. 48 chains at N = 8192 runs 17-29 % faster
 // cut 5 .. 7 ways, the backward of 12 .. 16 chains 11-16 %), and 4 ways in the backward of about
-// 20 chains with segments of at least 2048 tokens (13-19 %); never otherwise.
+// 20 chains with segments of at least 2048 tokens (13-19 %); shorter segments than these only where
+// finer_pays() says so.
 // bf16 kernels only.  Heads of 256 features always need four 64-column workgroups per chain
 // and segment, heads of 96 three of 32; there the form pays from 3 segments of at least 512
 // tokens on (measured: 2 .. 32 chains, N = 2048 .. 32768, forward and backward; heads of 96

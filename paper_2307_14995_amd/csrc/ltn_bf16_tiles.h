@@ -88,10 +88,10 @@ __device__ __forceinline__ void static_for(const F& f) { static_for_impl(f, std:
 // (i) fixes the chunk pair within 8 rows, (iii) gives the two rows that share a pair different
 // halves, and (ii) then wants those two rows on the same side of its split: row r + 8 of the 256
 // bytes takes the pair of row r ^ 4.  Row reads run at 243 bytes per cycle and unit, transpose
-// reads at 217; without (ii), pairs in the same order for rows 8-15, row reads ran at 128, and
-// without (iii), the half from row bit 2, heads of 64 features lost 3-5 % (forward of 48 chains x
-// 2000 tokens 21.8 us against 20.7, backward of 64 x 3500 44.7 against 43.3; wider heads the same
-// either way).  Adding a multiple of 16 rows does not change the key,
+// reads at 216, the writes at 64; without (ii), pairs in the same order for rows 8-15, row reads ran
+// at 128, and without (iii), the half from row bit 2, the writes into 128-byte rows at 32 (64 as well
+// into wider ones): heads of 64 features lost 3-5 % (forward of 48 chains x 2000 tokens 21.8 us
+// against 20.7, backward of 64 x 3500 44.7 against 43.3).  Adding a multiple of 16 rows does not change the key,
 // so row-block offsets stay compile-time immediates.
 template <int COLS>
 struct Swz {
