@@ -357,11 +357,12 @@ ltn_status ltn_attn_set_debug_plan(int dv, int segs);
  * ltn_attn_bwd, 2 for ltn_attn_fwd_gated.  A smaller workspace makes the call fail with
  * LTN_ERR_SHAPE; a NULL one with LTN_ERR_NULL when bytes are needed.  It is 0 except when
  * few chains of bf16 tensors are some hundreds of tokens long or longer (which sizes, is the
- * library's choice: ask here): then every chain is cut into segments that run in parallel (the recurrence of Sec. 3.3 is linear in the state, so the segments' end
- * states can be computed from zero and combined by a scan), and the workspace holds one
- * fp32 D x D state per (pass, chain, segment).  For ltn_attn_fwd_gated the figure covers
- * both of its forms (fused, and plain forward followed by the gate kernel).  Contents are
- * scratch: undefined before and after the call. */
+ * library's choice: ask here): then every chain is cut into segments that run in parallel
+ * (the recurrence of Sec. 3.3 is linear in the state, so the segments' end states can be
+ * computed from zero and combined by a scan), and the workspace holds one fp32 D x D state
+ * per (pass, chain, segment).  For ltn_attn_fwd_gated the figure covers both of its forms
+ * (fused, and plain forward followed by the gate kernel).  Contents are scratch: undefined
+ * before and after the call. */
 size_t ltn_attn_workspace_bytes(int Bt, int H, long long N, int D, int block,
                                 ltn_dtype dtype, int call);
 

@@ -97,7 +97,9 @@ struct Cfg {
 
 // MODE of a workgroup: the plain pass, the pass with the gated epilogue, or the
 // state-only sweep of the sequence-parallel form (no outputs: only the segment's end state).
-enum { kPlain = 0, kGated = 1, kStateOnly = 2 };
+// kGatedLate: the gated epilogue with the gate values fetched within the block that uses them.
+enum { kPlain = 0, kGated = 1, kStateOnly = 2, kGatedLate = 3 };
+constexpr bool has_gate(int mode) { return mode == kGated || mode == kGatedLate; }
 
 
 // Register prefetch loads of the AREG output waves are issued from inline assembly and
@@ -435,26 +437,28 @@ struct Chain {            // what every wave of the workgroup knows about its pr
 // =============================================================== pass body
 
 // "Block blk + 1 has landed" for a wave that issues, per block and in this order, L tile loads
-// (for block blk + PST - 1), S stores and G gate loads (for block blk + 1), after PST - 1 blocks'
-// tile loads and G gate loads up front: the operations it issued after that block's tile loads.
-template <int PST, int L, int S, int G>
+// (for block blk + PST - 1), S stores and, AHEAD, G gate loads (for block blk + 1), after PST - 1
+// blocks' tile loads and G gate loads up front; not AHEAD: G gate loads (for block blk) before the
+// tile loads, none up front.  The operations it issued after that block's tile loads:
+template <int PST, int L, int S, int G, bool AHEAD>
 __device__ __forceinline__ void wait_block(int blk) {
     static_assert(PST >= 2 && PST <= 4, "ring depths");
+    constexpr int X = AHEAD ? G : 0;
     if constexpr (PST == 2) {
-        wait_dma<S + G>();
+        wait_dma<S + X>();
     } else if constexpr (PST == 3) {
-        if (blk == 0) wait_dma<L + S + 2 * G>(); else wait_dma<L + 2 * S + 2 * G>();
+        if (blk == 0) wait_dma<L + S + G + X>(); else wait_dma<L + 2 * S + G + X>();
     } else {
-        if (blk == 0) wait_dma<2 * L + S + 2 * G>();
-        else if (blk == 1) wait_dma<2 * L + 2 * S + 3 * G>();
-        else wait_dma<2 * L + 3 * S + 3 * G>();
+        if (blk == 0) wait_dma<2 * L + S + G + X>();
+        else if (blk == 1) wait_dma<2 * L + 2 * S + 2 * G + X>();
+        else wait_dma<2 * L + 3 * S + 2 * G + X>();
     }
 }
 
 template <int D, int DV, int DC, int W, int MODE, int DR>
 __device__ __forceinline__ void pass_output_wave(const Chain& ch, char* smem, unsigned lds0, int lane) {
     using C = Cfg<D, DV>;
-    constexpr bool GATED = MODE == kGated;
+    constexpr bool GATED = has_gate(MODE), AHEAD = MODE == kGated;
     constexpr bool SO = MODE == kStateOnly;          // nothing to produce: tile loads and barriers only
     constexpr int KS = C::KS;
     constexpr long long ROW = DC * 2;      // the output's row (and U's, Y's)
@@ -469,7 +473,7 @@ __device__ __forceinline__ void pass_output_wave(const Chain& ch, char* smem, un
     constexpr bool NOA = SO || C::AREG;              // the A tile is not fetched into LDS
     constexpr int L = ISSUER ? ((NOA ? 1 : 2) * TileDmaU<D>::NI + TileDmaU<C::CW>::NI) / C::FW : 0;   // loads per block, this wave
     constexpr int S = SO ? 0 : C::NT / 2;            // stores per block and output tensor, this wave
-    constexpr int G = GATED ? C::NT / 2 : 0;         // gate loads per block, issued when the block before is done
+    constexpr int G = GATED ? C::NT / 2 : 0;         // gate loads per block, issued when the block before is done (AHEAD)
     static_assert((C::PST - 2) * L + (C::PST - 1) * ((GATED ? 2 : 1) * S + G) <= 63, "vmcnt field");
     constexpr long long AROW = DR * 2;
     TileDmaU<D, DR> dab;                              // A and B tiles: same shape, same offsets
@@ -507,8 +511,8 @@ __device__ __forceinline__ void pass_output_wave(const Chain& ch, char* smem, un
     const bool two_outputs = GATED && ch.out;          // the gated pass stores Y and, if asked, O
     auto wait_next = [&](int blk) {        // block blk + 1 has landed (this wave's part)
         if constexpr (ISSUER) {
-            if (two_outputs) wait_block<C::PST, L, 2 * S, G>(blk);
-            else wait_block<C::PST, L, S, G>(blk);
+            if (two_outputs) wait_block<C::PST, L, 2 * S, G, AHEAD>(blk);
+            else wait_block<C::PST, L, S, G, AHEAD>(blk);
         }
     };
     if constexpr (ISSUER) {                // blocks 0 .. PST-2 in flight, block 0 landed
@@ -557,7 +561,7 @@ __device__ __forceinline__ void pass_output_wave(const Chain& ch, char* smem, un
         static_for<G>([&](auto p) { gload16_masked<64 * decltype(p)::value>(uq[decltype(p)::value], pu, rows); });
         pu += step;
     };
-    if constexpr (GATED) load_gate(0);
+    if constexpr (AHEAD) load_gate(0);
 
     __syncthreads();                       // block 0 tiles and the initial state copy are in LDS
     int stage = 0;
@@ -565,6 +569,7 @@ __device__ __forceinline__ void pass_output_wave(const Chain& ch, char* smem, un
         const bool more = blk + 1 < ch.T;
         const bool row_ok = (16 * W + i16) < ((blk + 1 == ch.T) ? ch.last_valid : kBlock);
         const long long bo = (long long)blk * step;
+        if constexpr (GATED && !AHEAD) load_gate(blk);
         if constexpr (ISSUER) {
             int fs = stage + C::PST - 1;   // stage of block blk + PST - 1 (free since the last barrier)
             if (fs >= C::PST) fs -= C::PST;
@@ -583,14 +588,14 @@ __device__ __forceinline__ void pass_output_wave(const Chain& ch, char* smem, un
         // this block's values have just left (and, like every such load, on every path).  Issued at
         // the start of the block that uses them they arrived after its products were done: 2.3 us
         // a block of 128 features against 1.35 without the gate (32 chains; now 1.75).
-        if constexpr (GATED) load_gate(blk + 1);
+        if constexpr (AHEAD) load_gate(blk + 1);
         if (more) {
             wait_next(blk);
             __syncthreads();
         }
         stage = (stage + 1 == C::PST) ? 0 : stage + 1;
     }
-    if constexpr (GATED) wait_gate<0, G>(uq);   // the last prefetch was never consumed: retire it before its registers die
+    if constexpr (AHEAD) wait_gate<0, G>(uq);   // the last prefetch was never consumed: retire it before its registers die
     if constexpr (ISSUER) wait_dma<0>();   // nothing may land in LDS after this workgroup is gone
 }
 
@@ -769,7 +774,7 @@ __device__ __forceinline__ void pass_state_wave(const Chain& ch, char* smem, int
 template <int D, int DV, int DC, int MODE, int DR>
 __device__ __forceinline__ void pass_body(const PassBatch& pb, int nsplit, int xcd_ids, int wg, char* smem,
                                           unsigned lds0, int wave, int lane) {
-    constexpr bool GATED = MODE == kGated;
+    constexpr bool GATED = has_gate(MODE);
     // (chain, segment) pairs are dealt to workgroups like chains; with one segment per
     // chain the pair index is the chain index
     int vchain, within;
@@ -849,7 +854,7 @@ __device__ __forceinline__ void pass_body(const PassBatch& pb, int nsplit, int x
         __syncthreads();
     }
     if constexpr (Cfg<D, DV>::AREG) {
-        static_assert(MODE != kGated && DR == D, "the register-fed layout has no gated epilogue");
+        static_assert(!has_gate(MODE) && DR == D, "the register-fed layout has no gated epilogue");
         switch (wave) {
             case 0: case 1: case 2: case 3:
                 if constexpr (MODE == kStateOnly) {    // tile loads (waves 0 .. FW-1) and barriers only
@@ -891,7 +896,7 @@ void pass_bf16_kernel(const PassBatch pb, const int nsplit, const int xcd_ids) {
 template <int D, int DV, int MODE = kPlain, int DC = D, int DR = D>
 hipError_t launch_t(const PassBatch& pb, hipStream_t stream) {
     static_assert(DV <= DC && DC % DV == 0, "value-column slices tile the C operand");
-    static_assert(DC == D || MODE != kGated || (D == 128 && DC == 96 && DR == 96 && DV == 96),
+    static_assert(DC == D || !has_gate(MODE) || (D == 128 && DC == 96 && DR == 96 && DV == 96),
                   "unequal widths: no gated epilogue (heads of 96 features computed as 128 have one)");
     const int nsplit = DC / DV;
     const long long nch = (long long)pb.chains * pb.segs;
@@ -935,6 +940,11 @@ hipError_t launch_pass_bf16(const PassBatch& pb, int D, int dv, hipStream_t stre
     }
     if (pb.p[0].gate) {                    // gated epilogue: one pass, complete output rows
         if (pb.count != 1 || dv != D || !pb.p[0].gated_out || pb.state_only) return hipErrorInvalidValue;
+        // With O stored as well, 128 features: bound by memory (it runs fused from 192 chains on), and
+        // gate loads ahead of the barrier are slower there: 256 chains x 4096 tokens 339 us ahead, 321
+        // late; 200 x 4096 282 and 261.  64 features 156 and 163, 96 the same either way; without O
+        // 263 and 263, but 128 x 2048 78 and 82.
+        if (D == 128 && pb.p[0].out) return launch_t<128, 128, kGatedLate>(pb, stream);
         if (D == 128) return launch_t<128, 128, kGated>(pb, stream);
         if (D == 64) return launch_t<64, 64, kGated>(pb, stream);
         return hipErrorInvalidValue;

@@ -275,3 +275,20 @@ def test_forward_gated_argument_errors():
         ltn.ltn_attn_fwd_gated(q, k, v, u, dd, y_out=u)          # Y aliases the gate
     with pytest.raises(ltn.LtnError):
         ltn.ltn_attn_fwd_gated(q, k, v, u, dd, eps=float("nan"))
+
+
+@pytest.mark.parametrize("N", [1, 64, 65, 193])
+def test_bf16_many_chains_fused_with_o_stored(N):
+    """192 chains of 128 features with O stored run fused, gate values fetched within their block."""
+    Bt, H, D = 24, 8, 128
+    q, k, v = synth.make_qkv(Bt, H, N, D, torch.bfloat16, 480 + N)
+    u = synth.make_gate(Bt, H, N, D, torch.bfloat16, 480 + N)
+    decay = mixed_decay(H)
+    o_ref, y_ref = orc.fwd_gated(q, k, v, u, decay, eps=1e-6)
+    _, kv_ref = orc.fwd_recurrent(q, k, v, decay, return_state=True)
+    o, y, kv = ltn.ltn_attn_fwd_gated(*gpu(q, k, v, u, decay), eps=1e-6, return_state=True)
+    check("O", o, o_ref, 1e-2)
+    check("Y", y, y_ref, 1e-2)
+    check("kv", kv, kv_ref, 1e-2)
+    # the form without O fetches them a block ahead: the same values
+    assert torch.equal(ltn.ltn_attn_fwd_gated(*gpu(q, k, v, u, decay), eps=1e-6, store_o=False)[1], y)
