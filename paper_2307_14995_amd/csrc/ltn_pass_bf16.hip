@@ -932,7 +932,7 @@ hipError_t launch_pass_bf16(const PassBatch& pb, int D, int dv, hipStream_t stre
         if (dv != 32 && dv != 96) return hipErrorInvalidValue;
         if (pb.p[0].gate) {                // gated epilogue: one pass, all 96 columns of a row in one workgroup
             if (pb.count != 1 || dv != 96 || !pb.p[0].gated_out || pb.state_only) return hipErrorInvalidValue;
-            return launch_t<128, 96, kGated, 96, 96>(pb, stream);
+            return pb.p[0].out ? launch_t<128, 96, kGatedLate, 96, 96>(pb, stream) : launch_t<128, 96, kGated, 96, 96>(pb, stream);
         }
         if (pb.state_only) return dv == 32 ? launch_t<128, 32, kStateOnly, 96, 96>(pb, stream) : hipErrorInvalidValue;
         if (dv == 96) return launch_t<128, 96, kPlain, 96, 96>(pb, stream);
@@ -940,10 +940,11 @@ hipError_t launch_pass_bf16(const PassBatch& pb, int D, int dv, hipStream_t stre
     }
     if (pb.p[0].gate) {                    // gated epilogue: one pass, complete output rows
         if (pb.count != 1 || dv != D || !pb.p[0].gated_out || pb.state_only) return hipErrorInvalidValue;
-        // With O stored as well, 128 features: bound by memory (it runs fused from 192 chains on), and
-        // gate loads ahead of the barrier are slower there: 256 chains x 4096 tokens 339 us ahead, 321
-        // late; 200 x 4096 282 and 261.  64 features 156 and 163, 96 the same either way; without O
-        // 263 and 263, but 128 x 2048 78 and 82.
+        // With O stored as well (two outputs, bound by memory: it runs fused from 192 chains on) gate
+        // loads ahead of the barrier are slower for 128 and 96 features: 256 chains x 2048 tokens 168 us
+        // ahead, 158 late, 320 x 4096 509 and 478; 96 features 224 x 1000 51 and 47.  64 features
+        // 320 x 8192 479 and 504; without O ahead is the faster or the same at every size (64 .. 768
+        // chains x 64 .. 8192: 128 x 2048 77 and 80, 96 x 2048 60 and 72).
         if (D == 128 && pb.p[0].out) return launch_t<128, 128, kGatedLate>(pb, stream);
         if (D == 128) return launch_t<128, 128, kGated>(pb, stream);
         if (D == 64) return launch_t<64, 64, kGated>(pb, stream);

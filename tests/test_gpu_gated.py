@@ -277,10 +277,11 @@ def test_forward_gated_argument_errors():
         ltn.ltn_attn_fwd_gated(q, k, v, u, dd, eps=float("nan"))
 
 
+@pytest.mark.parametrize("D", [96, 128])
 @pytest.mark.parametrize("N", [1, 64, 65, 193])
-def test_bf16_many_chains_fused_with_o_stored(N):
-    """192 chains of 128 features with O stored run fused, gate values fetched within their block."""
-    Bt, H, D = 24, 8, 128
+def test_bf16_many_chains_fused_with_o_stored(D, N):
+    """192 chains with O stored run fused, the gate values of 96 and 128 features fetched within their block."""
+    Bt, H = 24, 8
     q, k, v = synth.make_qkv(Bt, H, N, D, torch.bfloat16, 480 + N)
     u = synth.make_gate(Bt, H, N, D, torch.bfloat16, 480 + N)
     decay = mixed_decay(H)
