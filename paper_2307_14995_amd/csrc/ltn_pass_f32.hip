@@ -559,6 +559,12 @@ hipError_t launch_pass_f32(const PassBatch& pb, int D, int dv, int block, hipStr
         for (int i = 0; i < pb.count; ++i)
             if (!pb.p[i].seg_rows || pb.seg_len < D || pb.N - (pb.segs - 1) * pb.seg_len < D) return hipErrorInvalidValue;
     const int mode = pb.state_only ? kStateOnly : (gated ? kGated : kPlain);
+    // 64 features, more workgroups than units: four waves without the exchange between row halves take
+    // 72 KB of LDS (88 with it), so two workgroups share a unit, out of step with each other.  Backward of
+    // 1024 chains x 64 tokens 71 -> 52 us, 512 x 512 201 -> 172, 128 x 2048 248 -> 219, forward of 300 x
+    // 2048 247 -> 220; up to 256 workgroups a unit holds one, and its four waves would be alone there.
+    if (mode == kPlain && D == 64 && DC == 64 && dv == 64 && block == 32 && (long long)pb.chains * pb.segs * pb.count > 256)
+        return launch_t<64, 64, 32, 1, 64, kPlain>(pb, stream);
 #define LTN_F32(m, d, c, v, b, kh) if (mode == m && D == d && DC == c && dv == v && block == b) return launch_t<d, v, b, kh, c, m>(pb, stream)
 #define LTN_F32_PLAIN(d, c, v, b, kh) LTN_F32(kPlain, d, c, v, b, kh);
     LTN_F32_SLICES(LTN_F32_PLAIN)

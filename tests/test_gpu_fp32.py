@@ -148,3 +148,22 @@ def test_fp32_gated_with_and_without_o(D, Bt, H, N):
     check("O", o, o_ref, TOL)
     check("Y", y, y_ref, 2 * TOL)          # the norm doubles a row's relative error at most
     assert torch.equal(y2, y) and torch.equal(kv2, kv)
+
+
+@pytest.mark.parametrize("Bt,H,N", [(29, 3, 1), (29, 3, 33), (29, 3, 64), (29, 9, 97)])
+def test_fp32_two_workgroups_a_unit(Bt, H, N):
+    """Heads of 64 features with more than 256 workgroups (3 x 87 and 261 chains): the four-wave instance, both
+    directions, the state carried."""
+    D = 64
+    q, k, v = synth.make_qkv(Bt, H, N, D, torch.float32, 700 + N)
+    g = synth.make_do(Bt, H, N, D, torch.float32, 700 + N)
+    decay = mixed_decay(H)
+    kv0 = torch.randn(Bt, H, D, D, generator=torch.Generator().manual_seed(N)) / D
+    with force_plan(D, 1):
+        o, kv = ltn.ltn_attn_fwd(*gpu(q, k, v, decay), kv_in=kv0.cuda(), return_state=True)
+        grads = ltn.ltn_attn_bwd(*gpu(q, k, v, g, decay))
+    o_ref, kv_ref = orc.fwd_recurrent(q, k, v, decay, kv_in=kv0, return_state=True)
+    check("O", o, o_ref, TOL)
+    check("kv", kv, kv_ref, TOL)
+    for n, x, r in zip(("dQ", "dK", "dV"), grads, orc.bwd_recurrent(q, k, v, g, decay)):
+        check(n, x, r, TOL)
