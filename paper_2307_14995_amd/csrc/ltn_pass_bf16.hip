@@ -932,7 +932,10 @@ hipError_t launch_pass_bf16(const PassBatch& pb, int D, int dv, hipStream_t stre
         if (dv != 32 && dv != 96) return hipErrorInvalidValue;
         if (pb.p[0].gate) {                // gated epilogue: one pass, all 96 columns of a row in one workgroup
             if (pb.count != 1 || dv != 96 || !pb.p[0].gated_out || pb.state_only) return hipErrorInvalidValue;
-            return pb.p[0].out ? launch_t<128, 96, kGatedLate, 96, 96>(pb, stream) : launch_t<128, 96, kGated, 96, 96>(pb, stream);
+            // with O stored as for 128 features below; and a single block has nothing to run ahead of (1024
+            // chains x 64 tokens 23.2 us ahead, 22.1 late; 128 features 512 x 64 11.0 and 12.4)
+            if (pb.p[0].out || pb.N <= kBlock) return launch_t<128, 96, kGatedLate, 96, 96>(pb, stream);
+            return launch_t<128, 96, kGated, 96, 96>(pb, stream);
         }
         if (pb.state_only) return dv == 32 ? launch_t<128, 32, kStateOnly, 96, 96>(pb, stream) : hipErrorInvalidValue;
         if (dv == 96) return launch_t<128, 96, kPlain, 96, 96>(pb, stream);
