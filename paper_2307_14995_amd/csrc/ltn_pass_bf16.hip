@@ -40,8 +40,9 @@
 //     fewest causal score tiles.  They wait for a block with an exact vmcnt that counts their
 //     own stores in between (VMEM operations of a wave retire in issue order), never for the
 //     stores themselves.  In the register-fed layout (256 features) all four output waves
-//     share the loads; in the gated pass the gate values are loaded from assembly too, at
-//     the end of the block before the one that uses them, and counted with the tile loads.  LDS
+//     share the loads; in the gated pass the gate values are loaded from assembly too, at the
+//     end of the block before the one that uses them or at the start of that block (the
+//     dispatch at the end says which when), and counted with the tile loads.  LDS
 //     rows are unpadded; the 16-byte chunk index is XOR-swizzled with the row so that row reads,
 //     transpose reads (ds_read_b64_tr_b16, for operands needed "down the token axis") and the
 //     state-copy writes spread over the banks.  Rows past the end of a short last block are
