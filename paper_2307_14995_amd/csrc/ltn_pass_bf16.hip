@@ -947,8 +947,9 @@ hipError_t launch_pass_bf16(const PassBatch& pb, int D, int dv, hipStream_t stre
         // With O stored as well (two outputs, bound by memory: it runs fused from 192 chains on) gate
         // loads ahead of the barrier are slower for 128 and 96 features: 256 chains x 2048 tokens 168 us
         // ahead, 158 late, 320 x 4096 509 and 478; 96 features 224 x 1000 51 and 47.  64 features
-        // 320 x 8192 479 and 504; without O ahead is the faster or the same at every size (64 .. 768
-        // chains x 64 .. 8192: 128 x 2048 77 and 80, 96 x 2048 60 and 72).
+        // 320 x 8192 479 and 504; without O ahead is the faster or within 3 % at every size (64 .. 768
+        // chains x 64 .. 8192: 128 x 2048 77 and 80, 96 x 2048 60 and 72, 160 x 2048 91.5 and 89.1;
+        // calls of 10 us, which the host bounds, scatter by 5 %).
         if (D == 128 && pb.p[0].out) return launch_t<128, 128, kGatedLate>(pb, stream);
         if (D == 128) return launch_t<128, 128, kGated>(pb, stream);
         if (D == 64) return launch_t<64, 64, kGated>(pb, stream);
