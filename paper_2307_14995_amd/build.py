@@ -5,6 +5,8 @@ it travels with the source tree; it is never installed elsewhere.  Every source 
 compiled to an object of its own (in parallel), then linked; the compiler's per-kernel
 resource report is read back and the build fails if a kernel that relies on registers
 staying put (see ``NO_SPILL``) was given scratch memory or spilled vector registers.
+Beside it goes the binding's native marshalling, paper_2307_14995_amd/_ltn_torch.so (host
+code against torch's headers; it calls the library through addresses it is handed).
 """
 from __future__ import annotations
 
@@ -19,6 +21,8 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libltn_attn.so")
+TORCH_SRC = os.path.join(CSRC, "ltn_torch.cpp")
+TORCH_LIB = os.path.join(PKG, "_ltn_torch.so")
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -63,7 +67,7 @@ def _stale(target: str, deps) -> bool:
 
 
 def is_stale() -> bool:
-    return _stale(LIB, sources() + _headers())
+    return _stale(LIB, sources() + _headers()) or _stale(TORCH_LIB, [TORCH_SRC] + _headers())
 
 
 def check_resource_report(report: str) -> None:
@@ -97,16 +101,42 @@ def _compile(src: str, hipcc: str, verbose: bool, objdir: str = OBJ, extra=()) -
     return obj
 
 
+def build_marshalling(verbose: bool = False) -> str:
+    """Compile the binding's native marshalling against the installed torch."""
+    import sysconfig
+
+    import torch
+    root = os.path.dirname(torch.__file__)
+    include, lib = os.path.join(root, "include"), os.path.join(root, "lib")
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-isystem", include,
+           "-isystem", os.path.join(include, "torch", "csrc", "api", "include"), "-isystem", "/opt/rocm/include",
+           "-isystem", sysconfig.get_paths()["include"], TORCH_SRC, "-o", TORCH_LIB, "-L", lib, "-ltorch_python",
+           "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError(f"{cmd[0]} failed on {TORCH_SRC}:\n" + res.stdout + res.stderr)
+    return TORCH_LIB
+
+
 def build_library(force: bool = True, verbose: bool = False) -> str:
     """Compile every HIP source for gfx950 (all of them when `force`, otherwise only those
-    older than a source or header) and link the shared library."""
+    older than a source or header), link the shared library, and build the marshalling beside it."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     os.makedirs(OBJ, exist_ok=True)
     srcs = sources()
     todo = [s for s in srcs if force or _stale(_obj_of(s), [s] + _headers())]
     jobs = int(os.environ.get("MAX_JOBS", "8") or 8)
     with ThreadPoolExecutor(max_workers=max(1, min(jobs, 16))) as pool:
+        if force or _stale(TORCH_LIB, [TORCH_SRC] + _headers()):
+            marshalling = pool.submit(build_marshalling, verbose)
+        else:
+            marshalling = None
         list(pool.map(lambda s: _compile(s, hipcc, verbose), todo))
+        if marshalling:
+            marshalling.result()
     objs = [_obj_of(s) for s in srcs]
     if todo or _stale(LIB, objs):
         cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC"] + objs + ["-o", LIB]
