@@ -3,8 +3,9 @@
 //     kv <- lambda kv + k_s^T v_s   (fp32),   o_s = q_s kv   (the updated state),  s = 0..S-1
 // The state is read once, kept in registers over the S iterations and written once, so a
 // call moves 2 D^2 fp32 values per chain whatever S is; with S = 1 (one token per call) the
-// step is bound by HBM bandwidth (about half a FLOP per byte).  Plain fp32 vector code with
-// 16-byte accesses; one workgroup per chain, each thread owns four adjacent state
+// step is bound by HBM bandwidth (about half a FLOP per byte), with few chains by latency.  Plain
+// fp32 vector code with 16-byte accesses; one workgroup per chain (or per 32 value columns of
+// one, below), each thread owns four adjacent state
 // columns of a strided set of rows, and the partial dot products per column are reduced
 // through LDS.  Queries and keys have DK features, values and outputs DV (the state is
 // [DK x DV]); the two differ only behind the LRPE-d expansion of Eq. 1.
@@ -102,6 +103,92 @@ void decode_kernel(const void* __restrict__ q, const void* __restrict__ k, const
     for (int it = 0; it < IT; ++it) S[(size_t)(ty + TY * it) * TX + tx] = s[it];
 }
 
+// The same with a chain's value columns split over DV / 32 workgroups: columns are independent of each
+// other, and a workgroup a chain waits for a whole state to cross one unit's load path (and leaves units
+// idle where chains are few).  A thread holds eight rows of four columns; the partial dot products of a
+// wave's rows meet by lane swaps, the waves' through LDS.  One token, us of GPU time a call, whole state
+// and slices: 128 x 128, 1 / 32 / 128 / 384 chains 3.88 / 4.25 / 5.23 / 8.21 and 2.85 / 3.14 / 4.39 / 7.60;
+// 256 x 256, 1 / 32 / 256 / 1024 chains 7.13 / 8.11 / 24.9 / 91.1 and 3.11 / 4.38 / 21.1 / 81.1.
+constexpr int kSliceCols = 32;
+
+template <int DK, int DV, bool BF16>
+__global__ __launch_bounds__(DK)
+void decode_slice_kernel(const void* __restrict__ q, const void* __restrict__ k, const void* __restrict__ v,
+                         void* __restrict__ o, float* __restrict__ kv, const float* __restrict__ decay, int H,
+                         int steps) {
+    constexpr int TX = kSliceCols / 4, TY = DK / TX, IT = DK / TY;       // threads = DK
+    constexpr int WAVES = (DK + 63) / 64, NS = DV / kSliceCols;
+    static_assert(DV % kSliceCols == 0 && DK % TX == 0 && IT == 8, "thread layout");
+    __shared__ float qs[DK], ks[DK], vs[kSliceCols];
+    __shared__ float4 part[WAVES][TX];
+
+    const int chain = blockIdx.x / NS, col0 = (blockIdx.x - chain * NS) * kSliceCols;
+    const int tid = threadIdx.x;
+    const float lam = decay[chain % H];
+    const int tx = tid % TX, ty = tid / TX;
+    float4* S = (float4*)(kv + (size_t)chain * DK * DV + col0);
+    float4 s[IT];
+#pragma unroll
+    for (int it = 0; it < IT; ++it) s[it] = S[(size_t)(ty + TY * it) * (DV / 4) + tx];
+
+    auto load = [](const void* p, size_t e) {
+        return BF16 ? bf16_bits_to_f32(((const unsigned short*)p)[e]) : ((const float*)p)[e];
+    };
+    for (int step = 0; step < steps; ++step) {
+        const size_t row = (size_t)chain * steps + step;
+        qs[tid] = load(q, row * DK + tid);
+        ks[tid] = load(k, row * DK + tid);
+        if (tid < kSliceCols) vs[tid] = load(v, row * DV + col0 + tid);
+        __syncthreads();
+        const float4 vv = *(const float4*)(&vs[4 * tx]);
+        float acc[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int it = 0; it < IT; ++it) {
+            const int i = ty + TY * it;
+            const float ki = ks[i], qi = qs[i];
+            s[it].x = fmaf(lam, s[it].x, ki * vv.x);
+            s[it].y = fmaf(lam, s[it].y, ki * vv.y);
+            s[it].z = fmaf(lam, s[it].z, ki * vv.z);
+            s[it].w = fmaf(lam, s[it].w, ki * vv.w);
+            acc[0] = fmaf(qi, s[it].x, acc[0]);
+            acc[1] = fmaf(qi, s[it].y, acc[1]);
+            acc[2] = fmaf(qi, s[it].z, acc[2]);
+            acc[3] = fmaf(qi, s[it].w, acc[3]);
+        }
+        // (96 threads: the second wave is half full, and its lanes 32 and up hold nothing to be added)
+#pragma unroll
+        for (int m = TX; m < 64; m *= 2)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const float other = __shfl_xor(acc[c], m, 64);
+                acc[c] += (tid & ~63) + ((tid & 63) ^ m) < DK ? other : 0.f;
+            }
+        if ((tid & 63) < TX) part[tid / 64][tx] = float4{acc[0], acc[1], acc[2], acc[3]};
+        __syncthreads();                  // also: everyone is done with qs/ks/vs of this step
+        if (tid < kSliceCols) {
+            float sum = 0.f;
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) sum += ((const float*)&part[w][tid / 4])[tid % 4];
+            const size_t e = row * DV + col0 + tid;
+            if (BF16) ((unsigned short*)o)[e] = f32_to_bf16_bits(sum);
+            else ((float*)o)[e] = sum;
+        }
+        // the next step's first barrier separates these reads of `part` from its next writes
+    }
+#pragma unroll
+    for (int it = 0; it < IT; ++it) S[(size_t)(ty + TY * it) * (DV / 4) + tx] = s[it];
+}
+
+// Slices up to which a call is split; past them the units are full either way, and a slice reads rows
+// of 128 bytes where a whole state is one piece (bf16 tokens, 1 and 4 of them, slower beyond:
+// 128 x 128, 512 chains 14.1 and 14.4 us for 4; 128 x 64, 1024 chains 13.7 and 14.8 for 4; 96 x 96, 1024 chains 16.0
+// and 18.5 for 4; 256 x 256, 2048 chains 204 and 214 for 1).  64 x 64: never, a wave a slice has nothing
+// to overlap (1 chain 2.46 and 2.74 us, 4.09 and 4.89 for 4).  The count does not depend on the number of
+// tokens, so a call of several has the bits of as many calls of one.
+constexpr int split_limit(int DK, int DV) {
+    return DK == 256 ? 8192 : DK == 64 ? 0 : DK * DV == 128 * 64 ? 1024 : 1536;
+}
+
 }  // namespace
 
 hipError_t launch_decode(const void* q, const void* k, const void* v, void* o, float* kv,
@@ -109,8 +196,15 @@ hipError_t launch_decode(const void* q, const void* k, const void* v, void* o, f
                          hipStream_t stream) {
     if (chains <= 0 || steps <= 0) return hipSuccess;
     const dim3 grid((unsigned)chains);
+    const bool split = (long long)chains * (DV / kSliceCols) <= split_limit(DK, DV);
+    const dim3 slices((unsigned)(split ? chains * (DV / kSliceCols) : 1));
 #define LTN_DECODE(dk, dv)                                                                              \
     if (DK == dk && DV == dv) {                                                                         \
+        if constexpr (split_limit(dk, dv) > 0) if (split) {                                             \
+            if (is_bf16) hipLaunchKernelGGL((decode_slice_kernel<dk, dv, true>), slices, dim3(dk), 0, stream, q, k, v, o, kv, decay, H, steps);  \
+            else hipLaunchKernelGGL((decode_slice_kernel<dk, dv, false>), slices, dim3(dk), 0, stream, q, k, v, o, kv, decay, H, steps);         \
+            return hipGetLastError();                                                                   \
+        }                                                                                               \
         const dim3 block(threads_for(dk, dv));                                                          \
         if (is_bf16) hipLaunchKernelGGL((decode_kernel<dk, dv, true>), grid, block, 0, stream, q, k, v, o, kv, decay, H, steps);  \
         else hipLaunchKernelGGL((decode_kernel<dk, dv, false>), grid, block, 0, stream, q, k, v, o, kv, decay, H, steps);         \
