@@ -140,13 +140,19 @@ __device__ __forceinline__ void wait_gate(u32x4* r) {
 }
 
 // lambda^n for 0 <= n <= 64 without one fp64 powering loop per constant: every lane powers
-// once (lambda^lane, and lambda^64), the rest are cross-lane reads.  Same values as
-// decay_pow(lam, n), bit for bit.  All 64 lanes must call get() together.
+// once (lambda^lane, and lambda^64, from the same squares), the rest are cross-lane reads.  Same
+// values as decay_pow(lam, n), bit for bit.  All 64 lanes must call get() together.
 struct DecayTable {
     float mine, p64;
     __device__ __forceinline__ void init(float lam, int lane) {
-        mine = decay_pow(lam, lane);
-        p64 = decay_pow(lam, 64);
+        double base = (double)lam, r = 1.0;
+#pragma unroll
+        for (int i = 0; i < 6; ++i) {
+            r = (lane >> i) & 1 ? r * base : r;
+            base *= base;
+        }
+        mine = (float)r;
+        p64 = (float)base;
     }
     __device__ __forceinline__ float get(int n) const {
         const float v = __shfl(mine, n & 63, 64);
@@ -516,13 +522,13 @@ __device__ __forceinline__ void pass_output_wave(const Chain& ch, char* smem, un
             else wait_block<C::PST, L, S, G, AHEAD>(blk);
         }
     };
-    if constexpr (ISSUER) {                // blocks 0 .. PST-2 in flight, block 0 landed
+    if constexpr (ISSUER) {                // blocks 0 .. PST-2 in flight
 #pragma unroll
         for (int b = 0; b < C::PST - 1; ++b) fetch(b, b);
-        wait_dma<(C::PST - 2) * L>();
     }
 
     if constexpr (SO) {
+        if constexpr (ISSUER) wait_dma<(C::PST - 2) * L>();    // block 0 landed
         __syncthreads();
         int stage = 0;
         for (int blk = 0; blk + 1 < ch.T; ++blk) {
@@ -562,6 +568,8 @@ __device__ __forceinline__ void pass_output_wave(const Chain& ch, char* smem, un
         static_for<G>([&](auto p) { gload16_masked<64 * decltype(p)::value>(uq[decltype(p)::value], pu, rows); });
         pu += step;
     };
+    // Block 0 landed; the constants above were computed meanwhile.
+    if constexpr (ISSUER) wait_dma<(C::PST - 2) * L>();
     if constexpr (AHEAD) load_gate(0);
 
     __syncthreads();                       // block 0 tiles and the initial state copy are in LDS
@@ -717,11 +725,7 @@ __device__ __forceinline__ void pass_state_wave(const Chain& ch, char* smem, int
     constexpr bool SO = MODE == kStateOnly;          // no published state copies
     const int g = lane >> 4, i16 = lane & 15;
     const int dk0 = u * (D / 4);
-    StateConsts<D, DV, C::CW> k;
-    k.set_block_len(ch.lam, kBlock, lane);
-    k.init_offsets(g, i16, dk0, 0);
-
-    // running state, fp32
+    // running state, fp32 (its loads first: they travel while the constants are computed)
     f32x4 st[MT][NT];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
@@ -737,6 +741,10 @@ __device__ __forceinline__ void pass_state_wave(const Chain& ch, char* smem, int
                 st[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
             }
         }
+
+    StateConsts<D, DV, C::CW> k;
+    k.set_block_len(ch.lam, kBlock, lane);
+    k.init_offsets(g, i16, dk0, 0);
 
     // prologue: the initial state copy published (the output waves run the tile pipeline:
     // block b lives in ring stage b % PST)
@@ -772,15 +780,41 @@ __device__ __forceinline__ void pass_state_wave(const Chain& ch, char* smem, int
     }
 }
 
+// pb.p[pi] by value: every pass's arguments are loaded at fixed addresses, in one batch with the
+// rest of the launch's; a load at pb.p[pi] would wait for those first, as long again.
+// A launch's start (arguments known after 2850 of the 11800 cycles that 200 tokens of 64 features take, block 0
+// ready after 6500) is bound by such chains of latencies.  Measured together, before and after: these
+// loads, the ids below without divisions, the powers of lambda without loops, the constants computed and
+// the incoming state fetched while the first tiles travel: gated forward 32 chains x 200 x 64 8.48 and 8.12 us,
+// mixer 128 x 2048 x 128 274.6 and 271.7.
+template <typename T>
+__device__ __forceinline__ T pick(int pi, T x0, T x1, T x2) {
+    return pi == 0 ? x0 : (pi == 1 ? x1 : x2);
+}
+
+// Workgroup index -> (chain x segment, pass, column slice), as map_workgroup_padded gives it; the
+// slices a chain has are a constant of the kernel and the passes one of three numbers, so nothing is
+// divided by a number read from memory.
+template <int NS>
+__device__ __forceinline__ void map_pass(unsigned wg, int count, int xcd_ids, int& vchain, int& pi, int& split) {
+    const unsigned xcd = wg & 7, slot = xcd_ids ? wg >> 3 : wg;
+    const unsigned q = count == 1 ? slot / NS : (count == 2 ? slot / (2 * NS) : slot / (3 * NS));
+    const unsigned within = slot - q * (unsigned)(count * NS);
+    vchain = (int)(xcd_ids ? q * 8 + xcd : q);
+    pi = (int)(within / NS);
+    split = (int)(within - (unsigned)pi * NS);
+}
+
 template <int D, int DV, int DC, int MODE, int DR>
-__device__ __forceinline__ void pass_body(const PassBatch& pb, int nsplit, int xcd_ids, int wg, char* smem,
+__device__ __forceinline__ void pass_body(const PassBatch& pb, int xcd_ids, int wg, char* smem,
                                           unsigned lds0, int wave, int lane) {
     constexpr bool GATED = has_gate(MODE);
     // (chain, segment) pairs are dealt to workgroups like chains; with one segment per
     // chain the pair index is the chain index
-    int vchain, within;
-    bool mine = map_workgroup_padded(wg, pb.count * nsplit, pb.chains * pb.segs, xcd_ids, vchain, within);
-    if (pb.pairs_first && pb.count == 3 && nsplit == 1 && xcd_ids) {
+    constexpr int NS = DC / DV;            // column slices
+    int vchain, pi, split;
+    map_pass<NS>((unsigned)wg, pb.count, xcd_ids, vchain, pi, split);
+    if (NS == 1 && pb.pairs_first && pb.count == 3 && xcd_ids) {
         // Backward at full width: passes 0 and 1 of a chain walk the token axis together and
         // share two operands, pass 2 walks the other way.  Ids: all (pass 0, pass 1) pairs
         // first, a chain's pair side by side on one XCD, then every pass 2.  With more
@@ -791,47 +825,52 @@ __device__ __forceinline__ void pass_body(const PassBatch& pb, int nsplit, int x
         const int nch = (pb.chains * pb.segs + 7) / 8 * 8;       // chain slots of the launch
         const int xcd = wg & 7, slot = wg >> 3;
         if (wg < 2 * nch) {
-            within = slot & 1;
+            pi = slot & 1;
             vchain = (slot >> 1) * 8 + xcd;
         } else {
-            within = 2;
+            pi = 2;
             vchain = (slot - (nch >> 2)) * 8 + xcd;
         }
-        mine = vchain < pb.chains * pb.segs;
     }
-    if (!mine) return;                     // a padding workgroup: the whole workgroup leaves before any barrier
-    const int chain = vchain / pb.segs;
+    if (vchain >= pb.chains * pb.segs) return;                     // a padding workgroup: the whole workgroup leaves before any barrier
+    const int chain = pb.segs == 1 ? vchain : vchain / pb.segs;
     const int seg = vchain - chain * pb.segs;
     if (MODE == kStateOnly && seg + 1 == pb.segs && !pb.need_last) return;   // nobody consumes this end state
-    const int pi = within / nsplit;
-    const int split = within - pi * nsplit;
-    const PassArgs P = pb.p[pi];
+    const float lam = pb.decay[(unsigned)chain % (unsigned)pb.H];
+    const PassArgs &P0 = pb.p[0], &P1 = pb.p[1], &P2 = pb.p[2];
+    const char* const a = pick(pi, (const char*)P0.a, (const char*)P1.a, (const char*)P2.a);
+    const char* const b = pick(pi, (const char*)P0.b, (const char*)P1.b, (const char*)P2.b);
+    const char* const c = pick(pi, (const char*)P0.c, (const char*)P1.c, (const char*)P2.c);
+    char* const out = pick(pi, (char*)P0.out, (char*)P1.out, (char*)P2.out);
+    const float* const state_in = pick(pi, P0.state_in, P1.state_in, P2.state_in);
+    float* const state_out = pick(pi, P0.state_out, P1.state_out, P2.state_out);
+    const int rev = pick(pi, P0.rev, P1.rev, P2.rev);
 
     // the segment's tokens [seg_start, seg_start + n) of the pass's (possibly reversed) token
     // axis are rows [row0, row0 + n) of the tensors
     const long long seg_start = (long long)seg * pb.seg_len;
     const long long n = (pb.segs > 1 && pb.N - seg_start > pb.seg_len) ? pb.seg_len : pb.N - seg_start;
-    const long long row0 = P.rev ? (pb.N - seg_start - n) : seg_start;
+    const long long row0 = rev ? (pb.N - seg_start - n) : seg_start;
 
     Chain ch;
     const size_t first_row = (size_t)chain * (size_t)pb.N + (size_t)row0;
     const size_t ab_off = first_row * DR * 2;           // A, B: DR features per token
     const size_t chain_off = first_row * DC * 2;        // C, out (U, Y): DC features per token
     const size_t col_off = (size_t)split * DV * 2;
-    ch.a = (const char*)P.a + ab_off;
-    ch.b = (const char*)P.b + ab_off;
-    ch.c = (const char*)P.c + chain_off + col_off;
-    ch.out = P.out ? (char*)P.out + chain_off + col_off : nullptr;
-    ch.gate = GATED ? (const char*)P.gate + chain_off : nullptr;
-    ch.y = GATED ? (char*)P.gated_out + chain_off : nullptr;
-    ch.eps = P.eps;
-    ch.state_in = P.state_in ? P.state_in + (size_t)vchain * DR * DC + (size_t)split * DV : nullptr;
-    ch.state_out = P.state_out ? P.state_out + (size_t)vchain * DR * DC + (size_t)split * DV : nullptr;
+    ch.a = a + ab_off;
+    ch.b = b + ab_off;
+    ch.c = c + chain_off + col_off;
+    ch.out = out ? out + chain_off + col_off : nullptr;
+    ch.gate = GATED ? (const char*)P0.gate + chain_off : nullptr;       // (the gated epilogue is one pass)
+    ch.y = GATED ? (char*)P0.gated_out + chain_off : nullptr;
+    ch.eps = P0.eps;
+    ch.state_in = state_in ? state_in + (size_t)vchain * DR * DC + (size_t)split * DV : nullptr;
+    ch.state_out = state_out ? state_out + (size_t)vchain * DR * DC + (size_t)split * DV : nullptr;
     ch.N = n;
     ch.T = (int)((n + kBlock - 1) / kBlock);
     ch.last_valid = (int)(n - (long long)(ch.T - 1) * kBlock);
-    ch.rev = P.rev;
-    ch.lam = pb.decay[chain % pb.H];
+    ch.rev = rev;
+    ch.lam = lam;
 
     if constexpr (DR != D || Cfg<D, DV>::CW != DV) {
         // Tiles wider than the tensors' rows: their loads leave the surplus chunks alone, which
@@ -887,11 +926,11 @@ __device__ __forceinline__ void pass_body(const PassBatch& pb, int nsplit, int x
 
 template <int D, int DV, int MODE, int DC = D, int DR = D>
 __global__ __launch_bounds__(kThreads)
-void pass_bf16_kernel(const PassBatch pb, const int nsplit, const int xcd_ids) {
+void pass_bf16_kernel(const PassBatch pb, const int xcd_ids) {
     __shared__ __attribute__((aligned(1024))) char smem[Cfg<D, DV>::PASS_TOTAL];
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // scalar: role dispatch is a uniform branch
-    pass_body<D, DV, DC, MODE, DR>(pb, nsplit, xcd_ids, blockIdx.x, smem, lds_address(smem), wave, tid & 63);
+    pass_body<D, DV, DC, MODE, DR>(pb, xcd_ids, blockIdx.x, smem, lds_address(smem), wave, tid & 63);
 }
 
 template <int D, int DV, int MODE = kPlain, int DC = D, int DR = D>
@@ -904,7 +943,7 @@ hipError_t launch_t(const PassBatch& pb, hipStream_t stream) {
     const int per_chain = pb.count * nsplit;
     const long long wgs = launch_chain_slots(nch, per_chain) * per_chain;
     if (wgs <= 0 || wgs > 0x7fffffffLL || pb.segs < 1) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((pass_bf16_kernel<D, DV, MODE, DC, DR>), dim3((unsigned)wgs), dim3(kThreads), 0, stream, pb, nsplit,
+    hipLaunchKernelGGL((pass_bf16_kernel<D, DV, MODE, DC, DR>), dim3((unsigned)wgs), dim3(kThreads), 0, stream, pb,
                        (int)xcd_ids_fit(nch, per_chain));
     return hipGetLastError();
 }
