@@ -98,9 +98,12 @@ struct Cfg {
 
 // MODE of a workgroup: the plain pass, the pass with the gated epilogue, or the
 // state-only sweep of the sequence-parallel form (no outputs: only the segment's end state).
-// kGatedLate: the gated epilogue with the gate values fetched within the block that uses them.
-enum { kPlain = 0, kGated = 1, kStateOnly = 2, kGatedLate = 3 };
-constexpr bool has_gate(int mode) { return mode == kGated || mode == kGatedLate; }
+// The gated epilogue's values are fetched one block ahead of their use, within the block that uses them
+// (kGatedLate) or two ahead (kGatedFar).
+enum { kPlain = 0, kGated = 1, kStateOnly = 2, kGatedLate = 3, kGatedFar = 4 };
+constexpr bool has_gate(int mode) { return mode == kGated || mode == kGatedLate || mode == kGatedFar; }
+// blocks ahead
+constexpr int gate_ahead(int mode) { return mode == kGated ? 1 : (mode == kGatedFar ? 2 : 0); }
 
 
 // Register prefetch loads of the AREG output waves are issued from inline assembly and
@@ -208,7 +211,7 @@ struct ReadOffs {
 //   y = o / sqrt(mean(o^2) + eps) (.) u, is applied before anything is stored; gate/yout are
 //   this lane's addresses in U and Y (same position as out), out may be null.
 //   uq (GATED): the gate values of this lane's token, loads issued by the caller from assembly
-//   at the end of the block before; GWAIT = the VMEM operations the wave issued after them.
+//   earlier; GWAIT = the VMEM operations the wave issued after them.
 template <int D, int DV, int W, int CCOLS, bool GATED = false, int DROW = D, int GWAIT = 0>
 __device__ __forceinline__ void output_pass(const char* btile, const char* ctile, const char* scopy,
                                             const Frag (&Af)[D / 32], const OutConsts<W>& k,
@@ -446,11 +449,12 @@ struct Chain {            // what every wave of the workgroup knows about its pr
 // "Block blk + 1 has landed" for a wave that issues, per block and in this order, L tile loads
 // (for block blk + PST - 1), S stores and, AHEAD, G gate loads (for block blk + 1), after PST - 1
 // blocks' tile loads and G gate loads up front; not AHEAD: G gate loads (for block blk) before the
-// tile loads, none up front.  The operations it issued after that block's tile loads:
-template <int PST, int L, int S, int G, bool AHEAD>
+// tile loads, none up front; AHEAD = 2: G gate loads (for block blk + 2) last, and two blocks' up front before
+// any tile.  The operations it issued after that block's tile loads:
+template <int PST, int L, int S, int G, int AHEAD>
 __device__ __forceinline__ void wait_block(int blk) {
-    static_assert(PST >= 2 && PST <= 4, "ring depths");
-    constexpr int X = AHEAD ? G : 0;
+    static_assert(PST >= 2 && PST <= 4 && (AHEAD < 2 || PST == 4), "ring depths");
+    constexpr int X = AHEAD == 1 ? G : 0;
     if constexpr (PST == 2) {
         wait_dma<S + X>();
     } else if constexpr (PST == 3) {
@@ -458,14 +462,15 @@ __device__ __forceinline__ void wait_block(int blk) {
     } else {
         if (blk == 0) wait_dma<2 * L + S + G + X>();
         else if (blk == 1) wait_dma<2 * L + 2 * S + 2 * G + X>();
-        else wait_dma<2 * L + 3 * S + 2 * G + X>();
+        else wait_dma<2 * L + 3 * S + 2 * G + (AHEAD == 2 ? G : X)>();
     }
 }
 
 template <int D, int DV, int DC, int W, int MODE, int DR>
 __device__ __forceinline__ void pass_output_wave(const Chain& ch, char* smem, unsigned lds0, int lane) {
     using C = Cfg<D, DV>;
-    constexpr bool GATED = has_gate(MODE), AHEAD = MODE == kGated;
+    constexpr bool GATED = has_gate(MODE);
+    constexpr int AHEAD = gate_ahead(MODE);
     constexpr bool SO = MODE == kStateOnly;          // nothing to produce: tile loads and barriers only
     constexpr int KS = C::KS;
     constexpr long long ROW = DC * 2;      // the output's row (and U's, Y's)
@@ -522,6 +527,27 @@ __device__ __forceinline__ void pass_output_wave(const Chain& ch, char* smem, un
             else wait_block<C::PST, L, S, G, AHEAD>(blk);
         }
     };
+    // this lane's token row (16W + i16) of block 0
+    const int g = lane >> 4, i16 = lane & 15;
+    const long long r0 = ch.rev ? (ch.N - 1 - (16 * W + i16)) : (long long)(16 * W + i16);
+    const long long lane_off = r0 * ROW + (8 * g) * 2;
+    const char* pu = GATED ? ch.gate + lane_off : nullptr;
+    u32x4 uq[GATED ? G : 1], uq1[AHEAD == 2 ? G : 1];
+#pragma unroll
+    for (int p = 0; p < (GATED ? G : 1); ++p) uq[p] = u32x4{0, 0, 0, 0};
+    // AHEAD = 2: the gate values of this lane's token in block b, or of the last token past the end: every
+    // load by all lanes, so that all of them count.
+    auto load_gate2 = [&](u32x4* u, int b) {
+        const long long r = 64LL * b + 16 * W + i16, last = ch.N - 1;
+        const char* p = ch.gate + (r < last ? r : last) * ROW + 16 * g;
+        static_for<AHEAD == 2 ? G : 0>([&](auto i) { gload16(u[decltype(i)::value], p + 64 * decltype(i)::value); });
+    };
+    if constexpr (AHEAD == 2) {
+#pragma unroll
+        for (int p = 0; p < G; ++p) uq1[p] = u32x4{0, 0, 0, 0};
+        load_gate2(uq, 0);
+        load_gate2(uq1, 1);
+    }
     if constexpr (ISSUER) {                // blocks 0 .. PST-2 in flight
 #pragma unroll
         for (int b = 0; b < C::PST - 1; ++b) fetch(b, b);
@@ -545,21 +571,13 @@ __device__ __forceinline__ void pass_output_wave(const Chain& ch, char* smem, un
         return;
     }
 
-    const int g = lane >> 4, i16 = lane & 15;
     OutConsts<W> k;
     k.init(ch.lam, g, i16);
     ReadOffs<D, DV, C::CW> ro;
     ro.init(g, i16, 0);
 
-    // this lane's token row (16W + i16) of block 0
-    const long long r0 = ch.rev ? (ch.N - 1 - (16 * W + i16)) : (long long)(16 * W + i16);
-    const long long lane_off = r0 * ROW + (8 * g) * 2;
     char* po = ch.out ? ch.out + lane_off : nullptr;
-    const char* pu = GATED ? ch.gate + lane_off : nullptr;
     char* py = GATED ? ch.y + lane_off : nullptr;
-    u32x4 uq[GATED ? G : 1];
-#pragma unroll
-    for (int p = 0; p < (GATED ? G : 1); ++p) uq[p] = u32x4{0, 0, 0, 0};
     // Gate values of this lane's token in block b (b = 0, 1, 2, ... in turn), by the lanes whose
     // token exists: none past the last block.
     const unsigned long long last_rows = __ballot(16 * W + i16 < ch.last_valid);
@@ -570,15 +588,16 @@ __device__ __forceinline__ void pass_output_wave(const Chain& ch, char* smem, un
     };
     // Block 0 landed; the constants above were computed meanwhile.
     if constexpr (ISSUER) wait_dma<(C::PST - 2) * L>();
-    if constexpr (AHEAD) load_gate(0);
+    else if constexpr (AHEAD == 2) wait_dma<0>();          // (the gate values of blocks 0 and 1; issuers': older than the tiles)
+    if constexpr (AHEAD == 1) load_gate(0);
 
     __syncthreads();                       // block 0 tiles and the initial state copy are in LDS
     int stage = 0;
-    for (int blk = 0; blk < ch.T; ++blk) {
+    auto block = [&](int blk, u32x4* u) __attribute__((always_inline)) {
         const bool more = blk + 1 < ch.T;
         const bool row_ok = (16 * W + i16) < ((blk + 1 == ch.T) ? ch.last_valid : kBlock);
         const long long bo = (long long)blk * step;
-        if constexpr (GATED && !AHEAD) load_gate(blk);
+        if constexpr (GATED && AHEAD == 0) load_gate(blk);
         if constexpr (ISSUER) {
             int fs = stage + C::PST - 1;   // stage of block blk + PST - 1 (free since the last barrier)
             if (fs >= C::PST) fs -= C::PST;
@@ -589,20 +608,30 @@ __device__ __forceinline__ void pass_output_wave(const Chain& ch, char* smem, un
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) Af[ks].u = *(const u32x4*)(st + (16 * W) * C::F::RB + ro.row[ks]);
         // with more blocks to come every lane stores (the count above relies on it)
-        output_pass<D, DV, W, C::CW, GATED, DC, L>(st + C::BOFF, st + C::COFF,
+        output_pass<D, DV, W, C::CW, GATED, DC, AHEAD == 2 ? 2 * L + S + G : L>(st + C::BOFF, st + C::COFF,
                                             smem + C::P_SB + (blk & 1) * C::SBYTES, Af, k, ro,
                                             po ? po + bo : nullptr, more || row_ok,
-                                            uq, GATED ? py + bo : nullptr, ch.eps);
+                                            u, GATED ? py + bo : nullptr, ch.eps);
         // The next block's gate values: a whole block ahead of their use, in the registers
         // this block's values have just left (and, like every such load, on every path).  Issued at
         // the start of the block that uses them they arrived after its products were done: 2.3 us
         // a block of 128 features against 1.35 without the gate (32 chains; now 1.75).
-        if constexpr (AHEAD) load_gate(blk + 1);
+        if constexpr (AHEAD == 1) load_gate(blk + 1);
+        if constexpr (AHEAD == 2) load_gate2(u, blk + 2);
         if (more) {
             wait_next(blk);
             __syncthreads();
         }
         stage = (stage + 1 == C::PST) ? 0 : stage + 1;
+    };
+    if constexpr (AHEAD == 2) {            // (each register set is one variable, loaded in place)
+        for (int blk = 0; blk < ch.T; blk += 2) {
+            block(blk, uq);
+            if (blk + 1 < ch.T) block(blk + 1, uq1);
+        }
+        wait_gate<0, G>(uq1);
+    } else {
+        for (int blk = 0; blk < ch.T; ++blk) block(blk, uq);
     }
     if constexpr (AHEAD) wait_gate<0, G>(uq);   // the last prefetch was never consumed: retire it before its registers die
     if constexpr (ISSUER) wait_dma<0>();   // nothing may land in LDS after this workgroup is gone
@@ -991,6 +1020,13 @@ hipError_t launch_pass_bf16(const PassBatch& pb, int D, int dv, hipStream_t stre
         // calls of 10 us, which the host bounds, scatter by 5 %).
         if (D == 128 && pb.p[0].out) return launch_t<128, 128, kGatedLate>(pb, stream);
         if (D == 128) return launch_t<128, 128, kGated>(pb, stream);
+        // 64 features: a block takes 0.55 us and its gate loads longer once the chip is busy, so two ahead
+        // from 128 whole chains on, 192 with O (one ahead and two: 128 x 1000 20.3 and 18.7, 128 x 3000 47.9 and
+        // 44.3, 512 x 200 19.2 and 17.8, 512 x 200 with O 20.7 and 19.5).  The loop is twice as long then, for two
+        // sets of registers, and costs up to 2.5 % where nothing is gained (128 x 200 with O 8.0 and 8.2, 32 x
+        // 200 with O 7.5 and 7.7, 32 x 3000 in segments 22.8 and 23.3).  Wider heads have no registers for it.
+        if (D == 64 && pb.segs == 1 && pb.N > kBlock && pb.chains >= (pb.p[0].out ? 192 : 128))
+            return launch_t<64, 64, kGatedFar>(pb, stream);
         if (D == 64) return launch_t<64, 64, kGated>(pb, stream);
         return hipErrorInvalidValue;
     }

@@ -57,3 +57,19 @@ def test_unequal_widths(Dk, N):
     for n, x, r in zip(("dQ", "dK", "dV"), ltn.ltn_attn_bwd_dkdv(*gpu(q, k, v, g, decay)),
                        orc.bwd_recurrent_dkdv(q, k, v, g, decay)):
         check(n, x, r, TOL[BF])
+
+
+@pytest.mark.parametrize("chains,store_o", [(127, False), (128, False), (191, True), (192, True)])
+@pytest.mark.parametrize("N", [65, 449])
+def test_gate_values_on_both_sides_of_the_line(chains, store_o, N):
+    # heads of 64 features: gate values fetched one block ahead, and two from so many chains on
+    q, k, v = synth.make_qkv(1, chains, N, 64, BF, 760 + N)
+    u = synth.make_gate(1, chains, N, 64, BF, 760 + N)
+    decay = mixed_decay(chains)
+    kv0 = torch.randn(1, chains, 64, 64, generator=torch.Generator().manual_seed(N)) / 64
+    o_ref, kv_ref = orc.fwd_recurrent(q, k, v, decay, kv_in=kv0, return_state=True)
+    y_ref = orc.gate_fwd(o_ref, u, eps=1e-6)
+    _, y, kv = ltn.ltn_attn_fwd_gated(*gpu(q, k, v, u, decay), eps=1e-6, kv_in=kv0.cuda(), return_state=True,
+                                      store_o=store_o)
+    check("Y", y, y_ref, TOL[BF])
+    check("kv", kv, kv_ref, TOL[BF])
