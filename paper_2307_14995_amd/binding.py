@@ -2,8 +2,8 @@
 
 Every function has the name and meaning of the C entry point in include/ltn_attn.h.  The hot ones
 hand their arguments to the native marshalling (_ltn_torch.so, csrc/ltn_torch.cpp) first, which does
-the plain case and returns None for any other; what follows in Python then raises the error or does
-the unusual thing.  A call of one launch took 7.4 to 11.2 us in Python and ctypes.
+the plain case, raises if its launch fails and returns None for any other; what follows in Python then raises
+the error or does the unusual thing.  A call of one launch took 7.4 to 11.2 us in Python and ctypes.
 PyTorch is used for device memory and the current HIP stream; all arithmetic of the
 attention path runs inside the library's kernels.
 """
@@ -125,7 +125,7 @@ def _bind_native(lib) -> None:
     spec = importlib.util.spec_from_file_location(name, path, loader=importlib.machinery.ExtensionFileLoader(name, path))
     module = importlib.util.module_from_spec(spec)
     spec.loader.exec_module(module)
-    module.bind(*(ctypes.cast(getattr(lib, f), ctypes.c_void_p).value for f in _NATIVE_ORDER))
+    module.bind(LtnError, *(ctypes.cast(getattr(lib, f), ctypes.c_void_p).value for f in _NATIVE_ORDER))
     _native = module
 
 

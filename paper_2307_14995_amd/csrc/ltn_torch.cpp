@@ -4,9 +4,11 @@
 //
 // Every function takes the arguments of its namesake in binding.py, in order, and returns its result,
 // or None for whatever is not the plain case (a wrong shape, type or device, a tensor subclass, an
-// active function mode, an error code of the library): the caller then takes the Python path, which
-// raises the error or does the unusual thing.  The library reports errors before it launches
-// anything, so a call that returned None has had no effect.
+// active function mode, an argument that the library refuses): the caller then takes the Python path,
+// which raises the error or does the unusual thing.  The library refuses arguments before it launches
+// anything, so a call that returned None has had no effect.  A launch that fails is another matter: a
+// state updated in place may have moved by then (the runtime also reports, with the next launch, an error
+// that something else left in the thread), so that status is raised here and the call is not made again.
 #include <c10/hip/HIPFunctions.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
@@ -37,8 +39,16 @@ struct Library {
     decltype(&ltn_prologue_workspace_bytes) prologue_workspace_bytes;
 } lib = {};
 
+PyObject* error_type = nullptr;            // binding.py's LtnError
+
 // Thrown where the plain case ends; becomes None.
 struct NotPlain {};
+
+// Thrown with a status that may have come after a launch; becomes an LtnError.
+struct Failed {
+    const char* where;
+    ltn_status status;
+};
 
 void need(bool ok) {
     if (!ok) throw NotPlain{};
@@ -154,12 +164,19 @@ at::Tensor new_state(std::array<int64_t, 4> shape, const at::Tensor& like) {
 }
 
 template <class F>
-void call(F&& f) {                         // as ctypes does: the interpreter is not held meanwhile
+void call(const char* where, F&& f) {      // as ctypes does: the interpreter is not held meanwhile
     ltn_status s;
     Py_BEGIN_ALLOW_THREADS
     s = f();
     Py_END_ALLOW_THREADS
-    need(s == LTN_OK);
+    switch (s) {
+        case LTN_OK: return;
+        case LTN_ERR_NULL:                 // found before any launch
+        case LTN_ERR_SHAPE:
+        case LTN_ERR_UNSUPPORTED:
+        case LTN_ERR_ALIGN: throw NotPlain{};
+        default: throw Failed{where, s};
+    }
 }
 
 void* at_or_null(const at::Tensor& t) { return t.defined() ? t.data_ptr() : nullptr; }
@@ -203,7 +220,7 @@ PyObject* fwd(const Args& x) {
     else if (want) kv.make(new_state(state, q));
     const size_t n = lib.workspace_bytes(d.Bt, d.H, d.N, d.D, block, dt, 0);
     const at::Tensor ws = scratch(n, q);
-    call([&] {
+    call("ltn_attn_fwd", [&] {
         return lib.fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.ptr, decay, kv_in, (float*)kv.ptr, d.Bt, d.H, d.N, d.D,
                        block, dt, at_or_null(ws), n, x.stream());
     });
@@ -233,7 +250,7 @@ PyObject* fwd_gated(const Args& x) {
     else if (want) kv.make(new_state(state, q));
     const size_t n = lib.workspace_bytes(d.Bt, d.H, d.N, d.D, block, dt, 2);
     const at::Tensor ws = scratch(n, q);
-    call([&] {
+    call("ltn_attn_fwd_gated", [&] {
         return lib.fwd_gated(q.data_ptr(), k.data_ptr(), v.data_ptr(), u.data_ptr(), o.ptr, y.ptr, decay, kv_in,
                              (float*)kv.ptr, eps, d.Bt, d.H, d.N, d.D, block, dt, at_or_null(ws), n, x.stream());
     });
@@ -259,7 +276,7 @@ PyObject* bwd(const Args& x) {
     for (Out* o : {&dq, &dk, &dv}) o->make(at::empty_like(q));
     const size_t n = lib.workspace_bytes(d.Bt, d.H, d.N, d.D, block, dt, 1);
     const at::Tensor ws = scratch(n, q);
-    call([&] {
+    call("ltn_attn_bwd", [&] {
         return lib.bwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), g.data_ptr(), dq.ptr, dk.ptr, dv.ptr, decay, d.Bt, d.H,
                        d.N, d.D, block, dt, at_or_null(ws), n, x.stream());
     });
@@ -278,7 +295,7 @@ PyObject* gate_bwd(const Args& x) {
     const int D = (int)t.size(-1);
     Out dx, du;
     for (Out* o : {&dx, &du}) o->make(at::empty_like(t));
-    call([&] {
+    call("ltn_gate_bwd", [&] {
         return lib.gate_bwd(t.data_ptr(), u.data_ptr(), g.data_ptr(), dx.ptr, du.ptr, eps, t.numel() / D, D, dt, x.stream());
     });
     const Out* r[] = {&dx, &du};
@@ -297,7 +314,7 @@ PyObject* decode(const Args& x, bool several) {
     need(kv.scalar_type() == at::kFloat && kv.sizes() == at::IntArrayRef({Bt, H, D, D}));
     const float* decay = x.decay(4, H);
     const Out o(x, 5, q);
-    call([&] {
+    call(several ? "ltn_attn_decode_steps" : "ltn_attn_decode_step", [&] {
         return lib.decode_steps(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.ptr, (float*)kv.data_ptr(), decay, (int)Bt, (int)H,
                                 (int)S, (int)D, dt, x.stream());
     });
@@ -334,7 +351,7 @@ PyObject* fwd_dkdv(const Args& x) {
     else if (want) kv.make(new_state(state, q));
     const size_t n = lib.workspace_bytes_dkdv(d.Bt, d.H, d.N, d.D, d.Dv, d.dt, 0);
     const at::Tensor ws = scratch(n, q);
-    call([&] {
+    call("ltn_attn_fwd_dkdv", [&] {
         return lib.fwd_dkdv(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.ptr, decay, kv_in, (float*)kv.ptr, d.Bt, d.H, d.N,
                             d.D, d.Dv, block, d.dt, at_or_null(ws), n, x.stream());
     });
@@ -356,7 +373,7 @@ PyObject* bwd_dkdv(const Args& x) {
     dv.make(at::empty_like(v));
     const size_t n = lib.workspace_bytes_dkdv(d.Bt, d.H, d.N, d.D, d.Dv, d.dt, 1);
     const at::Tensor ws = scratch(n, q);
-    call([&] {
+    call("ltn_attn_bwd_dkdv", [&] {
         return lib.bwd_dkdv(q.data_ptr(), k.data_ptr(), v.data_ptr(), g.data_ptr(), dq.ptr, dk.ptr, dv.ptr, decay, d.Bt, d.H,
                             d.N, d.D, d.Dv, block, d.dt, at_or_null(ws), n, x.stream());
     });
@@ -371,7 +388,7 @@ PyObject* decode_steps_dkdv(const Args& x) {
     need(d.N <= INT32_MAX && kv.scalar_type() == at::kFloat && kv.sizes() == at::IntArrayRef({d.Bt, d.H, d.D, d.Dv}));
     const float* decay = x.decay(4, d.H);
     const Out o(x, 5, v);
-    call([&] {
+    call("ltn_attn_decode_steps_dkdv", [&] {
         return lib.decode_steps_dkdv(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.ptr, (float*)kv.data_ptr(), decay, d.Bt, d.H,
                                      (int)d.N, d.D, d.Dv, d.dt, x.stream());
     });
@@ -402,7 +419,7 @@ PyObject* prologue_fwd(const Args& x) {
         const at::Tensor& g = x.tensor(4);
         need(g.scalar_type() == t.scalar_type() && g.sizes() == at::IntArrayRef(shape));
     }
-    call([&] { return lib.prologue_fwd(t.data_ptr(), theta, y.ptr, act, d.Bt, d.H, d.N, d.D, pos0, dt, x.stream()); });
+    call("ltn_prologue_fwd", [&] { return lib.prologue_fwd(t.data_ptr(), theta, y.ptr, act, d.Bt, d.H, d.N, d.D, pos0, dt, x.stream()); });
     return y.object();
 }
 
@@ -421,7 +438,7 @@ PyObject* prologue_bwd(const Args& x) {
     if (want) dth.make(at::empty({d.H, d.D}, t.options().dtype(at::kFloat)));
     const size_t n = want ? lib.prologue_workspace_bytes(d.Bt, d.H, d.N, d.D) : 0;
     const at::Tensor ws = scratch(n, t);
-    call([&] {
+    call("ltn_prologue_bwd", [&] {
         return lib.prologue_bwd(t.data_ptr(), theta, g.data_ptr(), dx.ptr, (float*)dth.ptr, act, d.Bt, d.H, d.N, d.D, pos0,
                                 dt, at_or_null(ws), n, x.stream());
     });
@@ -436,20 +453,27 @@ PyObject* entry(PyObject*, PyObject* const* args, Py_ssize_t n) {
         return F(Args(args, n, N));
     } catch (const NotPlain&) {
         Py_RETURN_NONE;
+    } catch (const Failed& f) {
+        PyObject* e = PyObject_CallFunction(error_type, "is", (int)f.status, f.where);
+        if (e) {
+            PyErr_SetObject(error_type, e);
+            Py_DECREF(e);
+        }
+        return nullptr;
     }
     END_HANDLE_TH_ERRORS
 }
 
-// The addresses of the library's functions, in the order of Library.
+// The error class, then the addresses of the library's functions in the order of Library.
 PyObject* bind(PyObject*, PyObject* const* args, Py_ssize_t n) {
     constexpr Py_ssize_t want = sizeof(Library) / sizeof(void*);
-    if (n != want) {
-        PyErr_SetString(PyExc_TypeError, "one address per entry point");
+    if (n != 1 + want || !PyExceptionClass_Check(args[0])) {
+        PyErr_SetString(PyExc_TypeError, "an exception class and one address per entry point");
         return nullptr;
     }
     void* p[want];
-    for (Py_ssize_t i = 0; i < n; ++i) {
-        p[i] = PyLong_AsVoidPtr(args[i]);
+    for (Py_ssize_t i = 0; i < want; ++i) {
+        p[i] = PyLong_AsVoidPtr(args[1 + i]);
         if (!p[i]) {
             if (!PyErr_Occurred()) PyErr_SetString(PyExc_ValueError, "null entry point");
             return nullptr;
@@ -457,6 +481,8 @@ PyObject* bind(PyObject*, PyObject* const* args, Py_ssize_t n) {
     }
     static_assert(sizeof p == sizeof lib, "Library holds one function pointer per entry point");
     memcpy(&lib, p, sizeof lib);
+    Py_INCREF(args[0]);
+    Py_XSETREF(error_type, args[0]);
     Py_RETURN_NONE;
 }
 
