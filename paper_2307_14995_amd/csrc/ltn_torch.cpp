@@ -163,12 +163,20 @@ at::Tensor new_state(std::array<int64_t, 4> shape, const at::Tensor& like) {
     return at::empty(shape, like.options().dtype(at::kFloat));
 }
 
+// The interpreter is not held while one of these lives, and is again however its scope is left.
+struct Released {
+    PyThreadState* const state = PyEval_SaveThread();
+    ~Released() { PyEval_RestoreThread(state); }
+};
+
+// The library's call `f`, as ctypes makes it: without the interpreter.  `f` also asks the tensors for
+// their addresses, which may throw (a storage that refuses access, a lazy copy that finds no memory).
 template <class F>
-void call(const char* where, F&& f) {      // as ctypes does: the interpreter is not held meanwhile
-    ltn_status s;
-    Py_BEGIN_ALLOW_THREADS
-    s = f();
-    Py_END_ALLOW_THREADS
+void call(const char* where, F&& f) {
+    const ltn_status s = [&] {
+        const Released released;
+        return f();
+    }();
     switch (s) {
         case LTN_OK: return;
         case LTN_ERR_NULL:                 // found before any launch

@@ -45,13 +45,16 @@ def stand_in(monkeypatch):
     binding._bind_native(real)
 
 
-def entries():
-    """Every entry point that is marshalled natively, as a call of plain arguments."""
+def entries(refuse=False):
+    """Every entry point that is marshalled natively, as a call of plain arguments; `refuse`: with one
+    input whose storage refuses access."""
     q, k, v = synth.make_qkv(Bt, H, N, D, torch.bfloat16, 3)
     q, k, v, decay, theta = gpu(q, k, v, synth.decay_bench_rule(H), synth.make_theta(H, D, 3))
     w = torch.cat((q, k), -1)
     kv, kvw = torch.zeros(Bt, H, D, D, device="cuda"), torch.zeros(Bt, H, 2 * D, D, device="cuda")
     q1 = q[:, :, 0].contiguous()
+    for t in (q, w, q1) if refuse else ():
+        torch._C._set_throw_on_mutable_data_ptr(t)
     return {
         "ltn_attn_fwd": lambda: ltn.ltn_attn_fwd(q, k, v, decay, kv_in=kv, kv_out=kv),
         "ltn_attn_fwd_gated": lambda: ltn.ltn_attn_fwd_gated(q, k, v, q, decay, kv_in=kv, kv_out=kv),
@@ -86,3 +89,11 @@ def test_a_refused_argument_raises(stand_in, name):
     with pytest.raises(ltn.LtnError, match=name + ":") as e:
         call()
     assert e.value.code == 3
+
+
+@pytest.mark.parametrize("name", LAUNCHING)
+def test_an_input_without_an_address_raises(name):
+    # (found while the interpreter is released: it has to be held again before the error is raised)
+    with pytest.raises(RuntimeError, match="data pointer"):
+        entries(refuse=True)[name]()
+    entries()[name]()
