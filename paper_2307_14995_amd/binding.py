@@ -201,6 +201,15 @@ def _devs(names: str, *tensors) -> None:
                 _dev(u, n)
 
 
+def _out(t: torch.Tensor, what: str, numel: int, dtype: torch.dtype) -> torch.Tensor:
+    """A caller's output of `numel` elements of `dtype`.  The library is handed an address and cannot tell
+    how much memory is behind it.  The shape is the caller's affair: a flat or a longer buffer will do."""
+    _dev(t, what)
+    if t.dtype != dtype or t.numel() < numel:
+        raise ValueError(f"{what} must hold {numel} elements of {dtype}")
+    return t
+
+
 def _ptr(t):
     return None if t is None else t.data_ptr()
 
@@ -232,12 +241,14 @@ def ltn_attn_fwd(q, k, v, decay, kv_in=None, return_state=False, block=0, out=No
     Bt, H, N, D = q.shape
     if decay.dtype != torch.float32 or decay.numel() != H:
         raise ValueError("decay must be fp32 [H]")
-    o = torch.empty_like(q) if out is None else _dev(out, "out")
+    o = torch.empty_like(q) if out is None else _out(out, "out", q.numel(), q.dtype)
     if kv_in is not None:
         _dev(kv_in, "kv_in")
         if kv_in.dtype != torch.float32 or tuple(kv_in.shape) != (Bt, H, D, D):
             raise ValueError("kv_in must be fp32 [Bt,H,D,D]")
-    if kv_out is None and return_state:
+    if kv_out is not None:
+        _out(kv_out, "kv_out", Bt * H * D * D, torch.float32)
+    elif return_state:
         kv_out = torch.empty((Bt, H, D, D), dtype=torch.float32, device=q.device)
     code = _dtype_code(q.dtype)
     ws_bytes = int(lib.ltn_attn_workspace_bytes(Bt, H, N, D, block, code, 0))
@@ -288,13 +299,15 @@ def ltn_attn_fwd_gated(q, k, v, u, decay, eps=0.0, kv_in=None, return_state=Fals
     Bt, H, N, D = q.shape
     if decay.dtype != torch.float32 or decay.numel() != H:
         raise ValueError("decay must be fp32 [H]")
-    o = (torch.empty_like(q) if out is None else _dev(out, "out")) if store_o else None
-    y = torch.empty_like(q) if y_out is None else _dev(y_out, "y_out")
+    o = (torch.empty_like(q) if out is None else _out(out, "out", q.numel(), q.dtype)) if store_o else None
+    y = torch.empty_like(q) if y_out is None else _out(y_out, "y_out", q.numel(), q.dtype)
     if kv_in is not None:
         _dev(kv_in, "kv_in")
         if kv_in.dtype != torch.float32 or tuple(kv_in.shape) != (Bt, H, D, D):
             raise ValueError("kv_in must be fp32 [Bt,H,D,D]")
-    if kv_out is None and return_state:
+    if kv_out is not None:
+        _out(kv_out, "kv_out", Bt * H * D * D, torch.float32)
+    elif return_state:
         kv_out = torch.empty((Bt, H, D, D), dtype=torch.float32, device=q.device)
     code = _dtype_code(q.dtype)
     ws_bytes = int(lib.ltn_attn_workspace_bytes(Bt, H, N, D, block, code, 2))
@@ -320,7 +333,7 @@ def ltn_gate_fwd(x, u, eps=0.0, out=None):
     _dev(u, "u")
     if u.shape != x.shape or u.dtype != x.dtype:
         raise ValueError("x and u must share shape and dtype")
-    y = torch.empty_like(x) if out is None else _dev(out, "out")
+    y = torch.empty_like(x) if out is None else _out(out, "out", x.numel(), x.dtype)
     rc = _call(lib.ltn_gate_fwd, x.device, _ptr(x), _ptr(u), _ptr(y), float(eps), rows, D, _dtype_code(x.dtype))
     if rc != 0:
         raise LtnError(rc, "ltn_gate_fwd")
@@ -341,7 +354,7 @@ def ltn_gate_bwd(x, u, d_y, eps=0.0, out=None):
     if out is None:
         dx, du = torch.empty_like(x), torch.empty_like(x)
     else:
-        dx, du = (_dev(t, "out") for t in out)
+        dx, du = (_out(t, "out", x.numel(), x.dtype) for t in out)
     rc = _call(lib.ltn_gate_bwd, x.device, _ptr(x), _ptr(u), _ptr(d_y), _ptr(dx), _ptr(du), float(eps), rows, D,
                _dtype_code(x.dtype))
     if rc != 0:
@@ -367,7 +380,7 @@ def ltn_attn_bwd(q, k, v, d_o, decay, block=0, out=None):
     if out is None:
         dq, dk, dv = torch.empty_like(q), torch.empty_like(q), torch.empty_like(q)
     else:
-        dq, dk, dv = (_dev(t, "out") for t in out)
+        dq, dk, dv = (_out(t, "out", q.numel(), q.dtype) for t in out)
     code = _dtype_code(q.dtype)
     ws_bytes = int(lib.ltn_attn_workspace_bytes(Bt, H, N, D, block, code, 1))
     ws = _workspace(ws_bytes, q.device)
@@ -392,7 +405,7 @@ def ltn_attn_decode_step(q, k, v, kv, decay, out=None):
         raise ValueError("kv must be fp32 [Bt,H,D,D]")
     if decay.dtype != torch.float32 or decay.numel() != H:
         raise ValueError("decay must be fp32 [H]")
-    o = torch.empty_like(q) if out is None else _dev(out, "out")
+    o = torch.empty_like(q) if out is None else _out(out, "out", q.numel(), q.dtype)
     rc = _call(lib.ltn_attn_decode_step, q.device, _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(kv), _ptr(decay), Bt, H,
                D, _dtype_code(q.dtype))
     if rc != 0:
@@ -414,7 +427,7 @@ def ltn_attn_decode_steps(q, k, v, kv, decay, out=None):
         raise ValueError("kv must be fp32 [Bt,H,D,D]")
     if decay.dtype != torch.float32 or decay.numel() != H:
         raise ValueError("decay must be fp32 [H]")
-    o = torch.empty_like(q) if out is None else _dev(out, "out")
+    o = torch.empty_like(q) if out is None else _out(out, "out", q.numel(), q.dtype)
     rc = _call(lib.ltn_attn_decode_steps, q.device, _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(kv), _ptr(decay), Bt, H,
                S, D, _dtype_code(q.dtype))
     if rc != 0:
@@ -431,7 +444,7 @@ def ltn_attn_fwd_tiled(q, k, v, decay, out=None):
     Bt, H, N, D = q.shape
     if decay.dtype != torch.float32 or decay.numel() != H:
         raise ValueError("decay must be fp32 [H]")
-    o = torch.empty_like(q) if out is None else _dev(out, "out")
+    o = torch.empty_like(q) if out is None else _out(out, "out", q.numel(), q.dtype)
     rc = _call(lib.ltn_attn_fwd_tiled, q.device, _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(decay), Bt, H, N, D,
                _dtype_code(q.dtype))
     if rc != 0:
@@ -453,7 +466,7 @@ def ltn_attn_bwd_tiled(q, k, v, d_o, decay, out=None):
     if out is None:
         dq, dk, dv = torch.empty_like(q), torch.empty_like(q), torch.empty_like(q)
     else:
-        dq, dk, dv = (_dev(t, "out") for t in out)
+        dq, dk, dv = (_out(t, "out", q.numel(), q.dtype) for t in out)
     rc = _call(lib.ltn_attn_bwd_tiled, q.device, _ptr(q), _ptr(k), _ptr(v), _ptr(d_o), _ptr(dq), _ptr(dk), _ptr(dv),
                _ptr(decay), Bt, H, N, D, _dtype_code(q.dtype))
     if rc != 0:
@@ -553,12 +566,14 @@ def ltn_attn_fwd_dkdv(q, k, v, decay, kv_in=None, return_state=False, block=0, o
         return r
     lib = load_library()
     Bt, H, N, Dk, Dv = _check_dkdv(q, k, v, decay)
-    o = torch.empty_like(v) if out is None else _dev(out, "out")
+    o = torch.empty_like(v) if out is None else _out(out, "out", v.numel(), v.dtype)
     if kv_in is not None:
         _dev(kv_in, "kv_in")
         if kv_in.dtype != torch.float32 or tuple(kv_in.shape) != (Bt, H, Dk, Dv):
             raise ValueError("kv_in must be fp32 [Bt,H,Dk,Dv]")
-    if kv_out is None and return_state:
+    if kv_out is not None:
+        _out(kv_out, "kv_out", Bt * H * Dk * Dv, torch.float32)
+    elif return_state:
         kv_out = torch.empty((Bt, H, Dk, Dv), dtype=torch.float32, device=q.device)
     code = _dtype_code(q.dtype)
     ws_bytes = int(lib.ltn_attn_workspace_bytes_dkdv(Bt, H, N, Dk, Dv, code, 0))
@@ -601,7 +616,7 @@ def ltn_attn_decode_steps_dkdv(q, k, v, kv, decay, out=None):
     _dev(kv, "kv")
     if kv.dtype != torch.float32 or tuple(kv.shape) != (Bt, H, Dk, Dv):
         raise ValueError("kv must be fp32 [Bt,H,Dk,Dv]")
-    o = torch.empty_like(v) if out is None else _dev(out, "out")
+    o = torch.empty_like(v) if out is None else _out(out, "out", v.numel(), v.dtype)
     rc = _call(lib.ltn_attn_decode_steps_dkdv, q.device, _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(kv), _ptr(decay),
                Bt, H, S, Dk, Dv, _dtype_code(q.dtype))
     if rc != 0:

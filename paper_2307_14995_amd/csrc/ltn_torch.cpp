@@ -110,7 +110,8 @@ struct Args {
     void* stream() const { return c10::hip::getCurrentHIPStream(device).stream(); }
 };
 
-// An output: the caller's tensor, or a new one.
+// An output: the caller's tensor (of the right type and with enough elements, in whatever shape), or a new
+// one.
 struct Out {
     PyObject* given = nullptr;
     at::Tensor made;
@@ -118,15 +119,22 @@ struct Out {
     Out() = default;
     Out(const Args& args, int i, const at::Tensor& like) {
         if (args.none(i)) make(at::empty_like(like));
-        else take(args, i);
+        else take(args, i, like.scalar_type(), like.numel());
     }
     void make(at::Tensor t) {
         made = std::move(t);
         ptr = made.data_ptr();
     }
-    void take(const Args& args, int i) {
-        ptr = args.tensor(i).data_ptr();
+    void take(const Args& args, int i, at::ScalarType type, int64_t numel) {
+        const at::Tensor& t = args.tensor(i);
+        need(t.scalar_type() == type && t.numel() >= numel);
+        ptr = t.data_ptr();
         given = args.a[i];
+    }
+    // a state: the caller's, a new one when `want`, or none
+    void state(const Args& args, int i, bool want, const std::array<int64_t, 4>& shape, const at::Tensor& like) {
+        if (!args.none(i)) take(args, i, at::kFloat, shape[0] * shape[1] * shape[2] * shape[3]);
+        else if (want) make(at::empty(shape, like.options().dtype(at::kFloat)));
     }
     PyObject* object() const {             // a new reference
         if (!given) return THPVariable_Wrap(made);
@@ -157,10 +165,6 @@ struct Dims {
 
 at::Tensor scratch(size_t bytes, const at::Tensor& like) {
     return bytes ? at::empty({(int64_t)bytes}, like.options().dtype(at::kByte)) : at::Tensor();
-}
-
-at::Tensor new_state(std::array<int64_t, 4> shape, const at::Tensor& like) {
-    return at::empty(shape, like.options().dtype(at::kFloat));
 }
 
 // The interpreter is not held while one of these lives, and is again however its scope is left.
@@ -224,8 +228,7 @@ PyObject* fwd(const Args& x) {
     const int block = x.int32(6);
     const Out o(x, 7, q);
     Out kv;
-    if (!x.none(8)) kv.take(x, 8);
-    else if (want) kv.make(new_state(state, q));
+    kv.state(x, 8, want, state, q);
     const size_t n = lib.workspace_bytes(d.Bt, d.H, d.N, d.D, block, dt, 0);
     const at::Tensor ws = scratch(n, q);
     call("ltn_attn_fwd", [&] {
@@ -254,8 +257,7 @@ PyObject* fwd_gated(const Args& x) {
     const Out o = store_o ? Out(x, 10, q) : Out();
     const Out y(x, 11, q);
     Out kv;
-    if (!x.none(12)) kv.take(x, 12);
-    else if (want) kv.make(new_state(state, q));
+    kv.state(x, 12, want, state, q);
     const size_t n = lib.workspace_bytes(d.Bt, d.H, d.N, d.D, block, dt, 2);
     const at::Tensor ws = scratch(n, q);
     call("ltn_attn_fwd_gated", [&] {
@@ -355,8 +357,7 @@ PyObject* fwd_dkdv(const Args& x) {
     const int block = x.int32(6);
     const Out o(x, 7, v);
     Out kv;
-    if (!x.none(8)) kv.take(x, 8);
-    else if (want) kv.make(new_state(state, q));
+    kv.state(x, 8, want, state, q);
     const size_t n = lib.workspace_bytes_dkdv(d.Bt, d.H, d.N, d.D, d.Dv, d.dt, 0);
     const at::Tensor ws = scratch(n, q);
     call("ltn_attn_fwd_dkdv", [&] {
@@ -423,9 +424,8 @@ PyObject* prologue_fwd(const Args& x) {
     if (x.none(4)) {
         y.make(at::empty(shape, t.options()));
     } else {
-        y.take(x, 4);
-        const at::Tensor& g = x.tensor(4);
-        need(g.scalar_type() == t.scalar_type() && g.sizes() == at::IntArrayRef(shape));
+        y.take(x, 4, t.scalar_type(), 0);
+        need(x.tensor(4).sizes() == at::IntArrayRef(shape));
     }
     call("ltn_prologue_fwd", [&] { return lib.prologue_fwd(t.data_ptr(), theta, y.ptr, act, d.Bt, d.H, d.N, d.D, pos0, dt, x.stream()); });
     return y.object();
