@@ -47,7 +47,7 @@ def load_library():
         return _lib
     if not os.path.exists(_LIB_PATH):
         from .build import build_library
-        build_library(force=True)
+        build_library(force=True, marshalling=False)     # (its turn comes below)
     if not os.path.exists(_LIB_PATH):
         raise RuntimeError(f"{_LIB_PATH} is missing: build it with __graft_entry__.build()")
     lib = ctypes.CDLL(_LIB_PATH)
@@ -106,27 +106,42 @@ def load_library():
     return lib
 
 
-#: the entry points that _ltn_torch.so calls, in the order of its Library
-_NATIVE_ORDER = ("ltn_attn_fwd", "ltn_attn_fwd_gated", "ltn_attn_bwd", "ltn_gate_bwd", "ltn_attn_decode_steps",
-                 "ltn_attn_workspace_bytes", "ltn_attn_fwd_dkdv", "ltn_attn_bwd_dkdv", "ltn_attn_decode_steps_dkdv",
-                 "ltn_attn_workspace_bytes_dkdv", "ltn_prologue_fwd", "ltn_prologue_bwd", "ltn_prologue_workspace_bytes")
+class _Declines:
+    """In the place of the native marshalling where there is none: every call goes on in Python."""
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
+def _open_native(lib):
+    """The native marshalling (built first only if it is not there), with `lib`'s functions in its hands."""
+    import importlib.machinery
+    import importlib.util
+
+    from . import build
+    if not os.path.exists(build.TORCH_LIB):
+        build.build_marshalling()
+    name = __package__ + "._ltn_torch"
+    loader = importlib.machinery.ExtensionFileLoader(name, build.TORCH_LIB)
+    module = importlib.util.module_from_spec(importlib.util.spec_from_file_location(name, build.TORCH_LIB, loader=loader))
+    loader.exec_module(module)
+    if module.built_for != build.marshalling_id():       # (it would call through other prototypes than the library's)
+        raise RuntimeError(f"built for {module.built_for}, this is {build.marshalling_id()}")
+    module.bind(LtnError, *(ctypes.cast(getattr(lib, f), ctypes.c_void_p).value for f in module.entry_points))
+    return module
 
 
 def _bind_native(lib) -> None:
-    """Open the native marshalling (built first only if it is not there) and hand it `lib`'s functions."""
+    """Set _native.  Without a compiler or torch's headers, or beside another torch or header than it was built
+    with, calls are marshalled in Python and ctypes: the same calls of the same library, a few us each slower."""
     global _native
-    import importlib.machinery
-    import importlib.util
-    path = os.path.join(_PKG, "_ltn_torch.so")
-    if not os.path.exists(path):
-        from .build import build_marshalling
-        build_marshalling()
-    name = __package__ + "._ltn_torch"
-    spec = importlib.util.spec_from_file_location(name, path, loader=importlib.machinery.ExtensionFileLoader(name, path))
-    module = importlib.util.module_from_spec(spec)
-    spec.loader.exec_module(module)
-    module.bind(LtnError, *(ctypes.cast(getattr(lib, f), ctypes.c_void_p).value for f in _NATIVE_ORDER))
-    _native = module
+    try:
+        _native = _open_native(lib)
+    except Exception as e:
+        import warnings
+        warnings.warn(f"no native marshalling, calls cost a few us more; `python -m {__package__}.build` builds it "
+                      f"({type(e).__name__}: {e})", RuntimeWarning, stacklevel=3)
+        _native = _Declines()
 
 
 def _fast():

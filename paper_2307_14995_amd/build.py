@@ -11,9 +11,11 @@ code against torch's headers; it calls the library through addresses it is hande
 from __future__ import annotations
 
 import glob
+import hashlib
 import os
 import re
 import subprocess
+import sys
 from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -66,8 +68,23 @@ def _stale(target: str, deps) -> bool:
     return any(os.path.getmtime(d) > t for d in deps)
 
 
+def marshalling_id() -> str:
+    """What the native marshalling is built against: torch, the interpreter and the library's header."""
+    import torch
+    with open(os.path.join(ROOT, "include", "ltn_attn.h"), "rb") as f:
+        header = hashlib.sha256(f.read()).hexdigest()[:16]
+    return f"torch {torch.__version__} python {sys.version_info[0]}.{sys.version_info[1]} header {header}"
+
+
+def marshalling_is_stale() -> bool:
+    if _stale(TORCH_LIB, [TORCH_SRC] + _headers()):
+        return True
+    with open(TORCH_LIB, "rb") as f:
+        return marshalling_id().encode() not in f.read()
+
+
 def is_stale() -> bool:
-    return _stale(LIB, sources() + _headers()) or _stale(TORCH_LIB, [TORCH_SRC] + _headers())
+    return _stale(LIB, sources() + _headers()) or marshalling_is_stale()
 
 
 def check_resource_report(report: str) -> None:
@@ -102,41 +119,44 @@ def _compile(src: str, hipcc: str, verbose: bool, objdir: str = OBJ, extra=()) -
 
 
 def build_marshalling(verbose: bool = False) -> str:
-    """Compile the binding's native marshalling against the installed torch."""
+    """Compile the binding's native marshalling against the installed torch.  It takes its place in one
+    step: a process that starts meanwhile finds the old file, the new one or none, never half of one."""
     import sysconfig
 
     import torch
     root = os.path.dirname(torch.__file__)
     include, lib = os.path.join(root, "include"), os.path.join(root, "lib")
-    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+    tmp = f"{TORCH_LIB}.{os.getpid()}.tmp"
+    cmd = [os.environ.get("CXX", "g++"), f'-DLTN_BUILT_FOR="{marshalling_id()}"', "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-isystem", include,
            "-isystem", os.path.join(include, "torch", "csrc", "api", "include"), "-isystem", "/opt/rocm/include",
-           "-isystem", sysconfig.get_paths()["include"], TORCH_SRC, "-o", TORCH_LIB, "-L", lib, "-ltorch_python",
+           "-isystem", sysconfig.get_paths()["include"], TORCH_SRC, "-o", tmp, "-L", lib, "-ltorch_python",
            "-ltorch_cpu", "-lc10", "-lc10_hip"]
     if verbose:
         print(" ".join(cmd), flush=True)
-    res = subprocess.run(cmd, capture_output=True, text=True)
-    if res.returncode != 0:
-        raise RuntimeError(f"{cmd[0]} failed on {TORCH_SRC}:\n" + res.stdout + res.stderr)
+    try:
+        res = subprocess.run(cmd, capture_output=True, text=True)
+        if res.returncode != 0:
+            raise RuntimeError(f"{cmd[0]} failed on {TORCH_SRC}:\n" + res.stdout + res.stderr)
+        os.replace(tmp, TORCH_LIB)
+    finally:
+        if os.path.exists(tmp):
+            os.remove(tmp)
     return TORCH_LIB
 
 
-def build_library(force: bool = True, verbose: bool = False) -> str:
+def build_library(force: bool = True, verbose: bool = False, marshalling: bool = True) -> str:
     """Compile every HIP source for gfx950 (all of them when `force`, otherwise only those
-    older than a source or header), link the shared library, and build the marshalling beside it."""
+    older than a source or header), link the shared library, and build the marshalling beside it
+    (a failure there is raised once the library is complete)."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     os.makedirs(OBJ, exist_ok=True)
     srcs = sources()
     todo = [s for s in srcs if force or _stale(_obj_of(s), [s] + _headers())]
     jobs = int(os.environ.get("MAX_JOBS", "8") or 8)
     with ThreadPoolExecutor(max_workers=max(1, min(jobs, 16))) as pool:
-        if force or _stale(TORCH_LIB, [TORCH_SRC] + _headers()):
-            marshalling = pool.submit(build_marshalling, verbose)
-        else:
-            marshalling = None
+        beside = pool.submit(build_marshalling, verbose) if marshalling and (force or marshalling_is_stale()) else None
         list(pool.map(lambda s: _compile(s, hipcc, verbose), todo))
-        if marshalling:
-            marshalling.result()
     objs = [_obj_of(s) for s in srcs]
     if todo or _stale(LIB, objs):
         cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC"] + objs + ["-o", LIB]
@@ -145,6 +165,8 @@ def build_library(force: bool = True, verbose: bool = False) -> str:
         res = subprocess.run(cmd, capture_output=True, text=True)
         if res.returncode != 0:
             raise RuntimeError("link failed:\n" + res.stdout + res.stderr)
+    if beside:
+        beside.result()
     return LIB
 
 
@@ -180,5 +202,4 @@ def build_sanitized(verbose: bool = False) -> str:
 
 
 if __name__ == "__main__":
-    import sys
     print(build_library(force="--stale-only" not in sys.argv, verbose=True))

@@ -22,21 +22,18 @@
 
 namespace {
 
-// Entry points of the library that binding.py has opened (bind() below).
+// Entry points of the library that binding.py has opened (bind() below, in this order).
+#define LTN_LIBRARY(X)                                                                                           \
+    X(fwd, ltn_attn_fwd) X(fwd_gated, ltn_attn_fwd_gated) X(bwd, ltn_attn_bwd) X(gate_bwd, ltn_gate_bwd)         \
+    X(decode_steps, ltn_attn_decode_steps) X(workspace_bytes, ltn_attn_workspace_bytes)                          \
+    X(fwd_dkdv, ltn_attn_fwd_dkdv) X(bwd_dkdv, ltn_attn_bwd_dkdv)                                                \
+    X(decode_steps_dkdv, ltn_attn_decode_steps_dkdv) X(workspace_bytes_dkdv, ltn_attn_workspace_bytes_dkdv)      \
+    X(prologue_fwd, ltn_prologue_fwd) X(prologue_bwd, ltn_prologue_bwd)                                          \
+    X(prologue_workspace_bytes, ltn_prologue_workspace_bytes)
 struct Library {
-    decltype(&ltn_attn_fwd) fwd;
-    decltype(&ltn_attn_fwd_gated) fwd_gated;
-    decltype(&ltn_attn_bwd) bwd;
-    decltype(&ltn_gate_bwd) gate_bwd;
-    decltype(&ltn_attn_decode_steps) decode_steps;
-    decltype(&ltn_attn_workspace_bytes) workspace_bytes;
-    decltype(&ltn_attn_fwd_dkdv) fwd_dkdv;
-    decltype(&ltn_attn_bwd_dkdv) bwd_dkdv;
-    decltype(&ltn_attn_decode_steps_dkdv) decode_steps_dkdv;
-    decltype(&ltn_attn_workspace_bytes_dkdv) workspace_bytes_dkdv;
-    decltype(&ltn_prologue_fwd) prologue_fwd;
-    decltype(&ltn_prologue_bwd) prologue_bwd;
-    decltype(&ltn_prologue_workspace_bytes) prologue_workspace_bytes;
+#define LTN_FIELD(field, symbol) decltype(&symbol) field;
+    LTN_LIBRARY(LTN_FIELD)
+#undef LTN_FIELD
 } lib = {};
 
 PyObject* error_type = nullptr;            // binding.py's LtnError
@@ -472,7 +469,7 @@ PyObject* entry(PyObject*, PyObject* const* args, Py_ssize_t n) {
     END_HANDLE_TH_ERRORS
 }
 
-// The error class, then the addresses of the library's functions in the order of Library.
+// The error class, then the addresses of the functions that `entry_points` names.
 PyObject* bind(PyObject*, PyObject* const* args, Py_ssize_t n) {
     constexpr Py_ssize_t want = sizeof(Library) / sizeof(void*);
     if (n != 1 + want || !PyExceptionClass_Check(args[0])) {
@@ -505,4 +502,24 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_ltn_torch", nullptr, -1, methods,
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__ltn_torch(void) { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__ltn_torch(void) {
+    PyObject* m = PyModule_Create(&module);
+    if (!m) return nullptr;
+    PyObject* names = PyTuple_New(sizeof(Library) / sizeof(void*));
+    bool ok = names != nullptr;
+    Py_ssize_t i = 0;
+#define LTN_NAME(field, symbol)                                \
+    if (ok) {                                                  \
+        PyObject* s = PyUnicode_FromString(#symbol);           \
+        ok = s != nullptr;                                     \
+        if (ok) PyTuple_SET_ITEM(names, i++, s);               \
+    }
+    LTN_LIBRARY(LTN_NAME)
+#undef LTN_NAME
+    // (LTN_BUILT_FOR: torch, the interpreter and the library's header, compared when the module is opened)
+    ok = ok && PyModule_AddObjectRef(m, "entry_points", names) == 0 &&
+         PyModule_AddStringConstant(m, "built_for", LTN_BUILT_FOR) == 0;
+    Py_XDECREF(names);
+    if (!ok) Py_CLEAR(m);
+    return m;
+}
