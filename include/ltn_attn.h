@@ -229,7 +229,7 @@ ltn_status ltn_attn_decode_step(const void* q, const void* k, const void* v, voi
  *   q, k, v in : device, [Bt,H,S,D] dtype     o out: device, [Bt,H,S,D] dtype
  *   kv  in/out : device, [Bt,H,D,D] fp32      S == 0 is a successful no-op
  * All arithmetic is fp32 whatever `dtype` is, and the result is bit for bit that of S
- * single-token calls.  The loop is bound by its fp32 multiply-adds from about 8 tokens per
+ * single-token calls; a sequence's does not depend on how many others are in the call.  The loop is bound by its fp32 multiply-adds from about 8 tokens per
  * call on: a caller with more tokens per sequence than that (bf16 tensors) gets the same
  * state and outputs, to rounding, faster from ltn_attn_fwd(q, k, v, o, ..., kv_in = kv,
  * kv_out = kv, N = S), which evaluates the S iterations blockwise with bf16 MFMA

@@ -33,6 +33,14 @@ __device__ __forceinline__ unsigned short f32_to_bf16_bits(float f) {   // round
     return (unsigned short)(u >> 16);
 }
 
+// Order of an output's sum, the same in both kernels below, so that a sequence's output does not depend on
+// how many others are in the call: rows in DK / 8 classes (row mod DK / 8) of eight, each summed in the
+// rows' order; the classes pairwise, neighbours first, in groups of eight (96 features: in threes); the
+// groups one after another.  A thread here has adjacent classes, whose queries and keys are one 16-byte
+// read.  One token, us a call, sums over every fourth or eighth row a thread as before, and so: 128 x 128, 400 / 2048
+// chains 10.2 / 56.2 and 9.9 / 55.6, 256 x 128, 3000 chains 148.8 and 146.6, 96 x 96, 1024 chains 12.8 and 12.9,
+// 256 x 256, 2048 chains 204 and 206.  Classes that lie apart, so that a wave reads adjacent rows: 10.0 /
+// 55.8, 146.9, 12.9 and 206.
 template <int DK, int DV, bool BF16>
 __global__ __launch_bounds__(threads_for(DK, DV))
 void decode_kernel(const void* __restrict__ q, const void* __restrict__ k, const void* __restrict__ v,
@@ -41,19 +49,23 @@ void decode_kernel(const void* __restrict__ q, const void* __restrict__ k, const
     constexpr int kThreads = threads_for(DK, DV);
     constexpr int TX = DV / 4;            // threads across one state row (float4 each)
     constexpr int TY = kThreads / TX;     // rows in flight per sweep
-    constexpr int IT = DK / TY;           // sweeps
-    static_assert(kThreads >= DK && kThreads >= DV && kThreads % TX == 0 && DK % TY == 0, "thread layout");
-    __shared__ float qs[DK], ks[DK], vs[DV];
+    constexpr int IT = DK / TY;           // rows of a thread
+    constexpr int CL = DK / 8, G = CL / TY;   // classes, and those of a thread: G ty .. G ty + G - 1
+    constexpr int PG = G == 3 ? 1 : 8 / G;    // threads whose partial sums make a group's
+    static_assert(kThreads >= DK && kThreads >= DV && kThreads % TX == 0 && IT == 8 * G && CL == G * TY &&
+                  (G == 3 || 8 % G == 0) && TY % PG == 0, "thread layout");
+    __shared__ __attribute__((aligned(16))) float qs[DK], ks[DK], vs[DV];
     __shared__ float4 part[TY][TX];
 
     const int chain = blockIdx.x;
     const int tid = threadIdx.x;
     const float lam = decay[chain % H];
     const int tx = tid % TX, ty = tid / TX;
-    float4* S = (float4*)(kv + (size_t)chain * DK * DV);
+    float4* S = (float4*)(kv + (size_t)chain * DK * DV) + G * ty * TX + tx;     // row G ty, and from there:
+    auto row = [](int it) { return CL * (it / G) + it % G; };
     float4 s[IT];
 #pragma unroll
-    for (int it = 0; it < IT; ++it) s[it] = S[(size_t)(ty + TY * it) * TX + tx];
+    for (int it = 0; it < IT; ++it) s[it] = S[row(it) * TX];
 
     for (int step = 0; step < steps; ++step) {
         if (tid < DK) {
@@ -72,27 +84,47 @@ void decode_kernel(const void* __restrict__ q, const void* __restrict__ k, const
         }
         __syncthreads();
         const float4 vv = *(const float4*)(&vs[4 * tx]);
-        float4 acc = {0.f, 0.f, 0.f, 0.f};
+        float4 acc[G];
+#pragma unroll
+        for (int j = 0; j < G; ++j) acc[j] = float4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int it = 0; it < IT; ++it) {
-            const int i = ty + TY * it;
-            const float ki = ks[i], qi = qs[i];
+            const float ki = ks[G * ty + row(it)], qi = qs[G * ty + row(it)];
+            float4& a = acc[it % G];
             s[it].x = fmaf(lam, s[it].x, ki * vv.x);
             s[it].y = fmaf(lam, s[it].y, ki * vv.y);
             s[it].z = fmaf(lam, s[it].z, ki * vv.z);
             s[it].w = fmaf(lam, s[it].w, ki * vv.w);
-            acc.x = fmaf(qi, s[it].x, acc.x);
-            acc.y = fmaf(qi, s[it].y, acc.y);
-            acc.z = fmaf(qi, s[it].z, acc.z);
-            acc.w = fmaf(qi, s[it].w, acc.w);
+            a.x = fmaf(qi, s[it].x, a.x);
+            a.y = fmaf(qi, s[it].y, a.y);
+            a.z = fmaf(qi, s[it].z, a.z);
+            a.w = fmaf(qi, s[it].w, a.w);
         }
-        part[ty][tx] = acc;
+#pragma unroll
+        for (int m = 1; m < G; m *= 2)
+#pragma unroll
+            for (int j = 0; j + m < G; j += 2 * m) {           // (three: 0 and 1, then 2)
+                acc[j].x += acc[j + m].x;
+                acc[j].y += acc[j + m].y;
+                acc[j].z += acc[j + m].z;
+                acc[j].w += acc[j + m].w;
+            }
+        part[ty][tx] = acc[0];
         __syncthreads();                  // also: everyone is done with qs/ks/vs of this step
         if (tid < DV) {
             const int cx = tid / 4, comp = tid % 4;
             float sum = 0.f;
 #pragma unroll
-            for (int y = 0; y < TY; ++y) sum += ((const float*)&part[y][cx])[comp];
+            for (int y = 0; y < TY; y += PG) {
+                float t[PG];
+#pragma unroll
+                for (int i = 0; i < PG; ++i) t[i] = ((const float*)&part[y + i][cx])[comp];
+#pragma unroll
+                for (int m = 1; m < PG; m *= 2)
+#pragma unroll
+                    for (int i = 0; i < PG; i += 2 * m) t[i] += t[i + m];
+                sum += t[0];
+            }
             const size_t e = ((size_t)chain * steps + step) * DV + tid;
             if (BF16) ((unsigned short*)o)[e] = f32_to_bf16_bits(sum);
             else ((float*)o)[e] = sum;
@@ -100,13 +132,13 @@ void decode_kernel(const void* __restrict__ q, const void* __restrict__ k, const
         // the next step's first barrier separates these reads of `part` from its next writes
     }
 #pragma unroll
-    for (int it = 0; it < IT; ++it) S[(size_t)(ty + TY * it) * TX + tx] = s[it];
+    for (int it = 0; it < IT; ++it) S[row(it) * TX] = s[it];
 }
 
 // The same with a chain's value columns split over DV / 32 workgroups: columns are independent of each
 // other, and a workgroup a chain waits for a whole state to cross one unit's load path (and leaves units
-// idle where chains are few).  A thread holds eight rows of four columns; the partial dot products of a
-// wave's rows meet by lane swaps, the waves' through LDS.  One token, us of GPU time a call, whole state
+// idle where chains are few).  A thread holds a class of eight rows of four columns; a wave's classes meet by
+// lane swaps, the waves (96 features, a wave and a half: the classes) through LDS.  One token, us of GPU time a call, whole state
 // and slices: 128 x 128, 1 / 32 / 128 / 384 chains 3.88 / 4.25 / 5.23 / 8.21 and 2.85 / 3.14 / 4.39 / 7.60;
 // 256 x 256, 1 / 32 / 256 / 1024 chains 7.13 / 8.11 / 24.9 / 91.1 and 3.11 / 4.38 / 21.1 / 81.1.
 constexpr int kSliceCols = 32;
@@ -117,10 +149,12 @@ void decode_slice_kernel(const void* __restrict__ q, const void* __restrict__ k,
                          void* __restrict__ o, float* __restrict__ kv, const float* __restrict__ decay, int H,
                          int steps) {
     constexpr int TX = kSliceCols / 4, TY = DK / TX, IT = DK / TY;       // threads = DK
-    constexpr int WAVES = (DK + 63) / 64, NS = DV / kSliceCols;
-    static_assert(DV % kSliceCols == 0 && DK % TX == 0 && IT == 8, "thread layout");
+    constexpr int NS = DV / kSliceCols;
+    constexpr bool WHOLE = DK % 64 == 0;  // whole waves: eight classes of rows in each, summed by lane swaps
+    constexpr int NP = WHOLE ? DK / 64 : TY;
+    static_assert(DV % kSliceCols == 0 && DK % TX == 0 && IT == 8 && (WHOLE || TY % 3 == 0), "thread layout");
     __shared__ float qs[DK], ks[DK], vs[kSliceCols];
-    __shared__ float4 part[WAVES][TX];
+    __shared__ float4 part[NP][TX];
 
     const int chain = blockIdx.x / NS, col0 = (blockIdx.x - chain * NS) * kSliceCols;
     const int tid = threadIdx.x;
@@ -155,20 +189,19 @@ void decode_slice_kernel(const void* __restrict__ q, const void* __restrict__ k,
             acc[2] = fmaf(qi, s[it].z, acc[2]);
             acc[3] = fmaf(qi, s[it].w, acc[3]);
         }
-        // (96 threads: the second wave is half full, and its lanes 32 and up hold nothing to be added)
+        if constexpr (WHOLE) {
 #pragma unroll
-        for (int m = TX; m < 64; m *= 2)
+            for (int m = TX; m < 64; m *= 2)
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const float other = __shfl_xor(acc[c], m, 64);
-                acc[c] += (tid & ~63) + ((tid & 63) ^ m) < DK ? other : 0.f;
-            }
-        if ((tid & 63) < TX) part[tid / 64][tx] = float4{acc[0], acc[1], acc[2], acc[3]};
+                for (int c = 0; c < 4; ++c) acc[c] += __shfl_xor(acc[c], m, 64);
+        }
+        if (!WHOLE || (tid & 63) < TX) part[WHOLE ? tid / 64 : ty][tx] = float4{acc[0], acc[1], acc[2], acc[3]};
         __syncthreads();                  // also: everyone is done with qs/ks/vs of this step
         if (tid < kSliceCols) {
+            auto p = [&](int i) { return ((const float*)&part[i][tid / 4])[tid % 4]; };
             float sum = 0.f;
 #pragma unroll
-            for (int w = 0; w < WAVES; ++w) sum += ((const float*)&part[w][tid / 4])[tid % 4];
+            for (int i = 0; i < NP; i += WHOLE ? 1 : 3) sum += WHOLE ? p(i) : (p(i) + p(i + 1)) + p(i + 2);
             const size_t e = row * DV + col0 + tid;
             if (BF16) ((unsigned short*)o)[e] = f32_to_bf16_bits(sum);
             else ((float*)o)[e] = sum;
@@ -183,8 +216,7 @@ void decode_slice_kernel(const void* __restrict__ q, const void* __restrict__ k,
 // of 128 bytes where a whole state is one piece (bf16 tokens, 1 and 4 of them, slower beyond:
 // 128 x 128, 512 chains 14.1 and 14.4 us for 4; 128 x 64, 1024 chains 13.7 and 14.8 for 4; 96 x 96, 1024 chains 16.0
 // and 18.5 for 4; 256 x 256, 2048 chains 204 and 214 for 1).  64 x 64: never, a wave a slice has nothing
-// to overlap (1 chain 2.46 and 2.74 us, 4.09 and 4.89 for 4).  The count does not depend on the number of
-// tokens, so a call of several has the bits of as many calls of one.
+// to overlap (1 chain 2.46 and 2.74 us, 4.09 and 4.89 for 4).
 constexpr int split_limit(int DK, int DV) {
     return DK == 256 ? 8192 : DK == 64 ? 0 : DK * DV == 128 * 64 ? 1024 : 1536;
 }

@@ -43,3 +43,22 @@ def test_few_chains(Dk, Dv, last, chains, S, dtype):
 @pytest.mark.parametrize("past", [0, 1])
 def test_both_sides_of_the_line(Dk, Dv, last, past):
     run(Dk, Dv, last + past, 1, 2, torch.bfloat16)
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("Dk,Dv,last", LINES[1:])
+@pytest.mark.parametrize("S", [1, 3])
+def test_a_sequence_does_not_depend_on_its_batch(Dk, Dv, last, S, dtype):
+    # the same chains in a call of whole states, of slices, and of few: the same bits
+    q, k, v = (synth.make_qkv(last + 1, 1, S, Dk, dtype, 33) if Dk == Dv else
+               synth.make_qkv_dkdv(last + 1, 1, S, Dk, Dv, dtype, 33))
+    fn = ltn.ltn_attn_decode_steps if Dk == Dv else ltn.ltn_attn_decode_steps_dkdv
+    q, k, v, decay = gpu(q, k, v, torch.tensor([0.97]))
+    kv = torch.randn(last + 1, 1, Dk, Dv, generator=torch.Generator("cuda").manual_seed(Dk), device="cuda") / Dk
+    got = []
+    for n in (last + 1, last, 3):
+        state = kv[:n].clone()
+        got.append((fn(q[:n], k[:n], v[:n], state, decay), state))
+    for n in (last, 3):
+        o, state = got.pop()
+        assert torch.equal(o, got[0][0][:o.shape[0]]) and torch.equal(state, got[0][1][:o.shape[0]])
