@@ -1021,11 +1021,12 @@ hipError_t launch_pass_bf16(const PassBatch& pb, int D, int dv, hipStream_t stre
         if (D == 128 && pb.p[0].out) return launch_t<128, 128, kGatedLate>(pb, stream);
         if (D == 128) return launch_t<128, 128, kGated>(pb, stream);
         // 64 features: a block takes 0.55 us and its gate loads longer once the chip is busy, so two ahead
-        // from 128 whole chains on, 192 with O (one ahead and two: 128 x 1000 20.3 and 18.7, 128 x 3000 47.9 and
-        // 44.3, 512 x 200 19.2 and 17.8, 512 x 200 with O 20.7 and 19.5).  The loop is twice as long then, for two
-        // sets of registers, and costs up to 2.5 % where nothing is gained (128 x 200 with O 8.0 and 8.2, 32 x
-        // 200 with O 7.5 and 7.7, 32 x 3000 in segments 22.8 and 23.3).  Wider heads have no registers for it.
-        if (D == 64 && pb.segs == 1 && pb.N > kBlock && pb.chains >= (pb.p[0].out ? 192 : 128))
+        // from 128 whole chains on, 192 with O (one ahead and two, kernels alone: 128 x 500 12.5 and 12.2, 128 x 1000
+        // 20.4 and 19.4, 128 x 3000 48.1 and 45.3, 191 x 500 13.9 and 13.4, 192 x 500 with O 15.3 and 15.1).  Up to four
+        // blocks the longer start, two blocks' gate values ahead of the first tiles, is not made up for (192 x 128
+        // 6.5 and 6.7, 256 x 129 8.0 and 8.2, 512 x 128 with O 13.5 and 14.2, 512 x 200 with O 19.6 and 20.2; five
+        // blocks: 256 x 257 11.8 and 11.5, 512 x 257 21.9 and 21.7).  Wider heads have no registers for it.
+        if (D == 64 && pb.segs == 1 && pb.N > 4 * kBlock && pb.chains >= (pb.p[0].out ? 192 : 128))
             return launch_t<64, 64, kGatedFar>(pb, stream);
         if (D == 64) return launch_t<64, 64, kGated>(pb, stream);
         return hipErrorInvalidValue;

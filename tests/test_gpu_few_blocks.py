@@ -60,9 +60,9 @@ def test_unequal_widths(Dk, N):
 
 
 @pytest.mark.parametrize("chains,store_o", [(127, False), (128, False), (191, True), (192, True)])
-@pytest.mark.parametrize("N", [65, 449])
+@pytest.mark.parametrize("N", [65, 256, 257, 449])
 def test_gate_values_on_both_sides_of_the_line(chains, store_o, N):
-    # heads of 64 features: gate values fetched one block ahead, and two from so many chains on
+    # heads of 64 features: gate values fetched one block ahead, and two from so many chains and more than four blocks on
     q, k, v = synth.make_qkv(1, chains, N, 64, BF, 760 + N)
     u = synth.make_gate(1, chains, N, 64, BF, 760 + N)
     decay = mixed_decay(chains)
