@@ -87,8 +87,8 @@ hipError_t launch_segment_scan(float* states, const float* kv_in, float* kv_out,
 // kv[c] (or zeros if null) -> kv_out[c], n floats.
 hipError_t launch_state_copy(const float* kv_in, float* kv_out, size_t n, hipStream_t stream);
 // `steps` consecutive decode steps per chain (q, k: [chains, steps, DK]; v, o: [chains,
-// steps, DV]; kv: [chains, DK, DV]), see ltn_attn_decode_steps.  (DK, DV) in {(128,128),
-// (64,64), (256,128), (128,64)}.
+// steps, DV]; kv: [chains, DK, DV]), see ltn_attn_decode_steps.  (DK, DV) in {(64,64), (96,96),
+// (128,128), (256,256), (128,64), (256,128)}.
 hipError_t launch_decode(const void* q, const void* k, const void* v, void* o, float* kv,
                          const float* decay, int chains, int H, int steps, int DK, int DV, int is_bf16,
                          hipStream_t stream);

@@ -41,8 +41,8 @@
 //     own stores in between (VMEM operations of a wave retire in issue order), never for the
 //     stores themselves.  In the register-fed layout (256 features) all four output waves
 //     share the loads; in the gated pass the gate values are loaded from assembly too, at the
-//     end of the block before the one that uses them or at the start of that block (the
-//     dispatch at the end says which when), and counted with the tile loads.  LDS
+//     start of the block that uses them, at the end of the block before it or of the one before
+//     that (the dispatch at the end says which when), and counted with the tile loads.  LDS
 //     rows are unpadded; the 16-byte chunk index is XOR-swizzled with the row so that row reads,
 //     transpose reads (ds_read_b64_tr_b16, for operands needed "down the token axis") and the
 //     state-copy writes spread over the banks.  Rows past the end of a short last block are
@@ -814,8 +814,8 @@ __device__ __forceinline__ void pass_state_wave(const Chain& ch, char* smem, int
 // A launch's start (arguments known after 2850 of the 11800 cycles that 200 tokens of 64 features take, block 0
 // ready after 6500) is bound by such chains of latencies.  Measured together, before and after: these
 // loads, the ids below without divisions, the powers of lambda without loops, the constants computed and
-// the incoming state fetched while the first tiles travel: gated forward 32 chains x 200 x 64 8.48 and 8.12 us,
-// mixer 128 x 2048 x 128 274.6 and 271.7.
+// the incoming state fetched while the first tiles travel: gated forward 32 chains x 200 x 64 8.48 and 8.12 us;
+// calls of 32 blocks and more do not show it.
 template <typename T>
 __device__ __forceinline__ T pick(int pi, T x0, T x1, T x2) {
     return pi == 0 ? x0 : (pi == 1 ? x1 : x2);

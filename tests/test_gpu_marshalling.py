@@ -18,6 +18,24 @@ class Refuses:
         return lambda *args: None
 
 
+class Recorder:
+    """The native module, keeping for each entry whether it did the call itself."""
+    def __init__(self, module):
+        self.module, self.did = module, {}
+
+    def __getattr__(self, name):
+        def call(*args):
+            r = getattr(self.module, name)(*args)
+            self.did.setdefault(name, []).append(r is not None)
+            return r
+        return call
+
+
+#: entries of the native module, and how many of calls() go through each
+ENTRIES = {"fwd": 2, "fwd_gated": 2, "bwd": 1, "gate_bwd": 1, "decode_step": 1, "decode_steps": 1, "fwd_dkdv": 1,
+           "bwd_dkdv": 1, "decode_steps_dkdv": 1, "prologue_fwd": 2, "prologue_bwd": 2}
+
+
 def inputs(dtype):
     q, k, v = synth.make_qkv(Bt, H, N, D, dtype, 5)
     u, g = synth.make_gate(Bt, H, N, D, dtype, 5), synth.make_do(Bt, H, N, D, dtype, 5)
@@ -60,7 +78,10 @@ def calls(q, k, v, u, g, decay, theta):
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 def test_same_bits_as_the_python_path(dtype, monkeypatch):
     fns = calls(*inputs(dtype))
+    recorder = Recorder(binding._fast())
+    monkeypatch.setattr(binding, "_native", recorder)
     native = {n: flat(f()) for n, f in fns.items()}
+    assert recorder.did == {n: [True] * c for n, c in ENTRIES.items()}         # none of them by way of Python
     monkeypatch.setattr(binding, "_native", Refuses())
     for n, f in fns.items():
         python = flat(f())
@@ -70,7 +91,9 @@ def test_same_bits_as_the_python_path(dtype, monkeypatch):
             assert a is None or (a.dtype == b.dtype and torch.equal(a, b)), n
 
 
-def test_callers_outputs_come_back():
+def test_callers_outputs_come_back(monkeypatch):
+    recorder = Recorder(binding._fast())
+    monkeypatch.setattr(binding, "_native", recorder)
     q, k, v, u, _, decay, _ = inputs(torch.bfloat16)
     o, y, kv = torch.empty_like(q), torch.empty_like(q), torch.empty(Bt, H, D, D, device="cuda")
     r = ltn.ltn_attn_fwd(q, k, v, decay, out=o, kv_out=kv)
@@ -80,6 +103,7 @@ def test_callers_outputs_come_back():
     q1 = q[:, :, 0].contiguous()
     o1 = torch.empty_like(q1)
     assert ltn.ltn_attn_decode_step(q1, q1, q1, kv, decay, out=o1) is o1
+    assert recorder.did == {"fwd": [True], "fwd_gated": [True], "decode_step": [True]}
 
 
 def test_what_is_not_plain_is_left_to_python():
@@ -125,3 +149,46 @@ def test_captured_call_replays():
         graph.replay()
         torch.cuda.synchronize()
         assert all(torch.equal(a, b) and torch.equal(a, c) for a, b, c in zip(ref, got, side))
+
+
+def native_arguments(dtype):
+    """The arguments that binding.py hands to each entry of the native module."""
+    q, k, v, u, g, decay, theta = inputs(dtype)
+    w = torch.cat((q, k), -1)
+    kv, kvw = torch.zeros(Bt, H, D, D, device="cuda"), torch.zeros(Bt, H, 2 * D, D, device="cuda")
+    q1, k1, v1 = (x[:, :, 3].contiguous() for x in (q, k, v))
+    return {
+        "fwd": [q, k, v, decay, kv, True, 0, None, None],
+        "fwd_gated": [q, k, v, u, decay, 0.0, kv, True, True, 0, None, None, None],
+        "bwd": [q, k, v, g, decay, 0],
+        "gate_bwd": [q, u, g, 0.0],
+        "decode_step": [q1, k1, v1, kv, decay, None],
+        "decode_steps": [q, k, v, kv, decay, None],
+        "fwd_dkdv": [w, w, v, decay, kvw, True, 0, None, None],
+        "bwd_dkdv": [w, w, v, g, decay, 0],
+        "decode_steps_dkdv": [w, w, v, kvw, decay, None],
+        "prologue_fwd": [q, theta, True, 0, None],
+        "prologue_bwd": [q, w, theta, True, 0, True],
+    }
+
+
+@pytest.mark.parametrize("entry", ENTRIES)
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_every_entry_refuses_each_wrong_argument(entry, dtype):
+    # one argument at a time, in the place of one that is taken: left to Python, nothing is launched
+    native, args = getattr(binding._fast(), entry), native_arguments(dtype)[entry]
+    assert native(*args) is not None
+    for i, a in enumerate(args):
+        if isinstance(a, torch.Tensor):
+            wrong = [a.cpu(), a.half(), a[..., :-1], a[..., :-1].contiguous(), torch.cat((a, a), -1)[..., ::2], 1, "x"]
+        elif a is None:
+            wrong = [1, "x", torch.empty(1, device="cuda"), torch.empty(Bt, H, N, 2 * D, dtype=torch.half, device="cuda")]
+        elif isinstance(a, bool):
+            wrong = [1, None, "x"]
+        elif isinstance(a, float):
+            wrong = [None, "x", torch.zeros(1)]
+        else:
+            wrong = [None, "x", 1.0, 1 << 70]
+        for w in wrong:
+            assert native(*args[:i], w, *args[i + 1:]) is None, (i, w)
+    assert native(*args[:-1]) is None and native(*args, None) is None
