@@ -138,9 +138,10 @@ void decode_kernel(const void* __restrict__ q, const void* __restrict__ k, const
 // The same with a chain's value columns split over DV / 32 workgroups: columns are independent of each
 // other, and a workgroup a chain waits for a whole state to cross one unit's load path (and leaves units
 // idle where chains are few).  A thread holds a class of eight rows of four columns; a wave's classes meet by
-// lane swaps, the waves (96 features, a wave and a half: the classes) through LDS.  One token, us of GPU time a call, whole state
-// and slices: 128 x 128, 1 / 32 / 128 / 384 chains 3.88 / 4.25 / 5.23 / 8.21 and 2.85 / 3.14 / 4.39 / 7.60;
-// 256 x 256, 1 / 32 / 256 / 1024 chains 7.13 / 8.11 / 24.9 / 91.1 and 3.11 / 4.38 / 21.1 / 81.1.
+// lane swaps, the waves (96 features, a wave and a half: the classes) through LDS.  One token, us of GPU time a call, whole
+// state and slices, one state repeated (and states that come from HBM): 128 x 128, 32 / 128 / 384 chains 4.05 /
+// 4.96 / 7.71 and 3.10 / 4.34 / 7.40 (4.93 / 6.56 / 12.7 and 3.41 / 6.10 / 12.7); 256 x 256, 32 / 256 / 1024 chains
+// 7.77 / 21.5 / 83.4 and 4.35 / 21.2 / 81.9 (10.9 / 29.5 / 107.5 and 6.11 / 30.0 / 106.4).
 constexpr int kSliceCols = 32;
 
 template <int DK, int DV, bool BF16>
@@ -213,10 +214,11 @@ void decode_slice_kernel(const void* __restrict__ q, const void* __restrict__ k,
 }
 
 // Slices up to which a call is split; past them the units are full either way, and a slice reads rows
-// of 128 bytes where a whole state is one piece (bf16 tokens, 1 and 4 of them, slower beyond:
-// 128 x 128, 512 chains 14.1 and 14.4 us for 4; 128 x 64, 1024 chains 13.7 and 14.8 for 4; 96 x 96, 1024 chains 16.0
-// and 18.5 for 4; 256 x 256, 2048 chains 204 and 214 for 1).  64 x 64: never, a wave a slice has nothing
-// to overlap (1 chain 2.46 and 2.74 us, 4.09 and 4.89 for 4).
+// of 128 bytes where a whole state is one piece (bf16 tokens, slower beyond: 128 x 128, 512 chains 13.5 and
+// 14.8 us for 4 tokens; 128 x 64, 1024 chains 14.1 and 15.0 for 4; 96 x 96, 1024 chains 15.8 and 17.3 for 4; 256 x 256,
+// 2048 chains 205 and 214 for 1).  Just below the lines the two are within 3 %, but for 256 x 256, 128 and 192 chains out
+// of HBM (16.6 and 18.0, 22.4 and 23.4; 384 to 1024 chains: slices ahead by 1 to 6 %).  64 x 64: never, a wave
+// a slice has nothing to overlap (1 chain 2.37 and 2.61 us, 4.08 and 4.69 for 4).
 constexpr int split_limit(int DK, int DV) {
     return DK == 256 ? 8192 : DK == 64 ? 0 : DK * DV == 128 * 64 ? 1024 : 1536;
 }
