@@ -100,7 +100,8 @@ struct Cfg {
 // state-only sweep of the sequence-parallel form (no outputs: only the segment's end state).
 // The gated epilogue's values are fetched one block ahead of their use, within the block that uses them
 // (kGatedLate) or two ahead (kGatedFar).
-enum { kPlain = 0, kGated = 1, kStateOnly = 2, kGatedLate = 3, kGatedFar = 4 };
+// kCut: the plain pass with some chains in two parts (cut_start below).
+enum { kPlain = 0, kGated = 1, kStateOnly = 2, kGatedLate = 3, kGatedFar = 4, kCut = 5 };
 constexpr bool has_gate(int mode) { return mode == kGated || mode == kGatedLate || mode == kGatedFar; }
 // blocks ahead
 constexpr int gate_ahead(int mode) { return mode == kGated ? 1 : (mode == kGatedFar ? 2 : 0); }
@@ -442,7 +443,39 @@ struct Chain {            // what every wave of the workgroup knows about its pr
     int last_valid;       // tokens in the last block (1..64)
     int rev;
     float lam;
+    int part;                // kCut: 0 the whole chain, 1 its first part, 2 its second part
+    char* handover;          // parts 1, 2: the slice's columns of the second part's first output row
 };
+
+// =============================================================== chains in two parts (kCut)
+//
+// A launch of W workgroups that take the same time each needs ceil(W / 256) rounds of the 256 compute units,
+// however few are in the last one.  So the workgroups that would be alone there (up to 128) are cut in two along
+// the tokens.  Ids, which is the order of dispatch: first parts, whole chains, second parts.  The units that
+// took first parts begin their next whole chain when those end, the others take the second parts when their
+// last whole chain ends, and the launch ends half a round after the last full one.  The second part
+// continues from the first's fp32 state: the same sums in the same order, the same bits as uncut.
+// Measured, whole and cut: backward of 96 features x 96 chains x 1999 tokens (288 workgroups) 85.6 and 74.2 us,
+// of 128 features x 96 x 2048 110.7 and 94.6, x 128 x 8192 (384, bound by memory) 536 and 516, of 256
+// features x 32 x 4096 (384) 257 and 226; forward of 256 features x 85 x 4479 (340) 336 and 281.
+//
+// That state needs no scratch memory: row r of the slice's [D x DV] lies in the slice's columns of
+// output rows 2r and 2r + 1 of the second part, which overwrites them when all its state waves have
+// loaded it (the barrier before its first block).  A flag word in row 2D, cleared by a launch before this
+// one, says that it is there.  State and flag are written and read with relaxed atomic operations of
+// device scope, which go past the caches that are not coherent, and ordered by the wait for the stores and the
+// barrier between them and the flag's store, and by the branch between the flag's load and theirs.  A release and
+// an acquire fence would write back and invalidate the XCD's L2 under all its other workgroups (96 x 1999: 80.8 us,
+// 256 features 250).
+// The wait ends: a second part waits for one first part only, which waits for nothing and comes earlier in the
+// dispatch order of the same XCD (ids congruent mod 8).  As a rule the state has been there for half a chain.
+template <int DV, int DC>
+__device__ __forceinline__ float* handover_at(char* p, int row, int nt, int i16) {      // column 16 nt + i16
+    constexpr int H = DV / 2;
+    return (float*)(p + (size_t)(2 * row + 16 * nt / H) * (DC * 2) + (16 * nt % H) * 4) + i16;
+}
+template <int D, int DC>
+__device__ __forceinline__ unsigned* handover_flag(char* p) { return (unsigned*)(p + (size_t)(2 * D) * (DC * 2)); }
 
 // =============================================================== pass body
 
@@ -754,13 +787,26 @@ __device__ __forceinline__ void pass_state_wave(const Chain& ch, char* smem, int
     constexpr bool SO = MODE == kStateOnly;          // no published state copies
     const int g = lane >> 4, i16 = lane & 15;
     const int dk0 = u * (D / 4);
+    if constexpr (MODE == kCut) {
+        if (ch.part == 2) {
+            while (__hip_atomic_load(handover_flag<DR, DC>(ch.handover), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0)
+                __builtin_amdgcn_s_sleep(16);
+            asm volatile("" ::: "memory");
+        }
+    }
     // running state, fp32 (its loads first: they travel while the constants are computed)
     f32x4 st[MT][NT];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
-            if (ch.state_in) {
+            if (MODE == kCut && ch.part == 2) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int row = dk0 + 16 * mt + 4 * g + j;
+                    st[mt][nt][j] = (DR == D || row < DR) ? __hip_atomic_load(handover_at<DV, DC>(ch.handover, row, nt, i16), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.0f;
+                }
+            } else if (ch.state_in) {
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     const int row = dk0 + 16 * mt + 4 * g + j;
@@ -784,7 +830,7 @@ __device__ __forceinline__ void pass_state_wave(const Chain& ch, char* smem, int
     for (int blk = 0; blk < ch.T; ++blk) {
         const bool more = blk + 1 < ch.T;
         if (!more) {
-            if (!ch.state_out) break;                // the last update only feeds the returned state
+            if (!ch.state_out && !(MODE == kCut && ch.part == 1)) break;     // the last update only feeds the returned state
             if (ch.last_valid != kBlock) k.set_block_len(ch.lam, ch.last_valid, lane);
         }
         const char* tb = smem + stage * C::PSTAGE;
@@ -796,6 +842,22 @@ __device__ __forceinline__ void pass_state_wave(const Chain& ch, char* smem, int
         stage = (stage + 1 == C::PST) ? 0 : stage + 1;
     }
 
+    if constexpr (MODE == kCut) {
+        if (ch.part == 1) {
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const int row = dk0 + 16 * mt + 4 * g + j;
+                        if (DR == D || row < DR)
+                            __hip_atomic_store(handover_at<DV, DC>(ch.handover, row, nt, i16), st[mt][nt][j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    }
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            return;
+        }
+    }
     if (ch.state_out) {
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
@@ -841,9 +903,22 @@ __device__ __forceinline__ void pass_body(const PassBatch& pb, int xcd_ids, int 
     // (chain, segment) pairs are dealt to workgroups like chains; with one segment per
     // chain the pair index is the chain index
     constexpr int NS = DC / DV;            // column slices
-    int vchain, pi, split;
-    map_pass<NS>((unsigned)wg, pb.count, xcd_ids, vchain, pi, split);
-    if (NS == 1 && pb.pairs_first && pb.count == 3 && xcd_ids) {
+    int vchain, pi, split, part = 0;
+    if constexpr (MODE == kCut) {          // first parts; whole passes but the last; whole last passes; second parts
+        const int last = pb.count - 1;
+        const bool others = wg >= pb.cut_ids[0] && wg < pb.cut_ids[1];
+        part = wg < pb.cut_ids[0] ? 1 : (wg >= pb.cut_ids[2] ? 2 : 0);
+        const int first_id = part == 1 ? 0 : (others ? pb.cut_ids[0] : (part == 2 ? pb.cut_ids[2] : pb.cut_ids[1]));
+        const unsigned w = (unsigned)(wg - first_id), slot = xcd_ids ? w >> 3 : w;
+        const unsigned per = others ? (unsigned)(last * NS) : NS, q = others ? (last == 1 ? slot / NS : slot / (2 * NS)) : slot / NS;
+        const int within = (int)(slot - q * per);
+        vchain = (int)(xcd_ids ? q * 8 + (w & 7) : q) + (part == 0 && !others ? pb.cut_chains : 0);
+        pi = others ? within / NS : last;
+        split = others ? within % NS : within;
+    } else {
+        map_pass<NS>((unsigned)wg, pb.count, xcd_ids, vchain, pi, split);
+    }
+    if (MODE != kCut && NS == 1 && pb.pairs_first && pb.count == 3 && xcd_ids) {
         // Backward at full width: passes 0 and 1 of a chain walk the token axis together and
         // share two operands, pass 2 walks the other way.  Ids: all (pass 0, pass 1) pairs
         // first, a chain's pair side by side on one XCD, then every pass 2.  With more
@@ -877,8 +952,9 @@ __device__ __forceinline__ void pass_body(const PassBatch& pb, int xcd_ids, int 
 
     // the segment's tokens [seg_start, seg_start + n) of the pass's (possibly reversed) token
     // axis are rows [row0, row0 + n) of the tensors
-    const long long seg_start = (long long)seg * pb.seg_len;
-    const long long n = (pb.segs > 1 && pb.N - seg_start > pb.seg_len) ? pb.seg_len : pb.N - seg_start;
+    const long long seg_start = MODE == kCut ? (part == 2 ? pb.cut_len : 0) : (long long)seg * pb.seg_len;
+    const long long n = MODE == kCut ? (part == 1 ? pb.cut_len : pb.N - seg_start)
+                                     : ((pb.segs > 1 && pb.N - seg_start > pb.seg_len) ? pb.seg_len : pb.N - seg_start);
     const long long row0 = rev ? (pb.N - seg_start - n) : seg_start;
 
     Chain ch;
@@ -893,6 +969,10 @@ __device__ __forceinline__ void pass_body(const PassBatch& pb, int xcd_ids, int 
     ch.gate = GATED ? (const char*)P0.gate + chain_off : nullptr;       // (the gated epilogue is one pass)
     ch.y = GATED ? (char*)P0.gated_out + chain_off : nullptr;
     ch.eps = P0.eps;
+    if constexpr (MODE == kCut) {
+        ch.part = part;
+        ch.handover = out + ((size_t)chain * (size_t)pb.N + (size_t)pb.cut_len) * DC * 2 + col_off;
+    }
     ch.state_in = state_in ? state_in + (size_t)vchain * DR * DC + (size_t)split * DV : nullptr;
     ch.state_out = state_out ? state_out + (size_t)vchain * DR * DC + (size_t)split * DV : nullptr;
     ch.N = n;
@@ -949,6 +1029,13 @@ __device__ __forceinline__ void pass_body(const PassBatch& pb, int xcd_ids, int 
             default: pass_state_wave<D, DV, DC, MODE, DR>(ch, smem, lane, wave - 4); break;
         }
     }
+    if constexpr (MODE == kCut) {
+        if (ch.part == 1) {                // every state wave has stored its rows of the state and released them
+            __syncthreads();
+            if (wave == 0 && lane == 0)
+                __hip_atomic_store(handover_flag<DR, DC>(ch.handover), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
 }
 
 // =============================================================== kernels
@@ -977,7 +1064,46 @@ hipError_t launch_t(const PassBatch& pb, hipStream_t stream) {
     return hipGetLastError();
 }
 
+__global__ void clear_handover_kernel(char* out, long long row_bytes, long long N, long long flag_row, int slices,
+                                      int slice_bytes, int n) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) *(unsigned*)(out + ((long long)(i / slices) * N + flag_row) * row_bytes + (i % slices) * slice_bytes) = 0u;
+}
+
+template <int D, int DV, int DC, int DR>
+hipError_t launch_cut_t(PassBatch& pb, hipStream_t stream) {
+    constexpr int NS = DC / DV;
+    const PassArgs& last = pb.p[pb.count - 1];
+    // every chain group's ids deal chains to XCDs (multiples of 8) or are chain-major, as in launch_t
+    const bool xcd = (pb.chains & 7) == 0;
+    if (pb.segs != 1 || last.rev || pb.cut_chains < 1 || pb.cut_chains > pb.chains || (xcd && (pb.cut_chains & 7)) ||
+        pb.cut_len < kBlock || pb.cut_len % kBlock || pb.N - pb.cut_len < cut_state_rows(DR))
+        return hipErrorInvalidValue;
+    const long long cut = (long long)pb.cut_chains * NS, others = (long long)pb.chains * (pb.count - 1) * NS,
+                    whole = (long long)(pb.chains - pb.cut_chains) * NS;
+    const long long second = (cut + others + whole + 7) / 8 * 8;       // congruent mod 8 to the first parts
+    if (second + cut > 0x7fffffffLL) return hipErrorInvalidValue;
+    pb.cut_ids[0] = (int)cut;
+    pb.cut_ids[1] = (int)(cut + others);
+    pb.cut_ids[2] = (int)second;
+    hipLaunchKernelGGL(clear_handover_kernel, dim3((unsigned)((cut + 63) / 64)), dim3(64), 0, stream, (char*)last.out,
+                       DC * 2LL, pb.N, pb.cut_len + 2 * DR, NS, DV * 2, (int)cut);
+    hipLaunchKernelGGL((pass_bf16_kernel<D, DV, kCut, DC, DR>), dim3((unsigned)(second + cut)), dim3(kThreads), 0, stream, pb,
+                       (int)xcd);
+    return hipGetLastError();
+}
+
 }  // namespace
+
+hipError_t launch_pass_cut_bf16(PassBatch& pb, int D, hipStream_t stream) {
+    switch (D) {
+        case 64: return launch_cut_t<64, 64, 64, 64>(pb, stream);
+        case 96: return launch_cut_t<128, 96, 96, 96>(pb, stream);
+        case 128: return launch_cut_t<128, 128, 128, 128>(pb, stream);
+        case 256: return launch_cut_t<256, 64, 256, 256>(pb, stream);
+        default: return hipErrorInvalidValue;
+    }
+}
 
 hipError_t launch_pass_bf16(const PassBatch& pb, int D, int dv, hipStream_t stream, int DC) {
     if (DC != 0 && DC != D) {              // queries/keys and values of different widths (plain pass only)

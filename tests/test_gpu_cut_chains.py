@@ -1,0 +1,117 @@
+"""Plain bf16 passes in a few more workgroups than the GPU has compute units: the chains whose last pass
+runs in two parts (the second starting from the first's state, kept in the output's own rows).
+
+The parts add the same terms in the same order as the whole chain, so every result must be the same bits as
+with the cut switched off; the chains on both sides of the line between cut and whole ones are held to
+the fp64 oracle as well."""
+import pytest
+import torch
+
+import paper_2307_14995_amd as ltn
+from paper_2307_14995_amd import synth
+from oracle import ltn_oracle as orc
+from _helpers import TOL, check, force_segs, gpu, mixed_decay
+
+pytestmark = pytest.mark.gpu
+
+BF = torch.bfloat16
+# (D, Bt, H, N, cut chains): 257 .. 384 workgroups in two rounds and 520 .. 640 in three, chain counts that
+# are multiples of 8 and not (their ids are dealt differently), the shortest length that is cut
+# (second parts of 321 tokens, 577 of 256 features) and a ragged one
+FORWARD = [(64, 4, 65, 705, 4), (64, 3, 96, 1090, 32), (64, 5, 105, 769, 13), (96, 1, 257, 705, 1), (96, 8, 40, 1100, 64),
+           (128, 3, 99, 705, 41), (128, 4, 66, 900, 8), (128, 1, 530, 770, 18), (256, 5, 13, 1217, 1), (256, 5, 16, 1300, 16),
+           (256, 3, 50, 1217, 22)]
+# (a last round half full with one workgroup per chain is cut only where the inputs exceed 320 MiB)
+BACKWARD = [(64, 1, 86, 705, 2), (64, 8, 14, 1000, 80), (96, 8, 12, 1090, 32), (96, 3, 31, 705, 23), (128, 5, 20, 705, 44),
+            (128, 8, 15, 900, 104), (256, 1, 22, 1217, 2), (256, 2, 16, 1250, 32)]
+
+
+def lines(chains, cut):
+    return sorted({0, cut - 1, min(cut, chains - 1), chains - 1})
+
+
+def some(t, chains, keep):
+    return t.reshape(1, chains, *t.shape[2:])[:, keep]
+
+
+@pytest.mark.parametrize("D,Bt,H,N,cut", FORWARD)
+def test_forward(D, Bt, H, N, cut):
+    q, k, v = synth.make_qkv(Bt, H, N, D, BF, 900 + N)
+    decay = mixed_decay(H)
+    kv0 = torch.randn(Bt, H, D, D, generator=torch.Generator().manual_seed(N)) / D
+    args = gpu(q, k, v, decay)
+    with force_segs(1):
+        o_whole, kv_whole = ltn.ltn_attn_fwd(*args, kv_in=kv0.cuda(), return_state=True)
+    state = kv0.cuda()
+    o, kv = ltn.ltn_attn_fwd(*args, kv_in=state, kv_out=state)
+    assert torch.equal(o, o_whole) and torch.equal(kv, kv_whole)
+    assert torch.equal(ltn.ltn_attn_fwd(*args, kv_in=kv0.cuda()), o_whole)
+    keep = lines(Bt * H, cut)
+    o_ref, kv_ref = orc.fwd_recurrent(*(some(t, Bt * H, keep) for t in (q, k, v)), decay.repeat(Bt)[keep],
+                                      kv_in=some(kv0, Bt * H, keep), return_state=True)
+    check("O", some(o, Bt * H, keep), o_ref, TOL[BF])
+    check("kv", some(kv, Bt * H, keep), kv_ref, TOL[BF])
+
+
+@pytest.mark.parametrize("D,Bt,H,N,cut", BACKWARD)
+def test_backward(D, Bt, H, N, cut):
+    q, k, v = synth.make_qkv(Bt, H, N, D, BF, 950 + N)
+    g = synth.make_do(Bt, H, N, D, BF, 950 + N)
+    decay = mixed_decay(H)
+    args = gpu(q, k, v, g, decay)
+    with force_segs(1):
+        whole = ltn.ltn_attn_bwd(*args)
+    grads = ltn.ltn_attn_bwd(*args)
+    assert all(torch.equal(x, y) for x, y in zip(grads, whole))
+    keep = lines(Bt * H, cut)
+    refs = orc.bwd_recurrent(*(some(t, Bt * H, keep) for t in (q, k, v, g)), decay.repeat(Bt)[keep])
+    for n, x, r in zip(("dQ", "dK", "dV"), grads, refs):
+        check(n, some(x, Bt * H, keep), r, TOL[BF])
+
+
+def test_outputs_inside_larger_buffers():
+    """The states and flags that pass through the output's rows stay inside them."""
+    D, Bt, H, N = 96, 8, 12, 1090
+    q, k, v = synth.make_qkv(Bt, H, N, D, BF, 31)
+    g = synth.make_do(Bt, H, N, D, BF, 31)
+    decay = synth.decay_bench_rule(H)
+    guard = 4096
+    raws = [torch.full((q.numel() + 2 * guard,), 7.0, device="cuda", dtype=BF) for _ in range(3)]
+    outs = [r[guard:guard + q.numel()].view_as(q) for r in raws]
+    args = gpu(q, k, v, g, decay)
+    ltn.ltn_attn_bwd(*args, out=outs)
+    with force_segs(1):
+        whole = ltn.ltn_attn_bwd(*args)
+    for x, y, raw in zip(outs, whole, raws):
+        assert torch.equal(x, y)
+        assert bool((raw[:guard] == 7.0).all()) and bool((raw[-guard:] == 7.0).all())
+
+
+def test_replayed_graph():
+    """Captured once and replayed over changing inputs, with eager calls in between: every replay waits for its own
+    states (the flags are cleared by a kernel of the call)."""
+    D, Bt, H, N = 128, 5, 20, 770
+    decay = synth.decay_bench_rule(H).cuda()
+    q, k, v, g = (torch.empty(Bt, H, N, D, device="cuda", dtype=BF) for _ in range(4))
+
+    def fill(seed):
+        for x, y in zip((q, k, v, g), (*synth.make_qkv(Bt, H, N, D, BF, seed), synth.make_do(Bt, H, N, D, BF, seed))):
+            x.copy_(y)
+
+    def call():
+        return ltn.ltn_attn_bwd(q, k, v, g, decay)
+
+    fill(1)
+    call()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        captured = call()
+    for seed in (2, 3, 4):
+        fill(seed)
+        graph.replay()
+        torch.cuda.synchronize()
+        got = [x.clone() for x in captured]
+        with force_segs(1):
+            whole = call()
+        assert all(torch.equal(x, y) for x, y in zip(got, whole))
