@@ -387,23 +387,25 @@ bool gated_in_two_steps(long long chains, long long N, int D, ltn_dtype dtype, i
 // The line, over 110 shapes (64 .. 256 features, forward and backward, 86 .. 1300 chains x 360 .. 5800 tokens; time
 // cut over time whole): up to half a round alone 0.84 .. 0.98 in two rounds, 0.89 .. 0.98 in three, 0.92 .. 1.00 in
 // four, 0.97 .. 1.10 beyond, where workgroups end so far apart that the last round fills up by itself; more than
-// half a round alone 1.01 .. 1.08 (the second parts then take more than the units that are left).  Shorter
-// than 12 blocks the launch that clears the flags takes what the cut gains (96 features x 763 tokens: 0.98).
+// half a round alone 1.01 .. 1.08 (the second parts then take more than the units that are left).  Unequal
+// widths, 17 such shapes: 0.84 .. 0.99.  Shorter than 12 blocks the launch that clears the flags takes
+// what the cut gains (96 features x 763 tokens: 0.98).
 // Near half a round one workgroup per chain and pass keeps memory busy in the last round too: backward of 128 chains
 // of 128 features x 8192 0.96, x 3000 0.97.  While its inputs are about what the 256 MiB memory-side cache holds,
 // dQ behind all of dV and dK finds more of them there: 128 x 1984 and x 2112 0.94 and 0.97, but 128 x 2048 (four
 // tensors of 64 MiB) 0.98 .. 1.04 from one card to another and 1.06 in a mixer's step; so it is cut there
 // only from 320 MiB on.
-bool pick_cut(ltn::PassBatch& pb, int D, int dv) {
+// widest: value columns of the widest slices that DC columns have here, the only ones that are cut.
+bool pick_cut(ltn::PassBatch& pb, int D, int DC, int dv, int widest) {
     constexpr long long kRounds = 4, kHalf = 6;
-    if (dv != (D == 256 ? 64 : D) || g_debug_segs.load(std::memory_order_relaxed) == 1) return false;
-    const int slices = D / dv;
+    if (dv != widest || g_debug_segs.load(std::memory_order_relaxed) == 1) return false;
+    const int slices = DC / dv;
     const long long per_chain = (long long)pb.count * slices;
     // one XCD's workgroups and units where ids deal chains to XCDs, else all of them
     const bool xcd = (pb.chains & 7) == 0;
     const long long wgs = xcd ? pb.chains / 8 * per_chain : pb.chains * per_chain, units = xcd ? 32 : 256;
     const long long chains = (wgs % units + slices - 1) / slices;
-    const long long input_mib = (pb.count == 3 ? 4 : 3) * pb.chains * pb.N * D * 2 >> 20;
+    const long long input_mib = (pb.count == 3 ? 4 * D : 2 * D + DC) * pb.chains * pb.N * 2 >> 20;
     if (slices == 1 && 16 * chains > 7 * units && input_mib < 320) return false;
     if (wgs < units || wgs > kRounds * units || chains == 0 || chains * slices > units / 2) return false;
     const long long first = ((pb.N + 63) / 64 + 1) / 2;                // of a chain's blocks
@@ -424,7 +426,7 @@ ltn_status run_passes(ltn::PassBatch& pb, int D, int blk, ltn_dtype dtype, void*
     pb.segs = 1;
     if (plan.segs == 1) {
         const int dv = full_width ? D : pick_dv(chain_passes, D, pb.count);
-        if (!full_width && pick_cut(pb, D, dv))
+        if (!full_width && pick_cut(pb, D, D, dv, D == 256 ? 64 : D))
             return ltn::launch_pass_cut_bf16(pb, D, stream) == hipSuccess ? LTN_OK : LTN_ERR_LAUNCH;
         return ltn::launch_pass_bf16(pb, D, dv, stream) == hipSuccess ? LTN_OK : LTN_ERR_LAUNCH;
     }
@@ -862,7 +864,8 @@ static ltn_status run_dkdv(ltn::PassBatch& pb, int DA, int DC, int blk, ltn_dtyp
     const int hi = dkdv_hi(DA, DC);
     const SegPlan plan = pick_segments_dkdv(chain_passes, pb.N, DA, DC, dtype);
     if (plan.segs == 1) {
-        e = ltn::launch_pass_bf16(pb, DA, pick_dv_range(chain_passes, DC, 32, hi), st, DC);
+        const int dv = pick_dv_range(chain_passes, DC, 32, hi);
+        e = pick_cut(pb, DA, DC, dv, hi) ? ltn::launch_pass_cut_bf16(pb, DA, st, DC) : ltn::launch_pass_bf16(pb, DA, dv, st, DC);
         return e == hipSuccess ? LTN_OK : LTN_ERR_LAUNCH;
     }
     if (!workspace) return LTN_ERR_NULL;

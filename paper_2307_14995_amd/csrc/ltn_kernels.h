@@ -68,11 +68,11 @@ struct PassBatch {
 // c, out [chains, N, DC]; states [chains, D, DC]; dv slices DC.  Plain pass, or the state-only
 // sweep with dv = 64 (128 for (128,256)).  (D, DC) in {(256,128), (128,256), (128,64), (64,128)}.
 hipError_t launch_pass_bf16(const PassBatch& pb, int D, int dv, hipStream_t stream, int DC = 0);
-// The same for plain passes at their widest slices (dv = D, 96 of 96, 64 of 256; equal widths) with
+// The same for plain passes at their widest slices (DC columns up to 128; 64 where D = 256 or DC = 2 D = 128) with
 // cut_chains and cut_len set and cut_ids to be filled in: two launches, as the flags that the second
 // parts wait for are cleared first.  cut_len is a multiple of 64, at least cut_state_rows(D) tokens less than N.
 inline long long cut_state_rows(int D) { return 2 * D + 64; }
-hipError_t launch_pass_cut_bf16(PassBatch& pb, int D, hipStream_t stream);
+hipError_t launch_pass_cut_bf16(PassBatch& pb, int D, hipStream_t stream, int DC = 0);
 // Forward by the quadratic tiling of App. B Algorithm 3 (comparison kernel), bf16, zero
 // initial state, D in {64,128}.
 hipError_t launch_tiled_fwd_bf16(const void* q, const void* k, const void* v, void* o, const float* decay,

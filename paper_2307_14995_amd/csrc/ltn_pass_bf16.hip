@@ -444,7 +444,7 @@ struct Chain {            // what every wave of the workgroup knows about its pr
     int rev;
     float lam;
     int part;                // kCut: 0 the whole chain, 1 its first part, 2 its second part
-    char* handover;          // parts 1, 2: the slice's columns of the second part's first output row
+    char* handover;          // parts 1, 2: the slice's columns of the second part's lowest output row
 };
 
 // =============================================================== chains in two parts (kCut)
@@ -971,7 +971,7 @@ __device__ __forceinline__ void pass_body(const PassBatch& pb, int xcd_ids, int 
     ch.eps = P0.eps;
     if constexpr (MODE == kCut) {
         ch.part = part;
-        ch.handover = out + ((size_t)chain * (size_t)pb.N + (size_t)pb.cut_len) * DC * 2 + col_off;
+        ch.handover = out + ((size_t)chain * (size_t)pb.N + (size_t)(rev ? 0 : pb.cut_len)) * DC * 2 + col_off;
     }
     ch.state_in = state_in ? state_in + (size_t)vchain * DR * DC + (size_t)split * DV : nullptr;
     ch.state_out = state_out ? state_out + (size_t)vchain * DR * DC + (size_t)split * DV : nullptr;
@@ -1076,7 +1076,7 @@ hipError_t launch_cut_t(PassBatch& pb, hipStream_t stream) {
     const PassArgs& last = pb.p[pb.count - 1];
     // every chain group's ids deal chains to XCDs (multiples of 8) or are chain-major, as in launch_t
     const bool xcd = (pb.chains & 7) == 0;
-    if (pb.segs != 1 || last.rev || pb.cut_chains < 1 || pb.cut_chains > pb.chains || (xcd && (pb.cut_chains & 7)) ||
+    if (pb.segs != 1 || pb.cut_chains < 1 || pb.cut_chains > pb.chains || (xcd && (pb.cut_chains & 7)) ||
         pb.cut_len < kBlock || pb.cut_len % kBlock || pb.N - pb.cut_len < cut_state_rows(DR))
         return hipErrorInvalidValue;
     const long long cut = (long long)pb.cut_chains * NS, others = (long long)pb.chains * (pb.count - 1) * NS,
@@ -1087,7 +1087,7 @@ hipError_t launch_cut_t(PassBatch& pb, hipStream_t stream) {
     pb.cut_ids[1] = (int)(cut + others);
     pb.cut_ids[2] = (int)second;
     hipLaunchKernelGGL(clear_handover_kernel, dim3((unsigned)((cut + 63) / 64)), dim3(64), 0, stream, (char*)last.out,
-                       DC * 2LL, pb.N, pb.cut_len + 2 * DR, NS, DV * 2, (int)cut);
+                       DC * 2LL, pb.N, (last.rev ? 0 : pb.cut_len) + 2 * DR, NS, DV * 2, (int)cut);
     hipLaunchKernelGGL((pass_bf16_kernel<D, DV, kCut, DC, DR>), dim3((unsigned)(second + cut)), dim3(kThreads), 0, stream, pb,
                        (int)xcd);
     return hipGetLastError();
@@ -1095,7 +1095,14 @@ hipError_t launch_cut_t(PassBatch& pb, hipStream_t stream) {
 
 }  // namespace
 
-hipError_t launch_pass_cut_bf16(PassBatch& pb, int D, hipStream_t stream) {
+hipError_t launch_pass_cut_bf16(PassBatch& pb, int D, hipStream_t stream, int DC) {
+    if (DC != 0 && DC != D) {
+        if (D == 256 && DC == 128) return launch_cut_t<256, 64, 128, 256>(pb, stream);
+        if (D == 128 && DC == 256) return launch_cut_t<128, 128, 256, 128>(pb, stream);
+        if (D == 128 && DC == 64) return launch_cut_t<128, 64, 64, 128>(pb, stream);
+        if (D == 64 && DC == 128) return launch_cut_t<64, 64, 128, 64>(pb, stream);
+        return hipErrorInvalidValue;
+    }
     switch (D) {
         case 64: return launch_cut_t<64, 64, 64, 64>(pb, stream);
         case 96: return launch_cut_t<128, 96, 96, 96>(pb, stream);

@@ -69,6 +69,30 @@ def test_backward(D, Bt, H, N, cut):
         check(n, some(x, Bt * H, keep), r, TOL[BF])
 
 
+# (Dk, Dv, Bt, H, N): forward and dV cut (the second part of dV's reversed token axis lies in front), or dK and dQ, or all
+@pytest.mark.parametrize("Dk,Dv,Bt,H,N", [(256, 128, 2, 65, 1217), (256, 128, 9, 16, 1300), (256, 128, 4, 18, 705),
+                                          (128, 64, 4, 65, 705), (128, 64, 3, 96, 800), (128, 64, 8, 10, 705),
+                                          (128, 64, 3, 30, 770)])
+def test_unequal_widths(Dk, Dv, Bt, H, N):
+    q, k, v = synth.make_qkv_dkdv(Bt, H, N, Dk, Dv, BF, 70 + N)
+    g = synth.make_do(Bt, H, N, Dv, BF, 70 + N)
+    decay = mixed_decay(H)
+    kv0 = torch.randn(Bt, H, Dk, Dv, generator=torch.Generator().manual_seed(N)) / Dk
+    args, do = gpu(q, k, v), g.cuda()
+    with force_segs(1):
+        whole = [*ltn.ltn_attn_fwd_dkdv(*args, decay.cuda(), kv_in=kv0.cuda(), return_state=True),
+                 *ltn.ltn_attn_bwd_dkdv(*args, do, decay.cuda())]
+    got = [*ltn.ltn_attn_fwd_dkdv(*args, decay.cuda(), kv_in=kv0.cuda(), return_state=True),
+           *ltn.ltn_attn_bwd_dkdv(*args, do, decay.cuda())]
+    assert all(torch.equal(x, y) for x, y in zip(got, whole))
+    keep = [0, Bt * H - 1]
+    ins = [some(t, Bt * H, keep) for t in (q, k, v)]
+    refs = [*orc.fwd_recurrent_dkdv(*ins, decay.repeat(Bt)[keep], kv_in=some(kv0, Bt * H, keep), return_state=True),
+            *orc.bwd_recurrent_dkdv(*ins, some(g, Bt * H, keep), decay.repeat(Bt)[keep])]
+    for n, x, r in zip(("O", "kv", "dQ", "dK", "dV"), got, refs):
+        check(n, some(x, Bt * H, keep), r, TOL[BF])
+
+
 def test_outputs_inside_larger_buffers():
     """The states and flags that pass through the output's rows stay inside them."""
     D, Bt, H, N = 96, 8, 12, 1090
