@@ -129,8 +129,8 @@ def write_traffic_profile(workload: str, fetch_csv: str, write_csv: str) -> int:
         mf = re.search(r"pass_f32_kernel<(\d+), (\d+), (\d+), \d+, (\d+), (\d+)>", name)   # D, DV, B, KH, DC, mode
         if not (m or mf) or name not in write:
             continue
-        if m:
-            key = f"pass_bf16_kernel<{m.group(1)},{m.group(2)}>" + ("" if m.group(3) == "0" else f" mode {m.group(3)}")
+        if m:                              # mode 5: the plain pass with some chains in two parts
+            key = f"pass_bf16_kernel<{m.group(1)},{m.group(2)}>" + ("" if m.group(3) in ("0", "5") else f" mode {m.group(3)}")
         else:
             key = (f"pass_f32_kernel<{mf.group(1)},{mf.group(2)},{mf.group(3)}>"
                    + ("" if mf.group(4) == mf.group(1) else f" DC {mf.group(4)}")

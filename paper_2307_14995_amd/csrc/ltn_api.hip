@@ -382,13 +382,13 @@ bool gated_in_two_steps(long long chains, long long N, int D, ltn_dtype dtype, i
     return fused.segs < 3 || plan_time(fused, chains, N, D, D, true) + 1.5 >= two_us;
 }
 
-// Plain passes in more workgroups than the 256 units hold at once: are those that would be alone in the last
+// Passes in more workgroups than the 256 units hold at once: are those that would be alone in the last
 // round to be cut in two (launch_pass_cut_bf16)?  Fills in cut_chains and cut_len, half a chain.
 // The line, over 110 shapes (64 .. 256 features, forward and backward, 86 .. 1300 chains x 360 .. 5800 tokens; time
 // cut over time whole): up to half a round alone 0.84 .. 0.98 in two rounds, 0.89 .. 0.98 in three, 0.92 .. 1.00 in
 // four, 0.97 .. 1.10 beyond, where workgroups end so far apart that the last round fills up by itself; more than
 // half a round alone 1.01 .. 1.08 (the second parts then take more than the units that are left).  Unequal
-// widths, 17 such shapes: 0.84 .. 0.99.  Shorter than 12 blocks the launch that clears the flags takes
+// widths, 17 such shapes: 0.84 .. 0.99; gated forward, 21 shapes with and without o: 0.87 .. 0.97.  Shorter than 12 blocks the launch that clears the flags takes
 // what the cut gains (96 features x 763 tokens: 0.98).
 // Near half a round one workgroup per chain and pass keeps memory busy in the last round too: backward of 128 chains
 // of 128 features x 8192 0.96, x 3000 0.97.  While its inputs are about what the 256 MiB memory-side cache holds,
@@ -426,7 +426,7 @@ ltn_status run_passes(ltn::PassBatch& pb, int D, int blk, ltn_dtype dtype, void*
     pb.segs = 1;
     if (plan.segs == 1) {
         const int dv = full_width ? D : pick_dv(chain_passes, D, pb.count);
-        if (!full_width && pick_cut(pb, D, D, dv, D == 256 ? 64 : D))
+        if (pick_cut(pb, D, D, dv, D == 256 ? 64 : D))
             return ltn::launch_pass_cut_bf16(pb, D, stream) == hipSuccess ? LTN_OK : LTN_ERR_LAUNCH;
         return ltn::launch_pass_bf16(pb, D, dv, stream) == hipSuccess ? LTN_OK : LTN_ERR_LAUNCH;
     }

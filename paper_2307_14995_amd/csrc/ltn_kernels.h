@@ -52,7 +52,7 @@ struct PassBatch {
     // count == 3 only: passes 0 and 1 read the same token rows at the same time (same direction,
     // two shared operands) and pass 2 does not; lets the bf16 kernel order workgroup ids for that
     int pairs_first;
-    // Plain passes in more workgroups than compute units (launch_pass_cut_bf16): the last pass of chains
+    // Passes in more workgroups than compute units (launch_pass_cut_bf16): the last pass of chains
     // 0 .. cut_chains - 1 runs as two workgroups per slice, tokens [0, cut_len) and the rest, the second
     // starting from the state the first leaves.  cut_ids: workgroup ids where the whole passes but the
     // last, the whole last passes and the second parts begin.  cut_chains = 0: no pass is cut.
@@ -68,7 +68,7 @@ struct PassBatch {
 // c, out [chains, N, DC]; states [chains, D, DC]; dv slices DC.  Plain pass, or the state-only
 // sweep with dv = 64 (128 for (128,256)).  (D, DC) in {(256,128), (128,256), (128,64), (64,128)}.
 hipError_t launch_pass_bf16(const PassBatch& pb, int D, int dv, hipStream_t stream, int DC = 0);
-// The same for plain passes at their widest slices (DC columns up to 128; 64 where D = 256 or DC = 2 D = 128) with
+// The same for plain and gated passes at their widest slices (DC columns up to 128; 64 where D = 256 or DC = 2 D = 128) with
 // cut_chains and cut_len set and cut_ids to be filled in: two launches, as the flags that the second
 // parts wait for are cleared first.  cut_len is a multiple of 64, at least cut_state_rows(D) tokens less than N.
 inline long long cut_state_rows(int D) { return 2 * D + 64; }

@@ -100,11 +100,13 @@ struct Cfg {
 // state-only sweep of the sequence-parallel form (no outputs: only the segment's end state).
 // The gated epilogue's values are fetched one block ahead of their use, within the block that uses them
 // (kGatedLate) or two ahead (kGatedFar).
-// kCut: the plain pass with some chains in two parts (cut_start below).
+// kCut and kCut + a gated mode: the same with some chains in two parts ("chains in two parts" below).
 enum { kPlain = 0, kGated = 1, kStateOnly = 2, kGatedLate = 3, kGatedFar = 4, kCut = 5 };
-constexpr bool has_gate(int mode) { return mode == kGated || mode == kGatedLate || mode == kGatedFar; }
+constexpr bool is_cut(int mode) { return mode >= kCut; }
+constexpr int uncut(int mode) { return is_cut(mode) ? mode - kCut : mode; }
+constexpr bool has_gate(int mode) { return uncut(mode) == kGated || uncut(mode) == kGatedLate || uncut(mode) == kGatedFar; }
 // blocks ahead
-constexpr int gate_ahead(int mode) { return mode == kGated ? 1 : (mode == kGatedFar ? 2 : 0); }
+constexpr int gate_ahead(int mode) { return uncut(mode) == kGated ? 1 : (uncut(mode) == kGatedFar ? 2 : 0); }
 
 
 // Register prefetch loads of the AREG output waves are issued from inline assembly and
@@ -447,7 +449,7 @@ struct Chain {            // what every wave of the workgroup knows about its pr
     char* handover;          // parts 1, 2: the slice's columns of the second part's lowest output row
 };
 
-// =============================================================== chains in two parts (kCut)
+// =============================================================== chains in two parts (is_cut)
 //
 // A launch of W workgroups that take the same time each needs ceil(W / 256) rounds of the 256 compute units,
 // however few are in the last one.  So the workgroups that would be alone there (up to 128) are cut in two along
@@ -457,9 +459,10 @@ struct Chain {            // what every wave of the workgroup knows about its pr
 // continues from the first's fp32 state: the same sums in the same order, the same bits as uncut.
 // Measured, whole and cut: backward of 96 features x 96 chains x 1999 tokens (288 workgroups) 85.6 and 74.2 us,
 // of 128 features x 96 x 2048 110.7 and 94.6, x 128 x 8192 (384, bound by memory) 536 and 516, of 256
-// features x 32 x 4096 (384) 257 and 226; forward of 256 features x 85 x 4479 (340) 336 and 281.
+// features x 32 x 4096 (384) 257 and 226; forward of 256 features x 85 x 4479 (340) 336 and 281, gated of
+// 128 features x 288 x 2048 205 and 184, with O 234 and 210.
 //
-// That state needs no scratch memory: row r of the slice's [D x DV] lies in the slice's columns of
+// That state needs no scratch memory (the gated pass keeps it in Y): row r of the slice's [D x DV] lies in the slice's columns of
 // output rows 2r and 2r + 1 of the second part, which overwrites them when all its state waves have
 // loaded it (the barrier before its first block).  A flag word in row 2D, cleared by a launch before this
 // one, says that it is there.  State and flag are written and read with relaxed atomic operations of
@@ -787,7 +790,7 @@ __device__ __forceinline__ void pass_state_wave(const Chain& ch, char* smem, int
     constexpr bool SO = MODE == kStateOnly;          // no published state copies
     const int g = lane >> 4, i16 = lane & 15;
     const int dk0 = u * (D / 4);
-    if constexpr (MODE == kCut) {
+    if constexpr (is_cut(MODE)) {
         if (ch.part == 2) {
             while (__hip_atomic_load(handover_flag<DR, DC>(ch.handover), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0)
                 __builtin_amdgcn_s_sleep(16);
@@ -800,7 +803,7 @@ __device__ __forceinline__ void pass_state_wave(const Chain& ch, char* smem, int
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
-            if (MODE == kCut && ch.part == 2) {
+            if (is_cut(MODE) && ch.part == 2) {
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     const int row = dk0 + 16 * mt + 4 * g + j;
@@ -830,7 +833,7 @@ __device__ __forceinline__ void pass_state_wave(const Chain& ch, char* smem, int
     for (int blk = 0; blk < ch.T; ++blk) {
         const bool more = blk + 1 < ch.T;
         if (!more) {
-            if (!ch.state_out && !(MODE == kCut && ch.part == 1)) break;     // the last update only feeds the returned state
+            if (!ch.state_out && !(is_cut(MODE) && ch.part == 1)) break;     // the last update only feeds the returned state
             if (ch.last_valid != kBlock) k.set_block_len(ch.lam, ch.last_valid, lane);
         }
         const char* tb = smem + stage * C::PSTAGE;
@@ -842,7 +845,7 @@ __device__ __forceinline__ void pass_state_wave(const Chain& ch, char* smem, int
         stage = (stage + 1 == C::PST) ? 0 : stage + 1;
     }
 
-    if constexpr (MODE == kCut) {
+    if constexpr (is_cut(MODE)) {
         if (ch.part == 1) {
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt)
@@ -904,7 +907,7 @@ __device__ __forceinline__ void pass_body(const PassBatch& pb, int xcd_ids, int 
     // chain the pair index is the chain index
     constexpr int NS = DC / DV;            // column slices
     int vchain, pi, split, part = 0;
-    if constexpr (MODE == kCut) {          // first parts; whole passes but the last; whole last passes; second parts
+    if constexpr (is_cut(MODE)) {          // first parts; whole passes but the last; whole last passes; second parts
         const int last = pb.count - 1;
         const bool others = wg >= pb.cut_ids[0] && wg < pb.cut_ids[1];
         part = wg < pb.cut_ids[0] ? 1 : (wg >= pb.cut_ids[2] ? 2 : 0);
@@ -918,7 +921,7 @@ __device__ __forceinline__ void pass_body(const PassBatch& pb, int xcd_ids, int 
     } else {
         map_pass<NS>((unsigned)wg, pb.count, xcd_ids, vchain, pi, split);
     }
-    if (MODE != kCut && NS == 1 && pb.pairs_first && pb.count == 3 && xcd_ids) {
+    if (!is_cut(MODE) && NS == 1 && pb.pairs_first && pb.count == 3 && xcd_ids) {
         // Backward at full width: passes 0 and 1 of a chain walk the token axis together and
         // share two operands, pass 2 walks the other way.  Ids: all (pass 0, pass 1) pairs
         // first, a chain's pair side by side on one XCD, then every pass 2.  With more
@@ -952,8 +955,8 @@ __device__ __forceinline__ void pass_body(const PassBatch& pb, int xcd_ids, int 
 
     // the segment's tokens [seg_start, seg_start + n) of the pass's (possibly reversed) token
     // axis are rows [row0, row0 + n) of the tensors
-    const long long seg_start = MODE == kCut ? (part == 2 ? pb.cut_len : 0) : (long long)seg * pb.seg_len;
-    const long long n = MODE == kCut ? (part == 1 ? pb.cut_len : pb.N - seg_start)
+    const long long seg_start = is_cut(MODE) ? (part == 2 ? pb.cut_len : 0) : (long long)seg * pb.seg_len;
+    const long long n = is_cut(MODE) ? (part == 1 ? pb.cut_len : pb.N - seg_start)
                                      : ((pb.segs > 1 && pb.N - seg_start > pb.seg_len) ? pb.seg_len : pb.N - seg_start);
     const long long row0 = rev ? (pb.N - seg_start - n) : seg_start;
 
@@ -969,9 +972,9 @@ __device__ __forceinline__ void pass_body(const PassBatch& pb, int xcd_ids, int 
     ch.gate = GATED ? (const char*)P0.gate + chain_off : nullptr;       // (the gated epilogue is one pass)
     ch.y = GATED ? (char*)P0.gated_out + chain_off : nullptr;
     ch.eps = P0.eps;
-    if constexpr (MODE == kCut) {
+    if constexpr (is_cut(MODE)) {
         ch.part = part;
-        ch.handover = out + ((size_t)chain * (size_t)pb.N + (size_t)(rev ? 0 : pb.cut_len)) * DC * 2 + col_off;
+        ch.handover = (GATED ? (char*)P0.gated_out : out) + ((size_t)chain * (size_t)pb.N + (size_t)(rev ? 0 : pb.cut_len)) * DC * 2 + col_off;
     }
     ch.state_in = state_in ? state_in + (size_t)vchain * DR * DC + (size_t)split * DV : nullptr;
     ch.state_out = state_out ? state_out + (size_t)vchain * DR * DC + (size_t)split * DV : nullptr;
@@ -1029,7 +1032,7 @@ __device__ __forceinline__ void pass_body(const PassBatch& pb, int xcd_ids, int 
             default: pass_state_wave<D, DV, DC, MODE, DR>(ch, smem, lane, wave - 4); break;
         }
     }
-    if constexpr (MODE == kCut) {
+    if constexpr (is_cut(MODE)) {
         if (ch.part == 1) {                // every state wave has stored its rows of the state and released them
             __syncthreads();
             if (wave == 0 && lane == 0)
@@ -1070,7 +1073,7 @@ __global__ void clear_handover_kernel(char* out, long long row_bytes, long long 
     if (i < n) *(unsigned*)(out + ((long long)(i / slices) * N + flag_row) * row_bytes + (i % slices) * slice_bytes) = 0u;
 }
 
-template <int D, int DV, int DC, int DR>
+template <int D, int DV, int DC, int DR, int MODE = kCut>
 hipError_t launch_cut_t(PassBatch& pb, hipStream_t stream) {
     constexpr int NS = DC / DV;
     const PassArgs& last = pb.p[pb.count - 1];
@@ -1086,9 +1089,9 @@ hipError_t launch_cut_t(PassBatch& pb, hipStream_t stream) {
     pb.cut_ids[0] = (int)cut;
     pb.cut_ids[1] = (int)(cut + others);
     pb.cut_ids[2] = (int)second;
-    hipLaunchKernelGGL(clear_handover_kernel, dim3((unsigned)((cut + 63) / 64)), dim3(64), 0, stream, (char*)last.out,
+    hipLaunchKernelGGL(clear_handover_kernel, dim3((unsigned)((cut + 63) / 64)), dim3(64), 0, stream, (char*)(has_gate(MODE) ? last.gated_out : last.out),
                        DC * 2LL, pb.N, (last.rev ? 0 : pb.cut_len) + 2 * DR, NS, DV * 2, (int)cut);
-    hipLaunchKernelGGL((pass_bf16_kernel<D, DV, kCut, DC, DR>), dim3((unsigned)(second + cut)), dim3(kThreads), 0, stream, pb,
+    hipLaunchKernelGGL((pass_bf16_kernel<D, DV, MODE, DC, DR>), dim3((unsigned)(second + cut)), dim3(kThreads), 0, stream, pb,
                        (int)xcd);
     return hipGetLastError();
 }
@@ -1101,6 +1104,15 @@ hipError_t launch_pass_cut_bf16(PassBatch& pb, int D, hipStream_t stream, int DC
         if (D == 128 && DC == 256) return launch_cut_t<128, 128, 256, 128>(pb, stream);
         if (D == 128 && DC == 64) return launch_cut_t<128, 64, 64, 128>(pb, stream);
         if (D == 64 && DC == 128) return launch_cut_t<64, 64, 128, 64>(pb, stream);
+        return hipErrorInvalidValue;
+    }
+    if (pb.p[0].gate) {                    // the forms of launch_pass_bf16 for this many chains
+        if (pb.count != 1 || !pb.p[0].gated_out) return hipErrorInvalidValue;
+        if (D == 64) return launch_cut_t<64, 64, 64, 64, kCut + kGatedFar>(pb, stream);
+        if (D == 96 && pb.p[0].out) return launch_cut_t<128, 96, 96, 96, kCut + kGatedLate>(pb, stream);
+        if (D == 96) return launch_cut_t<128, 96, 96, 96, kCut + kGated>(pb, stream);
+        if (D == 128 && pb.p[0].out) return launch_cut_t<128, 128, 128, 128, kCut + kGatedLate>(pb, stream);
+        if (D == 128) return launch_cut_t<128, 128, 128, 128, kCut + kGated>(pb, stream);
         return hipErrorInvalidValue;
     }
     switch (D) {

@@ -1,4 +1,4 @@
-"""Plain bf16 passes in a few more workgroups than the GPU has compute units: the chains whose last pass
+"""bf16 passes in a few more workgroups than the GPU has compute units: the chains whose last pass
 runs in two parts (the second starting from the first's state, kept in the output's own rows).
 
 The parts add the same terms in the same order as the whole chain, so every result must be the same bits as
@@ -50,6 +50,33 @@ def test_forward(D, Bt, H, N, cut):
     o_ref, kv_ref = orc.fwd_recurrent(*(some(t, Bt * H, keep) for t in (q, k, v)), decay.repeat(Bt)[keep],
                                       kv_in=some(kv0, Bt * H, keep), return_state=True)
     check("O", some(o, Bt * H, keep), o_ref, TOL[BF])
+    check("kv", some(kv, Bt * H, keep), kv_ref, TOL[BF])
+
+
+@pytest.mark.parametrize("D,Bt,H,N,cut", [c for c in FORWARD if c[0] != 256])
+def test_gated_forward(D, Bt, H, N, cut):
+    """The state passes through y's rows, whether o is stored or not."""
+    q, k, v = synth.make_qkv(Bt, H, N, D, BF, 920 + N)
+    u = synth.make_gate(Bt, H, N, D, BF, 920 + N)
+    decay = mixed_decay(H)
+    kv0 = torch.randn(Bt, H, D, D, generator=torch.Generator().manual_seed(N)) / D
+    args = gpu(q, k, v, u, decay)
+
+    def call(store_o):
+        return ltn.ltn_attn_fwd_gated(*args, eps=1e-6, kv_in=kv0.cuda(), return_state=True, store_o=store_o)
+
+    with force_segs(1):
+        o_whole, y_whole, kv_whole = call(True)
+        _, y_alone, _ = call(False)
+    o, y, kv = call(True)
+    assert torch.equal(o, o_whole) and torch.equal(y, y_whole) and torch.equal(kv, kv_whole)
+    _, y, kv = call(False)
+    assert torch.equal(y, y_alone) and torch.equal(kv, kv_whole)
+    keep = lines(Bt * H, cut)
+    o_ref, kv_ref = orc.fwd_recurrent(*(some(t, Bt * H, keep) for t in (q, k, v)), decay.repeat(Bt)[keep],
+                                      kv_in=some(kv0, Bt * H, keep), return_state=True)
+    check("O", some(o, Bt * H, keep), o_ref, TOL[BF])
+    check("Y", some(y, Bt * H, keep), orc.gate_fwd(o_ref, some(u, Bt * H, keep), 1e-6), TOL[BF])
     check("kv", some(kv, Bt * H, keep), kv_ref, TOL[BF])
 
 
