@@ -25,7 +25,8 @@
  *   - Work is enqueued on `stream` (a hipStream_t passed as void*; NULL = the
  *     default stream).  Calls return without synchronising.
  *   - Outputs are fully overwritten (fp32 passes of few chains keep their segments' states in
- *     the outputs' rows until those rows are written); inputs are never written.  An output whose
+ *     the outputs' rows until those rows are written, bf16 passes that cut some chains in two the
+ *     state between the two parts); inputs are never written.  An output whose
  *     bytes overlap an input's or another output's (not only equal base
  *     pointers; the workspace counts as an output) is rejected
  *     (LTN_ERR_UNSUPPORTED).  The one exception: kv_out may be kv_in itself.
