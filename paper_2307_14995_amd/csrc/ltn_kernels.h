@@ -55,11 +55,65 @@ struct PassBatch {
     // Passes in more workgroups than compute units (launch_pass_cut_bf16): the last pass of chains
     // 0 .. cut_chains - 1 runs as two workgroups per slice, tokens [0, cut_len) and the rest, the second
     // starting from the state the first leaves.  cut_ids: workgroup ids where the whole passes but the
-    // last, the whole last passes and the second parts begin.  cut_chains = 0: no pass is cut.
+    // last, the whole last passes and the second parts begin.  Read by the cut kernels only.
     int cut_chains;
     int cut_ids[3];
     long long cut_len;
 };
+
+// What a workgroup of a cut launch does.  part: 0 a whole pass, 1 the first and 2 the second part of the
+// last pass of a cut chain; split: column slice, of NS.  Ids [0, cut_ids[0]) and from cut_ids[2] (a multiple
+// of 8) on are those of the parts, as many first as second ones.  Which part such a workgroup runs is not told by its
+// id but by the number it draws: how many of the parts' workgroups with ids congruent mod 8 (one XCD's)
+// started before it.  The first parts go first, so whoever gets a second part knows that its first part has
+// started, whatever the order in which the GPU starts workgroups.
+struct CutRole { int part, pass, chain, split; };
+
+// fills in cut_ids; returns the workgroups of the launch
+inline long long cut_launch_ids(PassBatch& pb, int NS) {
+    const long long cut = (long long)pb.cut_chains * NS, others = (long long)pb.chains * (pb.count - 1) * NS,
+                    whole = (long long)(pb.chains - pb.cut_chains) * NS;
+    const long long second = (cut + others + whole + 7) / 8 * 8;       // congruent mod 8 to the first parts
+    pb.cut_ids[0] = (int)cut;
+    pb.cut_ids[1] = (int)(cut + others);
+    pb.cut_ids[2] = (int)second;
+    return second + cut;
+}
+
+__host__ __device__ inline bool cut_draws(const PassBatch& pb, int wg) { return wg < pb.cut_ids[0] || wg >= pb.cut_ids[2]; }
+// first parts (and second parts) of the ids congruent to c mod 8
+__host__ __device__ inline int cut_parts_of(const PassBatch& pb, int c) { return (pb.cut_ids[0] - c + 7) / 8; }
+// chain and slice of part w; xcd: chains are dealt to XCDs (their number and cut_chains are multiples of 8)
+template <int NS>
+__host__ __device__ inline void cut_part(int w, int xcd, int& chain, int& split) {
+    const int slot = xcd ? w >> 3 : w, q = slot / NS;
+    chain = xcd ? q * 8 + (w & 7) : q;
+    split = slot - q * NS;
+}
+// the part that the last workgroup of the ids congruent to c mod 8 to draw gets (if they have parts)
+__host__ __device__ inline int cut_last_part(const PassBatch& pb, int c) { return c + 8 * (cut_parts_of(pb, c) - 1); }
+
+// chain >= pb.chains: a padding workgroup.  number: what it drew, where cut_draws().
+template <int NS>
+__host__ __device__ inline CutRole cut_role(const PassBatch& pb, int xcd, int wg, int number) {
+    const int last = pb.count - 1;
+    CutRole r = {0, last, 0, 0};
+    if (cut_draws(pb, wg)) {
+        const int c = wg & 7, n = cut_parts_of(pb, c);
+        r.part = number < n ? 1 : 2;
+        cut_part<NS>(c + 8 * (r.part == 1 ? number : number - n), xcd, r.chain, r.split);
+    } else if (wg >= pb.cut_ids[1]) {
+        cut_part<NS>(wg - pb.cut_ids[1], xcd, r.chain, r.split);
+        r.chain += pb.cut_chains;
+    } else {                               // (count - 1 is 1 or 2 here: nothing is divided by a loaded number)
+        const int w = wg - pb.cut_ids[0], slot = xcd ? w >> 3 : w, q = last == 1 ? slot / NS : slot / (2 * NS);
+        const int within = slot - q * last * NS;
+        r.chain = xcd ? q * 8 + (w & 7) : q;
+        r.pass = within / NS;
+        r.split = within - r.pass * NS;
+    }
+    return r;
+}
 
 // bf16 MFMA kernel, block length 64.  D in {64,96,128,256}; dv = value columns per workgroup
 // (D, D/2 or, for D = 128, D/4; 64 or 32 for D = 256 and 32 for D = 96, plain pass only).
@@ -68,9 +122,9 @@ struct PassBatch {
 // c, out [chains, N, DC]; states [chains, D, DC]; dv slices DC.  Plain pass, or the state-only
 // sweep with dv = 64 (128 for (128,256)).  (D, DC) in {(256,128), (128,256), (128,64), (64,128)}.
 hipError_t launch_pass_bf16(const PassBatch& pb, int D, int dv, hipStream_t stream, int DC = 0);
-// The same for plain and gated passes at their widest slices (DC columns up to 128; 64 where D = 256 or DC = 2 D = 128) with
-// cut_chains and cut_len set and cut_ids to be filled in: two launches, as the flags that the second
-// parts wait for are cleared first.  cut_len is a multiple of 64, at least cut_state_rows(D) tokens less than N.
+// The same for plain and gated passes at their widest slices (DC columns up to 128; 64 where D = 256 or
+// DC = 2 D = 128) with cut_chains and cut_len set and cut_ids to be filled in: two launches, as the flags that the
+// second parts wait for and the counters are cleared first.  cut_len is a multiple of 64, at least cut_state_rows(D) tokens less than N.
 inline long long cut_state_rows(int D) { return 2 * D + 64; }
 hipError_t launch_pass_cut_bf16(PassBatch& pb, int D, hipStream_t stream, int DC = 0);
 // Forward by the quadratic tiling of App. B Algorithm 3 (comparison kernel), bf16, zero

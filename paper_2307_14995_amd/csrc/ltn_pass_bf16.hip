@@ -453,7 +453,7 @@ struct Chain {            // what every wave of the workgroup knows about its pr
 //
 // A launch of W workgroups that take the same time each needs ceil(W / 256) rounds of the 256 compute units,
 // however few are in the last one.  So the workgroups that would be alone there (up to 128) are cut in two along
-// the tokens.  Ids, which is the order of dispatch: first parts, whole chains, second parts.  The units that
+// the tokens.  Order of ids, and as a rule of dispatch: first parts, whole chains, second parts.  The units that
 // took first parts begin their next whole chain when those end, the others take the second parts when their
 // last whole chain ends, and the launch ends half a round after the last full one.  The second part
 // continues from the first's fp32 state: the same sums in the same order, the same bits as uncut.
@@ -462,16 +462,20 @@ struct Chain {            // what every wave of the workgroup knows about its pr
 // features x 32 x 4096 (384) 257 and 226; forward of 256 features x 85 x 4479 (340) 336 and 281, gated of
 // 128 features x 288 x 2048 205 and 184, with O 234 and 210.
 //
-// That state needs no scratch memory (the gated pass keeps it in Y): row r of the slice's [D x DV] lies in the slice's columns of
-// output rows 2r and 2r + 1 of the second part, which overwrites them when all its state waves have
-// loaded it (the barrier before its first block).  A flag word in row 2D, cleared by a launch before this
+// That state needs no scratch memory (the gated pass keeps it in Y): row r of the slice's [D x DV] lies in the
+// slice's columns of output rows 2r and 2r + 1 of the second part, which overwrites them when all its state waves
+// have loaded it (the barrier before its first block).  A flag word in row 2D, cleared by a launch before this
 // one, says that it is there.  State and flag are written and read with relaxed atomic operations of
 // device scope, which go past the caches that are not coherent, and ordered by the wait for the stores and the
 // barrier between them and the flag's store, and by the branch between the flag's load and theirs.  A release and
 // an acquire fence would write back and invalidate the XCD's L2 under all its other workgroups (96 x 1999: 80.8 us,
 // 256 features 250).
-// The wait ends: a second part waits for one first part only, which waits for nothing and comes earlier in the
-// dispatch order of the same XCD (ids congruent mod 8).  As a rule the state has been there for half a chain.
+//
+// The wait ends, in whatever order workgroups are started: who runs which part is drawn when they start
+// (cut_role), so a second part waits for a first part that has started and itself waits for nothing.  The
+// counters they draw from, one per XCD, lie behind the flag of the second part that is drawn last: its
+// workgroup overwrites them when everybody has drawn.  Parts told by their ids alone were no faster (96 x 1999 74.2
+// us, now 73 on another card; 256 features 226 and 224).  As a rule the state has been there for half a chain.
 template <int DV, int DC>
 __device__ __forceinline__ float* handover_at(char* p, int row, int nt, int i16) {      // column 16 nt + i16
     constexpr int H = DV / 2;
@@ -479,6 +483,14 @@ __device__ __forceinline__ float* handover_at(char* p, int row, int nt, int i16)
 }
 template <int D, int DC>
 __device__ __forceinline__ unsigned* handover_flag(char* p) { return (unsigned*)(p + (size_t)(2 * D) * (DC * 2)); }
+// How many workgroups drew from `counter` before this one (every wave of it calls this; LDS is not in use yet).
+__device__ __forceinline__ int draw_number(unsigned* counter, char* smem, int tid) {
+    if (tid == 0) *(unsigned*)smem = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    const int number = __builtin_amdgcn_readfirstlane(*(int*)smem);
+    __syncthreads();
+    return number;
+}
 
 // =============================================================== pass body
 
@@ -907,17 +919,26 @@ __device__ __forceinline__ void pass_body(const PassBatch& pb, int xcd_ids, int 
     // chain the pair index is the chain index
     constexpr int NS = DC / DV;            // column slices
     int vchain, pi, split, part = 0;
-    if constexpr (is_cut(MODE)) {          // first parts; whole passes but the last; whole last passes; second parts
+    char* handover = nullptr;              // is_cut: of this part
+    if constexpr (is_cut(MODE)) {
         const int last = pb.count - 1;
-        const bool others = wg >= pb.cut_ids[0] && wg < pb.cut_ids[1];
-        part = wg < pb.cut_ids[0] ? 1 : (wg >= pb.cut_ids[2] ? 2 : 0);
-        const int first_id = part == 1 ? 0 : (others ? pb.cut_ids[0] : (part == 2 ? pb.cut_ids[2] : pb.cut_ids[1]));
-        const unsigned w = (unsigned)(wg - first_id), slot = xcd_ids ? w >> 3 : w;
-        const unsigned per = others ? (unsigned)(last * NS) : NS, q = others ? (last == 1 ? slot / NS : slot / (2 * NS)) : slot / NS;
-        const int within = (int)(slot - q * per);
-        vchain = (int)(xcd_ids ? q * 8 + (w & 7) : q) + (part == 0 && !others ? pb.cut_chains : 0);
-        pi = others ? within / NS : last;
-        split = others ? within % NS : within;
+        char* const last_out = GATED ? (char*)pb.p[0].gated_out : pick(last, (char*)pb.p[0].out, (char*)pb.p[1].out, (char*)pb.p[2].out);
+        const long long row = pick(last, pb.p[0].rev, pb.p[1].rev, pb.p[2].rev) ? 0 : pb.cut_len;
+        auto handover_of = [&](int chain, int slice) {
+            return last_out + ((size_t)chain * (size_t)pb.N + (size_t)row) * DC * 2 + (size_t)slice * DV * 2;
+        };
+        int number = 0;
+        if (cut_draws(pb, wg)) {
+            int chain, slice;
+            cut_part<NS>(cut_last_part(pb, wg & 7), xcd_ids, chain, slice);
+            number = draw_number(handover_flag<DR, DC>(handover_of(chain, slice)) + 1, smem, wave * 64 + lane);
+        }
+        const CutRole r = cut_role<NS>(pb, xcd_ids, wg, number);
+        vchain = r.chain;
+        pi = r.pass;
+        split = r.split;
+        part = r.part;
+        handover = handover_of(vchain, split);
     } else {
         map_pass<NS>((unsigned)wg, pb.count, xcd_ids, vchain, pi, split);
     }
@@ -974,7 +995,7 @@ __device__ __forceinline__ void pass_body(const PassBatch& pb, int xcd_ids, int 
     ch.eps = P0.eps;
     if constexpr (is_cut(MODE)) {
         ch.part = part;
-        ch.handover = (GATED ? (char*)P0.gated_out : out) + ((size_t)chain * (size_t)pb.N + (size_t)(rev ? 0 : pb.cut_len)) * DC * 2 + col_off;
+        ch.handover = handover;
     }
     ch.state_in = state_in ? state_in + (size_t)vchain * DR * DC + (size_t)split * DV : nullptr;
     ch.state_out = state_out ? state_out + (size_t)vchain * DR * DC + (size_t)split * DV : nullptr;
@@ -1033,7 +1054,7 @@ __device__ __forceinline__ void pass_body(const PassBatch& pb, int xcd_ids, int 
         }
     }
     if constexpr (is_cut(MODE)) {
-        if (ch.part == 1) {                // every state wave has stored its rows of the state and released them
+        if (ch.part == 1) {                // every state wave has stored its rows of the state and waited for the stores
             __syncthreads();
             if (wave == 0 && lane == 0)
                 __hip_atomic_store(handover_flag<DR, DC>(ch.handover), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1070,7 +1091,10 @@ hipError_t launch_t(const PassBatch& pb, hipStream_t stream) {
 __global__ void clear_handover_kernel(char* out, long long row_bytes, long long N, long long flag_row, int slices,
                                       int slice_bytes, int n) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) *(unsigned*)(out + ((long long)(i / slices) * N + flag_row) * row_bytes + (i % slices) * slice_bytes) = 0u;
+    if (i >= n) return;
+    unsigned* const flag = (unsigned*)(out + ((long long)(i / slices) * N + flag_row) * row_bytes + (i % slices) * slice_bytes);
+    flag[0] = 0u;
+    flag[1] = 0u;                          // the counter, in one part of each XCD's
 }
 
 template <int D, int DV, int DC, int DR, int MODE = kCut>
@@ -1082,16 +1106,12 @@ hipError_t launch_cut_t(PassBatch& pb, hipStream_t stream) {
     if (pb.segs != 1 || pb.cut_chains < 1 || pb.cut_chains > pb.chains || (xcd && (pb.cut_chains & 7)) ||
         pb.cut_len < kBlock || pb.cut_len % kBlock || pb.N - pb.cut_len < cut_state_rows(DR))
         return hipErrorInvalidValue;
-    const long long cut = (long long)pb.cut_chains * NS, others = (long long)pb.chains * (pb.count - 1) * NS,
-                    whole = (long long)(pb.chains - pb.cut_chains) * NS;
-    const long long second = (cut + others + whole + 7) / 8 * 8;       // congruent mod 8 to the first parts
-    if (second + cut > 0x7fffffffLL) return hipErrorInvalidValue;
-    pb.cut_ids[0] = (int)cut;
-    pb.cut_ids[1] = (int)(cut + others);
-    pb.cut_ids[2] = (int)second;
+    const long long wgs = cut_launch_ids(pb, NS);
+    if (wgs > 0x7fffffffLL) return hipErrorInvalidValue;
+    const int cut = pb.cut_ids[0];
     hipLaunchKernelGGL(clear_handover_kernel, dim3((unsigned)((cut + 63) / 64)), dim3(64), 0, stream, (char*)(has_gate(MODE) ? last.gated_out : last.out),
-                       DC * 2LL, pb.N, (last.rev ? 0 : pb.cut_len) + 2 * DR, NS, DV * 2, (int)cut);
-    hipLaunchKernelGGL((pass_bf16_kernel<D, DV, MODE, DC, DR>), dim3((unsigned)(second + cut)), dim3(kThreads), 0, stream, pb,
+                       DC * 2LL, pb.N, (last.rev ? 0 : pb.cut_len) + 2 * DR, NS, DV * 2, cut);
+    hipLaunchKernelGGL((pass_bf16_kernel<D, DV, MODE, DC, DR>), dim3((unsigned)wgs), dim3(kThreads), 0, stream, pb,
                        (int)xcd);
     return hipGetLastError();
 }
