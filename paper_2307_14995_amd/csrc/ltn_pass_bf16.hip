@@ -1109,8 +1109,10 @@ hipError_t launch_cut_t(PassBatch& pb, hipStream_t stream) {
     const long long wgs = cut_launch_ids(pb, NS);
     if (wgs > 0x7fffffffLL) return hipErrorInvalidValue;
     const int cut = pb.cut_ids[0];
-    hipLaunchKernelGGL(clear_handover_kernel, dim3((unsigned)((cut + 63) / 64)), dim3(64), 0, stream, (char*)(has_gate(MODE) ? last.gated_out : last.out),
-                       DC * 2LL, pb.N, (last.rev ? 0 : pb.cut_len) + 2 * DR, NS, DV * 2, cut);
+    hipLaunchKernelGGL(clear_handover_kernel, dim3((unsigned)((cut + 63) / 64)), dim3(64), 0, stream,
+                       (char*)(has_gate(MODE) ? last.gated_out : last.out), DC * 2LL, pb.N, (last.rev ? 0 : pb.cut_len) + 2 * DR, NS, DV * 2, cut);
+    // without it the pass would read flags and counters that nobody cleared
+    if (const hipError_t e = hipGetLastError(); e != hipSuccess) return e;
     hipLaunchKernelGGL((pass_bf16_kernel<D, DV, MODE, DC, DR>), dim3((unsigned)wgs), dim3(kThreads), 0, stream, pb,
                        (int)xcd);
     return hipGetLastError();
