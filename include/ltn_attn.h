@@ -345,6 +345,14 @@ int ltn_attn_pick_block(int D, ltn_dtype dtype);
 ltn_status ltn_attn_query_plan(int Bt, int H, long long N, int D, ltn_dtype dtype, int call,
                                int* dv, int* segs);
 
+/* bf16 passes of whole chains in a few more workgroups than the GPU has compute units run some
+ * chains' last pass (of a backward, dQ) in two parts: how many chains in *chains (0 = none) and the
+ * tokens of a first part in *tokens.  Dk = Dv with `call` as in ltn_attn_query_plan, or Dk = 2 Dv
+ * with 0 for the forward (and dV) and 1 for the backward's launch of dK and dQ.  For reports and
+ * tests that need to know which kernel ran. */
+ltn_status ltn_attn_query_cut(int Bt, int H, long long N, int Dk, int Dv, ltn_dtype dtype, int call,
+                              int* chains, long long* tokens);
+
 /* TEST ONLY.  Forces the launch plan of ltn_attn_fwd / ltn_attn_bwd / ltn_attn_fwd_gated for
  * the whole process until called again: dv = value columns per workgroup (0 = the library's
  * choice; a value the kernels do not have for a given D is ignored), segs = segments per

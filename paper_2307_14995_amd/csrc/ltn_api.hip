@@ -383,7 +383,7 @@ bool gated_in_two_steps(long long chains, long long N, int D, ltn_dtype dtype, i
 }
 
 // Passes in more workgroups than the 256 units hold at once: are those that would be alone in the last
-// round to be cut in two (launch_pass_cut_bf16)?  Fills in cut_chains and cut_len, half a chain.
+// round to be cut in two (launch_pass_cut_bf16), at half a chain?  chains = 0: no.
 // The line, over 110 shapes (64 .. 256 features, forward and backward, 86 .. 1300 chains x 360 .. 5800 tokens; time
 // cut over time whole): up to half a round alone 0.84 .. 0.98 in two rounds, 0.89 .. 0.98 in three, 0.92 .. 1.00 in
 // four, 0.97 .. 1.10 beyond, where workgroups end so far apart that the last round fills up by itself; more than
@@ -396,24 +396,36 @@ bool gated_in_two_steps(long long chains, long long N, int D, ltn_dtype dtype, i
 // tensors of 64 MiB) 0.98 .. 1.04 from one card to another and 1.06 in a mixer's step; so it is cut there
 // only from 320 MiB on.
 // widest: value columns of the widest slices that DC columns have here, the only ones that are cut.
-bool pick_cut(ltn::PassBatch& pb, int D, int DC, int dv, int widest) {
+struct Cut { int chains; long long len; };
+Cut pick_cut(int chains, int count, long long N, int D, int DC, int dv, int widest) {
     constexpr long long kRounds = 4, kHalf = 6;
-    if (dv != widest || g_debug_segs.load(std::memory_order_relaxed) == 1) return false;
+    const Cut none = {0, 0};
+    if (dv != widest || g_debug_segs.load(std::memory_order_relaxed) == 1) return none;
     const int slices = DC / dv;
-    const long long per_chain = (long long)pb.count * slices;
+    const long long per_chain = (long long)count * slices;
     // one XCD's workgroups and units where ids deal chains to XCDs, else all of them
-    const bool xcd = (pb.chains & 7) == 0;
-    const long long wgs = xcd ? pb.chains / 8 * per_chain : pb.chains * per_chain, units = xcd ? 32 : 256;
-    const long long chains = (wgs % units + slices - 1) / slices;
-    const long long input_mib = (pb.count == 3 ? 4 * D : 2 * D + DC) * pb.chains * pb.N * 2 >> 20;
-    if (slices == 1 && 16 * chains > 7 * units && input_mib < 320) return false;
-    if (wgs < units || wgs > kRounds * units || chains == 0 || chains * slices > units / 2) return false;
-    const long long first = ((pb.N + 63) / 64 + 1) / 2;                // of a chain's blocks
-    if (pb.N - 64 * first <= 64 * (kHalf - 1) || pb.N - 64 * first < ltn::cut_state_rows(D)) return false;
-    pb.cut_chains = (int)(xcd ? 8 * chains : chains);
-    pb.cut_len = 64 * first;
-    return pb.cut_chains <= pb.chains;
+    const bool xcd = (chains & 7) == 0;
+    const long long wgs = xcd ? chains / 8 * per_chain : chains * per_chain, units = xcd ? 32 : 256;
+    const long long alone = (wgs % units + slices - 1) / slices;       // chains
+    const long long input_mib = (count == 3 ? 4 * D : 2 * D + DC) * chains * N * 2 >> 20;
+    if (slices == 1 && 16 * alone > 7 * units && input_mib < 320) return none;
+    if (wgs < units || wgs > kRounds * units || alone == 0 || alone * slices > units / 2) return none;
+    const long long first = ((N + 63) / 64 + 1) / 2;                   // of a chain's blocks
+    if (N - 64 * first <= 64 * (kHalf - 1) || N - 64 * first < ltn::cut_state_rows(D)) return none;
+    const Cut cut = {(int)(xcd ? 8 * alone : alone), 64 * first};
+    return cut.chains <= chains ? cut : none;
 }
+
+// the passes of `pb` in whole chains, dv value columns a workgroup, or cut in two
+ltn_status launch_whole_or_cut(ltn::PassBatch& pb, int D, int DC, int dv, int widest, hipStream_t stream) {
+    const Cut cut = pick_cut(pb.chains, pb.count, pb.N, D, DC, dv, widest);
+    pb.cut_chains = cut.chains;
+    pb.cut_len = cut.len;
+    const hipError_t e = cut.chains ? ltn::launch_pass_cut_bf16(pb, D, stream, DC) : ltn::launch_pass_bf16(pb, D, dv, stream, DC);
+    return e == hipSuccess ? LTN_OK : LTN_ERR_LAUNCH;
+}
+
+int widest_dv(int D) { return D == 256 ? 64 : D; }
 
 // full_width: the pass carries the gated epilogue, which needs complete output rows in one
 // workgroup (slices of all D value columns).
@@ -426,9 +438,7 @@ ltn_status run_passes(ltn::PassBatch& pb, int D, int blk, ltn_dtype dtype, void*
     pb.segs = 1;
     if (plan.segs == 1) {
         const int dv = full_width ? D : pick_dv(chain_passes, D, pb.count);
-        if (pick_cut(pb, D, D, dv, D == 256 ? 64 : D))
-            return ltn::launch_pass_cut_bf16(pb, D, stream) == hipSuccess ? LTN_OK : LTN_ERR_LAUNCH;
-        return ltn::launch_pass_bf16(pb, D, dv, stream) == hipSuccess ? LTN_OK : LTN_ERR_LAUNCH;
+        return launch_whole_or_cut(pb, D, D, dv, widest_dv(D), stream);
     }
     // three launches: segment end states from zero, scan, then the pass proper per segment
     if (!workspace) return LTN_ERR_NULL;
@@ -859,15 +869,10 @@ static SegPlan pick_segments_dkdv(long long chain_passes, long long N, int DA, i
 static ltn_status run_dkdv(ltn::PassBatch& pb, int DA, int DC, int blk, ltn_dtype dtype, void* workspace, hipStream_t st) {
     const long long chain_passes = (long long)pb.chains * pb.count;
     pb.segs = 1;
-    hipError_t e;
     if (dtype != LTN_BF16) return run_f32(pb, DA, DC, blk, st);
     const int hi = dkdv_hi(DA, DC);
     const SegPlan plan = pick_segments_dkdv(chain_passes, pb.N, DA, DC, dtype);
-    if (plan.segs == 1) {
-        const int dv = pick_dv_range(chain_passes, DC, 32, hi);
-        e = pick_cut(pb, DA, DC, dv, hi) ? ltn::launch_pass_cut_bf16(pb, DA, st, DC) : ltn::launch_pass_bf16(pb, DA, dv, st, DC);
-        return e == hipSuccess ? LTN_OK : LTN_ERR_LAUNCH;
-    }
+    if (plan.segs == 1) return launch_whole_or_cut(pb, DA, DC, pick_dv_range(chain_passes, DC, 32, hi), hi, st);
     if (!workspace) return LTN_ERR_NULL;
     float* states = static_cast<float*>(workspace);
     const size_t per_pass = (size_t)pb.chains * plan.segs * DA * DC;
@@ -894,8 +899,8 @@ static ltn_status run_dkdv(ltn::PassBatch& pb, int DA, int DC, int blk, ltn_dtyp
         main.p[i].state_in = states + i * per_pass;
         main.p[i].state_out = nullptr;
     }
-    e = ltn::launch_pass_bf16(main, DA, pick_dv_range(chain_passes * plan.segs, DC, 32, hi), st, DC);
-    return e == hipSuccess ? LTN_OK : LTN_ERR_LAUNCH;
+    const int dv = pick_dv_range(chain_passes * plan.segs, DC, 32, hi);
+    return ltn::launch_pass_bf16(main, DA, dv, st, DC) == hipSuccess ? LTN_OK : LTN_ERR_LAUNCH;
 }
 
 size_t ltn_attn_workspace_bytes_dkdv(int Bt, int H, long long N, int Dk, int Dv, ltn_dtype dtype, int call) {
@@ -913,6 +918,31 @@ size_t ltn_attn_workspace_bytes_dkdv(int Bt, int H, long long N, int Dk, int Dv,
         if (nb > need) need = nb;
     }
     return need;
+}
+
+ltn_status ltn_attn_query_cut(int Bt, int H, long long N, int Dk, int Dv, ltn_dtype dtype, int call,
+                              int* chains_out, long long* tokens_out) {
+    if (!chains_out || !tokens_out) return LTN_ERR_NULL;
+    if (Bt <= 0 || H <= 0 || N <= 0 || call < 0 || call > 2 || (long long)Bt * H > 0x3fffffffLL) return LTN_ERR_SHAPE;
+    int blk = 0;
+    const ltn_status s = Dk == Dv ? check_common(Bt, H, N, Dk, 0, dtype, &blk) : check_dkdv(Bt, H, N, Dk, Dv, 0, dtype, &blk);
+    if (s != LTN_OK) return s;
+    if (Dk != Dv && call == 2) return LTN_ERR_UNSUPPORTED;
+    const int chains = Bt * H;
+    Cut cut = {0, 0};
+    if (dtype == LTN_BF16 && Dk == Dv) {
+        const int count = call == 1 ? 3 : 1;
+        const bool fused = call == 2 && !gated_in_two_steps(chains, N, Dk, dtype, blk, false);
+        if (pick_segments((long long)chains * count, N, Dk, dtype, fused, call == 1 ? chains : 0).segs == 1)
+            cut = pick_cut(chains, count, N, Dk, Dk, fused ? Dk : pick_dv((long long)chains * count, Dk, count), widest_dv(Dk));
+    } else if (dtype == LTN_BF16) {        // of a backward: the launch of dK and dQ
+        const int count = call == 1 ? 2 : 1, DA = call == 1 ? Dv : Dk, DC = call == 1 ? Dk : Dv, hi = dkdv_hi(DA, DC);
+        if (pick_segments_dkdv((long long)chains * count, N, DA, DC, dtype).segs == 1)
+            cut = pick_cut(chains, count, N, DA, DC, pick_dv_range((long long)chains * count, DC, 32, hi), hi);
+    }
+    *chains_out = cut.chains;
+    *tokens_out = cut.len;
+    return LTN_OK;
 }
 
 ltn_status ltn_attn_fwd_dkdv(const void* q, const void* k, const void* v, void* o,

@@ -360,6 +360,36 @@ def test_debug_plan_and_plan_query(lib):
     assert lib.ltn_attn_query_plan(1, 1, 64, 128, 1, 7, ctypes.byref(dv), ctypes.byref(segs)) == E_SHAPE
 
 
+def test_which_chains_run_in_two_parts(lib):
+    """As many as there are workgroups more than whole rounds of 256, up to half a round, in two to four rounds of
+    chains long enough; whole chains elsewhere."""
+    import torch
+    BF, F32 = torch.bfloat16, torch.float32
+
+    def cut(chains, N, D, call, dtype=BF, Dv=None):
+        return ltn.ltn_attn_query_cut(1, chains, N, D, Dv or D, dtype, call)
+
+    assert cut(96, 1999, 96, 1) == (32, 1024)                    # 288 workgroups: 32 more than a round
+    assert cut(85, 4479, 256, 0) == (21, 2240)                   # 340, four a chain
+    assert cut(300, 2000, 96, 2) == cut(300, 2000, 96, 0) == (44, 1024)
+    assert cut(65, 1217, 256, 0, Dv=128) == (0, 0) and cut(130, 1217, 256, 0, Dv=128) == (2, 640)
+    assert cut(256, 2000, 64, 0) == cut(255, 2000, 64, 0) == cut(512, 2000, 64, 0) == (0, 0)     # whole rounds
+    assert cut(257, 2000, 64, 0)[0] == 1 and cut(385, 2000, 64, 0)[0] == 0                       # more than half a round alone
+    assert cut(800, 2000, 64, 0)[0] == 32 and cut(1048, 2000, 64, 0)[0] == 0                     # more than four rounds
+    assert cut(257, 704, 64, 0)[0] == 0 and cut(257, 705, 64, 0) == (1, 384)                     # second part of 5 blocks and 1 token
+    assert cut(65, 1215, 256, 0)[0] == 0 and cut(65, 1216, 256, 0) == (1, 640)                   # rows for the state
+    assert cut(300, 2000, 96, 0, F32) == (0, 0)
+    chains, tokens = ctypes.c_int(), ctypes.c_longlong()
+    out = ctypes.byref(chains), ctypes.byref(tokens)
+    assert lib.ltn_attn_query_cut(1, 1, 64, 128, 128, 1, 0, None, out[1]) == E_NULL
+    assert lib.ltn_attn_query_cut(1, 1, 64, 128, 128, 1, 3, *out) == E_SHAPE
+    assert lib.ltn_attn_query_cut(1, 0, 64, 128, 128, 1, 0, *out) == E_SHAPE
+    assert lib.ltn_attn_query_cut(1, 1, 64, 80, 80, 1, 0, *out) == E_UNSUP
+    assert lib.ltn_attn_query_cut(1, 1, 64, 256, 64, 1, 0, *out) == E_UNSUP
+    assert lib.ltn_attn_query_cut(1, 1, 64, 256, 128, 1, 2, *out) == E_UNSUP
+    assert lib.ltn_attn_query_cut(1, 1, 64, 128, 128, 2, 0, *out) == E_UNSUP
+
+
 def test_environment_does_not_change_the_plan(lib, monkeypatch):
     import torch
     monkeypatch.setenv("LTN_ATTN_DV", "32")

@@ -30,12 +30,20 @@ def lines(chains, cut):
     return sorted({0, cut - 1, min(cut, chains - 1), chains - 1})
 
 
+def is_cut(Bt, H, N, D, call, chains, Dv=None):
+    """The library's own word for it: so many chains in two parts (with whole chains forced none)."""
+    with force_segs(1):
+        assert ltn.ltn_attn_query_cut(Bt, H, N, D, Dv or D, BF, call)[0] == 0
+    return ltn.ltn_attn_query_cut(Bt, H, N, D, Dv or D, BF, call)[0] == chains
+
+
 def some(t, chains, keep):
     return t.reshape(1, chains, *t.shape[2:])[:, keep]
 
 
 @pytest.mark.parametrize("D,Bt,H,N,cut", FORWARD)
 def test_forward(D, Bt, H, N, cut):
+    assert is_cut(Bt, H, N, D, 0, cut)
     q, k, v = synth.make_qkv(Bt, H, N, D, BF, 900 + N)
     decay = mixed_decay(H)
     kv0 = torch.randn(Bt, H, D, D, generator=torch.Generator().manual_seed(N)) / D
@@ -56,6 +64,7 @@ def test_forward(D, Bt, H, N, cut):
 @pytest.mark.parametrize("D,Bt,H,N,cut", [c for c in FORWARD if c[0] != 256])
 def test_gated_forward(D, Bt, H, N, cut):
     """The state passes through y's rows, whether o is stored or not."""
+    assert is_cut(Bt, H, N, D, 2, cut)
     q, k, v = synth.make_qkv(Bt, H, N, D, BF, 920 + N)
     u = synth.make_gate(Bt, H, N, D, BF, 920 + N)
     decay = mixed_decay(H)
@@ -82,6 +91,7 @@ def test_gated_forward(D, Bt, H, N, cut):
 
 @pytest.mark.parametrize("D,Bt,H,N,cut", BACKWARD)
 def test_backward(D, Bt, H, N, cut):
+    assert is_cut(Bt, H, N, D, 1, cut)
     q, k, v = synth.make_qkv(Bt, H, N, D, BF, 950 + N)
     g = synth.make_do(Bt, H, N, D, BF, 950 + N)
     decay = mixed_decay(H)
@@ -96,11 +106,14 @@ def test_backward(D, Bt, H, N, cut):
         check(n, some(x, Bt * H, keep), r, TOL[BF])
 
 
-# (Dk, Dv, Bt, H, N): forward and dV cut (the second part of dV's reversed token axis lies in front), or dK and dQ, or all
-@pytest.mark.parametrize("Dk,Dv,Bt,H,N", [(256, 128, 2, 65, 1217), (256, 128, 9, 16, 1300), (256, 128, 4, 18, 705),
-                                          (128, 64, 4, 65, 705), (128, 64, 3, 96, 800), (128, 64, 8, 10, 705),
-                                          (128, 64, 3, 30, 770)])
-def test_unequal_widths(Dk, Dv, Bt, H, N):
+# (Dk, Dv, Bt, H, N, chains cut in the forward and dV (the second part of dV's reversed token axis lies in front),
+# of dQ's)
+@pytest.mark.parametrize("Dk,Dv,Bt,H,N,cut,cut_q", [(256, 128, 2, 65, 1217, 2, 4), (256, 128, 9, 16, 1300, 16, 32),
+                                                    (256, 128, 4, 18, 705, 0, 16), (128, 64, 4, 65, 705, 4, 0),
+                                                    (128, 64, 3, 96, 800, 32, 0), (128, 64, 8, 10, 705, 0, 32),
+                                                    (128, 64, 3, 30, 770, 0, 52)])
+def test_unequal_widths(Dk, Dv, Bt, H, N, cut, cut_q):
+    assert is_cut(Bt, H, N, Dk, 0, cut, Dv) and is_cut(Bt, H, N, Dk, 1, cut_q, Dv)
     q, k, v = synth.make_qkv_dkdv(Bt, H, N, Dk, Dv, BF, 70 + N)
     g = synth.make_do(Bt, H, N, Dv, BF, 70 + N)
     decay = mixed_decay(H)
@@ -123,6 +136,7 @@ def test_unequal_widths(Dk, Dv, Bt, H, N):
 def test_outputs_inside_larger_buffers():
     """The states and flags that pass through the output's rows stay inside them."""
     D, Bt, H, N = 96, 8, 12, 1090
+    assert is_cut(Bt, H, N, D, 1, 32)
     q, k, v = synth.make_qkv(Bt, H, N, D, BF, 31)
     g = synth.make_do(Bt, H, N, D, BF, 31)
     decay = synth.decay_bench_rule(H)
@@ -142,6 +156,7 @@ def test_replayed_graph():
     """Captured once and replayed over changing inputs, with eager calls in between: every replay waits for its own
     states (the flags are cleared by a kernel of the call)."""
     D, Bt, H, N = 128, 5, 20, 770
+    assert is_cut(Bt, H, N, D, 1, 44)
     decay = synth.decay_bench_rule(H).cuda()
     q, k, v, g = (torch.empty(Bt, H, N, D, device="cuda", dtype=BF) for _ in range(4))
 
