@@ -407,7 +407,7 @@ Cut pick_cut(int chains, int count, long long N, int D, int DC, int dv, int wide
     const bool xcd = (chains & 7) == 0;
     const long long wgs = xcd ? chains / 8 * per_chain : chains * per_chain, units = xcd ? 32 : 256;
     const long long alone = (wgs % units + slices - 1) / slices;       // chains
-    const long long input_mib = (count == 3 ? 4 * D : 2 * D + DC) * chains * N * 2 >> 20;
+    const long long input_mib = (count == 3 ? 4LL * D : 2LL * D + DC) * chains * N * 2 >> 20;
     if (slices == 1 && 16 * alone > 7 * units && input_mib < 320) return none;
     if (wgs < units || wgs > kRounds * units || alone == 0 || alone * slices > units / 2) return none;
     const long long first = ((N + 63) / 64 + 1) / 2;                   // of a chain's blocks

@@ -379,6 +379,10 @@ def test_which_chains_run_in_two_parts(lib):
     assert cut(257, 704, 64, 0)[0] == 0 and cut(257, 705, 64, 0) == (1, 384)                     # second part of 5 blocks and 1 token
     assert cut(65, 1215, 256, 0)[0] == 0 and cut(65, 1216, 256, 0) == (1, 640)                   # rows for the state
     assert cut(300, 2000, 96, 0, F32) == (0, 0)
+    # the most chains there can be (the sizes in 64 bits: this file also runs under the sanitizers)
+    for call in range(3):
+        assert ltn.ltn_attn_query_cut(0x3fff, 0x10000, 8, 256, 256, BF, call) == (0, 0)
+        assert ltn.ltn_attn_query_cut(3000, 1001, 8, 128, 128, BF, call) == (0, 0)
     chains, tokens = ctypes.c_int(), ctypes.c_longlong()
     out = ctypes.byref(chains), ctypes.byref(tokens)
     assert lib.ltn_attn_query_cut(1, 1, 64, 128, 128, 1, 0, None, out[1]) == E_NULL
