@@ -103,41 +103,48 @@ def write_traffic_profile(workload: str, fetch_csv: str, write_csv: str) -> int:
     import csv
     import re
 
-    def per_kernel(path, counter):
-        acc = {}
+    def key_of(name):
+        """How a kernel is recorded; None for one that is not."""
+        m = re.search(r"pass_bf16_kernel<(\d+), (\d+), (\d+)", name)
+        if m:                              # modes from 5 on: those 5 below with some chains in two parts
+            mode = int(m.group(3)) % 5
+            return f"pass_bf16_kernel<{m.group(1)},{m.group(2)}>" + (f" mode {mode}" if mode else "")
+        m = re.search(r"pass_f32_kernel<(\d+), (\d+), (\d+), \d+, (\d+), (\d+)>", name)   # D, DV, B, KH, DC, mode
+        if m:
+            return (f"pass_f32_kernel<{m.group(1)},{m.group(2)},{m.group(3)}>"
+                    + ("" if m.group(4) == m.group(1) else f" DC {m.group(4)}")
+                    + ("" if m.group(5) == "0" else f" mode {m.group(5)}"))
+        return None
+
+    def per_kernel(path, counter):         # launches that are recorded under one key are averaged
+        acc, copies = {}, []
         with open(path, newline="") as f:
             for row in csv.DictReader(f):
                 if row["Counter_Name"] != counter:
                     continue
-                acc.setdefault(row["Kernel_Name"], []).append(float(row["Counter_Value"]))
-        return acc
+                name, value = row["Kernel_Name"], float(row["Counter_Value"])
+                if "copyBuffer" in name and value > 1e5:
+                    copies.append(value)
+                elif key_of(name):
+                    acc.setdefault(key_of(name), []).append(value)
+        return acc, copies
 
     GIB = float(1 << 30)
     out = {"workload": workload, "kernel_source_hash": kernel_source_hash(), "kernels": {},
            "how": "rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE (KiB per dispatch), one counter per run, scaled by the "
                   "counter's reading of a 1 GiB device-to-device copy in the same run"}
-    fetch, write = per_kernel(fetch_csv, "FETCH_SIZE"), per_kernel(write_csv, "WRITE_SIZE")
-    cal_f = [v for k, vs in fetch.items() if "copyBuffer" in k for v in vs if v > 1e5]
-    cal_w = [v for k, vs in write.items() if "copyBuffer" in k for v in vs if v > 1e5]
+    (fetch, cal_f), (write, cal_w) = per_kernel(fetch_csv, "FETCH_SIZE"), per_kernel(write_csv, "WRITE_SIZE")
     if not cal_f or not cal_w:
         print("no calibration copy found in the counter runs (run bench.py with --copy-calibration)", file=sys.stderr)
         return 1
     sf, sw = GIB / (sum(cal_f) / len(cal_f) * 1024.0), GIB / (sum(cal_w) / len(cal_w) * 1024.0)
     out["scale"] = {"FETCH_SIZE": round(sf, 4), "WRITE_SIZE": round(sw, 4)}
-    for name in fetch:
-        m = re.search(r"pass_bf16_kernel<(\d+), (\d+), (\d+)", name)
-        mf = re.search(r"pass_f32_kernel<(\d+), (\d+), (\d+), \d+, (\d+), (\d+)>", name)   # D, DV, B, KH, DC, mode
-        if not (m or mf) or name not in write:
+    for key in fetch:
+        if key not in write:
             continue
-        if m:                              # mode 5: the plain pass with some chains in two parts
-            key = f"pass_bf16_kernel<{m.group(1)},{m.group(2)}>" + ("" if m.group(3) in ("0", "5") else f" mode {m.group(3)}")
-        else:
-            key = (f"pass_f32_kernel<{mf.group(1)},{mf.group(2)},{mf.group(3)}>"
-                   + ("" if mf.group(4) == mf.group(1) else f" DC {mf.group(4)}")
-                   + ("" if mf.group(5) == "0" else f" mode {mf.group(5)}"))
-        rd = sum(fetch[name]) / len(fetch[name]) * 1024.0 * sf
-        wr = sum(write[name]) / len(write[name]) * 1024.0 * sw
-        out["kernels"][key] = {"launches": len(fetch[name]), "read_bytes_per_launch": round(rd),
+        rd = sum(fetch[key]) / len(fetch[key]) * 1024.0 * sf
+        wr = sum(write[key]) / len(write[key]) * 1024.0 * sw
+        out["kernels"][key] = {"launches": len(fetch[key]), "read_bytes_per_launch": round(rd),
                                "written_bytes_per_launch": round(wr), "hbm_bytes_per_launch": round(rd + wr)}
     with open(traffic_profile_path(workload), "w") as f:
         json.dump(out, f, indent=1)
