@@ -373,10 +373,25 @@ def test_which_chains_run_in_two_parts(lib):
     assert cut(85, 4479, 256, 0) == (21, 2240)                   # 340, four a chain
     assert cut(300, 2000, 96, 2) == cut(300, 2000, 96, 0) == (44, 1024)
     assert cut(65, 1217, 256, 0, Dv=128) == (0, 0) and cut(130, 1217, 256, 0, Dv=128) == (2, 640)
+    # small inputs, which the memory-side cache holds, stay whole
+    assert cut(300, 1080, 64, 0)[0] == 0 and cut(300, 1110, 64, 0)[0] == 44 and cut(300, 705, 64, 2)[0] == 44
+    assert cut(384, 1060, 64, 0)[0] == 0 and cut(384, 1100, 64, 0)[0] == 128 and cut(384, 705, 64, 2)[0] == 128
+    assert cut(88, 1040, 64, 1)[0] == 0 and cut(88, 1060, 64, 1)[0] == 8                       # 45 MiB
+    assert cut(120, 1060, 128, 1)[0] == 0 and cut(120, 1100, 128, 1)[0] == 104                 # 13 of 32 alone: 125 MiB
+    assert cut(128, 1380, 128, 1)[0] == 0 and cut(128, 1400, 128, 1)[0] == 128                 # 173 MiB
+    assert cut(120 + 8 * 11, 700, 128, 1)[0] == 0 and cut(208, 900, 128, 1)[0] == 112 and cut(208, 820, 128, 1)[0] == 0
+    assert cut(300, 705, 64, 1)[0] == 0 and cut(127, 705, 128, 1)[0] == 125
+    assert cut(240, 1500, 128, 1, Dv=64)[0] == 0 and cut(130, 1500, 128, 1, Dv=64)[0] == 4     # dK and dQ
+    # chains of 512 KiB, more than 7/16 of a round alone
+    for D in (64, 128):
+        at = 1 << 19 - (D.bit_length())                          # tokens
+        assert cut(128, at, D, 1)[0] == cut(128, at + 3, D, 1)[0] == cut(213, at - 3, D, 1)[0] == 0
+        assert cut(128, at + 8, D, 1)[0] == cut(128, at - 8, D, 1)[0] == 128 and cut(120, at, D, 1)[0] == 104
+    assert cut(128, 2731, 96, 1)[0] == 0 and cut(128, 2740, 96, 1)[0] == 128
     assert cut(256, 2000, 64, 0) == cut(255, 2000, 64, 0) == cut(512, 2000, 64, 0) == (0, 0)     # whole rounds
     assert cut(257, 2000, 64, 0)[0] == 1 and cut(385, 2000, 64, 0)[0] == 0                       # more than half a round alone
     assert cut(800, 2000, 64, 0)[0] == 32 and cut(1048, 2000, 64, 0)[0] == 0                     # more than four rounds
-    assert cut(257, 704, 64, 0)[0] == 0 and cut(257, 705, 64, 0) == (1, 384)                     # second part of 5 blocks and 1 token
+    assert cut(257, 704, 128, 0)[0] == 0 and cut(257, 705, 128, 0) == (1, 384)                   # second part of 5 blocks and 1 token
     assert cut(65, 1215, 256, 0)[0] == 0 and cut(65, 1216, 256, 0) == (1, 640)                   # rows for the state
     assert cut(300, 2000, 96, 0, F32) == (0, 0)
     # the most chains there can be (the sizes in 64 bits: this file also runs under the sanitizers)

@@ -15,19 +15,25 @@ from _helpers import TOL, check, force_segs, gpu, mixed_decay
 pytestmark = pytest.mark.gpu
 
 BF = torch.bfloat16
-# (D, Bt, H, N, cut chains): 257 .. 384 workgroups in two rounds and 520 .. 640 in three, chain counts that
-# are multiples of 8 and not (their ids are dealt differently), the shortest length that is cut
-# (second parts of 321 tokens, 577 of 256 features) and a ragged one
-FORWARD = [(64, 4, 65, 705, 4), (64, 3, 96, 1090, 32), (64, 5, 105, 769, 13), (96, 1, 257, 705, 1), (96, 8, 40, 1100, 64),
-           (128, 3, 99, 705, 41), (128, 4, 66, 900, 8), (128, 1, 530, 770, 18), (256, 5, 13, 1217, 1), (256, 5, 16, 1300, 16),
-           (256, 3, 50, 1217, 22)]
-# (a last round half full with one workgroup per chain is cut only where the inputs exceed 320 MiB)
-BACKWARD = [(64, 1, 86, 705, 2), (64, 8, 14, 1000, 80), (96, 8, 12, 1090, 32), (96, 3, 31, 705, 23), (128, 5, 20, 705, 44),
-            (128, 8, 15, 900, 104), (256, 1, 22, 1217, 2), (256, 2, 16, 1250, 32)]
+# (D, Bt, H, N, cut chains, of the gated forward too): 257 .. 384 workgroups in two rounds and 520 .. 640 in three,
+# chain counts that are multiples of 8 and not (their ids are dealt differently), the shortest length that is cut
+# (second parts of 321 tokens, 577 of 256 features) and a ragged one, last rounds exactly half full (384 and 640); plain
+# forwards of small inputs run whole
+FORWARD = [(64, 4, 65, 705, 0, 4), (64, 3, 96, 1090, 0, 32), (64, 5, 105, 769, 13, 13), (96, 1, 257, 705, 0, 1),
+           (96, 8, 40, 1100, 64, 64), (128, 3, 99, 705, 41, 41), (128, 4, 66, 900, 8, 8), (128, 1, 530, 770, 18, 18),
+           (256, 5, 13, 1217, 1, 0), (256, 5, 16, 1300, 16, 0), (256, 3, 50, 1217, 22, 0),
+           (64, 4, 65, 1300, 4, 4), (64, 3, 96, 1500, 32, 32), (96, 1, 257, 900, 1, 1), (96, 4, 96, 800, 128, 128),
+           (128, 1, 383, 705, 127, 127), (64, 8, 80, 705, 128, 128)]
+# (D, Bt, H, N, cut chains); the first of 64 features and 128, 8, 15, 900 are too small; last rounds exactly half full
+# on either side of the line, and of chains of 512 KiB
+BACKWARD = [(64, 1, 86, 705, 0), (64, 8, 14, 1000, 0), (96, 8, 12, 1090, 32), (96, 3, 31, 705, 23), (128, 5, 20, 705, 44),
+            (128, 8, 15, 900, 0), (256, 1, 22, 1217, 2), (256, 2, 16, 1250, 32),
+            (64, 1, 86, 1100, 2), (64, 8, 14, 1500, 80), (128, 8, 15, 1100, 104), (128, 4, 32, 1450, 128),
+            (128, 4, 32, 1300, 0), (128, 4, 32, 2048, 0), (128, 4, 32, 2080, 128), (128, 1, 128, 2625, 128)]
 
 
 def lines(chains, cut):
-    return sorted({0, cut - 1, min(cut, chains - 1), chains - 1})
+    return sorted({0, max(cut - 1, 0), min(cut, chains - 1), chains - 1})
 
 
 def is_cut(Bt, H, N, D, call, chains, Dv=None):
@@ -41,7 +47,7 @@ def some(t, chains, keep):
     return t.reshape(1, chains, *t.shape[2:])[:, keep]
 
 
-@pytest.mark.parametrize("D,Bt,H,N,cut", FORWARD)
+@pytest.mark.parametrize("D,Bt,H,N,cut", [c[:5] for c in FORWARD])
 def test_forward(D, Bt, H, N, cut):
     assert is_cut(Bt, H, N, D, 0, cut)
     q, k, v = synth.make_qkv(Bt, H, N, D, BF, 900 + N)
@@ -61,7 +67,7 @@ def test_forward(D, Bt, H, N, cut):
     check("kv", some(kv, Bt * H, keep), kv_ref, TOL[BF])
 
 
-@pytest.mark.parametrize("D,Bt,H,N,cut", [c for c in FORWARD if c[0] != 256])
+@pytest.mark.parametrize("D,Bt,H,N,cut", [(*c[:4], c[5]) for c in FORWARD if c[0] != 256])
 def test_gated_forward(D, Bt, H, N, cut):
     """The state passes through y's rows, whether o is stored or not."""
     assert is_cut(Bt, H, N, D, 2, cut)
@@ -109,9 +115,9 @@ def test_backward(D, Bt, H, N, cut):
 # (Dk, Dv, Bt, H, N, chains cut in the forward and dV (the second part of dV's reversed token axis lies in front),
 # of dQ's)
 @pytest.mark.parametrize("Dk,Dv,Bt,H,N,cut,cut_q", [(256, 128, 2, 65, 1217, 2, 4), (256, 128, 9, 16, 1300, 16, 32),
-                                                    (256, 128, 4, 18, 705, 0, 16), (128, 64, 4, 65, 705, 4, 0),
+                                                    (256, 128, 4, 18, 705, 0, 16), (128, 64, 4, 65, 705, 0, 0),
                                                     (128, 64, 3, 96, 800, 32, 0), (128, 64, 8, 10, 705, 0, 32),
-                                                    (128, 64, 3, 30, 770, 0, 52)])
+                                                    (128, 64, 3, 30, 770, 0, 52), (128, 64, 4, 65, 780, 4, 0)])
 def test_unequal_widths(Dk, Dv, Bt, H, N, cut, cut_q):
     assert is_cut(Bt, H, N, Dk, 0, cut, Dv) and is_cut(Bt, H, N, Dk, 1, cut_q, Dv)
     q, k, v = synth.make_qkv_dkdv(Bt, H, N, Dk, Dv, BF, 70 + N)
@@ -155,7 +161,7 @@ def test_outputs_inside_larger_buffers():
 def test_replayed_graph():
     """Captured once and replayed over changing inputs, with eager calls in between: every replay waits for its own
     states (the flags are cleared by a kernel of the call)."""
-    D, Bt, H, N = 128, 5, 20, 770
+    D, Bt, H, N = 128, 5, 20, 770          # 44 of the 100 chains
     assert is_cut(Bt, H, N, D, 1, 44)
     decay = synth.decay_bench_rule(H).cuda()
     q, k, v, g = (torch.empty(Bt, H, N, D, device="cuda", dtype=BF) for _ in range(4))
