@@ -187,3 +187,71 @@ def test_replayed_graph():
         with force_segs(1):
             whole = call()
         assert all(torch.equal(x, y) for x, y in zip(got, whole))
+
+
+def same(x, y):
+    return torch.equal(x.isnan(), y.isnan()) and torch.equal(x.nan_to_num(), y.nan_to_num())
+
+
+@pytest.mark.parametrize("token", [100, 447, 448, 600])
+def test_infinite_token_on_either_side_of_the_cut(token):
+    """Cut at 448 (dQ walks from the first token): Inf and NaN appear where they do in whole chains, in the
+    outputs, in the state that passes through them and in the returned state."""
+    D, Bt, H, N = 128, 5, 20, 770
+    assert is_cut(Bt, H, N, D, 1, 44) and ltn.ltn_attn_query_cut(Bt, H, N, D, D, BF, 1)[1] == 448
+    q, k, v = synth.make_qkv(Bt, H, N, D, BF, 41)
+    g = synth.make_do(Bt, H, N, D, BF, 41)
+    k[..., token, 5] = float("inf")
+    args = gpu(q, k, v, g, mixed_decay(H))
+    with force_segs(1):
+        whole = ltn.ltn_attn_bwd(*args)
+    grads = ltn.ltn_attn_bwd(*args)
+    assert all(same(x, y) for x, y in zip(grads, whole))
+    # (within the token's own block of 64, masked scores are zeros: 0 x Inf there, as in whole chains)
+    finite = grads[0].isfinite().all(-1)
+    assert bool(finite[..., :token // 64 * 64].all()) and not bool(finite[..., token:].all())
+
+
+@pytest.mark.parametrize("token", [100, 600])
+def test_infinite_token_and_state_in_a_gated_forward(token):
+    D, Bt, H, N = 128, 3, 99, 705
+    assert is_cut(Bt, H, N, D, 2, 41) and is_cut(Bt, H, N, D, 0, 41)
+    q, k, v = synth.make_qkv(Bt, H, N, D, BF, 43)
+    k[:, ::2, token, 5] = float("inf")
+    kv0 = torch.zeros(Bt, H, D, D)
+    kv0[:, 1::2, 3, 7] = float("-inf")
+    args, u = gpu(q, k, v), synth.make_gate(Bt, H, N, D, BF, 43).cuda()
+    decay = mixed_decay(H).cuda()
+
+    def calls():
+        return [*ltn.ltn_attn_fwd(*args, decay, kv_in=kv0.cuda(), return_state=True),
+                *ltn.ltn_attn_fwd_gated(*args, u, decay, eps=1e-6, kv_in=kv0.cuda(), return_state=True)]
+
+    with force_segs(1):
+        whole = calls()
+    got = calls()
+    assert all(same(x, y) for x, y in zip(got, whole))
+    finite = bool(got[1].isfinite().all())
+    assert not finite
+
+
+def test_two_streams():
+    """Cut launches of two streams in flight at once: each waits for its own states."""
+    D, Bt, H, N = 96, 8, 12, 1090
+    assert is_cut(Bt, H, N, D, 1, 32)
+    decay = synth.decay_bench_rule(H).cuda()
+    ins = [gpu(*synth.make_qkv(Bt, H, N, D, BF, s), synth.make_do(Bt, H, N, D, BF, s)) for s in (51, 52)]
+    with force_segs(1):
+        whole = [ltn.ltn_attn_bwd(*x, decay) for x in ins]
+    streams = [torch.cuda.Stream() for _ in ins]
+    for s in streams:
+        s.wait_stream(torch.cuda.current_stream())
+    got = [[], []]
+    for _ in range(4):
+        for i, s in enumerate(streams):
+            with torch.cuda.stream(s):
+                got[i].append(ltn.ltn_attn_bwd(*ins[i], decay))
+    torch.cuda.synchronize()
+    for w, each in zip(whole, got):
+        for grads in each:
+            assert all(torch.equal(x, y) for x, y in zip(grads, w))
