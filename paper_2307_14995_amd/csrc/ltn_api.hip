@@ -382,35 +382,40 @@ bool gated_in_two_steps(long long chains, long long N, int D, ltn_dtype dtype, i
     return fused.segs < 3 || plan_time(fused, chains, N, D, D, true) + 1.5 >= two_us;
 }
 
-// Passes in more workgroups than the 256 units hold at once: are those that would be alone in the last
-// round to be cut in two (launch_pass_cut_bf16), at half a chain?  chains = 0: no.
+// Passes in more workgroups than the 256 units hold at once: are those that would be alone in the last round to be
+// cut in two (launch_pass_cut_bf16), at half a chain?  chains = 0: no.
 // Up to four rounds: beyond, workgroups end so far apart that the last round fills up by itself (time cut over
-// time whole 0.97 .. 1.10).  Up to half a round alone: with more, the second parts take more than the units that are left
-// (1.01 .. 1.08).  Shorter than 12 blocks the launch that clears the flags takes what the cut gains.  And inputs of at
-// least least_cut_mib: while they stay in the 256 MiB memory-side cache, workgroups that are alone in the last
-// round find them there and run faster than those of a full round, so that half of a short last round is
-// less than what two parts and the clearing cost.  Measured at 17800 shapes of 20 .. 1024 chains x 700 .. 6000 tokens on
-// two cards, every width, kernels alone and in training and mixer steps.  Time cut over time whole of those that
-// are cut, mean: training and mixer steps of 64 / 96 / 128 / 256 features 0.96 / 0.96 / 0.96 / 0.93, forward 0.95 / 0.93 /
-// 0.94 / 0.87, gated 0.94 / 0.93 / 0.93, with o 0.92; 0.8 % of them lose more than 1 %, none 6 %.
-// Chains of 512 KiB (to within 1 KiB: 2048 tokens of 128 features, 4096 of 64, 2731 of 96) lie so that second parts slow
-// each other down: backwards of more than 7/16 of a round alone lose there (training and mixer step 128 x 2048 x
-// 128 1.03 and 1.04, 213 x 2048 1.02 and 1.03, 126 x 2048 0.98 and 1.02, 213 x 2731 x 96 1.03 and 1.01) where 8 KiB
-// more or fewer a chain gain (128 x 2016 0.98 and 1.00, x 2080 0.985 and 0.99, x 1984 0.96 and 0.98, 213 x 1500 0.98 and 0.99);
-// with less alone the cut gains there too (120 x 2048 0.95 and 0.97).
+// time whole 0.97 .. 1.10).  Up to half a round alone: with more, the second parts take more than the units that
+// are left (1.01 .. 1.08).  Shorter than 12 blocks the launch that clears the flags takes what the cut gains.  And
+// inputs of at least least_cut_mib: while they stay in the 256 MiB memory-side cache, workgroups that are alone in
+// the last round find them there and run faster than those of a full round, so that half of a short last round is
+// less than what two parts and the clearing cost.
+// Measured at 17800 shapes of 20 .. 1024 chains x 700 .. 6000 tokens on two cards, every width, kernels alone and
+// in training and mixer steps.  Time cut over time whole of those that are cut, mean: training and mixer steps of
+// 64 / 96 / 128 / 256 features 0.96 / 0.96 / 0.96 / 0.93, forward 0.95 / 0.93 / 0.94 / 0.87, gated 0.94 / 0.93 /
+// 0.93, with o 0.92; 0.8 % of them lose more than 1 %, none 6 %.
+// Chains of 512 KiB (to within 1 KiB: 2048 tokens of 128 features, 4096 of 64, 2731 of 96): the distance from
+// chain to chain costs the cut 3 .. 6 % (not the inputs' total size: 112 x 2340 and 120 x 2180 x 128 are 256 MiB
+// as well and gain 7 and 5 %; which addresses collide has not been traced), so backwards of more than 7/16 of a
+// round alone lose (training and mixer step 128 x 2048 x 128 1.03 and 1.04, 213 x 2048 1.02 and 1.03, 126 x 2048
+// 0.98 and 1.02, 213 x 2731 x 96 1.03 and 1.01) where 8 KiB more or fewer a chain gain (128 x 2016 0.98 and 1.00,
+// x 2080 0.985 and 0.99, x 1984 0.96 and 0.98, 213 x 1500 0.98 and 0.99); with less alone the cut gains there too
+// (120 x 2048 0.95 and 0.97).
 // widest: value columns of the widest slices that DC columns have here, the only ones that are cut.
 struct Cut { int chains; long long len; };
 
-// Inputs, each read once, from which on the cut pays, in MiB.  rounds: full ones (1 .. 3); alone: workgroups in the last
-// one, of `units`; xcd: ids deal chains to XCDs (whole passes that share tokens then meet in one L2, and a cut gains less).
+// Inputs, each read once, from which on the cut pays, in MiB.  rounds: full ones (1 .. 3); alone: workgroups in
+// the last one, of `units`; xcd: ids deal chains to XCDs (whole passes that share tokens then meet in one L2, and
+// a cut gains less).
 // Time cut over whole below and above each line:
-//   forward: 64 features 1.00 .. 1.03 at 90 .. 120 MiB, 0.95 .. 0.99 at 120 .. 150; more than 7/16 alone 1.03 and 1.00
-//   backward, three passes of full width, xcd: up to a quarter of a round alone 1.01 below 40 MiB, 0.97 .. 1.00 from
-//     there; 5/16 1.01 at 64 .. 90, 1.00 at 90 .. 150; 7/16 1.02 at 90 .. 120, 0.98 .. 0.99 at 150 .. 180; 8/16 1.02 at
-//     120 .. 150, 0.99 at 150 .. 180; two and three full rounds 1.00 .. 1.03 below 150, 0.97 from 200
+//   forward: 64 features 1.00 .. 1.03 at 90 .. 120 MiB, 0.95 .. 0.99 at 120 .. 150; more than 7/16 alone 1.03 and
+//     1.00
+//   backward, three passes of full width, xcd: up to a quarter of a round alone 1.01 below 40 MiB, 0.97 .. 1.00
+//     from there; 5/16 1.01 at 64 .. 90, 1.00 at 90 .. 150; 7/16 1.02 at 90 .. 120, 0.98 .. 0.99 at 150 .. 180;
+//     8/16 1.02 at 120 .. 150, 0.99 at 150 .. 180; two and three full rounds 1.00 .. 1.03 below 150, 0.97 from 200
 //   backward, not xcd: one full round 0.95 .. 1.00 from 45, two 0.97 .. 1.00 from 120, three 0.97 .. 1.00 from 180
-//   dK and dQ of unequal widths, xcd: one full round 1.03 below 40 and 0.98 above (up to a quarter alone 0.99 there too),
-//     two 1.01 at 90 .. 120 and 0.97 at 150 .. 180, three 0.99 .. 1.03; not xcd 0.92 .. 1.00 everywhere
+//   dK and dQ of unequal widths, xcd: one full round 1.03 below 40 and 0.98 above (up to a quarter alone 0.99 there
+//     too), two 1.01 at 90 .. 120 and 0.97 at 150 .. 180, three 0.99 .. 1.03; not xcd 0.92 .. 1.01 everywhere
 // 256-feature and gated passes, whose blocks take longest, gain at every size (0.80 .. 1.00).
 long long least_cut_mib(int count, int slices, bool gated, bool xcd, long long rounds, long long alone, long long units) {
     constexpr long long kNever = 1LL << 40;
@@ -439,7 +444,8 @@ Cut pick_cut(int chains, int count, long long N, int D, int DC, int dv, int wide
     const long long first = ((N + 63) / 64 + 1) / 2;                   // of a chain's blocks
     if (N - 64 * first <= 64 * (kHalf - 1) || N - 64 * first < ltn::cut_state_rows(D)) return none;
     const long long row_bytes = count == 3 ? 8LL * D : 2 * (2LL * D + DC);       // of every input
-    if (row_bytes * chains * N < least_cut_mib(count, slices, gated, xcd, wgs / units, alone, units) * kKiB * kKiB) return none;
+    const long long least = least_cut_mib(count, slices, gated, xcd, wgs / units, alone, units) * kKiB * kKiB;
+    if (row_bytes * chains * N < least) return none;
     const long long chain_bytes = 2LL * D * N;
     if (count == 3 && slices == 1 && 16 * alone > 7 * units && chain_bytes > 511 * kKiB && chain_bytes < 513 * kKiB) return none;
     const Cut cut = {(int)(xcd ? 8 * cut_chains : cut_chains), 64 * first};
@@ -451,7 +457,8 @@ ltn_status launch_whole_or_cut(ltn::PassBatch& pb, int D, int DC, int dv, int wi
     const Cut cut = pick_cut(pb.chains, pb.count, pb.N, D, DC, dv, widest, pb.p[0].gate != nullptr);
     pb.cut_chains = cut.chains;
     pb.cut_len = cut.len;
-    const hipError_t e = cut.chains ? ltn::launch_pass_cut_bf16(pb, D, stream, DC) : ltn::launch_pass_bf16(pb, D, dv, stream, DC);
+    const hipError_t e = cut.chains ? ltn::launch_pass_cut_bf16(pb, D, stream, DC)
+                                    : ltn::launch_pass_bf16(pb, D, dv, stream, DC);
     return e == hipSuccess ? LTN_OK : LTN_ERR_LAUNCH;
 }
 
@@ -955,7 +962,8 @@ ltn_status ltn_attn_query_cut(int Bt, int H, long long N, int Dk, int Dv, ltn_dt
     if (!chains_out || !tokens_out) return LTN_ERR_NULL;
     if (Bt <= 0 || H <= 0 || N <= 0 || call < 0 || call > 2 || (long long)Bt * H > 0x3fffffffLL) return LTN_ERR_SHAPE;
     int blk = 0;
-    const ltn_status s = Dk == Dv ? check_common(Bt, H, N, Dk, 0, dtype, &blk) : check_dkdv(Bt, H, N, Dk, Dv, 0, dtype, &blk);
+    const ltn_status s = Dk == Dv ? check_common(Bt, H, N, Dk, 0, dtype, &blk)
+                                  : check_dkdv(Bt, H, N, Dk, Dv, 0, dtype, &blk);
     if (s != LTN_OK) return s;
     if (Dk != Dv && call == 2) return LTN_ERR_UNSUPPORTED;
     const int chains = Bt * H;
@@ -964,7 +972,8 @@ ltn_status ltn_attn_query_cut(int Bt, int H, long long N, int Dk, int Dv, ltn_dt
         const int count = call == 1 ? 3 : 1;
         const bool fused = call == 2 && !gated_in_two_steps(chains, N, Dk, dtype, blk, false);
         if (pick_segments((long long)chains * count, N, Dk, dtype, fused, call == 1 ? chains : 0).segs == 1)
-            cut = pick_cut(chains, count, N, Dk, Dk, fused ? Dk : pick_dv((long long)chains * count, Dk, count), widest_dv(Dk), fused);
+            cut = pick_cut(chains, count, N, Dk, Dk, fused ? Dk : pick_dv((long long)chains * count, Dk, count),
+                           widest_dv(Dk), fused);
     } else if (dtype == LTN_BF16) {        // of a backward: the launch of dK and dQ
         const int count = call == 1 ? 2 : 1, DA = call == 1 ? Dv : Dk, DC = call == 1 ? Dk : Dv, hi = dkdv_hi(DA, DC);
         if (pick_segments_dkdv((long long)chains * count, N, DA, DC, dtype).segs == 1)

@@ -61,12 +61,12 @@ struct PassBatch {
     long long cut_len;
 };
 
-// What a workgroup of a cut launch does.  part: 0 a whole pass, 1 the first and 2 the second part of the
-// last pass of a cut chain; split: column slice, of NS.  Ids [0, cut_ids[0]) and from cut_ids[2] (a multiple
-// of 8) on are those of the parts, as many first as second ones.  Which part such a workgroup runs is not told by its
-// id but by the number it draws: how many of the parts' workgroups with ids congruent mod 8 (one XCD's)
-// started before it.  The first parts go first, so whoever gets a second part knows that its first part has
-// started, whatever the order in which the GPU starts workgroups.
+// What a workgroup of a cut launch does.  part: 0 a whole pass, 1 the first and 2 the second part of the last
+// pass of a cut chain; split: column slice, of NS.  Ids [0, cut_ids[0]) and from cut_ids[2] (a multiple of 8) on
+// are those of the parts, as many first as second ones.  Which part such a workgroup runs is not told by its id
+// but by the number it draws: how many of the parts' workgroups with ids congruent mod 8 (one XCD's) started
+// before it.  The first parts go first, so whoever gets a second part knows that its first part has started,
+// whatever the order in which the GPU starts workgroups.
 struct CutRole { int part, pass, chain, split; };
 
 // fills in cut_ids; returns the workgroups of the launch
@@ -80,7 +80,9 @@ inline long long cut_launch_ids(PassBatch& pb, int NS) {
     return second + cut;
 }
 
-__host__ __device__ inline bool cut_draws(const PassBatch& pb, int wg) { return wg < pb.cut_ids[0] || wg >= pb.cut_ids[2]; }
+__host__ __device__ inline bool cut_draws(const PassBatch& pb, int wg) {
+    return wg < pb.cut_ids[0] || wg >= pb.cut_ids[2];
+}
 // first parts (and second parts) of the ids congruent to c mod 8
 __host__ __device__ inline int cut_parts_of(const PassBatch& pb, int c) { return (pb.cut_ids[0] - c + 7) / 8; }
 // chain and slice of part w; xcd: chains are dealt to XCDs (their number and cut_chains are multiples of 8)

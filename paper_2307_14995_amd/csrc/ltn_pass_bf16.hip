@@ -819,7 +819,9 @@ __device__ __forceinline__ void pass_state_wave(const Chain& ch, char* smem, int
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     const int row = dk0 + 16 * mt + 4 * g + j;
-                    st[mt][nt][j] = (DR == D || row < DR) ? __hip_atomic_load(handover_at<DV, DC>(ch.handover, row, nt, i16), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.0f;
+                    st[mt][nt][j] = (DR == D || row < DR) ? __hip_atomic_load(handover_at<DV, DC>(ch.handover, row, nt, i16),
+                                                                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                                                          : 0.0f;
                 }
             } else if (ch.state_in) {
 #pragma unroll
@@ -867,7 +869,8 @@ __device__ __forceinline__ void pass_state_wave(const Chain& ch, char* smem, int
                     for (int j = 0; j < 4; ++j) {
                         const int row = dk0 + 16 * mt + 4 * g + j;
                         if (DR == D || row < DR)
-                            __hip_atomic_store(handover_at<DV, DC>(ch.handover, row, nt, i16), st[mt][nt][j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                            __hip_atomic_store(handover_at<DV, DC>(ch.handover, row, nt, i16), st[mt][nt][j],
+                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     }
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             return;
@@ -922,7 +925,8 @@ __device__ __forceinline__ void pass_body(const PassBatch& pb, int xcd_ids, int 
     char* handover = nullptr;              // is_cut: of this part
     if constexpr (is_cut(MODE)) {
         const int last = pb.count - 1;
-        char* const last_out = GATED ? (char*)pb.p[0].gated_out : pick(last, (char*)pb.p[0].out, (char*)pb.p[1].out, (char*)pb.p[2].out);
+        char* const last_out = GATED ? (char*)pb.p[0].gated_out
+                                     : pick(last, (char*)pb.p[0].out, (char*)pb.p[1].out, (char*)pb.p[2].out);
         const long long row = pick(last, pb.p[0].rev, pb.p[1].rev, pb.p[2].rev) ? 0 : pb.cut_len;
         auto handover_of = [&](int chain, int slice) {
             return last_out + ((size_t)chain * (size_t)pb.N + (size_t)row) * DC * 2 + (size_t)slice * DV * 2;
@@ -1092,7 +1096,8 @@ __global__ void clear_handover_kernel(char* out, long long row_bytes, long long 
                                       int slice_bytes, int n) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    unsigned* const flag = (unsigned*)(out + ((long long)(i / slices) * N + flag_row) * row_bytes + (i % slices) * slice_bytes);
+    unsigned* const flag =
+        (unsigned*)(out + ((long long)(i / slices) * N + flag_row) * row_bytes + (i % slices) * slice_bytes);
     flag[0] = 0u;
     flag[1] = 0u;                          // the counter, in one part of each XCD's
 }
