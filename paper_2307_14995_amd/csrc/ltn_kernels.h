@@ -61,12 +61,12 @@ struct PassBatch {
     long long cut_len;
 };
 
-// What a workgroup of a cut launch does.  part: 0 a whole pass, 1 the first and 2 the second part of the last
-// pass of a cut chain; split: column slice, of NS.  Ids [0, cut_ids[0]) and from cut_ids[2] (a multiple of 8) on
-// are those of the parts, as many first as second ones.  Which part such a workgroup runs is not told by its id
-// but by the number it draws: how many of the parts' workgroups with ids congruent mod 8 (one XCD's) started
-// before it.  The first parts go first, so whoever gets a second part knows that its first part has started,
-// whatever the order in which the GPU starts workgroups.
+// What the workgroup that goes by id `id` of a cut launch does.  part: 0 a whole pass, 1 the first and 2 the
+// second part of the last pass of a cut chain; split: column slice, of NS.  Ids [0, cut_ids[0]) are first parts,
+// from cut_ids[2] (a multiple of 8) on second parts, in the same order.  The workgroups of either go by an id
+// that they draw when they start (cut_id): the next one of those congruent mod 8 to their own (one XCD's), first
+// parts first.  So whoever gets a second part knows that its first part has started, whatever the order in which
+// the GPU starts workgroups.
 struct CutRole { int part, pass, chain, split; };
 
 // fills in cut_ids; returns the workgroups of the launch
@@ -95,25 +95,26 @@ __host__ __device__ inline void cut_part(int w, int xcd, int& chain, int& split)
 // the part that the last workgroup of the ids congruent to c mod 8 to draw gets (if they have parts)
 __host__ __device__ inline int cut_last_part(const PassBatch& pb, int c) { return c + 8 * (cut_parts_of(pb, c) - 1); }
 
-// chain >= pb.chains: a padding workgroup.  number: what it drew, where cut_draws().
+// number: how many of those that draw with ids congruent to wg mod 8 drew before it
+__host__ __device__ inline int cut_id(const PassBatch& pb, int wg, int number) {
+    const int c = wg & 7, n = cut_parts_of(pb, c);
+    return c + 8 * number + (number < n ? 0 : pb.cut_ids[2] - 8 * n);
+}
+
+// chain >= pb.chains: a padding workgroup
 template <int NS>
-__host__ __device__ inline CutRole cut_role(const PassBatch& pb, int xcd, int wg, int number) {
+__host__ __device__ inline CutRole cut_role(const PassBatch& pb, int xcd, int id) {
     const int last = pb.count - 1;
-    CutRole r = {0, last, 0, 0};
-    if (cut_draws(pb, wg)) {
-        const int c = wg & 7, n = cut_parts_of(pb, c);
-        r.part = number < n ? 1 : 2;
-        cut_part<NS>(c + 8 * (r.part == 1 ? number : number - n), xcd, r.chain, r.split);
-    } else if (wg >= pb.cut_ids[1]) {
-        cut_part<NS>(wg - pb.cut_ids[1], xcd, r.chain, r.split);
-        r.chain += pb.cut_chains;
-    } else {                               // (count - 1 is 1 or 2 here: nothing is divided by a loaded number)
-        const int w = wg - pb.cut_ids[0], slot = xcd ? w >> 3 : w, q = last == 1 ? slot / NS : slot / (2 * NS);
-        const int within = slot - q * last * NS;
-        r.chain = xcd ? q * 8 + (w & 7) : q;
-        r.pass = within / NS;
-        r.split = within - r.pass * NS;
-    }
+    const bool others = id >= pb.cut_ids[0] && id < pb.cut_ids[1];     // (count - 1 is 1 or 2 then: no divisions)
+    CutRole r;
+    r.part = id < pb.cut_ids[0] ? 1 : (id >= pb.cut_ids[2] ? 2 : 0);
+    const int w = id - (r.part == 1 ? 0 : (others ? pb.cut_ids[0] : (r.part == 2 ? pb.cut_ids[2] : pb.cut_ids[1])));
+    const unsigned slot = xcd ? (unsigned)w >> 3 : (unsigned)w;
+    const unsigned q = others ? (last == 1 ? slot / NS : slot / (2 * NS)) : slot / NS;
+    const int within = (int)(slot - q * (others ? (unsigned)(last * NS) : NS));
+    r.chain = (int)(xcd ? q * 8 + (w & 7) : q) + (r.part == 0 && !others ? pb.cut_chains : 0);
+    r.pass = others ? within / NS : last;
+    r.split = others ? within % NS : within;
     return r;
 }
 

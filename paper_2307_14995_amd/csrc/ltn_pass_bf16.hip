@@ -472,7 +472,7 @@ struct Chain {            // what every wave of the workgroup knows about its pr
 // 256 features 250).
 //
 // The wait ends, in whatever order workgroups are started: who runs which part is drawn when they start
-// (cut_role), so a second part waits for a first part that has started and itself waits for nothing.  The
+// (cut_id), so a second part waits for a first part that has started and itself waits for nothing.  The
 // counters they draw from, one per XCD, lie behind the flag of the second part that is drawn last: its
 // workgroup overwrites them when everybody has drawn.  Parts told by their ids alone were no faster (96 x 1999 74.2
 // us, now 73 on another card; 256 features 226 and 224).  As a rule the state has been there for half a chain.
@@ -931,13 +931,12 @@ __device__ __forceinline__ void pass_body(const PassBatch& pb, int xcd_ids, int 
         auto handover_of = [&](int chain, int slice) {
             return last_out + ((size_t)chain * (size_t)pb.N + (size_t)row) * DC * 2 + (size_t)slice * DV * 2;
         };
-        int number = 0;
         if (cut_draws(pb, wg)) {
             int chain, slice;
             cut_part<NS>(cut_last_part(pb, wg & 7), xcd_ids, chain, slice);
-            number = draw_number(handover_flag<DR, DC>(handover_of(chain, slice)) + 1, smem, wave * 64 + lane);
+            wg = cut_id(pb, wg, draw_number(handover_flag<DR, DC>(handover_of(chain, slice)) + 1, smem, wave * 64 + lane));
         }
-        const CutRole r = cut_role<NS>(pb, xcd_ids, wg, number);
+        const CutRole r = cut_role<NS>(pb, xcd_ids, __builtin_amdgcn_readfirstlane(wg));     // (scalar, and known to be)
         vchain = r.chain;
         pi = r.pass;
         split = r.split;

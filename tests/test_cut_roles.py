@@ -40,7 +40,7 @@ int launch(int chains, int count, int cut_chains, int order) {
     for (int i = 0; i < grid; ++i) {
         const int wg = ids[i], c = wg & 7;
         const bool draws = ltn::cut_draws(pb, wg);
-        const ltn::CutRole r = ltn::cut_role<NS>(pb, xcd, wg, draws ? drawn[c]++ : -1);
+        const ltn::CutRole r = ltn::cut_role<NS>(pb, xcd, draws ? ltn::cut_id(pb, wg, drawn[c]++) : wg);
         if (r.chain >= chains) continue;                     // a padding workgroup
         CHECK(r.chain >= 0 && r.split >= 0 && r.split < NS && r.pass >= 0 && r.pass < count);
         CHECK(runs.emplace(std::make_tuple(r.pass, r.chain, r.split, r.part), i).second);
