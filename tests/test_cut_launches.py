@@ -56,7 +56,8 @@ def test_the_pass_is_not_launched_when_the_flags_are_not_cleared(tmp_path):
     src, rt = tmp_path / "stand_ins.cpp", str(tmp_path / "stand_ins.so")
     src.write_text(STAND_INS)
     subprocess.run([cxx, "-O1", "-fPIC", "-shared", str(src), "-o", rt], check=True)
-    r = subprocess.run([sys.executable, "-c", CHILD, rt, LIB], capture_output=True, text=True, timeout=120)
+    env = dict(os.environ, HIP_VISIBLE_DEVICES="-1", ROCR_VISIBLE_DEVICES="-1")       # (nothing can reach a GPU)
+    r = subprocess.run([sys.executable, "-c", CHILD, rt, LIB], env=env, capture_output=True, text=True, timeout=120)
     # 96 chains x 3 passes of 96 features: 32 chains more than a round of 256 workgroups, in two parts each.
     # Both launches; the clearing refused (nothing more is launched); the pass refused
     assert r.returncode == 0, r.stderr[-2000:]
