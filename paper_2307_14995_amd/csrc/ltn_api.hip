@@ -452,11 +452,54 @@ Cut pick_cut(int chains, int count, long long N, int D, int DC, int dv, int wide
     return cut.chains <= chains ? cut : none;
 }
 
+// Cache hints of a launch of `pb` in slices of dv value columns.  Launches of these sizes are bound by memory (with
+// every product taken out of the kernels they take 0 .. 6 % less), and what they read once goes through an L2 of 4 MiB
+// an XCD and a memory-side cache of 256 MiB on its way, where it takes the place of tiles that another slice, the
+// other pass of a pair or the segments' sweep has brought in and that are about to be read again.
+// Measured without and with, us, rotating inputs:
+//   forward, whole chains of full width, all operands once: 128 features 256 chains x 500 / 1500 / 4096 tokens 27.6 and
+//     27.2, 81 and 71.5, 207 and 180; 64 features 512 x 1000 50.3 and 48.8, 1024 x 1000 103 and 93; 96 features 320 x
+//     2000 111 and 103; (128, 64) 200 x 4000 128 and 121; gated 256 x 500 38.9 and 34.8, 512 x 1000 139 and 131.  Below 64
+//     MiB nothing or a loss (200 x 200 12.1 and 12.5), and rows of 192 bytes, whose lines two loads share, need a full
+//     chip (160 x 1999 x 96 57.4 and 57.9, 96 x 1999 51.3 and 52.1, 200 x 1000 34.4 and 34.2)
+//   forward in two column slices, C and the last slice's A and B once: 128 x 8192 x 128 212 and 206, 128 x 4000 x 64 57.2
+//     and 54.2; all operands once in both 235, as the slice that comes second then misses; four slices lose
+//     (64 x 2048 37.9 and 38.4)
+//   segments, the pass after the sweep, all once and outputs past the caches, so that K and V of the sweep stay:
+//     32 x 16301 176 and 140 (156 without the latter), 8 x 65536 179 and 154; gated (through the caches: the same)
+//     32 x 8192 103 and 92, 64 x 3000 79 and 76; 16 x 8192, 134 MiB, 51.5 and 52.2
+//   backward, whole chains of full width, each pass's A once and outputs past the caches, which keep what dQ's pass
+//     reads again: 128 features 128 x 2048 / 4096 / 8192 tokens 132.5 and 130.4, 256 and 240, 507 and 480, 60 x 6000 193
+//     and 186, 1024 x 500 259 and 246; 64 features 320 x 2048 155 and 149; 96 features 200 x 3000 225 and 219.  Inputs
+//     that the memory-side cache holds lose (64 x 1000 34.0 and 36.6, 128 x 1000 65.4 and 69.2), 96 x 2048, 201 MB,
+//     neither; 64-column slices lose (32 x 16301 322 and 334; 320 outputs past the caches alone)
+// 256 features: nothing within 1 %.
+void set_hints(ltn::PassBatch& pb, int D, int DC, int dv, bool segmented) {
+    constexpr long long kMiB = 1 << 20;
+    const long long tokens = pb.chains * pb.N;
+    const bool gated = pb.p[0].gate != nullptr, full = dv == DC;
+    pb.hints = 0;
+    if (D == 256 || DC == 256) return;
+    if (pb.count == 3) {
+        if (full && !segmented && 8LL * D * tokens >= 240 * kMiB) pb.hints = ltn::kOnceA | ltn::kPast;
+        return;
+    }
+    if (pb.count != 1 || pb.p[0].rev) return;
+    const long long bytes = (4LL * D + 2LL * DC * (gated ? 3 : 2)) * tokens;
+    if (segmented) {
+        if (full && D == DC && D != 96 && bytes >= 192 * kMiB) pb.hints = ltn::kOnce | (D == 128 && !gated ? ltn::kPast : 0);
+    } else if (bytes >= 64 * kMiB) {
+        if (full) pb.hints = D == 96 && pb.chains < 192 ? 0 : ltn::kOnce;
+        else if (DC == 2 * dv) pb.hints = ltn::kSliceOnce;
+    }
+}
+
 // the passes of `pb` in whole chains, dv value columns a workgroup, or cut in two
 ltn_status launch_whole_or_cut(ltn::PassBatch& pb, int D, int DC, int dv, int widest, hipStream_t stream) {
     const Cut cut = pick_cut(pb.chains, pb.count, pb.N, D, DC, dv, widest, pb.p[0].gate != nullptr);
     pb.cut_chains = cut.chains;
     pb.cut_len = cut.len;
+    set_hints(pb, D, DC, dv, false);
     const hipError_t e = cut.chains ? ltn::launch_pass_cut_bf16(pb, D, stream, DC)
                                     : ltn::launch_pass_bf16(pb, D, dv, stream, DC);
     return e == hipSuccess ? LTN_OK : LTN_ERR_LAUNCH;
@@ -512,6 +555,7 @@ ltn_status run_passes(ltn::PassBatch& pb, int D, int blk, ltn_dtype dtype, void*
         main.p[i].state_out = nullptr;
     }
     const int dv = full_width ? D : pick_dv(chain_passes * plan.segs, D, pb.count);
+    set_hints(main, D, D, dv, true);
     return ltn::launch_pass_bf16(main, D, dv, stream) == hipSuccess ? LTN_OK : LTN_ERR_LAUNCH;
 }
 
@@ -937,6 +981,7 @@ static ltn_status run_dkdv(ltn::PassBatch& pb, int DA, int DC, int blk, ltn_dtyp
         main.p[i].state_out = nullptr;
     }
     const int dv = pick_dv_range(chain_passes * plan.segs, DC, 32, hi);
+    set_hints(main, DA, DC, dv, true);
     return ltn::launch_pass_bf16(main, DA, dv, st, DC) == hipSuccess ? LTN_OK : LTN_ERR_LAUNCH;
 }
 

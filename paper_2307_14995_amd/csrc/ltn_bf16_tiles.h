@@ -36,18 +36,33 @@ __device__ __forceinline__ void dma16(unsigned lds, const char* g) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds), "v"(g) : "memory", "m0");
 }
 // The same load with a wave-uniform 64-bit base (scalar registers) and a 32-bit unsigned
-// per-lane byte offset: no per-lane 64-bit address arithmetic at the point of issue.
+// per-lane byte offset: no per-lane 64-bit address arithmetic at the point of issue.  ONCE: non-temporal.
+template <bool ONCE>
 __device__ __forceinline__ void dma16s(unsigned lds, const char* base, unsigned off) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds), "v"(off), "s"(base) : "memory", "m0");
+    if constexpr (ONCE)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" : : "s"(lds), "v"(off), "s"(base) : "memory", "m0");
+    else
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds), "v"(off), "s"(base) : "memory", "m0");
 }
 // The same with only the lanes of `mask` taking part (wave-uniform; all 64 lanes are active at
 // the call): the other lanes' LDS slots are left as they are.  EXEC is put back inside the
 // statement.
+template <bool ONCE>
 __device__ __forceinline__ void dma16s_masked(unsigned lds, const char* base, unsigned off, unsigned long long mask) {
     unsigned long long saved;
-    asm volatile("s_mov_b64 %0, exec\n\ts_mov_b64 exec, %4\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
-                 "global_load_lds_dwordx4 %2, %3\n\ts_mov_b64 exec, %0"
-                 : "=&s"(saved) : "s"(lds), "v"(off), "s"(base), "s"(mask) : "memory", "m0");
+    if constexpr (ONCE)
+        asm volatile("s_mov_b64 %0, exec\n\ts_mov_b64 exec, %4\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
+                     "global_load_lds_dwordx4 %2, %3 nt\n\ts_mov_b64 exec, %0"
+                     : "=&s"(saved) : "s"(lds), "v"(off), "s"(base), "s"(mask) : "memory", "m0");
+    else
+        asm volatile("s_mov_b64 %0, exec\n\ts_mov_b64 exec, %4\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
+                     "global_load_lds_dwordx4 %2, %3\n\ts_mov_b64 exec, %0"
+                     : "=&s"(saved) : "s"(lds), "v"(off), "s"(base), "s"(mask) : "memory", "m0");
+}
+// 16-byte store past the caches (system scope, non-temporal): the line is not kept on its way to memory.  The
+// registers may be overwritten two wait states after a store of more than 8 bytes.
+__device__ __forceinline__ void store16_past(char* p, const u32x4& v) {
+    asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1 nt\n\ts_nop 1" : : "v"(p), "v"(v) : "memory");
 }
 template <int N>
 __device__ __forceinline__ void wait_dma() { asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory"); }
@@ -194,13 +209,13 @@ struct TileDmaU {
         }
         return m;
     }
-    template <int V>
+    template <int V, bool ONCE>
     __device__ __forceinline__ void load(unsigned lds, const char* grp) const {
         if constexpr (REAL == COLS) {
-            dma16s(lds, grp, off[V]);
+            dma16s<ONCE>(lds, grp, off[V]);
         } else {
             constexpr unsigned long long m = real_lanes(V);
-            dma16s_masked(lds, grp, off[V], m);
+            dma16s_masked<ONCE>(lds, grp, off[V], m);
         }
     }
     unsigned off[NV];     // (row within its 16-row group, from the group's lowest-address row) * pitch + chunk * 16
@@ -215,7 +230,7 @@ struct TileDmaU {
     }
     // row0: wave-uniform global address of the block's row 0 (plus the slice's column offset);
     // rows follow at +pitch, or at -pitch on a reversed token axis.  All kBlock rows are read.
-    template <int NW, int W_>
+    template <int NW, int W_, bool ONCE = false>
     __device__ __forceinline__ void issue_full(const char* row0, long long pitch, int rev, unsigned lds) const {
         static_assert(NI % NW == 0, "every issuing wave takes the same number of loads");
 #pragma unroll
@@ -223,7 +238,7 @@ struct TileDmaU {
             const char* grp = row0 + (rev ? -(long long)(16 * m + 15) * pitch : (long long)(16 * m) * pitch);
             static_for<NV>([&](auto vc) {
                 constexpr int v = decltype(vc)::value;
-                if ((m * NV + v) % NW == W_) load<v>(lds + 1024u * (unsigned)(m * NV + v), grp);
+                if ((m * NV + v) % NW == W_) load<v, ONCE>(lds + 1024u * (unsigned)(m * NV + v), grp);
             });
         }
     }
@@ -252,8 +267,8 @@ struct TileDmaU {
 // swaps per tile pair (rows of 16 lanes: first between the wave's halves, then between
 // neighbouring rows) regroup them so that the lane holds the eight consecutive features
 // 32p + 8g .. +7 of its token: one 16-byte store per tile pair, and the four lanes of a
-// token write 64 contiguous bytes.  `out`: the lane's token row, column 8g.
-template <int NT>
+// token write 64 contiguous bytes.  `out`: the lane's token row, column 8g.  PAST: past the caches.
+template <int NT, bool PAST = false>
 __device__ __forceinline__ void store_strip(const f32x4 (&r)[NT], char* out, bool store) {
     unsigned w[NT][2];
 #pragma unroll
@@ -273,7 +288,10 @@ __device__ __forceinline__ void store_strip(const f32x4 (&r)[NT], char* out, boo
             q[d] = t[0];
             q[2 + d] = t[1];
         }
-        if (store) *(u32x4*)(out + 64 * p) = q;
+        if (store) {
+            if constexpr (PAST) store16_past(out + 64 * p, q);
+            else *(u32x4*)(out + 64 * p) = q;
+        }
     }
 }
 

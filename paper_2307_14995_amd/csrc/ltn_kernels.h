@@ -34,6 +34,12 @@ struct PassArgs {
     float* seg_rows;
 };
 
+// Cache hints of a bf16 launch; results do not depend on them.  kOnce*: an operand's tiles are loaded
+// non-temporally, so that they leave the caches first.  kLastSliceOnce: A and B by the last of a chain's
+// column slices only.  kPast: outputs are stored past the caches, which then keep what will be read again.
+enum { kOnceA = 1, kOnceB = 2, kOnceC = 4, kPast = 8, kLastSliceOnce = 16 };
+constexpr int kOnce = kOnceA | kOnceB | kOnceC, kSliceOnce = kOnceC | kLastSliceOnce;
+
 struct PassBatch {
     PassArgs p[3];
     int count;            // 1..3 passes run concurrently in one launch
@@ -59,6 +65,7 @@ struct PassBatch {
     int cut_chains;
     int cut_ids[3];
     long long cut_len;
+    int hints;            // those of the kernels that have them (launch_pass_bf16, launch_pass_cut_bf16)
 };
 
 // What the workgroup that goes by id `id` of a cut launch does.  part: 0 a whole pass, 1 the first and 2 the

@@ -215,7 +215,7 @@ struct ReadOffs {
 //   this lane's addresses in U and Y (same position as out), out may be null.
 //   uq (GATED): the gate values of this lane's token, loads issued by the caller from assembly
 //   earlier; GWAIT = the VMEM operations the wave issued after them.
-template <int D, int DV, int W, int CCOLS, bool GATED = false, int DROW = D, int GWAIT = 0>
+template <int D, int DV, int W, int CCOLS, bool GATED = false, int DROW = D, int GWAIT = 0, bool PAST = false>
 __device__ __forceinline__ void output_pass(const char* btile, const char* ctile, const char* scopy,
                                             const Frag (&Af)[D / 32], const OutConsts<W>& k,
                                             const ReadOffs<D, DV, CCOLS>& ro, char* out, bool store,
@@ -296,7 +296,7 @@ __device__ __forceinline__ void output_pass(const char* btile, const char* ctile
         for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
             for (int j = 0; j < 4; ++j) oi[nt][j] += k.qscale * oe[nt][j];
-        store_strip<NT>(oi, out, store);
+        store_strip<NT, PAST>(oi, out, store);
     } else {
         // the same regrouping on fp32 values, after the row's mean square: the four lanes of
         // a token (one per lane row) each hold a quarter of its D features
@@ -445,6 +445,7 @@ struct Chain {            // what every wave of the workgroup knows about its pr
     int last_valid;       // tokens in the last block (1..64)
     int rev;
     float lam;
+    int last_slice;          // this is the last of the chain's column slices
     int part;                // kCut: 0 the whole chain, 1 its first part, 2 its second part
     char* handover;          // parts 1, 2: the slice's columns of the second part's lowest output row
 };
@@ -514,9 +515,10 @@ __device__ __forceinline__ void wait_block(int blk) {
     }
 }
 
-template <int D, int DV, int DC, int W, int MODE, int DR>
+template <int D, int DV, int DC, int W, int MODE, int DR, int HINTS>
 __device__ __forceinline__ void pass_output_wave(const Chain& ch, char* smem, unsigned lds0, int lane) {
     using C = Cfg<D, DV>;
+    static_assert(!has_gate(MODE) || !(HINTS & kPast), "the gated pass stores through the caches");
     constexpr bool GATED = has_gate(MODE);
     constexpr int AHEAD = gate_ahead(MODE);
     constexpr bool SO = MODE == kStateOnly;          // nothing to produce: tile loads and barriers only
@@ -549,6 +551,8 @@ __device__ __forceinline__ void pass_output_wave(const Chain& ch, char* smem, un
         pc0 = ch.c + (ch.rev ? (ch.N - 1) * ROW : 0);
     }
     const long long astep = ch.rev ? -(long long)kBlock * AROW : (long long)kBlock * AROW;
+    // (Hints are constants: read from the launch's arguments they cost the kernels that have none up to 8 %, 96
+    // chains x 1999 x 96 forward and backward 131 and 142 us, by what the branches do to the block loop.)
     auto fetch = [&](int b, int stage) {
         if constexpr (ISSUER) {
             b = b < ch.T ? b : ch.T - 1;   // past the end: re-read the last block into a free stage
@@ -558,9 +562,20 @@ __device__ __forceinline__ void pass_output_wave(const Chain& ch, char* smem, un
             const char* pb = pb0 + (long long)b * astep;
             const char* pc = pc0 + (long long)b * step;
             if (valid == kBlock) {
-                if constexpr (!NOA) dab.template issue_full<C::FW, W>(pa, AROW, ch.rev, lds);
-                dab.template issue_full<C::FW, W>(pb, AROW, ch.rev, lds + C::BOFF);
-                dcc.template issue_full<C::FW, W>(pc, ROW, ch.rev, lds + C::COFF);
+                if constexpr (HINTS & kLastSliceOnce) {
+                    static_assert(!NOA, "no slices share less");
+                    if (ch.last_slice) {
+                        dab.template issue_full<C::FW, W, true>(pa, AROW, ch.rev, lds);
+                        dab.template issue_full<C::FW, W, true>(pb, AROW, ch.rev, lds + C::BOFF);
+                    } else {
+                        dab.template issue_full<C::FW, W>(pa, AROW, ch.rev, lds);
+                        dab.template issue_full<C::FW, W>(pb, AROW, ch.rev, lds + C::BOFF);
+                    }
+                } else {
+                    if constexpr (!NOA) dab.template issue_full<C::FW, W, (HINTS & kOnceA) != 0>(pa, AROW, ch.rev, lds);
+                    dab.template issue_full<C::FW, W, (HINTS & kOnceB) != 0>(pb, AROW, ch.rev, lds + C::BOFF);
+                }
+                dcc.template issue_full<C::FW, W, (HINTS & kOnceC) != 0>(pc, ROW, ch.rev, lds + C::COFF);
             } else {
                 if constexpr (!NOA) dab.template issue_partial<C::FW, W>(pa, AROW, ch.rev, lds, valid, lane);
                 dab.template issue_partial<C::FW, W>(pb, AROW, ch.rev, lds + C::BOFF, valid, lane);
@@ -656,7 +671,7 @@ __device__ __forceinline__ void pass_output_wave(const Chain& ch, char* smem, un
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) Af[ks].u = *(const u32x4*)(st + (16 * W) * C::F::RB + ro.row[ks]);
         // with more blocks to come every lane stores (the count above relies on it)
-        output_pass<D, DV, W, C::CW, GATED, DC, AHEAD == 2 ? 2 * L + S + G : L>(st + C::BOFF, st + C::COFF,
+        output_pass<D, DV, W, C::CW, GATED, DC, AHEAD == 2 ? 2 * L + S + G : L, (HINTS & kPast) != 0>(st + C::BOFF, st + C::COFF,
                                             smem + C::P_SB + (blk & 1) * C::SBYTES, Af, k, ro,
                                             po ? po + bo : nullptr, more || row_ok,
                                             u, GATED ? py + bo : nullptr, ch.eps);
@@ -914,7 +929,7 @@ __device__ __forceinline__ void map_pass(unsigned wg, int count, int xcd_ids, in
     split = (int)(within - (unsigned)pi * NS);
 }
 
-template <int D, int DV, int DC, int MODE, int DR>
+template <int D, int DV, int DC, int MODE, int DR, int HINTS>
 __device__ __forceinline__ void pass_body(const PassBatch& pb, int xcd_ids, int wg, char* smem,
                                           unsigned lds0, int wave, int lane) {
     constexpr bool GATED = has_gate(MODE);
@@ -1007,6 +1022,7 @@ __device__ __forceinline__ void pass_body(const PassBatch& pb, int xcd_ids, int 
     ch.last_valid = (int)(n - (long long)(ch.T - 1) * kBlock);
     ch.rev = rev;
     ch.lam = lam;
+    if constexpr (HINTS & kLastSliceOnce) ch.last_slice = split == NS - 1;
 
     if constexpr (DR != D || Cfg<D, DV>::CW != DV) {
         // Tiles wider than the tensors' rows: their loads leave the surplus chunks alone, which
@@ -1034,10 +1050,10 @@ __device__ __forceinline__ void pass_body(const PassBatch& pb, int xcd_ids, int 
         switch (wave) {
             case 0: case 1: case 2: case 3:
                 if constexpr (MODE == kStateOnly) {    // tile loads (waves 0 .. FW-1) and barriers only
-                    if (wave == 0) pass_output_wave<D, DV, DC, 0, MODE, DR>(ch, smem, lds0, lane);
-                    else if (wave == 1) pass_output_wave<D, DV, DC, 1, MODE, DR>(ch, smem, lds0, lane);
-                    else if (wave == 2) pass_output_wave<D, DV, DC, 2, MODE, DR>(ch, smem, lds0, lane);
-                    else pass_output_wave<D, DV, DC, 3, MODE, DR>(ch, smem, lds0, lane);
+                    if (wave == 0) pass_output_wave<D, DV, DC, 0, MODE, DR, HINTS>(ch, smem, lds0, lane);
+                    else if (wave == 1) pass_output_wave<D, DV, DC, 1, MODE, DR, HINTS>(ch, smem, lds0, lane);
+                    else if (wave == 2) pass_output_wave<D, DV, DC, 2, MODE, DR, HINTS>(ch, smem, lds0, lane);
+                    else pass_output_wave<D, DV, DC, 3, MODE, DR, HINTS>(ch, smem, lds0, lane);
                 } else {
                     if (wave == 0) areg_output_wave<D, DV, DC, 0>(ch, smem, lds0, lane);
                     else if (wave == 1) areg_output_wave<D, DV, DC, 1>(ch, smem, lds0, lane);
@@ -1049,10 +1065,10 @@ __device__ __forceinline__ void pass_body(const PassBatch& pb, int xcd_ids, int 
         }
     } else {
         switch (wave) {
-            case 0: pass_output_wave<D, DV, DC, 0, MODE, DR>(ch, smem, lds0, lane); break;
-            case 1: pass_output_wave<D, DV, DC, 1, MODE, DR>(ch, smem, lds0, lane); break;
-            case 2: pass_output_wave<D, DV, DC, 2, MODE, DR>(ch, smem, lds0, lane); break;
-            case 3: pass_output_wave<D, DV, DC, 3, MODE, DR>(ch, smem, lds0, lane); break;
+            case 0: pass_output_wave<D, DV, DC, 0, MODE, DR, HINTS>(ch, smem, lds0, lane); break;
+            case 1: pass_output_wave<D, DV, DC, 1, MODE, DR, HINTS>(ch, smem, lds0, lane); break;
+            case 2: pass_output_wave<D, DV, DC, 2, MODE, DR, HINTS>(ch, smem, lds0, lane); break;
+            case 3: pass_output_wave<D, DV, DC, 3, MODE, DR, HINTS>(ch, smem, lds0, lane); break;
             default: pass_state_wave<D, DV, DC, MODE, DR>(ch, smem, lane, wave - 4); break;
         }
     }
@@ -1067,16 +1083,16 @@ __device__ __forceinline__ void pass_body(const PassBatch& pb, int xcd_ids, int 
 
 // =============================================================== kernels
 
-template <int D, int DV, int MODE, int DC = D, int DR = D>
+template <int D, int DV, int MODE, int DC = D, int DR = D, int HINTS = 0>
 __global__ __launch_bounds__(kThreads)
 void pass_bf16_kernel(const PassBatch pb, const int xcd_ids) {
     __shared__ __attribute__((aligned(1024))) char smem[Cfg<D, DV>::PASS_TOTAL];
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // scalar: role dispatch is a uniform branch
-    pass_body<D, DV, DC, MODE, DR>(pb, xcd_ids, blockIdx.x, smem, lds_address(smem), wave, tid & 63);
+    pass_body<D, DV, DC, MODE, DR, HINTS>(pb, xcd_ids, blockIdx.x, smem, lds_address(smem), wave, tid & 63);
 }
 
-template <int D, int DV, int MODE = kPlain, int DC = D, int DR = D>
+template <int D, int DV, int MODE = kPlain, int DC = D, int DR = D, int HINTS = 0>
 hipError_t launch_t(const PassBatch& pb, hipStream_t stream) {
     static_assert(DV <= DC && DC % DV == 0, "value-column slices tile the C operand");
     static_assert(DC == D || !has_gate(MODE) || (D == 128 && DC == 96 && DR == 96 && DV == 96),
@@ -1086,9 +1102,17 @@ hipError_t launch_t(const PassBatch& pb, hipStream_t stream) {
     const int per_chain = pb.count * nsplit;
     const long long wgs = launch_chain_slots(nch, per_chain) * per_chain;
     if (wgs <= 0 || wgs > 0x7fffffffLL || pb.segs < 1) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((pass_bf16_kernel<D, DV, MODE, DC, DR>), dim3((unsigned)wgs), dim3(kThreads), 0, stream, pb,
+    hipLaunchKernelGGL((pass_bf16_kernel<D, DV, MODE, DC, DR, HINTS>), dim3((unsigned)wgs), dim3(kThreads), 0, stream, pb,
                        (int)xcd_ids_fit(nch, per_chain));
     return hipGetLastError();
+}
+
+// The same with the launch's cache hints where the kernel exists with them (H...), else without.
+template <int D, int DV, int MODE, int DC, int DR, int... H>
+hipError_t launch_hints(const PassBatch& pb, hipStream_t stream) {
+    hipError_t e = hipErrorInvalidValue;
+    if (((pb.hints == H && (e = launch_t<D, DV, MODE, DC, DR, H>(pb, stream), true)) || ...)) return e;
+    return launch_t<D, DV, MODE, DC, DR>(pb, stream);
 }
 
 __global__ void clear_handover_kernel(char* out, long long row_bytes, long long N, long long flag_row, int slices,
@@ -1101,7 +1125,7 @@ __global__ void clear_handover_kernel(char* out, long long row_bytes, long long 
     flag[1] = 0u;                          // the counter, in one part of each XCD's
 }
 
-template <int D, int DV, int DC, int DR, int MODE = kCut>
+template <int D, int DV, int DC, int DR, int MODE = kCut, int HINTS = 0>
 hipError_t launch_cut_t(PassBatch& pb, hipStream_t stream) {
     constexpr int NS = DC / DV;
     const PassArgs& last = pb.p[pb.count - 1];
@@ -1117,10 +1141,19 @@ hipError_t launch_cut_t(PassBatch& pb, hipStream_t stream) {
                        (char*)(has_gate(MODE) ? last.gated_out : last.out), DC * 2LL, pb.N, (last.rev ? 0 : pb.cut_len) + 2 * DR, NS, DV * 2, cut);
     // without it the pass would read flags and counters that nobody cleared
     if (const hipError_t e = hipGetLastError(); e != hipSuccess) return e;
-    hipLaunchKernelGGL((pass_bf16_kernel<D, DV, MODE, DC, DR>), dim3((unsigned)wgs), dim3(kThreads), 0, stream, pb,
+    hipLaunchKernelGGL((pass_bf16_kernel<D, DV, MODE, DC, DR, HINTS>), dim3((unsigned)wgs), dim3(kThreads), 0, stream, pb,
                        (int)xcd);
     return hipGetLastError();
 }
+
+template <int D, int DV, int DC, int DR, int MODE, int... H>
+hipError_t launch_cut_hints(PassBatch& pb, hipStream_t stream) {
+    hipError_t e = hipErrorInvalidValue;
+    if (((pb.hints == H && (e = launch_cut_t<D, DV, DC, DR, MODE, H>(pb, stream), true)) || ...)) return e;
+    return launch_cut_t<D, DV, DC, DR, MODE>(pb, stream);
+}
+
+constexpr int kBackward = kOnceA | kPast;
 
 }  // namespace
 
@@ -1128,23 +1161,23 @@ hipError_t launch_pass_cut_bf16(PassBatch& pb, int D, hipStream_t stream, int DC
     if (DC != 0 && DC != D) {
         if (D == 256 && DC == 128) return launch_cut_t<256, 64, 128, 256>(pb, stream);
         if (D == 128 && DC == 256) return launch_cut_t<128, 128, 256, 128>(pb, stream);
-        if (D == 128 && DC == 64) return launch_cut_t<128, 64, 64, 128>(pb, stream);
+        if (D == 128 && DC == 64) return launch_cut_hints<128, 64, 64, 128, kCut, kOnce>(pb, stream);
         if (D == 64 && DC == 128) return launch_cut_t<64, 64, 128, 64>(pb, stream);
         return hipErrorInvalidValue;
     }
     if (pb.p[0].gate) {                    // the forms of launch_pass_bf16 for this many chains
         if (pb.count != 1 || !pb.p[0].gated_out) return hipErrorInvalidValue;
-        if (D == 64) return launch_cut_t<64, 64, 64, 64, kCut + kGatedFar>(pb, stream);
-        if (D == 96 && pb.p[0].out) return launch_cut_t<128, 96, 96, 96, kCut + kGatedLate>(pb, stream);
-        if (D == 96) return launch_cut_t<128, 96, 96, 96, kCut + kGated>(pb, stream);
-        if (D == 128 && pb.p[0].out) return launch_cut_t<128, 128, 128, 128, kCut + kGatedLate>(pb, stream);
-        if (D == 128) return launch_cut_t<128, 128, 128, 128, kCut + kGated>(pb, stream);
+        if (D == 64) return launch_cut_hints<64, 64, 64, 64, kCut + kGatedFar, kOnce>(pb, stream);
+        if (D == 96 && pb.p[0].out) return launch_cut_hints<128, 96, 96, 96, kCut + kGatedLate, kOnce>(pb, stream);
+        if (D == 96) return launch_cut_hints<128, 96, 96, 96, kCut + kGated, kOnce>(pb, stream);
+        if (D == 128 && pb.p[0].out) return launch_cut_hints<128, 128, 128, 128, kCut + kGatedLate, kOnce>(pb, stream);
+        if (D == 128) return launch_cut_hints<128, 128, 128, 128, kCut + kGated, kOnce>(pb, stream);
         return hipErrorInvalidValue;
     }
     switch (D) {
-        case 64: return launch_cut_t<64, 64, 64, 64>(pb, stream);
-        case 96: return launch_cut_t<128, 96, 96, 96>(pb, stream);
-        case 128: return launch_cut_t<128, 128, 128, 128>(pb, stream);
+        case 64: return launch_cut_hints<64, 64, 64, 64, kCut, kOnce, kBackward>(pb, stream);
+        case 96: return launch_cut_hints<128, 96, 96, 96, kCut, kOnce, kBackward>(pb, stream);
+        case 128: return launch_cut_hints<128, 128, 128, 128, kCut, kOnce, kBackward>(pb, stream);
         case 256: return launch_cut_t<256, 64, 256, 256>(pb, stream);
         default: return hipErrorInvalidValue;
     }
@@ -1163,7 +1196,8 @@ hipError_t launch_pass_bf16(const PassBatch& pb, int D, int dv, hipStream_t stre
 #define LTN_BF16_DC(d, v, c) if (D == d && dv == v && DC == c) return launch_t<d, v, kPlain, c>(pb, stream)
         LTN_BF16_DC(256, 64, 128); LTN_BF16_DC(256, 32, 128);
         LTN_BF16_DC(128, 128, 256); LTN_BF16_DC(128, 64, 256); LTN_BF16_DC(128, 32, 256);
-        LTN_BF16_DC(128, 64, 64); LTN_BF16_DC(128, 32, 64);
+        if (D == 128 && dv == 64 && DC == 64) return launch_hints<128, 64, kPlain, 64, 128, kOnce>(pb, stream);
+        LTN_BF16_DC(128, 32, 64);
         LTN_BF16_DC(64, 64, 128); LTN_BF16_DC(64, 32, 128);
 #undef LTN_BF16_DC
         return hipErrorInvalidValue;
@@ -1174,11 +1208,11 @@ hipError_t launch_pass_bf16(const PassBatch& pb, int D, int dv, hipStream_t stre
             if (pb.count != 1 || dv != 96 || !pb.p[0].gated_out || pb.state_only) return hipErrorInvalidValue;
             // with O stored as for 128 features below; and a single block has nothing to run ahead of (1024
             // chains x 64 tokens 23.2 us ahead, 22.1 late; 128 features 512 x 64 11.0 and 12.4)
-            if (pb.p[0].out || pb.N <= kBlock) return launch_t<128, 96, kGatedLate, 96, 96>(pb, stream);
-            return launch_t<128, 96, kGated, 96, 96>(pb, stream);
+            if (pb.p[0].out || pb.N <= kBlock) return launch_hints<128, 96, kGatedLate, 96, 96, kOnce>(pb, stream);
+            return launch_hints<128, 96, kGated, 96, 96, kOnce>(pb, stream);
         }
         if (pb.state_only) return dv == 32 ? launch_t<128, 32, kStateOnly, 96, 96>(pb, stream) : hipErrorInvalidValue;
-        if (dv == 96) return launch_t<128, 96, kPlain, 96, 96>(pb, stream);
+        if (dv == 96) return launch_hints<128, 96, kPlain, 96, 96, kOnce, kBackward>(pb, stream);
         return launch_t<128, 32, kPlain, 96, 96>(pb, stream);
     }
     if (pb.p[0].gate) {                    // gated epilogue: one pass, complete output rows
@@ -1189,8 +1223,8 @@ hipError_t launch_pass_bf16(const PassBatch& pb, int D, int dv, hipStream_t stre
         // 320 x 8192 479 and 504; without O ahead is the faster or within 3 % at every size (64 .. 768
         // chains x 64 .. 8192: 128 x 2048 77 and 80, 96 x 2048 60 and 72, 160 x 2048 91.5 and 89.1;
         // calls of 10 us, which the host bounds, scatter by 5 %).
-        if (D == 128 && pb.p[0].out) return launch_t<128, 128, kGatedLate>(pb, stream);
-        if (D == 128) return launch_t<128, 128, kGated>(pb, stream);
+        if (D == 128 && pb.p[0].out) return launch_hints<128, 128, kGatedLate, 128, 128, kOnce>(pb, stream);
+        if (D == 128) return launch_hints<128, 128, kGated, 128, 128, kOnce>(pb, stream);
         // 64 features: a block takes 0.55 us and its gate loads longer once the chip is busy, so two ahead
         // from 128 whole chains on, 192 with O (one ahead and two, kernels alone: 128 x 500 12.5 and 12.2, 128 x 1000
         // 20.4 and 19.4, 128 x 3000 48.1 and 45.3, 191 x 500 13.9 and 13.4, 192 x 500 with O 15.3 and 15.1).  Up to four
@@ -1198,8 +1232,8 @@ hipError_t launch_pass_bf16(const PassBatch& pb, int D, int dv, hipStream_t stre
         // 6.5 and 6.7, 256 x 129 8.0 and 8.2, 512 x 128 with O 13.5 and 14.2, 512 x 200 with O 19.6 and 20.2; five
         // blocks: 256 x 257 11.8 and 11.5, 512 x 257 21.9 and 21.7).  Wider heads have no registers for it.
         if (D == 64 && pb.segs == 1 && pb.N > 4 * kBlock && pb.chains >= (pb.p[0].out ? 192 : 128))
-            return launch_t<64, 64, kGatedFar>(pb, stream);
-        if (D == 64) return launch_t<64, 64, kGated>(pb, stream);
+            return launch_hints<64, 64, kGatedFar, 64, 64, kOnce>(pb, stream);
+        if (D == 64) return launch_hints<64, 64, kGated, 64, 64, kOnce>(pb, stream);
         return hipErrorInvalidValue;
     }
     if (pb.state_only) {                   // segment end states only (sequence-parallel form)
@@ -1213,11 +1247,11 @@ hipError_t launch_pass_bf16(const PassBatch& pb, int D, int dv, hipStream_t stre
     }
     if (D == 256 && dv == 64) return launch_t<256, 64>(pb, stream);
     if (D == 256 && dv == 32) return launch_t<256, 32>(pb, stream);
-    if (D == 128 && dv == 128) return launch_t<128, 128>(pb, stream);
-    if (D == 128 && dv == 64) return launch_t<128, 64>(pb, stream);
+    if (D == 128 && dv == 128) return launch_hints<128, 128, kPlain, 128, 128, kOnce, kOnce | kPast, kBackward>(pb, stream);
+    if (D == 128 && dv == 64) return launch_hints<128, 64, kPlain, 128, 128, kSliceOnce>(pb, stream);
     if (D == 128 && dv == 32) return launch_t<128, 32>(pb, stream);
-    if (D == 64 && dv == 64) return launch_t<64, 64>(pb, stream);
-    if (D == 64 && dv == 32) return launch_t<64, 32>(pb, stream);
+    if (D == 64 && dv == 64) return launch_hints<64, 64, kPlain, 64, 64, kOnce, kBackward>(pb, stream);
+    if (D == 64 && dv == 32) return launch_hints<64, 32, kPlain, 64, 64, kSliceOnce>(pb, stream);
     return hipErrorInvalidValue;
 }
 

@@ -1,0 +1,72 @@
+"""bf16 passes of inputs large enough for cache hints (non-temporal tile loads, outputs stored past the caches): the
+same bits as the two halves of the batch, which are below the sizes where hints begin."""
+import pytest
+import torch
+
+import paper_2307_14995_amd as ltn
+from _helpers import force_plan, mixed_decay
+
+pytestmark = pytest.mark.gpu
+
+
+def rand(g, *shape):
+    return torch.randn(shape, generator=g, device="cuda", dtype=torch.bfloat16)
+
+
+def inputs(H, N, D, n, Dv=None):
+    g = torch.Generator(device="cuda").manual_seed(N)
+    return [rand(g, 2, H, N, Dv if Dv and i >= 2 else D) for i in range(n)], mixed_decay(H).cuda()
+
+
+def halves(call, tensors, dv, segs):
+    """call on each half of the batch (its only dimension but chains), under a forced plan"""
+    with force_plan(dv=dv, segs=segs):
+        parts = [call(*(t[i:i + 1].contiguous() for t in tensors)) for i in range(2)]
+    return [torch.cat(p) for p in zip(*parts)]
+
+
+# (D, H, N, dv, segs) of half the chains: whole chains at full width (64 features, 96 and 128; ragged last blocks), two
+# slices, segments; dv and segs are what the whole batch gets by itself
+@pytest.mark.parametrize("D,H,N,dv,segs", [(128, 128, 257, 128, 1), (64, 256, 257, 64, 1), (96, 160, 300, 96, 1),
+                                           (128, 60, 641, 64, 1), (64, 60, 1217, 32, 1), (128, 16, 6200, 128, 8),
+                                           (64, 16, 12350, 64, 8), (128, 130, 770, 128, 1)])
+def test_forward(D, H, N, dv, segs):
+    t, decay = inputs(H, N, D, 3)
+    with force_plan(segs=segs if segs > 1 else 0):
+        o, kv = ltn.ltn_attn_fwd(*t, decay, return_state=True)
+    want = halves(lambda *x: ltn.ltn_attn_fwd(*x, decay, return_state=True), t, dv, segs)
+    assert torch.equal(o, want[0]) and torch.equal(kv, want[1])
+
+
+def test_forward_unequal_widths():
+    t, decay = inputs(128, 350, 128, 3, Dv=64)
+    o = ltn.ltn_attn_fwd_dkdv(*t, decay)
+    want = halves(lambda *x: (ltn.ltn_attn_fwd_dkdv(*x, decay),), t, 64, 1)
+    assert torch.equal(o, want[0])
+
+
+@pytest.mark.parametrize("store_o", [False, True])
+@pytest.mark.parametrize("D,H,N,segs", [(128, 192, 137, 1), (96, 192, 190, 1), (64, 192, 300, 1), (64, 192, 1217, 1),
+                                        (128, 200, 705, 1), (96, 200, 769, 1), (128, 16, 5000, 8)])
+def test_gated_forward(D, H, N, segs, store_o):
+    if segs > 1 and store_o:
+        pytest.skip("few chains with o stored run in two steps")
+    t, decay = inputs(H, N, D, 4)
+
+    def call(*x):
+        o, y, kv = ltn.ltn_attn_fwd_gated(*x, decay, eps=1e-6, return_state=True, store_o=store_o)
+        return (y, kv, o) if store_o else (y, kv)
+
+    with force_plan(segs=segs if segs > 1 else 0):
+        got = call(*t)
+    assert all(torch.equal(a, b) for a, b in zip(got, halves(call, t, 0, segs)))
+
+
+# both by themselves (dQ's chains may run in two parts) and in whole chains
+@pytest.mark.parametrize("D,H,N", [(128, 64, 1921), (96, 86, 1921), (64, 130, 1921)])
+def test_backward(D, H, N):
+    t, decay = inputs(H, N, D, 4)
+    want = halves(lambda *x: ltn.ltn_attn_bwd(*x, decay), t, D, 1)
+    assert all(torch.equal(a, b) for a, b in zip(ltn.ltn_attn_bwd(*t, decay), want))
+    with force_plan(segs=1):
+        assert all(torch.equal(a, b) for a, b in zip(ltn.ltn_attn_bwd(*t, decay), want))
