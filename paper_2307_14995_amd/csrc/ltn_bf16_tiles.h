@@ -4,6 +4,7 @@
 #pragma once
 #include <type_traits>
 #include <utility>
+#include "ltn_cache.h"
 #include "ltn_kernels.h"
 
 namespace ltn {
@@ -14,7 +15,6 @@ typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
 typedef __attribute__((__vector_size__(4 * sizeof(short)))) short s16x4;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 typedef __attribute__((__vector_size__(8 * sizeof(float)))) float f32x8;
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
 union Frag {          // one 16x16x32 MFMA operand: 8 bf16 per lane
     bf16x8 v;
@@ -58,11 +58,6 @@ __device__ __forceinline__ void dma16s_masked(unsigned lds, const char* base, un
         asm volatile("s_mov_b64 %0, exec\n\ts_mov_b64 exec, %4\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
                      "global_load_lds_dwordx4 %2, %3\n\ts_mov_b64 exec, %0"
                      : "=&s"(saved) : "s"(lds), "v"(off), "s"(base), "s"(mask) : "memory", "m0");
-}
-// 16-byte store past the caches (system scope, non-temporal): the line is not kept on its way to memory.  The
-// registers may be overwritten two wait states after a store of more than 8 bytes.
-__device__ __forceinline__ void store16_past(char* p, const u32x4& v) {
-    asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1 nt\n\ts_nop 1" : : "v"(p), "v"(v) : "memory");
 }
 template <int N>
 __device__ __forceinline__ void wait_dma() { asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory"); }

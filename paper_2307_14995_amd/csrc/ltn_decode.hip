@@ -9,6 +9,7 @@
 // columns of a strided set of rows, and the partial dot products per column are reduced
 // through LDS.  Queries and keys have DK features, values and outputs DV (the state is
 // [DK x DV]); the two differ only behind the LRPE-d expansion of Eq. 1.
+#include "ltn_cache.h"
 #include "ltn_kernels.h"
 
 namespace ltn {
@@ -33,6 +34,34 @@ __device__ __forceinline__ unsigned short f32_to_bf16_bits(float f) {   // round
     return (unsigned short)(u >> 16);
 }
 
+// A state is read once and written once, and the next call that wants it comes after every other layer's.  Loads and
+// stores that leave the caches first, or are written through, keep the lines from being written back
+// in the middle of the reads.  us a call, 128 x 128, plain / once / read once and written through, states of many layers
+// (1.1 GiB in turn) and of few (160 .. 192 MiB): 128 chains (8 MiB) 6.0 / 4.7 / 4.8 and 5.0 / 4.7 / 4.7; 256 9.7 / 6.9 /
+// 7.2 and 7.9 / 6.8 / 6.9; 512 15.7 / 11.4 / 11.7 and 11.7 / 11.0 / 11.7; 1024 28.6 / 22.5 / 23.4 and 19.9 / 20.8 / 22.6 (two
+// sets); 1536 44.6 / 38.1 / 39.6 and 30.6 / 37.1 / 33.4; 2048 55.4 / 49.3 / 50.5 and 43.2 / 48.8 / 40.4, one state repeated
+// 39.9 / 47.2 / 39.0.  256 x 256, 128 chains (32 MiB) 18.0 / 13.5 / 14.3 and 11.4 / 13.2 / 11.2, 256 30.5 / 26.8 / 28.3 and 21.3 /
+// 26.4 / 21.2; 64 x 64, 2048 chains (32 MiB) 15.3 / 12.4 / 12.7 and 11.1 / 11.9 / 10.6, 4096 27.4 / 23.5 / 24.0 and 21.3 /
+// 22.8 / 20.2; whole 128 x 64 and 96 x 96 as 64 x 64 from 50 MiB on (2000 chains 29.7 / 24.0 once and 19.1 / 23.0).  Hence
+// the line of write_through().
+union Bits { u32x4 u; float4 f; };
+__device__ __forceinline__ float4 load_state(const float4* p) {
+    Bits b;
+    b.u = load16_once(p);
+    return b.f;
+}
+template <bool THROUGH>
+__device__ __forceinline__ void store_state(float4* p, float4 v) {      // (by reference: 256 registers, not 200)
+    Bits b;
+    b.f = v;
+    if constexpr (THROUGH) store16_through(p, b.u);
+    else store16_once(p, b.u);
+}
+bool write_through(int chains, int DK, int DV) {
+    const long long mib = (long long)chains * DK * DV * 4 >> 20;
+    return mib >= (DK == 256 || DK == 64 ? 24 : DV == 128 ? 72 : 40);
+}
+
 // Order of an output's sum, the same in both kernels below, so that a sequence's output does not depend on
 // how many others are in the call: rows in DK / 8 classes (row mod DK / 8) of eight, each summed in the
 // rows' order; the classes pairwise, neighbours first, in groups of eight (96 features: in threes); the
@@ -41,7 +70,7 @@ __device__ __forceinline__ unsigned short f32_to_bf16_bits(float f) {   // round
 // chains 10.2 / 56.2 and 9.9 / 55.6, 256 x 128, 3000 chains 148.8 and 146.6, 96 x 96, 1024 chains 12.8 and 12.9,
 // 256 x 256, 2048 chains 204 and 206.  Classes that lie apart, so that a wave reads adjacent rows: 10.0 /
 // 55.8, 146.9, 12.9 and 206.
-template <int DK, int DV, bool BF16>
+template <int DK, int DV, bool BF16, bool THROUGH>
 __global__ __launch_bounds__(threads_for(DK, DV))
 void decode_kernel(const void* __restrict__ q, const void* __restrict__ k, const void* __restrict__ v,
                    void* __restrict__ o, float* __restrict__ kv, const float* __restrict__ decay, int H,
@@ -65,7 +94,7 @@ void decode_kernel(const void* __restrict__ q, const void* __restrict__ k, const
     auto row = [](int it) { return CL * (it / G) + it % G; };
     float4 s[IT];
 #pragma unroll
-    for (int it = 0; it < IT; ++it) s[it] = S[row(it) * TX];
+    for (int it = 0; it < IT; ++it) s[it] = load_state(S + row(it) * TX);
 
     for (int step = 0; step < steps; ++step) {
         if (tid < DK) {
@@ -132,7 +161,7 @@ void decode_kernel(const void* __restrict__ q, const void* __restrict__ k, const
         // the next step's first barrier separates these reads of `part` from its next writes
     }
 #pragma unroll
-    for (int it = 0; it < IT; ++it) S[row(it) * TX] = s[it];
+    for (int it = 0; it < IT; ++it) store_state<THROUGH>(S + row(it) * TX, s[it]);
 }
 
 // The same with a chain's value columns split over DV / 32 workgroups: columns are independent of each
@@ -144,7 +173,7 @@ void decode_kernel(const void* __restrict__ q, const void* __restrict__ k, const
 // 7.77 / 21.5 / 83.4 and 4.35 / 21.2 / 81.9 (10.9 / 29.5 / 107.5 and 6.11 / 30.0 / 106.4).
 constexpr int kSliceCols = 32;
 
-template <int DK, int DV, bool BF16>
+template <int DK, int DV, bool BF16, bool THROUGH>
 __global__ __launch_bounds__(DK)
 void decode_slice_kernel(const void* __restrict__ q, const void* __restrict__ k, const void* __restrict__ v,
                          void* __restrict__ o, float* __restrict__ kv, const float* __restrict__ decay, int H,
@@ -164,7 +193,7 @@ void decode_slice_kernel(const void* __restrict__ q, const void* __restrict__ k,
     float4* S = (float4*)(kv + (size_t)chain * DK * DV + col0);
     float4 s[IT];
 #pragma unroll
-    for (int it = 0; it < IT; ++it) s[it] = S[(size_t)(ty + TY * it) * (DV / 4) + tx];
+    for (int it = 0; it < IT; ++it) s[it] = load_state(S + (size_t)(ty + TY * it) * (DV / 4) + tx);
 
     auto load = [](const void* p, size_t e) {
         return BF16 ? bf16_bits_to_f32(((const unsigned short*)p)[e]) : ((const float*)p)[e];
@@ -210,7 +239,7 @@ void decode_slice_kernel(const void* __restrict__ q, const void* __restrict__ k,
         // the next step's first barrier separates these reads of `part` from its next writes
     }
 #pragma unroll
-    for (int it = 0; it < IT; ++it) S[(size_t)(ty + TY * it) * (DV / 4) + tx] = s[it];
+    for (int it = 0; it < IT; ++it) store_state<THROUGH>(S + (size_t)(ty + TY * it) * (DV / 4) + tx, s[it]);
 }
 
 // Slices up to which a call is split; past them the units are full either way, and a slice reads rows
@@ -230,22 +259,27 @@ hipError_t launch_decode(const void* q, const void* k, const void* v, void* o, f
                          hipStream_t stream) {
     if (chains <= 0 || steps <= 0) return hipSuccess;
     const dim3 grid((unsigned)chains);
+    const bool through = write_through(chains, DK, DV);
     const bool split = (long long)chains * (DV / kSliceCols) <= split_limit(DK, DV);
     const dim3 slices((unsigned)(split ? chains * (DV / kSliceCols) : 1));
-#define LTN_DECODE(dk, dv)                                                                              \
-    if (DK == dk && DV == dv) {                                                                         \
+    // a state of this width: as slices or whole, written through or not
+#define LTN_DECODE_T(dk, dv, bf, th)                                                                    \
+    do {                                                                                                \
         if constexpr (split_limit(dk, dv) > 0) if (split) {                                             \
-            if (is_bf16) hipLaunchKernelGGL((decode_slice_kernel<dk, dv, true>), slices, dim3(dk), 0, stream, q, k, v, o, kv, decay, H, steps);  \
-            else hipLaunchKernelGGL((decode_slice_kernel<dk, dv, false>), slices, dim3(dk), 0, stream, q, k, v, o, kv, decay, H, steps);         \
+            hipLaunchKernelGGL((decode_slice_kernel<dk, dv, bf, th>), slices, dim3(dk), 0, stream, q, k, v, o, kv, decay, H, steps); \
             return hipGetLastError();                                                                   \
         }                                                                                               \
-        const dim3 block(threads_for(dk, dv));                                                          \
-        if (is_bf16) hipLaunchKernelGGL((decode_kernel<dk, dv, true>), grid, block, 0, stream, q, k, v, o, kv, decay, H, steps);  \
-        else hipLaunchKernelGGL((decode_kernel<dk, dv, false>), grid, block, 0, stream, q, k, v, o, kv, decay, H, steps);         \
+        hipLaunchKernelGGL((decode_kernel<dk, dv, bf, th>), grid, dim3(threads_for(dk, dv)), 0, stream, q, k, v, o, kv, decay, H, steps); \
         return hipGetLastError();                                                                       \
+    } while (0)
+#define LTN_DECODE(dk, dv)                                                                              \
+    if (DK == dk && DV == dv) {                                                                         \
+        if (is_bf16) { if (through) LTN_DECODE_T(dk, dv, true, true); else LTN_DECODE_T(dk, dv, true, false); }   \
+        else { if (through) LTN_DECODE_T(dk, dv, false, true); else LTN_DECODE_T(dk, dv, false, false); }         \
     }
     LTN_DECODE(128, 128) LTN_DECODE(64, 64) LTN_DECODE(96, 96) LTN_DECODE(256, 256) LTN_DECODE(256, 128) LTN_DECODE(128, 64)
 #undef LTN_DECODE
+#undef LTN_DECODE_T
     return hipErrorInvalidValue;
 }
 

@@ -1,4 +1,4 @@
-"""bf16 passes of inputs large enough for cache hints (non-temporal tile loads, outputs stored past the caches): the
+"""Calls large enough for cache hints (non-temporal loads, outputs and states stored through or past the caches): the
 same bits as the two halves of the batch, which are below the sizes where hints begin."""
 import pytest
 import torch
@@ -70,3 +70,19 @@ def test_backward(D, H, N):
     assert all(torch.equal(a, b) for a, b in zip(ltn.ltn_attn_bwd(*t, decay), want))
     with force_plan(segs=1):
         assert all(torch.equal(a, b) for a, b in zip(ltn.ltn_attn_bwd(*t, decay), want))
+
+
+# states of just the size that is written through, and the halves, which are not
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("Dk,Dv,chains,steps", [(128, 128, 1152, 1), (128, 128, 1152, 3), (256, 256, 96, 2), (64, 64, 1536, 1),
+                                                (96, 96, 1140, 2), (128, 64, 1280, 1), (256, 128, 192, 1)])
+def test_decode(Dk, Dv, chains, steps, dtype):
+    g = torch.Generator(device="cuda").manual_seed(chains)
+    q, k, v = (torch.randn(2, chains // 2, steps, D, generator=g, device="cuda").to(dtype) for D in (Dk, Dk, Dv))
+    kv = torch.randn(2, chains // 2, Dk, Dv, generator=g, device="cuda")
+    decay = mixed_decay(chains // 2).cuda()
+    call = ltn.ltn_attn_decode_steps if Dk == Dv else ltn.ltn_attn_decode_steps_dkdv
+    parts = [kv[i:i + 1].clone() for i in range(2)]
+    want = [call(*(t[i:i + 1].contiguous() for t in (q, k, v)), parts[i], decay) for i in range(2)]
+    o = call(q, k, v, kv, decay)
+    assert torch.equal(o, torch.cat(want)) and torch.equal(kv, torch.cat(parts))
