@@ -10,43 +10,68 @@
 // Streaming kernels, HBM-bound: every lane owns 16 bytes of one row, a row's lanes are
 // neighbours in one wave and reduce with cross-lane shuffles (rows of 96 features take 16 or 32
 // lanes of which 12 or 24 hold data); fp32 arithmetic.
+// ONCE: loads and stores that leave the caches first, from kOnceBytes a tensor on.  us, rotating inputs, without and with: 128
+// features, 2^18 rows forward 38.6 and 34.3, derivative 63.9 and 58.0; 2^20 rows 160 and 144, 278 and 255.  In a mixer
+// step, whose attention reads what the derivative has written: 128 chains x 2048 267.5 and 263.0, 64 x 2048 150 and
+// 144, 128 x 8192 1119 and 1064; smaller tensors stay in the caches in between (16 chains x 1000 38.8 and 40.7).
+#include "ltn_cache.h"
 #include "ltn_kernels.h"
 
 namespace ltn {
 namespace {
 
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(8 * sizeof(float)))) float f32x8;
+
+constexpr long long kOnceBytes = 16 << 20;
+
+template <bool ONCE> __device__ __forceinline__ u32x4 load16(const void* p) {
+    if constexpr (ONCE) return load16_once(p);
+    else return *(const u32x4*)p;
+}
+template <bool ONCE> __device__ __forceinline__ void store16(void* p, u32x4 v) {
+    if constexpr (ONCE) store16_once(p, v);
+    else *(u32x4*)p = v;
+}
 
 template <bool BF16> struct Vec;            // the 16 bytes of one lane as fp32 values
 template <> struct Vec<true> {
     static constexpr int N = 8;
     float v[8];
+    template <bool ONCE>
     __device__ __forceinline__ void load(const void* p) {
         union { u32x4 u; bf16x8 h; } c;
-        c.u = *(const u32x4*)p;
+        c.u = load16<ONCE>(p);
         const f32x8 f = __builtin_convertvector(c.h, f32x8);
 #pragma unroll
         for (int i = 0; i < 8; ++i) v[i] = f[i];
     }
+    template <bool ONCE>
     __device__ __forceinline__ void store(void* p) const {
         f32x8 f;
 #pragma unroll
         for (int i = 0; i < 8; ++i) f[i] = v[i];
         union { u32x4 u; bf16x8 h; } c;
         c.h = __builtin_convertvector(f, bf16x8);
-        *(u32x4*)p = c.u;
+        store16<ONCE>(p, c.u);
     }
 };
 template <> struct Vec<false> {
     static constexpr int N = 4;
     float v[4];
+    template <bool ONCE>
     __device__ __forceinline__ void load(const void* p) {
-        const float4 f = *(const float4*)p;
-        v[0] = f.x; v[1] = f.y; v[2] = f.z; v[3] = f.w;
+        const u32x4 u = load16<ONCE>(p);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = __uint_as_float(u[i]);
     }
-    __device__ __forceinline__ void store(void* p) const { *(float4*)p = make_float4(v[0], v[1], v[2], v[3]); }
+    template <bool ONCE>
+    __device__ __forceinline__ void store(void* p) const {
+        u32x4 u;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) u[i] = __float_as_uint(v[i]);
+        store16<ONCE>(p, u);
+    }
 };
 
 template <int LPR>
@@ -58,7 +83,7 @@ __device__ __forceinline__ float row_sum(float x) {   // sum over the LPR neighb
 
 constexpr int kThreads = 256;
 
-template <int D, bool BF16, bool BWD>
+template <int D, bool BF16, bool BWD, bool ONCE>
 __global__ __launch_bounds__(kThreads)
 void gate_kernel(const char* x, const char* __restrict__ u, const char* __restrict__ dy,
                  char* o0, char* __restrict__ o1, float eps, long long rows) {
@@ -76,8 +101,8 @@ void gate_kernel(const char* x, const char* __restrict__ u, const char* __restri
     for (; r < rows; r += stride) {
         const size_t off = ((size_t)r * ACT + (live ? sub : 0)) * 16;
         V xv, uv;
-        xv.load(x + off);
-        uv.load(u + off);
+        xv.template load<ONCE>(x + off);
+        uv.template load<ONCE>(u + off);
         if (!live) {
 #pragma unroll
             for (int i = 0; i < V::N; ++i) xv.v[i] = 0.f;
@@ -91,10 +116,10 @@ void gate_kernel(const char* x, const char* __restrict__ u, const char* __restri
             V yv;
 #pragma unroll
             for (int i = 0; i < V::N; ++i) yv.v[i] = xv.v[i] * rstd * uv.v[i];
-            if (live) yv.store(o0 + off);
+            if (live) yv.template store<ONCE>(o0 + off);
         } else {
             V gv;
-            gv.load(dy + off);
+            gv.template load<ONCE>(dy + off);
             float dot = 0.f;
 #pragma unroll
             for (int i = 0; i < V::N; ++i) dot = fmaf(gv.v[i] * uv.v[i], xv.v[i], dot);
@@ -110,8 +135,8 @@ void gate_kernel(const char* x, const char* __restrict__ u, const char* __restri
                 dx.v[i] = (gv.v[i] * uv.v[i] - n * mean) * rstd;
             }
             if (live) {
-                dx.store(o0 + off);
-                du.store(o1 + off);
+                dx.template store<ONCE>(o0 + off);
+                du.template store<ONCE>(o1 + off);
             }
         }
     }
@@ -125,8 +150,12 @@ hipError_t launch_gate_t(const void* x, const void* u, const void* dy, void* o0,
     long long wgs = (rows + RPW - 1) / RPW;
     if (wgs > 256 * 16) wgs = 256 * 16;           // grid-stride beyond 16 workgroups per compute unit
     if (wgs <= 0) return hipSuccess;
-    hipLaunchKernelGGL((gate_kernel<D, BF16, BWD>), dim3((unsigned)wgs), dim3(kThreads), 0, stream,
-                       (const char*)x, (const char*)u, (const char*)dy, (char*)o0, (char*)o1, eps, rows);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)wgs), dim3(kThreads), 0, stream,
+                           (const char*)x, (const char*)u, (const char*)dy, (char*)o0, (char*)o1, eps, rows);
+    };
+    if (rows * ACT * 16 >= kOnceBytes) launch(gate_kernel<D, BF16, BWD, true>);
+    else launch(gate_kernel<D, BF16, BWD, false>);
     return hipGetLastError();
 }
 

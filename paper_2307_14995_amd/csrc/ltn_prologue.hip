@@ -21,12 +21,18 @@
 // dtheta is reduced without atomics: every thread sums its few tokens (times the batch) in
 // fp32, the workgroup adds its threads' sums in a fixed order in fp64 through LDS and writes
 // one partial, and a second kernel adds the partials in order -- bitwise reproducible.
+#include "ltn_cache.h"
 #include "ltn_kernels.h"
 
 namespace ltn {
 namespace {
 
 constexpr int kThreads = 256;
+// From so many bytes of x on, loads leave the caches first and outputs are stored past them.  us, rotating inputs, plain and
+// so: expansion of 64 chains x 2048 x 128 24.9 and 22.9, derivative 30.5 and 28.4; of 32 x 30000 148 and 145, 211 and
+// 198.  The first layer's step, whose attention reads the expansions, 64 chains x 2048 (with the batch entries below)
+// 310 and 295; tensors that stay in the caches in between lose (16 x 1000 114 and 128).
+constexpr long long kOnceBytes = 16 << 20;
 constexpr int kTok = 64;                 // tokens per workgroup
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
@@ -39,44 +45,55 @@ __device__ __forceinline__ float sigmoid(float x) {
 }
 
 // E consecutive features of one token, 16 bytes in either dtype.
-template <bool BF16>
+template <bool BF16, bool ONCE>
 struct Vec {
     static constexpr int E = BF16 ? 8 : 4;
     float v[E];
-    __device__ __forceinline__ void load(const void* base, size_t elem) {
-        if constexpr (BF16) {
-            const uint4 w = *(const uint4*)((const unsigned short*)base + elem);
-            const unsigned int u[4] = {w.x, w.y, w.z, w.w};
+    static __device__ __forceinline__ u32x4 load(const void* base, size_t elem) {
+        const char* p = (const char*)base + elem * (16 / E);
+        if constexpr (ONCE) return load16_once(p);
+        else return *(const u32x4*)p;
+    }
+    __device__ __forceinline__ void set(u32x4 u) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < 4; ++i) {
+            if constexpr (BF16) {
                 v[2 * i] = __uint_as_float(u[i] << 16);
                 v[2 * i + 1] = __uint_as_float(u[i] & 0xffff0000u);
+            } else {
+                v[i] = __uint_as_float(u[i]);
             }
-        } else {
-            const float4 w = *(const float4*)((const float*)base + elem);
-            v[0] = w.x; v[1] = w.y; v[2] = w.z; v[3] = w.w;
         }
     }
     __device__ __forceinline__ void store(void* base, size_t elem) const {
+        u32x4 u;
         if constexpr (BF16) {
             f32x8 f;
 #pragma unroll
             for (int i = 0; i < 8; ++i) f[i] = v[i];
-            union { bf16x8 h; uint4 w; } cv;
+            union { bf16x8 h; u32x4 w; } cv;
             cv.h = __builtin_convertvector(f, bf16x8);       // round to nearest even
-            *(uint4*)((unsigned short*)base + elem) = cv.w;
+            u = cv.w;
         } else {
-            *(float4*)((float*)base + elem) = make_float4(v[0], v[1], v[2], v[3]);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) u[i] = __float_as_uint(v[i]);
         }
+        char* p = (char*)base + elem * (16 / E);
+        if constexpr (ONCE) store16_past(p, u);
+        else *(u32x4*)p = u;
     }
 };
 
-template <int D, bool BF16, bool BWD>
+// AHEAD: batch entries whose loads are issued together (a thread's other tokens come one after another, as their angles do
+// not overlap with loads).  us, AHEAD 1 / 2 / 4: expansion 16 x 8 x 1000 x 64 28.6 / 25.5 / 19.6, derivative 33.6 / 30.2 / 28.2;
+// 4 x 16 x 2048 x 128 22.9 / 21.2 / 22.2 and 28.4 / 29.4 / 29.8; one batch entry, where it only takes registers, 1 x 32 x 30000
+// 145 / 148 / 167 and 198 / 198 / 227.
+template <int D, bool BF16, bool BWD, bool ONCE, int AHEAD>
 __global__ __launch_bounds__(kThreads)
 void prologue_kernel(const void* __restrict__ x, const float* __restrict__ theta, const void* __restrict__ dy,
                      void* __restrict__ out, double* __restrict__ partials, int act, int Bt, int H,
                      long long N, long long pos0, int nchunks) {
-    using V = Vec<BF16>;
+    using V = Vec<BF16, ONCE>;
     constexpr int E = V::E;
     constexpr int TX = D / E;                 // threads across one token's features
     constexpr int TY = kThreads / TX;         // tokens in flight
@@ -114,39 +131,55 @@ void prologue_kernel(const void* __restrict__ x, const float* __restrict__ theta
                 sn[e] = 0.0f;
             }
         }
-        for (int b = 0; b < Bt; ++b) {
-            const size_t row = ((size_t)b * H + h) * (size_t)N + (size_t)t;
-            V xv;
-            xv.load(x, row * D + d0);
-            float z[E], dphi[E];
+        auto row_of = [&](int b) { return ((size_t)b * H + h) * (size_t)N + (size_t)t; };
+        for (int b0 = 0; b0 < Bt; b0 += AHEAD) {
+            u32x4 xs[AHEAD], gcs[BWD ? AHEAD : 1], gss[BWD ? AHEAD : 1];
 #pragma unroll
-            for (int e = 0; e < E; ++e) {
-                const float s = sigmoid(xv.v[e]);
-                z[e] = act ? xv.v[e] * s : xv.v[e];
-                dphi[e] = act ? s * (1.0f + xv.v[e] * (1.0f - s)) : 1.0f;
-            }
-            if constexpr (!BWD) {
-                V yc;
-#pragma unroll
-                for (int e = 0; e < E; ++e) yc.v[e] = z[e] * cs[e];
-                yc.store(out, row * W + d0);
-                if (lrpe) {
-                    V ys;
-#pragma unroll
-                    for (int e = 0; e < E; ++e) ys.v[e] = z[e] * sn[e];
-                    ys.store(out, row * W + D + d0);
+            for (int i = 0; i < AHEAD; ++i) {
+                if (b0 + i >= Bt) break;
+                const size_t row = row_of(b0 + i);
+                xs[i] = V::load(x, row * D + d0);
+                if constexpr (BWD) {
+                    gcs[i] = V::load(dy, row * W + d0);
+                    if (lrpe) gss[i] = V::load(dy, row * W + D + d0);
                 }
-            } else {
-                V gc, gs, dx;
-                gc.load(dy, row * W + d0);
-                if (lrpe) gs.load(dy, row * W + D + d0);
+            }
+#pragma unroll
+            for (int i = 0; i < AHEAD; ++i) {
+                if (b0 + i >= Bt) break;
+                const size_t row = row_of(b0 + i);
+                V xv;
+                xv.set(xs[i]);
+                float z[E], dphi[E];
 #pragma unroll
                 for (int e = 0; e < E; ++e) {
-                    const float g_s = lrpe ? gs.v[e] : 0.0f;
-                    dx.v[e] = (gc.v[e] * cs[e] + g_s * sn[e]) * dphi[e];
-                    acc[e] = fmaf(pf, z[e] * (g_s * cs[e] - gc.v[e] * sn[e]), acc[e]);
+                    const float s = sigmoid(xv.v[e]);
+                    z[e] = act ? xv.v[e] * s : xv.v[e];
+                    dphi[e] = act ? s * (1.0f + xv.v[e] * (1.0f - s)) : 1.0f;
                 }
-                dx.store(out, row * D + d0);
+                if constexpr (!BWD) {
+                    V yc;
+#pragma unroll
+                    for (int e = 0; e < E; ++e) yc.v[e] = z[e] * cs[e];
+                    yc.store(out, row * W + d0);
+                    if (lrpe) {
+                        V ys;
+#pragma unroll
+                        for (int e = 0; e < E; ++e) ys.v[e] = z[e] * sn[e];
+                        ys.store(out, row * W + D + d0);
+                    }
+                } else {
+                    V gc, gs, dx;
+                    gc.set(gcs[i]);
+                    if (lrpe) gs.set(gss[i]);
+#pragma unroll
+                    for (int e = 0; e < E; ++e) {
+                        const float g_s = lrpe ? gs.v[e] : 0.0f;
+                        dx.v[e] = (gc.v[e] * cs[e] + g_s * sn[e]) * dphi[e];
+                        acc[e] = fmaf(pf, z[e] * (g_s * cs[e] - gc.v[e] * sn[e]), acc[e]);
+                    }
+                    dx.store(out, row * D + d0);
+                }
             }
         }
     }
@@ -189,8 +222,14 @@ void prologue_reduce_kernel(const double* __restrict__ partials, float* __restri
 template <int D, bool BF16, bool BWD>
 hipError_t launch_t(const void* x, const float* theta, const void* dy, void* out, double* partials, int act,
                     int Bt, int H, long long N, long long pos0, int nchunks, hipStream_t stream) {
-    hipLaunchKernelGGL((prologue_kernel<D, BF16, BWD>), dim3((unsigned)(nchunks * H)), dim3(kThreads), 0, stream,
-                       x, theta, dy, out, partials, act, Bt, H, N, pos0, nchunks);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(nchunks * H)), dim3(kThreads), 0, stream,
+                           x, theta, dy, out, partials, act, Bt, H, N, pos0, nchunks);
+    };
+    const bool once = (long long)Bt * H * N * D * (BF16 ? 2 : 4) >= kOnceBytes;
+    if (Bt >= 8) once ? launch(prologue_kernel<D, BF16, BWD, true, 4>) : launch(prologue_kernel<D, BF16, BWD, false, 4>);
+    else if (Bt >= 4 && !BWD) once ? launch(prologue_kernel<D, BF16, BWD, true, BWD ? 1 : 2>) : launch(prologue_kernel<D, BF16, BWD, false, BWD ? 1 : 2>);
+    else once ? launch(prologue_kernel<D, BF16, BWD, true, 1>) : launch(prologue_kernel<D, BF16, BWD, false, 1>);
     return hipGetLastError();
 }
 

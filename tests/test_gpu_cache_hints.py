@@ -86,3 +86,36 @@ def test_decode(Dk, Dv, chains, steps, dtype):
     want = [call(*(t[i:i + 1].contiguous() for t in (q, k, v)), parts[i], decay) for i in range(2)]
     o = call(q, k, v, kv, decay)
     assert torch.equal(o, torch.cat(want)) and torch.equal(kv, torch.cat(parts))
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("D,rows", [(128, 65536), (96, 87400), (64, 131072), (256, 32768)])
+def test_gate(D, rows, dtype):
+    g = torch.Generator(device="cuda").manual_seed(D)
+    if dtype == torch.float32:
+        rows //= 2
+    x, u, dy = (torch.randn(1, 2, rows // 2, D, generator=g, device="cuda").to(dtype) for _ in range(3))
+    got = [ltn.ltn_gate_fwd(x, u, eps=1e-6), *ltn.ltn_gate_bwd(x, u, dy, eps=1e-6)]
+    parts = [[t[:, i:i + 1].contiguous() for t in (x, u, dy)] for i in range(2)]
+    want = [[ltn.ltn_gate_fwd(p[0], p[1], eps=1e-6), *ltn.ltn_gate_bwd(*p, eps=1e-6)] for p in parts]
+    for a, *b in zip(got, *want):
+        assert torch.equal(a, torch.cat(b, 1))
+
+
+# batch entries whose loads are issued one, two and four at a time, with remainders, below and above the line for hints
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("D,Bt,H,N", [(128, 2, 16, 2049), (128, 6, 4, 2801), (128, 18, 2, 2000), (64, 18, 8, 1000),
+                                      (64, 10, 3, 70), (64, 5, 3, 70), (128, 1, 3, 65)])
+def test_input_side(D, Bt, H, N, dtype):
+    g = torch.Generator(device="cuda").manual_seed(N)
+    x = torch.randn(Bt, H, N, D, generator=g, device="cuda").to(dtype)
+    dy = torch.randn(Bt, H, N, 2 * D, generator=g, device="cuda").to(dtype)
+    theta = torch.rand(H, D, generator=g, device="cuda")
+    y = ltn.ltn_prologue_fwd(x, theta, pos0=5)
+    dx, dth = ltn.ltn_prologue_bwd(x, dy, theta, pos0=5)
+    one = [(ltn.ltn_prologue_fwd(x[b:b + 1].contiguous(), theta, pos0=5),
+            *ltn.ltn_prologue_bwd(x[b:b + 1].contiguous(), dy[b:b + 1].contiguous(), theta, pos0=5)) for b in range(Bt)]
+    assert torch.equal(y, torch.cat([o[0] for o in one])) and torch.equal(dx, torch.cat([o[1] for o in one]))
+    # sums over the batch in another order: at most Bt kTok / TY = 288 fp32 terms a thread
+    ref = torch.stack([o[2] for o in one]).double().sum(0)
+    assert (dth.double() - ref).norm() <= 288 * 2.0 ** -24 * torch.stack([o[2] for o in one]).double().abs().sum(0).norm()
