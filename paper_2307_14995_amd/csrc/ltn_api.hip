@@ -470,7 +470,8 @@ Cut pick_cut(int chains, int count, long long N, int D, int DC, int dv, int wide
 //     32 x 8192 103 and 92, 64 x 3000 79 and 76; 16 x 8192, 134 MiB, 51.5 and 52.2
 //   backward, whole chains of full width, each pass's A once and outputs past the caches, which keep what dQ's pass
 //     reads again: 128 features 128 x 2048 / 4096 / 8192 tokens 132.5 and 130.4, 256 and 240, 507 and 480, 60 x 6000 193
-//     and 186, 1024 x 500 259 and 246; 64 features 320 x 2048 155 and 149; 96 features 200 x 3000 225 and 219.  Inputs
+//     and 186, 1024 x 500 259 and 246; 64 features 320 x 2048 155 and 149; 96 features 200 x 3000 225 and 219; segments
+//     8 x 65536 379 and 359, 20 x 16301 237 and 225, 16 x 60000 x 64 329 and 297 (x 96 the same).  Inputs
 //     that the memory-side cache holds lose (64 x 1000 34.0 and 36.6, 128 x 1000 65.4 and 69.2), 96 x 2048, 201 MB,
 //     neither; 64-column slices lose (32 x 16301 322 and 334; 320 outputs past the caches alone)
 // 256 features: nothing within 1 %.
@@ -481,7 +482,7 @@ void set_hints(ltn::PassBatch& pb, int D, int DC, int dv, bool segmented) {
     pb.hints = 0;
     if (D == 256 || DC == 256) return;
     if (pb.count == 3) {
-        if (full && !segmented && 8LL * D * tokens >= 240 * kMiB) pb.hints = ltn::kOnceA | ltn::kPast;
+        if (full && (!segmented || D != 96) && 8LL * D * tokens >= 240 * kMiB) pb.hints = ltn::kOnceA | ltn::kPast;
         return;
     }
     if (pb.count != 1 || pb.p[0].rev) return;
