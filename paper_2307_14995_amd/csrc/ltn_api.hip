@@ -113,7 +113,10 @@ F32Plan pick_f32(long long chains, int count, long long N, int D, int DC, int bl
     auto consider = [&](int dv, int segs, long long len) {
         const long long pieces = chains * count * segs, wgs = pieces * (DC / dv), blocks = ((segs > 1 ? len : N) + blk - 1) / blk;
         double t = (double)((wgs + 255) / 256) * blocks * slice_cost(dv);
-        if (segs > 1) t += (double)((pieces * (DC / full) + 255) / 256) * blocks * sweep_cost + 2 * kF32Launch;
+        // A backward's dK is not swept where that saves a round.  (Not counted so for other widths, where the plans it leads to
+        // are slower: 20 x 2048 x 64 56 and 64 us, 12 x 1999 x 96 78 and 82, 16 x 2048 x 256 332 and 354.)
+        const long long swept = count == 3 && D == 128 ? pieces / 3 * 2 : pieces;
+        if (segs > 1) t += (double)((swept * (DC / full) + 255) / 256) * blocks * sweep_cost + 2 * kF32Launch;
         if (segs > 1 && gated) t += kF32State * D * DC * pieces;
         if (!best.dv || t < best.t) best = F32Plan{dv, segs, len, t};
     };
@@ -153,6 +156,17 @@ F32Plan pick_f32(long long chains, int count, long long N, int D, int DC, int bl
     return best;
 }
 
+// The passes of `pb` that a state-only sweep is run for: all, or of a backward's three dV's and dQ's, since dK's
+// states are dV's transposed (launch_segment_scan_pair).  In fp32, where a sweep is bound by its products (us a backward,
+// three sweeps and two: 32 chains x 2048 tokens of 128 features 222 and 198, 32 x 2000 of 64 84.8 and 77.3, 16 x 2048 of 96
+// 92.4 and 84.5), and for 256 features in bf16 (4 x 8192 121 and 116).  The other bf16 sweeps of dV and dK share their loads, and
+// take no longer for being two (4 x 32768 of 128 106.0 and 106.9, 2 x 4000 22.4 and 23.2, 4 x 8192 of 96 42.6 and 44.0).
+int swept_passes(const ltn::PassBatch& pb, bool pay_for_products, int (&pass)[3]) {
+    const bool pair = pb.count == 3 && pb.pairs_first && pay_for_products;
+    for (int i = 0; i < 3; ++i) pass[i] = pair ? 2 * i : i;
+    return pair ? 2 : pb.count;
+}
+
 // One launch of fp32 passes of one shape, cut into segments (state-only sweep, scan, per-segment
 // pass) when the plan says so; the segments' states live in the output's rows.
 ltn_status run_f32(ltn::PassBatch& pb, int D, int DC, int blk, hipStream_t stream, bool gated = false) {
@@ -167,12 +181,24 @@ ltn_status run_f32(ltn::PassBatch& pb, int D, int DC, int blk, hipStream_t strea
         ltn::PassBatch sweep = pb;
         sweep.state_only = 1;
         sweep.need_last = kv_out != nullptr;
-        for (int i = 0; i < pb.count; ++i) {
+        int pass[3];
+        // (a third sweep that its units would be idle for costs nothing: 2 chains x 1952 x 64 28.1 with three, 29.0)
+        const long long swept = (long long)pb.chains * pb.segs * (DC == 256 ? 2 : 1);
+        sweep.count = swept_passes(pb, (3 * swept + 255) / 256 > (2 * swept + 255) / 256, pass);
+        for (int i = 0; i < sweep.count; ++i) {
+            sweep.p[i] = pb.p[pass[i]];
             sweep.p[i].gate = nullptr;
             sweep.p[i].state_in = nullptr;
         }
         if (ltn::launch_pass_f32(sweep, D, DC == 256 ? 128 : DC, blk, stream, DC) != hipSuccess) return LTN_ERR_LAUNCH;
-        if (ltn::launch_segment_scan_rows(pb, pb.p[0].state_in, kv_out, D, stream, DC) != hipSuccess) return LTN_ERR_LAUNCH;
+        if (sweep.count != pb.count) {
+            const ltn::ScanStates s = {{pb.p[0].seg_rows, pb.p[1].seg_rows, pb.p[2].seg_rows}, (size_t)pb.N * D,
+                                       {pb.p[0].rev, pb.p[1].rev, pb.p[2].rev}, 1};
+            if (ltn::launch_segment_scan_pair(s, pb.decay, pb.chains, pb.H, pb.segs, pb.seg_len, pb.N, D, stream) != hipSuccess)
+                return LTN_ERR_LAUNCH;
+        } else if (ltn::launch_segment_scan_rows(pb, pb.p[0].state_in, kv_out, D, stream, DC) != hipSuccess) {
+            return LTN_ERR_LAUNCH;
+        }
         pb.p[0].state_out = nullptr;
     }
     return ltn::launch_pass_f32(pb, D, plan.dv, blk, stream, DC) == hipSuccess ? LTN_OK : LTN_ERR_LAUNCH;
@@ -532,22 +558,30 @@ ltn_status run_passes(ltn::PassBatch& pb, int D, int blk, ltn_dtype dtype, void*
     sweep.seg_len = plan.seg_len;
     sweep.state_only = 1;
     sweep.need_last = kv_out != nullptr;
-    for (int i = 0; i < pb.count; ++i) {
+    int pass[3];
+    sweep.count = swept_passes(pb, D == 256, pass);
+    for (int i = 0; i < sweep.count; ++i) {
+        sweep.p[i] = pb.p[pass[i]];
         sweep.p[i].out = nullptr;
         sweep.p[i].gate = nullptr;
         sweep.p[i].gated_out = nullptr;
         sweep.p[i].state_in = nullptr;
-        sweep.p[i].state_out = states + i * per_pass;
+        sweep.p[i].state_out = states + pass[i] * per_pass;
     }
     // one full-width workgroup per segment; narrower slices while those fit one round of compute
     // units (128 features, full width, 64 and 32 columns: forward of 2 chains x 8192 tokens 24.9, 22.4
     // and 21.9 us, 8 x 8000 32.5 and 29.7; 64 features, 64 and 32 columns: 17.7 and 17.1; same values)
     int sweep_dv = D == 256 ? 64 : D == 96 ? 32 : D;
-    while ((D == 64 || D == 128) && sweep_dv > 32 && chain_passes * plan.segs * (2 * D / sweep_dv) <= 256) sweep_dv /= 2;
+    while ((D == 64 || D == 128) && sweep_dv > 32 && (long long)pb.chains * sweep.count * plan.segs * (2 * D / sweep_dv) <= 256) sweep_dv /= 2;
     if (ltn::launch_pass_bf16(sweep, D, sweep_dv, stream) != hipSuccess) return LTN_ERR_LAUNCH;
-    if (ltn::launch_segment_scan(states, kv_in, kv_out, pb.decay, pb.count, pb.chains, pb.H, plan.segs,
-                                 plan.seg_len, pb.N, D, stream) != hipSuccess)
+    if (sweep.count != pb.count) {
+        const ltn::ScanStates s = {{states, states + per_pass, states + 2 * per_pass}, (size_t)plan.segs * D * D, {0, 0, 0}, 0};
+        if (ltn::launch_segment_scan_pair(s, pb.decay, pb.chains, pb.H, plan.segs, plan.seg_len, pb.N, D, stream) != hipSuccess)
+            return LTN_ERR_LAUNCH;
+    } else if (ltn::launch_segment_scan(states, kv_in, kv_out, pb.decay, pb.count, pb.chains, pb.H, plan.segs,
+                                        plan.seg_len, pb.N, D, stream) != hipSuccess) {
         return LTN_ERR_LAUNCH;
+    }
     ltn::PassBatch main = pb;
     main.segs = plan.segs;
     main.seg_len = plan.seg_len;

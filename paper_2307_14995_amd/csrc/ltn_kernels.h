@@ -160,6 +160,12 @@ hipError_t launch_segment_scan_rows(const PassBatch& pb, const float* kv_in, flo
 hipError_t launch_segment_scan(float* states, const float* kv_in, float* kv_out, const float* decay,
                                int count, int chains, int H, int segs, long long seg_len, long long N,
                                int D, hipStream_t stream, int DC = 0 /* 0: = D; states are [D x DC] */);
+// The same for the three passes of a backward of D features, of which dV's and dQ's (p[0], p[2]) have been swept; dK's
+// states (p[1]) are dV's transposed.  A chain's states of pass i begin at p[i] + chain * chain_stride, segment after
+// segment, or, with `rows`, in the first D rows of the segments of a [N, D] buffer (as in PassArgs::seg_rows).
+struct ScanStates { float* p[3]; size_t chain_stride; int rev[3]; int rows; };
+hipError_t launch_segment_scan_pair(const ScanStates& s, const float* decay, int chains, int H, int segs, long long seg_len,
+                                    long long N, int D, hipStream_t stream);
 // kv[c] (or zeros if null) -> kv_out[c], n floats.
 hipError_t launch_state_copy(const float* kv_in, float* kv_out, size_t n, hipStream_t stream);
 // `steps` consecutive decode steps per chain (q, k: [chains, steps, DK]; v, o: [chains,

@@ -70,7 +70,80 @@ void segment_scan_kernel(float* states, const float* __restrict__ kv_in, float* 
     if (final_state) *(f32x4*)(kv_out + (size_t)chain * DD + e) = run;
 }
 
+// The scan of a backward's three passes from the end states of two: dV = pass(K, Q, dO) and dK = pass(V, dO, Q) walk the
+// tokens together, and their states, sums of q_t^T dO_t and of dO_t^T q_t, are each other's transposes.  So no
+// sweep is run for dK; its states are written here.  A workgroup has a tile of kTile x kTile elements of a (dV and dK, or
+// dQ) state of one chain and walks the segments; dK's tile is turned round in LDS.
+constexpr int kTile = 32;
+
+__global__ __launch_bounds__(kTile * kTile / 4)
+void segment_scan_pair_kernel(const ScanStates s, const float* __restrict__ decay, int chains, int H, int segs, int seg_len,
+                              long long N, int D) {
+    constexpr int PITCH = kTile + 4;       // whole 16-byte pieces
+    __shared__ __attribute__((aligned(16))) float tile[2][kTile * PITCH];
+    const int per = (D / kTile) * (D / kTile);
+    const int uc = blockIdx.x / per, t = blockIdx.x % per;
+    const int unit = uc / chains, chain = uc % chains;         // 0: dV and dK, 1: dQ
+    const int row0 = t / (D / kTile) * kTile, col0 = t % (D / kTile) * kTile;
+    const int r = threadIdx.x / (kTile / 4), c = threadIdx.x % (kTile / 4) * 4;
+    const int pass = unit ? 2 : 0;
+    auto seg_off = [&](int g) -> size_t {
+        if (!s.rows) return (size_t)g * D * D;
+        const long long start = (long long)g * seg_len, n = g + 1 == segs ? N - start : seg_len;
+        return (size_t)(s.rev[pass] ? N - start - n : start) * D;
+    };
+    float* const own = s.p[pass] + (size_t)chain * s.chain_stride + (size_t)(row0 + r) * D + col0 + c;
+    float* const turned = s.p[1] + (size_t)chain * s.chain_stride + (size_t)(col0 + r) * D + row0 + c;
+    f32x4 run = {0.f, 0.f, 0.f, 0.f};
+    float lam_full = 0.f;
+    bool flushed = false;
+    for (int g0 = 0; g0 < segs; g0 += kAhead) {
+        f32x4 local[kAhead];
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i)
+            local[i] = g0 + i + 1 < segs ? *(const f32x4*)(own + seg_off(g0 + i)) : f32x4{0.f, 0.f, 0.f, 0.f};
+        if (g0 == 0) {
+            const float lam = decay[chain % H];
+            lam_full = decay_pow(lam, seg_len);
+            flushed = lam > 0.f && lam_full == 0.f;
+        }
+        auto walk = [&](auto keep_inf) {                       // (as above)
+#pragma unroll
+            for (int i = 0; i < kAhead; ++i) {
+                const int g = g0 + i;
+                if (g >= segs) break;
+                *(f32x4*)(own + seg_off(g)) = run;
+                if (unit == 0) {
+                    // two tiles in turn: the barrier of the next segment separates these reads from the writes after it
+                    float* const lds = tile[i & 1];
+                    *(f32x4*)(lds + r * PITCH + c) = run;
+                    __syncthreads();
+                    f32x4 x;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) x[j] = lds[(c + j) * PITCH + r];
+                    *(f32x4*)(turned + seg_off(g)) = x;
+                }
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    run[j] = fmaf(decltype(keep_inf)::value && __builtin_isinf(run[j]) ? 1.f : lam_full, run[j], local[i][j]);
+            }
+        };
+        if (flushed) walk(std::true_type{});
+        else walk(std::false_type{});
+    }
+}
+
 }  // namespace
+
+hipError_t launch_segment_scan_pair(const ScanStates& s, const float* decay, int chains, int H, int segs, long long seg_len,
+                                    long long N, int D, hipStream_t stream) {
+    if (chains < 1 || segs < 1 || seg_len <= 0 || seg_len > 0x7fffffffLL || D % kTile != 0) return hipErrorInvalidValue;
+    const long long wgs = 2LL * chains * (D / kTile) * (D / kTile);
+    if (wgs > 0x7fffffffLL) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(segment_scan_pair_kernel, dim3((unsigned)wgs), dim3(kTile * kTile / 4), 0, stream, s, decay, chains, H,
+                       segs, (int)seg_len, N, D);
+    return hipGetLastError();
+}
 
 hipError_t launch_segment_scan(float* states, const float* kv_in, float* kv_out, const float* decay,
                                int count, int chains, int H, int segs, long long seg_len, long long N,
