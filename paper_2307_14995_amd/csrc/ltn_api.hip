@@ -480,44 +480,35 @@ Cut pick_cut(int chains, int count, long long N, int D, int DC, int dv, int wide
 
 // Cache hints of a launch of `pb` in slices of dv value columns.  Launches of these sizes are bound by memory (with
 // every product taken out of the kernels they take 0 .. 6 % less), and what they read once goes through an L2 of 4 MiB
-// an XCD and a memory-side cache of 256 MiB on its way, where it takes the place of tiles that another slice, the
-// other pass of a pair or the segments' sweep has brought in and that are about to be read again.
-// Measured without and with, us, rotating inputs:
-//   forward, whole chains of full width, all operands once: 128 features 256 chains x 500 / 1500 / 4096 tokens 27.6 and
-//     27.2, 81 and 71.5, 207 and 180; 64 features 512 x 1000 50.3 and 48.8, 1024 x 1000 103 and 93; 96 features 320 x
-//     2000 111 and 103; (128, 64) 200 x 4000 128 and 121; gated 256 x 500 38.9 and 34.8, 512 x 1000 139 and 131.  Below 64
-//     MiB nothing or a loss (200 x 200 12.1 and 12.5), and rows of 192 bytes, whose lines two loads share, need a full
-//     chip (160 x 1999 x 96 57.4 and 57.9, 96 x 1999 51.3 and 52.1, 200 x 1000 34.4 and 34.2)
-//   forward in two column slices, C and the last slice's A and B once: 128 x 8192 x 128 212 and 206, 128 x 4000 x 64 57.2
-//     and 54.2; all operands once in both 235, as the slice that comes second then misses; four slices lose
-//     (64 x 2048 37.9 and 38.4)
-//   segments, the pass after the sweep, all once and outputs past the caches, so that K and V of the sweep stay:
-//     32 x 16301 176 and 140 (156 without the latter), 8 x 65536 179 and 154; gated (through the caches: the same)
-//     32 x 8192 103 and 92, 64 x 3000 79 and 76; 16 x 8192, 134 MiB, 51.5 and 52.2
-//   backward, whole chains of full width, each pass's A once and outputs past the caches, which keep what dQ's pass
-//     reads again: 128 features 128 x 2048 / 4096 / 8192 tokens 132.5 and 130.4, 256 and 240, 507 and 480, 60 x 6000 193
-//     and 186, 1024 x 500 259 and 246; 64 features 320 x 2048 155 and 149; 96 features 200 x 3000 225 and 219; segments
-//     8 x 65536 379 and 359, 20 x 16301 237 and 225, 16 x 60000 x 64 329 and 297 (x 96 the same).  Inputs
-//     that the memory-side cache holds lose (64 x 1000 34.0 and 36.6, 128 x 1000 65.4 and 69.2), 96 x 2048, 201 MB,
-//     neither; 64-column slices lose (32 x 16301 322 and 334; 320 outputs past the caches alone)
-// 256 features: nothing within 1 %.
+// an XCD and a memory-side cache of 256 MiB on its way, where it takes the place of what another pass is about to read
+// again.  Measured without and with, us, rotating inputs:
+//   backward, full width, each pass's A once and outputs past the caches, which keep what dQ's pass reads again; after its
+//     forward: 128 features 128 chains x 2048 / 8192 tokens 184.5 and 172.7, 713 and 688, 200 x 3000 414 and 402, 16 x
+//     16384 (segments) 265 and 257; 96 features 544 x 928 299 and 282; 64 features 320 x 2048 227 and 216, 128 x 6000 269
+//     and 256, but 180 x 2829 (249 MiB) 187 and 193.  Inputs that the memory-side cache holds lose (alone: 64 x 1000
+//     34.0 and 36.6, 128 x 1000 65.4 and 69.2), and so do 64-column slices (32 x 16301 322 and 334)
+//   forward in segments, all once in the pass after the sweep and outputs past the caches, so that K and V of the sweep
+//     stay: 32 x 16301 and its backward 501 and 475; alone 176 and 140, 8 x 65536 179 and 154; 16 x 16384 and its
+//     backward, 256 MiB, lose (265 and 273)
+//   gated forward without o (inference), all once, outputs through the caches: 128 features 256 x 500 38.9 and 34.8, 512 x
+//     1000 139 and 131, segments 32 x 8192 103 and 92, 64 x 3000 79 and 76; 64 features 320 x 2048 92 and 87; 96
+//     features 320 x 2000 139 and 129, but rows of 192 bytes, whose lines two loads share, need a full chip (128 x 1999
+//     63.8 and 65.3).  Below 64 MiB (192 in segments) nothing
+// The plain forward of whole chains gains alone (all once: 256 x 4096 207 and 180) and loses with the backward that finds
+// less of Q, K and V in the memory-side cache (fwd and bwd 320 x 2048 x 64 216 and 227, 200 x 3000 402 and 414, 256 x 1000
+// 168 and 172; 256 x 4096 684 and 672).  256 features: nothing within 1 %.
 void set_hints(ltn::PassBatch& pb, int D, int DC, int dv, bool segmented) {
     constexpr long long kMiB = 1 << 20;
     const long long tokens = pb.chains * pb.N;
-    const bool gated = pb.p[0].gate != nullptr, full = dv == DC;
     pb.hints = 0;
-    if (D == 256 || DC == 256) return;
+    if (D == 256 || D != DC || dv != D) return;
     if (pb.count == 3) {
-        if (full && (!segmented || D != 96) && 8LL * D * tokens >= 240 * kMiB) pb.hints = ltn::kOnceA | ltn::kPast;
-        return;
-    }
-    if (pb.count != 1 || pb.p[0].rev) return;
-    const long long bytes = (4LL * D + 2LL * DC * (gated ? 3 : 2)) * tokens;
-    if (segmented) {
-        if (full && D == DC && D != 96 && bytes >= 192 * kMiB) pb.hints = ltn::kOnce | (D == 128 && !gated ? ltn::kPast : 0);
-    } else if (bytes >= 64 * kMiB) {
-        if (full) pb.hints = D == 96 && pb.chains < 192 ? 0 : ltn::kOnce;
-        else if (DC == 2 * dv) pb.hints = ltn::kSliceOnce;
+        if ((!segmented || D != 96) && 8LL * D * tokens >= (D == 64 ? 288 : 240) * kMiB) pb.hints = ltn::kOnceA | ltn::kPast;
+    } else if (pb.p[0].gate) {
+        const bool fills = D != 96 || (!segmented && pb.chains >= 192);
+        if (!pb.p[0].out && fills && 10LL * D * tokens >= (segmented ? 192 : 64) * kMiB) pb.hints = ltn::kOnce;
+    } else if (segmented && D == 128 && 8LL * D * tokens >= 400 * kMiB) {
+        pb.hints = ltn::kOnce | ltn::kPast;
     }
 }
 

@@ -35,10 +35,10 @@ struct PassArgs {
 };
 
 // Cache hints of a bf16 launch; results do not depend on them.  kOnce*: an operand's tiles are loaded
-// non-temporally, so that they leave the caches first.  kLastSliceOnce: A and B by the last of a chain's
-// column slices only.  kPast: outputs are stored past the caches, which then keep what will be read again.
-enum { kOnceA = 1, kOnceB = 2, kOnceC = 4, kPast = 8, kLastSliceOnce = 16 };
-constexpr int kOnce = kOnceA | kOnceB | kOnceC, kSliceOnce = kOnceC | kLastSliceOnce;
+// non-temporally, so that they leave the caches first.  kPast: outputs are stored past the caches, which then
+// keep what will be read again.
+enum { kOnceA = 1, kOnceB = 2, kOnceC = 4, kPast = 8 };
+constexpr int kOnce = kOnceA | kOnceB | kOnceC;
 
 struct PassBatch {
     PassArgs p[3];

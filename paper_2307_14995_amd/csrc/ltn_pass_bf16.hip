@@ -445,7 +445,6 @@ struct Chain {            // what every wave of the workgroup knows about its pr
     int last_valid;       // tokens in the last block (1..64)
     int rev;
     float lam;
-    int last_slice;          // this is the last of the chain's column slices
     int part;                // kCut: 0 the whole chain, 1 its first part, 2 its second part
     char* handover;          // parts 1, 2: the slice's columns of the second part's lowest output row
 };
@@ -562,19 +561,8 @@ __device__ __forceinline__ void pass_output_wave(const Chain& ch, char* smem, un
             const char* pb = pb0 + (long long)b * astep;
             const char* pc = pc0 + (long long)b * step;
             if (valid == kBlock) {
-                if constexpr (HINTS & kLastSliceOnce) {
-                    static_assert(!NOA, "no slices share less");
-                    if (ch.last_slice) {
-                        dab.template issue_full<C::FW, W, true>(pa, AROW, ch.rev, lds);
-                        dab.template issue_full<C::FW, W, true>(pb, AROW, ch.rev, lds + C::BOFF);
-                    } else {
-                        dab.template issue_full<C::FW, W>(pa, AROW, ch.rev, lds);
-                        dab.template issue_full<C::FW, W>(pb, AROW, ch.rev, lds + C::BOFF);
-                    }
-                } else {
-                    if constexpr (!NOA) dab.template issue_full<C::FW, W, (HINTS & kOnceA) != 0>(pa, AROW, ch.rev, lds);
-                    dab.template issue_full<C::FW, W, (HINTS & kOnceB) != 0>(pb, AROW, ch.rev, lds + C::BOFF);
-                }
+                if constexpr (!NOA) dab.template issue_full<C::FW, W, (HINTS & kOnceA) != 0>(pa, AROW, ch.rev, lds);
+                dab.template issue_full<C::FW, W, (HINTS & kOnceB) != 0>(pb, AROW, ch.rev, lds + C::BOFF);
                 dcc.template issue_full<C::FW, W, (HINTS & kOnceC) != 0>(pc, ROW, ch.rev, lds + C::COFF);
             } else {
                 if constexpr (!NOA) dab.template issue_partial<C::FW, W>(pa, AROW, ch.rev, lds, valid, lane);
@@ -1022,7 +1010,6 @@ __device__ __forceinline__ void pass_body(const PassBatch& pb, int xcd_ids, int 
     ch.last_valid = (int)(n - (long long)(ch.T - 1) * kBlock);
     ch.rev = rev;
     ch.lam = lam;
-    if constexpr (HINTS & kLastSliceOnce) ch.last_slice = split == NS - 1;
 
     if constexpr (DR != D || Cfg<D, DV>::CW != DV) {
         // Tiles wider than the tensors' rows: their loads leave the surplus chunks alone, which
@@ -1161,23 +1148,23 @@ hipError_t launch_pass_cut_bf16(PassBatch& pb, int D, hipStream_t stream, int DC
     if (DC != 0 && DC != D) {
         if (D == 256 && DC == 128) return launch_cut_t<256, 64, 128, 256>(pb, stream);
         if (D == 128 && DC == 256) return launch_cut_t<128, 128, 256, 128>(pb, stream);
-        if (D == 128 && DC == 64) return launch_cut_hints<128, 64, 64, 128, kCut, kOnce>(pb, stream);
+        if (D == 128 && DC == 64) return launch_cut_t<128, 64, 64, 128>(pb, stream);
         if (D == 64 && DC == 128) return launch_cut_t<64, 64, 128, 64>(pb, stream);
         return hipErrorInvalidValue;
     }
     if (pb.p[0].gate) {                    // the forms of launch_pass_bf16 for this many chains
         if (pb.count != 1 || !pb.p[0].gated_out) return hipErrorInvalidValue;
         if (D == 64) return launch_cut_hints<64, 64, 64, 64, kCut + kGatedFar, kOnce>(pb, stream);
-        if (D == 96 && pb.p[0].out) return launch_cut_hints<128, 96, 96, 96, kCut + kGatedLate, kOnce>(pb, stream);
+        if (D == 96 && pb.p[0].out) return launch_cut_t<128, 96, 96, 96, kCut + kGatedLate>(pb, stream);
         if (D == 96) return launch_cut_hints<128, 96, 96, 96, kCut + kGated, kOnce>(pb, stream);
-        if (D == 128 && pb.p[0].out) return launch_cut_hints<128, 128, 128, 128, kCut + kGatedLate, kOnce>(pb, stream);
+        if (D == 128 && pb.p[0].out) return launch_cut_t<128, 128, 128, 128, kCut + kGatedLate>(pb, stream);
         if (D == 128) return launch_cut_hints<128, 128, 128, 128, kCut + kGated, kOnce>(pb, stream);
         return hipErrorInvalidValue;
     }
     switch (D) {
-        case 64: return launch_cut_hints<64, 64, 64, 64, kCut, kOnce, kBackward>(pb, stream);
-        case 96: return launch_cut_hints<128, 96, 96, 96, kCut, kOnce, kBackward>(pb, stream);
-        case 128: return launch_cut_hints<128, 128, 128, 128, kCut, kOnce, kBackward>(pb, stream);
+        case 64: return launch_cut_hints<64, 64, 64, 64, kCut, kBackward>(pb, stream);
+        case 96: return launch_cut_hints<128, 96, 96, 96, kCut, kBackward>(pb, stream);
+        case 128: return launch_cut_hints<128, 128, 128, 128, kCut, kBackward>(pb, stream);
         case 256: return launch_cut_t<256, 64, 256, 256>(pb, stream);
         default: return hipErrorInvalidValue;
     }
@@ -1196,8 +1183,7 @@ hipError_t launch_pass_bf16(const PassBatch& pb, int D, int dv, hipStream_t stre
 #define LTN_BF16_DC(d, v, c) if (D == d && dv == v && DC == c) return launch_t<d, v, kPlain, c>(pb, stream)
         LTN_BF16_DC(256, 64, 128); LTN_BF16_DC(256, 32, 128);
         LTN_BF16_DC(128, 128, 256); LTN_BF16_DC(128, 64, 256); LTN_BF16_DC(128, 32, 256);
-        if (D == 128 && dv == 64 && DC == 64) return launch_hints<128, 64, kPlain, 64, 128, kOnce>(pb, stream);
-        LTN_BF16_DC(128, 32, 64);
+        LTN_BF16_DC(128, 64, 64); LTN_BF16_DC(128, 32, 64);
         LTN_BF16_DC(64, 64, 128); LTN_BF16_DC(64, 32, 128);
 #undef LTN_BF16_DC
         return hipErrorInvalidValue;
@@ -1208,11 +1194,11 @@ hipError_t launch_pass_bf16(const PassBatch& pb, int D, int dv, hipStream_t stre
             if (pb.count != 1 || dv != 96 || !pb.p[0].gated_out || pb.state_only) return hipErrorInvalidValue;
             // with O stored as for 128 features below; and a single block has nothing to run ahead of (1024
             // chains x 64 tokens 23.2 us ahead, 22.1 late; 128 features 512 x 64 11.0 and 12.4)
-            if (pb.p[0].out || pb.N <= kBlock) return launch_hints<128, 96, kGatedLate, 96, 96, kOnce>(pb, stream);
+            if (pb.p[0].out || pb.N <= kBlock) return launch_t<128, 96, kGatedLate, 96, 96>(pb, stream);
             return launch_hints<128, 96, kGated, 96, 96, kOnce>(pb, stream);
         }
         if (pb.state_only) return dv == 32 ? launch_t<128, 32, kStateOnly, 96, 96>(pb, stream) : hipErrorInvalidValue;
-        if (dv == 96) return launch_hints<128, 96, kPlain, 96, 96, kOnce, kBackward>(pb, stream);
+        if (dv == 96) return launch_hints<128, 96, kPlain, 96, 96, kBackward>(pb, stream);
         return launch_t<128, 32, kPlain, 96, 96>(pb, stream);
     }
     if (pb.p[0].gate) {                    // gated epilogue: one pass, complete output rows
@@ -1223,7 +1209,7 @@ hipError_t launch_pass_bf16(const PassBatch& pb, int D, int dv, hipStream_t stre
         // 320 x 8192 479 and 504; without O ahead is the faster or within 3 % at every size (64 .. 768
         // chains x 64 .. 8192: 128 x 2048 77 and 80, 96 x 2048 60 and 72, 160 x 2048 91.5 and 89.1;
         // calls of 10 us, which the host bounds, scatter by 5 %).
-        if (D == 128 && pb.p[0].out) return launch_hints<128, 128, kGatedLate, 128, 128, kOnce>(pb, stream);
+        if (D == 128 && pb.p[0].out) return launch_t<128, 128, kGatedLate>(pb, stream);
         if (D == 128) return launch_hints<128, 128, kGated, 128, 128, kOnce>(pb, stream);
         // 64 features: a block takes 0.55 us and its gate loads longer once the chip is busy, so two ahead
         // from 128 whole chains on, 192 with O (one ahead and two, kernels alone: 128 x 500 12.5 and 12.2, 128 x 1000
@@ -1247,11 +1233,11 @@ hipError_t launch_pass_bf16(const PassBatch& pb, int D, int dv, hipStream_t stre
     }
     if (D == 256 && dv == 64) return launch_t<256, 64>(pb, stream);
     if (D == 256 && dv == 32) return launch_t<256, 32>(pb, stream);
-    if (D == 128 && dv == 128) return launch_hints<128, 128, kPlain, 128, 128, kOnce, kOnce | kPast, kBackward>(pb, stream);
-    if (D == 128 && dv == 64) return launch_hints<128, 64, kPlain, 128, 128, kSliceOnce>(pb, stream);
+    if (D == 128 && dv == 128) return launch_hints<128, 128, kPlain, 128, 128, kOnce | kPast, kBackward>(pb, stream);
+    if (D == 128 && dv == 64) return launch_t<128, 64>(pb, stream);
     if (D == 128 && dv == 32) return launch_t<128, 32>(pb, stream);
-    if (D == 64 && dv == 64) return launch_hints<64, 64, kPlain, 64, 64, kOnce, kBackward>(pb, stream);
-    if (D == 64 && dv == 32) return launch_hints<64, 32, kPlain, 64, 64, kSliceOnce>(pb, stream);
+    if (D == 64 && dv == 64) return launch_hints<64, 64, kPlain, 64, 64, kBackward>(pb, stream);
+    if (D == 64 && dv == 32) return launch_t<64, 32>(pb, stream);
     return hipErrorInvalidValue;
 }
 
