@@ -109,16 +109,19 @@ F32Plan pick_f32(long long chains, int count, long long N, int D, int DC, int bl
     };
     const int full = DC == 256 ? 128 : DC;                                   // columns of a sweep's workgroup
     const double sweep_cost = full / 16 / 4.0 * ts * (D / 4) + kF32Block;
-    F32Plan best = {0, 1, 0, 0.0};
-    auto consider = [&](int dv, int segs, long long len) {
-        const long long pieces = chains * count * segs, wgs = pieces * (DC / dv), blocks = ((segs > 1 ? len : N) + blk - 1) / blk;
+    F32Plan best = {0, 1, 0, 0.0}, paired = best;
+    // `sweeps` passes of a piece are swept; `states`: with the bytes of the segments' states
+    auto estimate = [&](int dv, int segs, long long len, int sweeps, bool states) {
+        const long long pieces = chains * segs, wgs = pieces * count * (DC / dv), blocks = ((segs > 1 ? len : N) + blk - 1) / blk;
         double t = (double)((wgs + 255) / 256) * blocks * slice_cost(dv);
-        // A backward's dK is not swept where that saves a round.  (Not counted so for other widths, where the plans it leads to
-        // are slower: 20 x 2048 x 64 56 and 64 us, 12 x 1999 x 96 78 and 82, 16 x 2048 x 256 332 and 354.)
-        const long long swept = count == 3 && D == 128 ? pieces / 3 * 2 : pieces;
-        if (segs > 1) t += (double)((swept * (DC / full) + 255) / 256) * blocks * sweep_cost + 2 * kF32Launch;
-        if (segs > 1 && gated) t += kF32State * D * DC * pieces;
+        if (segs > 1) t += (double)((pieces * sweeps * (DC / full) + 255) / 256) * blocks * sweep_cost + 2 * kF32Launch;
+        if (segs > 1 && states) t += kF32State * D * DC * pieces * count;
+        return t;
+    };
+    auto consider = [&](int dv, int segs, long long len) {
+        const double t = estimate(dv, segs, len, count, gated), t2 = estimate(dv, segs, len, count - 1, gated);
         if (!best.dv || t < best.t) best = F32Plan{dv, segs, len, t};
+        if (!paired.dv || t2 < paired.t) paired = F32Plan{dv, segs, len, t2};
     };
     int dvs[5], n_dv = 0;
     if (gated) dvs[n_dv++] = DC;
@@ -153,6 +156,16 @@ F32Plan pick_f32(long long chains, int count, long long N, int D, int DC, int bl
         }
         if (forced_segs > 1 && !best.dv) consider(dvs[i], 1, 0);
     }
+    // A backward sweeps two passes of three (swept_passes), which makes more and shorter cuts look worth it than are: the
+    // segments' states, 64 KiB a piece, are no part of that estimate.  So the plan it leads to is taken only where
+    // it is ahead of the other by 1 % with them counted.  At the 154 ends of the ranges of 1 .. 129 chains x 640 .. 16384
+    // tokens where the two differ the choice is at most 1.1 % slower than the plan for three sweeps and up to 8 faster (us:
+    // 24 x 8192 593 and 552, 52 x 16384 2611 and 2410); the other plan, always taken, lost up to 18 (16 x 1024 67 and 75, 32 x
+    // 1024 102 and 120, 56 x 1500 240 and 269, 64 x 4096 654 and 693).  Other widths keep the plan for three
+    // (20 x 2048 x 64 56 and 64, 12 x 1999 x 96 78 and 82, 16 x 2048 x 256 332 and 354).
+    if (count == 3 && D == 128 && (paired.dv != best.dv || paired.segs != best.segs) &&
+        estimate(paired.dv, paired.segs, paired.seg_len, 2, true) < 0.99 * estimate(best.dv, best.segs, best.seg_len, 2, true))
+        return paired;
     return best;
 }
 
