@@ -10,10 +10,16 @@
 // Streaming kernels, HBM-bound: every lane owns 16 bytes of one row, a row's lanes are
 // neighbours in one wave and reduce with cross-lane shuffles (rows of 96 features take 16 or 32
 // lanes of which 12 or 24 hold data); fp32 arithmetic.
-// ONCE: loads and stores that leave the caches first, from kOnceBytes a tensor on.  us, rotating inputs, without and with: 128
-// features, 2^18 rows forward 38.6 and 34.3, derivative 63.9 and 58.0; 2^20 rows 160 and 144, 278 and 255.  In a mixer
-// step, whose attention reads what the derivative has written: 128 chains x 2048 267.5 and 263.0, 64 x 2048 150 and
-// 144, 128 x 8192 1119 and 1064; smaller tensors stay in the caches in between (16 chains x 1000 38.8 and 40.7).
+// ONCE, from kOnceBytes a tensor on: loads that leave the caches first, and a derivative's du stored so, which a projection's
+// gradient reads later.  y and dx are stored plainly: the output projection and the attention's backward read them
+// next.  us, rotating inputs, no hints / loads / loads and du / everything.  Derivative, attention backward, copies of
+// dq, dk, dv, du: 32 chains x 2048 x 128 (16 MiB a tensor) 117.5 / 117.5 / 118.5 / 118.9, 48 x 2048 145.6 / 145.6 /
+// 144.4 / 144.4, 64 x 2048 177.5 / 175.1 / 171.5 / 173.4, 128 x 2048 332 / 332 / 327 / 338, 128 x 8192 1291 / 1294 / 1268
+// / 1275; the copy of du before the attention 96 x 2048 186.8 / 177.0 / 174.0 / 187.0, 128 x 2048 222.7 / 217.5 / 217.7 /
+// 225.7; no copies 128 x 2048 184.0 / 182.5 / 180.1 / 188.3.  Attention forward, gate, copy of y (none / loads / with y):
+// 48 x 2048 64.8 / 63.8 / 64.7, 128 x 2048 121.1 / 122.4 / 121.0, 128 x 4096 247 / 235 / 240, fp32 64 x 2048 184.5 / 186.5 /
+// 187.8.  The kernels alone, 2^18 rows of 128, outputs in other memory each time (in one place): forward 38.5 and 34.3 (34.0 and
+// 34.5), derivative 64.3 and 54.6 (62.8 and 54.7).
 #include "ltn_cache.h"
 #include "ltn_kernels.h"
 
@@ -23,7 +29,7 @@ namespace {
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(8 * sizeof(float)))) float f32x8;
 
-constexpr long long kOnceBytes = 16 << 20;
+constexpr long long kOnceBytes = 24 << 20;
 
 template <bool ONCE> __device__ __forceinline__ u32x4 load16(const void* p) {
     if constexpr (ONCE) return load16_once(p);
@@ -116,7 +122,7 @@ void gate_kernel(const char* x, const char* __restrict__ u, const char* __restri
             V yv;
 #pragma unroll
             for (int i = 0; i < V::N; ++i) yv.v[i] = xv.v[i] * rstd * uv.v[i];
-            if (live) yv.template store<ONCE>(o0 + off);
+            if (live) yv.template store<false>(o0 + off);
         } else {
             V gv;
             gv.template load<ONCE>(dy + off);
@@ -135,7 +141,7 @@ void gate_kernel(const char* x, const char* __restrict__ u, const char* __restri
                 dx.v[i] = (gv.v[i] * uv.v[i] - n * mean) * rstd;
             }
             if (live) {
-                dx.template store<ONCE>(o0 + off);
+                dx.template store<false>(o0 + off);
                 du.template store<ONCE>(o1 + off);
             }
         }

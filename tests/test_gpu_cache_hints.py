@@ -79,7 +79,7 @@ def test_decode(Dk, Dv, chains, steps, dtype):
 
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
-@pytest.mark.parametrize("D,rows", [(128, 65536), (96, 87400), (64, 131072), (256, 32768)])
+@pytest.mark.parametrize("D,rows", [(128, 98304), (96, 131072), (64, 196608), (256, 49152)])
 def test_gate(D, rows, dtype):
     g = torch.Generator(device="cuda").manual_seed(D)
     if dtype == torch.float32:
