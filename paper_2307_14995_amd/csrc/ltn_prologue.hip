@@ -85,9 +85,21 @@ struct Vec {
 };
 
 // AHEAD: batch entries whose loads are issued together (a thread's other tokens come one after another, as their angles do
-// not overlap with loads).  us, AHEAD 1 / 2 / 4: expansion 16 x 8 x 1000 x 64 28.6 / 25.5 / 19.6, derivative 33.6 / 30.2 / 28.2;
-// 4 x 16 x 2048 x 128 22.9 / 21.2 / 22.2 and 28.4 / 29.4 / 29.8; one batch entry, where it only takes registers, 1 x 32 x 30000
-// 145 / 148 / 167 and 198 / 198 / 227.
+// not overlap with loads).  It takes registers, so it pays while workgroups (64 tokens of one head) do not fill the
+// chip: up to 512, and below 512 for derivatives, in fp32 two at a time at most.  us, AHEAD 1 / 2 / 4: expansions of 128
+// features, 8 batch entries x 128 workgroups 29.5 / 21.5 / 18.1, 16 x 256 64.3 / 47.6 / 39.9, 8 x 512 41.9 / 38.8 / 40.4, 8 x
+// 1024 77.8 / 83.1 / 83.1; 4 x 512 23.4 / 21.2 / 22.3; fp32 8 x 1024 154 / 162 / 161.  Derivatives 8 x 128 35.9 / 30.3 / 29.0,
+// 16 x 256 69.1 / 58.0 / 59.6, 8 x 384 45.3 / 40.7 / 43.0, 8 x 512 49.9 / 52.4 / 53.9, 8 x 1024 105 / 117 / 116; fp32 8 x 128
+// 53.5 / 42.1 / 60.1, 16 x 256 113 / 94 / 125, 8 x 384 72.0 / 72.5 / 78.6, 8 x 512 96.3 / 99.6 / 97.7, 4 x 128 30.1 / 24.7 / 33.6.
+template <bool BF16, bool BWD>
+constexpr int most_ahead = BWD && !BF16 ? 2 : 4;
+
+template <bool BF16, bool BWD>
+int entries_ahead(int Bt, long long wgs) {
+    if (wgs > (BWD ? 511 : 512)) return 1;
+    if (Bt >= 8) return most_ahead<BF16, BWD>;
+    return Bt >= 4 && !(BF16 && BWD) ? 2 : 1;
+}
 template <int D, bool BF16, bool BWD, bool ONCE, int AHEAD>
 __global__ __launch_bounds__(kThreads)
 void prologue_kernel(const void* __restrict__ x, const float* __restrict__ theta, const void* __restrict__ dy,
@@ -225,12 +237,15 @@ hipError_t launch_t(const void* x, const float* theta, const void* dy, void* out
     auto launch = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)(nchunks * H)), dim3(kThreads), 0, stream,
                            x, theta, dy, out, partials, act, Bt, H, N, pos0, nchunks);
+        return hipGetLastError();
     };
     const bool once = (long long)Bt * H * N * D * (BF16 ? 2 : 4) >= kOnceBytes;
-    if (Bt >= 8) once ? launch(prologue_kernel<D, BF16, BWD, true, 4>) : launch(prologue_kernel<D, BF16, BWD, false, 4>);
-    else if (Bt >= 4 && !BWD) once ? launch(prologue_kernel<D, BF16, BWD, true, BWD ? 1 : 2>) : launch(prologue_kernel<D, BF16, BWD, false, BWD ? 1 : 2>);
-    else once ? launch(prologue_kernel<D, BF16, BWD, true, 1>) : launch(prologue_kernel<D, BF16, BWD, false, 1>);
-    return hipGetLastError();
+    const int ahead = entries_ahead<BF16, BWD>(Bt, (long long)nchunks * H);
+    constexpr int MOST = most_ahead<BF16, BWD>;
+    if (ahead == MOST) return once ? launch(prologue_kernel<D, BF16, BWD, true, MOST>) : launch(prologue_kernel<D, BF16, BWD, false, MOST>);
+    if constexpr (!BWD)
+        if (ahead == 2) return once ? launch(prologue_kernel<D, BF16, BWD, true, 2>) : launch(prologue_kernel<D, BF16, BWD, false, 2>);
+    return once ? launch(prologue_kernel<D, BF16, BWD, true, 1>) : launch(prologue_kernel<D, BF16, BWD, false, 1>);
 }
 
 }  // namespace
