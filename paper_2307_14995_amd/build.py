@@ -30,8 +30,9 @@ HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     # keep the compiler from forming packed-fp32 VALU ops
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-    # a kernel's first scalar arguments in registers at its start: decode of 32 chains of 128 x 128 3.52 -> 3.31 us
-    # (structs, the passes' arguments, are loaded as before)
+    # a kernel's first scalar arguments (14 words) in registers at its start: decode of 256 chains of 128 x 128 5.17 -> 4.86 us a
+    # call, gate of 65536 rows 8.90 -> 8.72, the passes' scans; up to 128 chains, which the host bounds, nothing.  (Structs,
+    # the passes' arguments, are loaded as before.)
     "-mllvm", "-amdgpu-kernarg-preload-count=16",
     "-Wno-unused-command-line-argument",
     "-Rpass-analysis=kernel-resource-usage",

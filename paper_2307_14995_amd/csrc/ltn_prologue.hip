@@ -100,11 +100,15 @@ int entries_ahead(int Bt, long long wgs) {
     if (Bt >= 8) return most_ahead<BF16, BWD>;
     return Bt >= 4 && !(BF16 && BWD) ? 2 : 1;
 }
+//
+// Arguments: what the angles and the first loads need comes first, in the 14 words that arrive in registers.  With x, theta,
+// dy, out and the partials there, and the sizes loaded, small calls took longer than with everything loaded (us,
+// loaded / pointers first / this: expansion 8 x 256 x 128 5.05 / 5.16 / 4.75, 4 x 8 x 256 x 64 in fp32 6.5 / 6.8 / 6.2,
+// derivative 8 x 256 x 128 8.04 / 8.36 / 7.99, 2 x 8 x 1024 x 128 10.39 / 10.67 / 10.39).
 template <int D, bool BF16, bool BWD, bool ONCE, int AHEAD>
 __global__ __launch_bounds__(kThreads)
-void prologue_kernel(const void* __restrict__ x, const float* __restrict__ theta, const void* __restrict__ dy,
-                     void* __restrict__ out, double* __restrict__ partials, int act, int Bt, int H,
-                     long long N, long long pos0, int nchunks) {
+void prologue_kernel(int nchunks, int H, long long N, long long pos0, const float* __restrict__ theta, const void* __restrict__ x,
+                     int act, int Bt, const void* __restrict__ dy, void* __restrict__ out, double* __restrict__ partials) {
     using V = Vec<BF16, ONCE>;
     constexpr int E = V::E;
     constexpr int TX = D / E;                 // threads across one token's features
@@ -236,7 +240,7 @@ hipError_t launch_t(const void* x, const float* theta, const void* dy, void* out
                     int Bt, int H, long long N, long long pos0, int nchunks, hipStream_t stream) {
     auto launch = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)(nchunks * H)), dim3(kThreads), 0, stream,
-                           x, theta, dy, out, partials, act, Bt, H, N, pos0, nchunks);
+                           nchunks, H, N, pos0, theta, x, act, Bt, dy, out, partials);
         return hipGetLastError();
     };
     const bool once = (long long)Bt * H * N * D * (BF16 ? 2 : 4) >= kOnceBytes;
