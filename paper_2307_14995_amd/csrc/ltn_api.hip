@@ -499,24 +499,34 @@ Cut pick_cut(int chains, int count, long long N, int D, int DC, int dv, int wide
 //     forward: 128 features 128 chains x 2048 / 8192 tokens 184.5 and 172.7, 713 and 688, 200 x 3000 414 and 402, 16 x
 //     16384 (segments) 265 and 257; 96 features 544 x 928 299 and 282; 64 features 320 x 2048 227 and 216, 128 x 6000 269
 //     and 256, but 180 x 2829 (249 MiB) 187 and 193.  Inputs that the memory-side cache holds lose (alone: 64 x 1000
-//     34.0 and 36.6, 128 x 1000 65.4 and 69.2), and so do 64-column slices (32 x 16301 322 and 334)
+//     34.0 and 36.6, 128 x 1000 65.4 and 69.2), and so do 64-column slices (32 x 16301 322 and 334).
+//     With the gradients read next (forward, backward, copies of dQ, dK, dV): 128 features 128 x 2048 269 and 262, 128 x 8192
+//     1017 and 975, 200 x 3000 589 and 576; 96 features 544 x 928 411 and 393; 64 features 320 x 2048 334 and 320, 600 x 2048
+//     (600 MiB) 627 and 621, but from 650 MiB on most lose (512 x 2600 666 and 671, 640 x 2200 699 and 709, 640 x 3000 948
+//     and 966, 1024 x 2048 1011 and 1025; 250 x 8192 982 and 971).  96 features in segments: nothing (16 x 24000 440 and 440)
 //   forward in segments, all once in the pass after the sweep and outputs past the caches, so that K and V of the sweep
-//     stay: 32 x 16301 and its backward 501 and 475; alone 176 and 140, 8 x 65536 179 and 154; 16 x 16384 and its
-//     backward, 256 MiB, lose (265 and 273)
+//     stay: 32 x 16301 and its backward 501 and 475; alone 176 and 140, 8 x 65536 179 and 154.  With a gate that reads O, and
+//     the backward: 16 x 16384 (256 MiB) 297 and 307, 16 x 20000 359 and 367, 32 x 12000 (375) 407 and 404, 32 x 13000
+//     (406) 453 and 449, 32 x 16301 571 and 554 (O kept 550; with a copy of O and no backward 235, 201 and 206)
 //   gated forward without o (inference), all once, outputs through the caches: 128 features 256 x 500 38.9 and 34.8, 512 x
 //     1000 139 and 131, segments 32 x 8192 103 and 92, 64 x 3000 79 and 76; 64 features 320 x 2048 92 and 87; 96
-//     features 320 x 2000 139 and 129, but rows of 192 bytes, whose lines two loads share, need a full chip (128 x 1999
-//     63.8 and 65.3).  Below 64 MiB (192 in segments) nothing
+//     features 320 x 2000 139 and 129, but rows of 192 bytes, whose lines two loads share, need a nearly full chip (x 2000:
+//     128 chains 60.3 and 62.4, 160 68.1 and 67.8, 192 78.1 and 76.4, 224 88.3 and 83.9).  Below 64 MiB (192 in
+//     segments) nothing
 // The plain forward of whole chains gains alone (all once: 256 x 4096 207 and 180) and loses with the backward that finds
 // less of Q, K and V in the memory-side cache (fwd and bwd 320 x 2048 x 64 216 and 227, 200 x 3000 402 and 414, 256 x 1000
-// 168 and 172; 256 x 4096 684 and 672).  256 features: nothing within 1 %.
+// 168 and 172; 256 x 4096 684 and 672).  256 features: nothing within 1 %.  Unequal widths, the first layer's step with copies of
+// its gradients: forward and dV nothing; dK and dQ with C once and past 4 x 16 x 2048 x 128 338 and 332, 4 x 32 x 4096 1159
+// and 1136, 1 x 32 x 30000 nothing, 4 x 32 x 4096 x 64 569 and 574: no hints.
 void set_hints(ltn::PassBatch& pb, int D, int DC, int dv, bool segmented) {
     constexpr long long kMiB = 1 << 20;
     const long long tokens = pb.chains * pb.N;
     pb.hints = 0;
     if (D == 256 || D != DC || dv != D) return;
     if (pb.count == 3) {
-        if ((!segmented || D != 96) && 8LL * D * tokens >= (D == 64 ? 288 : 240) * kMiB) pb.hints = ltn::kOnceA | ltn::kPast;
+        const long long bytes = 8LL * D * tokens;
+        const bool pays = D == 64 ? bytes >= 288 * kMiB && (segmented || bytes < 640 * kMiB) : bytes >= 240 * kMiB && !(segmented && D == 96);
+        if (pays) pb.hints = ltn::kOnceA | ltn::kPast;
     } else if (pb.p[0].gate) {
         const bool fills = D != 96 || (!segmented && pb.chains >= 192);
         if (!pb.p[0].out && fills && 10LL * D * tokens >= (segmented ? 192 : 64) * kMiB) pb.hints = ltn::kOnce;
