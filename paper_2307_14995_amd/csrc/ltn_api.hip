@@ -1030,7 +1030,6 @@ static ltn_status run_dkdv(ltn::PassBatch& pb, int DA, int DC, int blk, ltn_dtyp
         main.p[i].state_out = nullptr;
     }
     const int dv = pick_dv_range(chain_passes * plan.segs, DC, 32, hi);
-    set_hints(main, DA, DC, dv, true);
     return ltn::launch_pass_bf16(main, DA, dv, st, DC) == hipSuccess ? LTN_OK : LTN_ERR_LAUNCH;
 }
 
