@@ -36,14 +36,31 @@ __device__ __forceinline__ unsigned short f32_to_bf16_bits(float f) {   // round
 
 // A state is read once and written once, and the next call that wants it comes after every other layer's.  Loads and
 // stores that leave the caches first, or are written through, keep the lines from being written back
-// in the middle of the reads.  us a call, 128 x 128, plain / once / read once and written through, states of many layers
-// (1.1 GiB in turn) and of few (160 .. 192 MiB): 128 chains (8 MiB) 6.0 / 4.7 / 4.8 and 5.0 / 4.7 / 4.7; 256 9.7 / 6.9 /
-// 7.2 and 7.9 / 6.8 / 6.9; 512 15.7 / 11.4 / 11.7 and 11.7 / 11.0 / 11.7; 1024 28.6 / 22.5 / 23.4 and 19.9 / 20.8 / 22.6 (two
-// sets); 1536 44.6 / 38.1 / 39.6 and 30.6 / 37.1 / 33.4; 2048 55.4 / 49.3 / 50.5 and 43.2 / 48.8 / 40.4, one state repeated
-// 39.9 / 47.2 / 39.0.  256 x 256, 128 chains (32 MiB) 18.0 / 13.5 / 14.3 and 11.4 / 13.2 / 11.2, 256 30.5 / 26.8 / 28.3 and 21.3 /
-// 26.4 / 21.2; 64 x 64, 2048 chains (32 MiB) 15.3 / 12.4 / 12.7 and 11.1 / 11.9 / 10.6, 4096 27.4 / 23.5 / 24.0 and 21.3 /
-// 22.8 / 20.2; whole 128 x 64 and 96 x 96 as 64 x 64 from 50 MiB on (2000 chains 29.7 / 24.0 once and 19.1 / 23.0).  Hence
-// the line of write_through().
+// in the middle of the reads.  us a call, plain / once / read once and written through; states of many layers (1.1 GiB in
+// turn), of few (176 MiB in turn, all of them in the memory-side cache), and one repeated:
+//     128 x 128    512 chains (32 MiB)   15.7 / 11.2 / 11.4     11.1 / 10.8 / 10.5      8.3 /  8.2 / 10.6
+//                  768                   23.6 / 17.2 / 17.7     14.9 / 16.5 / 14.8     13.1 / 12.5 / 14.8
+//                 1024 (64)              29.7 / 22.4 / 23.7     19.5 / 21.8 / 19.6     19.5 / 19.0 / 19.5
+//                 1280 (80)              37.4 / 31.0 / 32.1     24.5 / 30.0 / 27.1     24.5 / 28.0 / 27.1
+//                 1536                   44.6 / 37.8 / 40.0     30.3 / 36.8 / 32.7     30.3 / 35.5 / 32.7
+//                 2048 (128)             56.9 / 50.2 / 50.9                            39.8 / 47.8 / 41.3
+//     64 x 64     1024 (16)               8.5 /  6.0 /  6.3      6.8 /  5.9 /  5.7      5.3 /  5.2 /  5.7
+//                 1536 (24)              12.2 /  9.3 /  9.8      8.7 /  8.9 /  8.2      6.4 /  6.0 /  8.2
+//                 2048 (32)              15.1 / 12.3 / 12.4     10.7 / 11.8 / 10.2      8.2 /  9.1 / 10.2
+//     96 x 96     1140 (40)              20.0 / 16.3 / 17.5     12.4 / 15.7 / 14.1     11.7 / 13.1 / 14.0
+//                 1424 (50)              24.1 / 20.1 / 20.9     16.1 / 19.3 / 16.7     16.0 / 17.2 / 16.6
+//                 2000 (70)              32.5 / 27.3 / 29.0     22.3 / 26.3 / 23.2     22.3 / 24.8 / 23.2
+//     128 x 64    1280 (40)              20.0 / 14.2 / 15.1     13.1 / 13.3 / 12.9     12.7 / 10.9 / 12.9
+//                 1600 (50)              24.8 / 19.6 / 20.5     15.7 / 19.0 / 16.4     15.7 / 16.3 / 16.4
+//     256 x 128    192 (24)              11.9 /  9.2 /  9.3      9.2 /  8.8 /  8.8      7.6 /  7.7 /  8.8
+//                  256 (32)              16.6 / 12.8 / 13.6     10.7 / 12.4 / 11.0      8.2 /  8.6 / 10.9
+//                  512 (64)              29.2 / 25.0 / 26.9     20.8 / 24.4 / 20.8     20.8 / 23.3 / 20.8
+//     256 x 256     96 (24)              12.2 /  9.2 /  9.5      9.4 /  8.9 /  8.8      6.8 /  6.6 /  8.8
+//                  128 (32)              17.6 / 13.5 / 14.4     11.1 / 13.1 / 11.2      8.7 / 10.0 / 11.0
+// Many layers are what a model has and few what a small one has; writing through costs the many up to 8 % and spares the few up
+// to 15 from the line of each width on (through_bytes; 128 x 128 later: below it the many lose 6 %, and the few are within 12 %
+// of plain).  Plain ones are ahead where all states of a program fit the cache (the few and the repeated), by up to 14 %
+// and 30, and cost the many 10 to 30 %.
 union Bits { u32x4 u; float4 f; };
 __device__ __forceinline__ float4 load_state(const float4* p) {
     Bits b;
@@ -57,10 +74,8 @@ __device__ __forceinline__ void store_state(float4* p, float4 v) {      // (by r
     if constexpr (THROUGH) store16_through(p, b.u);
     else store16_once(p, b.u);
 }
-bool write_through(int chains, int DK, int DV) {
-    const long long mib = (long long)chains * DK * DV * 4 >> 20;
-    return mib >= (DK == 256 || DK == 64 ? 24 : DV == 128 ? 72 : 40);
-}
+constexpr long long through_bytes(int DK, int DV) { return (DK == 256 || DK == 64 ? 24LL : DV == 128 ? 72 : 40) << 20; }
+bool write_through(int chains, int DK, int DV) { return (long long)chains * DK * DV * 4 >= through_bytes(DK, DV); }
 
 // Order of an output's sum, the same in both kernels below, so that a sequence's output does not depend on
 // how many others are in the call: rows in DK / 8 classes (row mod DK / 8) of eight, each summed in the
@@ -252,34 +267,38 @@ constexpr int split_limit(int DK, int DV) {
     return DK == 256 ? 8192 : DK == 64 ? 0 : DK * DV == 128 * 64 ? 1024 : 1536;
 }
 
+// A state of this width, as slices or whole.  (Slices are written through only where their sizes reach that line: 256 rows.)
+template <int DK, int DV, bool BF16, bool THROUGH>
+hipError_t launch_t(const void* q, const void* k, const void* v, void* o, float* kv, const float* decay, int chains, int H,
+                    int steps, hipStream_t stream) {
+    constexpr int PER = DV / kSliceCols, MOST = split_limit(DK, DV) / PER;      // slices of a chain, chains that are split
+    if constexpr (MOST > 0 && (!THROUGH || 4LL * MOST * DK * DV >= through_bytes(DK, DV))) {
+        if (chains <= MOST) {
+            hipLaunchKernelGGL((decode_slice_kernel<DK, DV, BF16, THROUGH>), dim3((unsigned)(chains * PER)), dim3(DK), 0, stream,
+                               q, k, v, o, kv, decay, H, steps);
+            return hipGetLastError();
+        }
+    }
+    hipLaunchKernelGGL((decode_kernel<DK, DV, BF16, THROUGH>), dim3((unsigned)chains), dim3(threads_for(DK, DV)), 0, stream,
+                       q, k, v, o, kv, decay, H, steps);
+    return hipGetLastError();
+}
+
 }  // namespace
 
 hipError_t launch_decode(const void* q, const void* k, const void* v, void* o, float* kv,
                          const float* decay, int chains, int H, int steps, int DK, int DV, int is_bf16,
                          hipStream_t stream) {
     if (chains <= 0 || steps <= 0) return hipSuccess;
-    const dim3 grid((unsigned)chains);
     const bool through = write_through(chains, DK, DV);
-    const bool split = (long long)chains * (DV / kSliceCols) <= split_limit(DK, DV);
-    const dim3 slices((unsigned)(split ? chains * (DV / kSliceCols) : 1));
-    // a state of this width: as slices or whole, written through or not
-#define LTN_DECODE_T(dk, dv, bf, th)                                                                    \
-    do {                                                                                                \
-        if constexpr (split_limit(dk, dv) > 0) if (split) {                                             \
-            hipLaunchKernelGGL((decode_slice_kernel<dk, dv, bf, th>), slices, dim3(dk), 0, stream, q, k, v, o, kv, decay, H, steps); \
-            return hipGetLastError();                                                                   \
-        }                                                                                               \
-        hipLaunchKernelGGL((decode_kernel<dk, dv, bf, th>), grid, dim3(threads_for(dk, dv)), 0, stream, q, k, v, o, kv, decay, H, steps); \
-        return hipGetLastError();                                                                       \
-    } while (0)
+    auto launch = [&](auto kernel) { return kernel(q, k, v, o, kv, decay, chains, H, steps, stream); };
 #define LTN_DECODE(dk, dv)                                                                              \
     if (DK == dk && DV == dv) {                                                                         \
-        if (is_bf16) { if (through) LTN_DECODE_T(dk, dv, true, true); else LTN_DECODE_T(dk, dv, true, false); }   \
-        else { if (through) LTN_DECODE_T(dk, dv, false, true); else LTN_DECODE_T(dk, dv, false, false); }         \
+        if (is_bf16) return through ? launch(launch_t<dk, dv, true, true>) : launch(launch_t<dk, dv, true, false>);    \
+        return through ? launch(launch_t<dk, dv, false, true>) : launch(launch_t<dk, dv, false, false>);               \
     }
     LTN_DECODE(128, 128) LTN_DECODE(64, 64) LTN_DECODE(96, 96) LTN_DECODE(256, 256) LTN_DECODE(256, 128) LTN_DECODE(128, 64)
 #undef LTN_DECODE
-#undef LTN_DECODE_T
     return hipErrorInvalidValue;
 }
 
