@@ -353,6 +353,10 @@ ltn_status ltn_attn_query_plan(int Bt, int H, long long N, int D, ltn_dtype dtyp
 ltn_status ltn_attn_query_cut(int Bt, int H, long long N, int Dk, int Dv, ltn_dtype dtype, int call,
                               int* chains, long long* tokens);
 
+/* State-only sweeps of a backward whose chains are cut into segments: 3, or 2 where the states of dK are
+ * written as those of dV transposed; 0 for whole chains.  For reports and tests, as above. */
+ltn_status ltn_attn_query_sweeps(int Bt, int H, long long N, int D, ltn_dtype dtype, int* sweeps);
+
 /* TEST ONLY.  Forces the launch plan of ltn_attn_fwd / ltn_attn_bwd / ltn_attn_fwd_gated for
  * the whole process until called again: dv = value columns per workgroup (0 = the library's
  * choice; a value the kernels do not have for a given D is ignored), segs = segments per

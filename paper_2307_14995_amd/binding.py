@@ -26,7 +26,7 @@ SYMBOLS = (
     "ltn_attn_workspace_bytes", "ltn_attn_check_decay", "ltn_status_str",
     "ltn_prologue_fwd", "ltn_prologue_bwd", "ltn_prologue_workspace_bytes",
     "ltn_attn_fwd_dkdv", "ltn_attn_bwd_dkdv", "ltn_attn_decode_steps_dkdv",
-    "ltn_attn_query_plan", "ltn_attn_query_cut", "ltn_attn_set_debug_plan", "ltn_attn_fwd_static", "ltn_attn_bwd_tiled", "ltn_probe_stream_read", "ltn_attn_workspace_bytes_dkdv",
+    "ltn_attn_query_plan", "ltn_attn_query_cut", "ltn_attn_query_sweeps", "ltn_attn_set_debug_plan", "ltn_attn_fwd_static", "ltn_attn_bwd_tiled", "ltn_probe_stream_read", "ltn_attn_workspace_bytes_dkdv",
 )
 
 
@@ -101,6 +101,8 @@ def load_library():
     lib.ltn_attn_query_plan.restype = ci
     lib.ltn_attn_query_cut.argtypes = [ci, ci, cl, ci, ci, ci, ci, ctypes.POINTER(ci), ctypes.POINTER(cl)]
     lib.ltn_attn_query_cut.restype = ci
+    lib.ltn_attn_query_sweeps.argtypes = [ci, ci, cl, ci, ci, ctypes.POINTER(ci)]
+    lib.ltn_attn_query_sweeps.restype = ci
     lib.ltn_attn_set_debug_plan.argtypes = [ci, ci]
     lib.ltn_attn_set_debug_plan.restype = ci
     _bind_native(lib)
@@ -183,6 +185,15 @@ def ltn_attn_query_cut(Bt, H, N, Dk, Dv, dtype, call):
     if rc != 0:
         raise LtnError(rc, "ltn_attn_query_cut")
     return chains.value, tokens.value
+
+
+def ltn_attn_query_sweeps(Bt, H, N, D, dtype):
+    """State-only sweeps of a backward: 0 (whole chains), 2 or 3."""
+    sweeps = ctypes.c_int(0)
+    rc = load_library().ltn_attn_query_sweeps(int(Bt), int(H), int(N), int(D), _dtype_code(dtype), ctypes.byref(sweeps))
+    if rc != 0:
+        raise LtnError(rc, "ltn_attn_query_sweeps")
+    return sweeps.value
 
 
 def ltn_attn_set_debug_plan(dv=0, segs=0) -> None:

@@ -174,8 +174,16 @@ F32Plan pick_f32(long long chains, int count, long long N, int D, int DC, int bl
 // three sweeps and two: 32 chains x 2048 tokens of 128 features 222 and 198, 32 x 2000 of 64 84.8 and 77.3, 16 x 2048 of 96
 // 92.4 and 84.5), and for 256 features in bf16 (4 x 8192 121 and 116).  The other bf16 sweeps of dV and dK share their loads, and
 // take no longer for being two (4 x 32768 of 128 106.0 and 106.9, 2 x 4000 22.4 and 23.2, 4 x 8192 of 96 42.6 and 44.0).
-int swept_passes(const ltn::PassBatch& pb, bool pay_for_products, int (&pass)[3]) {
-    const bool pair = pb.count == 3 && pb.pairs_first && pay_for_products;
+int backward_sweeps(long long chains, int segs, int D, ltn_dtype dtype) {
+    if (segs <= 1) return 0;
+    if (dtype == LTN_BF16) return D == 256 ? 2 : 3;
+    // (a third sweep that its units would be idle for costs nothing: 2 chains x 1952 x 64 28.1 with three, 29.0)
+    const long long swept = chains * segs * (D == 256 ? 2 : 1);
+    return (3 * swept + 255) / 256 > (2 * swept + 255) / 256 ? 2 : 3;
+}
+
+int swept_passes(const ltn::PassBatch& pb, int segs, int D, ltn_dtype dtype, int (&pass)[3]) {
+    const bool pair = pb.count == 3 && pb.pairs_first && backward_sweeps(pb.chains, segs, D, dtype) == 2;
     for (int i = 0; i < 3; ++i) pass[i] = pair ? 2 * i : i;
     return pair ? 2 : pb.count;
 }
@@ -195,9 +203,7 @@ ltn_status run_f32(ltn::PassBatch& pb, int D, int DC, int blk, hipStream_t strea
         sweep.state_only = 1;
         sweep.need_last = kv_out != nullptr;
         int pass[3];
-        // (a third sweep that its units would be idle for costs nothing: 2 chains x 1952 x 64 28.1 with three, 29.0)
-        const long long swept = (long long)pb.chains * pb.segs * (DC == 256 ? 2 : 1);
-        sweep.count = swept_passes(pb, (3 * swept + 255) / 256 > (2 * swept + 255) / 256, pass);
+        sweep.count = swept_passes(pb, pb.segs, D, LTN_F32, pass);
         for (int i = 0; i < sweep.count; ++i) {
             sweep.p[i] = pb.p[pass[i]];
             sweep.p[i].gate = nullptr;
@@ -573,7 +579,7 @@ ltn_status run_passes(ltn::PassBatch& pb, int D, int blk, ltn_dtype dtype, void*
     sweep.state_only = 1;
     sweep.need_last = kv_out != nullptr;
     int pass[3];
-    sweep.count = swept_passes(pb, D == 256, pass);
+    sweep.count = swept_passes(pb, plan.segs, D, dtype, pass);
     for (int i = 0; i < sweep.count; ++i) {
         sweep.p[i] = pb.p[pass[i]];
         sweep.p[i].out = nullptr;
@@ -664,6 +670,14 @@ ltn_status ltn_attn_query_plan(int Bt, int H, long long N, int D, ltn_dtype dtyp
     *segs_out = plan.segs;
     *dv_out = fused ? D : pick_dv(chains * count * plan.segs, D, count);
     return LTN_OK;
+}
+
+ltn_status ltn_attn_query_sweeps(int Bt, int H, long long N, int D, ltn_dtype dtype, int* sweeps_out) {
+    if (!sweeps_out) return LTN_ERR_NULL;
+    int dv, segs;
+    const ltn_status s = ltn_attn_query_plan(Bt, H, N, D, dtype, 1, &dv, &segs);
+    if (s == LTN_OK) *sweeps_out = backward_sweeps((long long)Bt * H, segs, D, dtype);
+    return s;
 }
 
 int ltn_attn_pick_block(int D, ltn_dtype dtype) {

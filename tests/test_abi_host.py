@@ -360,6 +360,30 @@ def test_debug_plan_and_plan_query(lib):
     assert lib.ltn_attn_query_plan(1, 1, 64, 128, 1, 7, ctypes.byref(dv), ctypes.byref(segs)) == E_SHAPE
 
 
+def test_sweeps_of_a_backward(lib):
+    """Two where dK's states are dV's transposed: in fp32 where three take a round of 256 workgroups more, in bf16 for 256
+    features; none for whole chains."""
+    import torch
+    BF, F32 = torch.bfloat16, torch.float32
+    assert ltn.ltn_attn_query_sweeps(4, 32, 8192, 128, BF) == 0
+    try:
+        ltn.ltn_attn_set_debug_plan(0, 8)
+        for D in (64, 96, 128):
+            at = [ltn.ltn_attn_query_sweeps(1, c, 4096, D, F32) for c in (10, 11, 16, 17, 21, 22, 32, 33)]
+            assert at == [3, 2, 2, 3, 3, 2, 2, 2]                  # 80, 88, 128, 136, 168, 176, 256 and 264 segments
+            assert ltn.ltn_attn_query_sweeps(1, 12, 4096, D, BF) == 3
+        assert [ltn.ltn_attn_query_sweeps(1, c, 4096, 256, F32) for c in (5, 6, 8, 9)] == [3, 2, 2, 3]
+        assert ltn.ltn_attn_query_sweeps(1, 1, 4096, 256, BF) == 2
+    finally:
+        ltn.ltn_attn_set_debug_plan(0, 0)
+    n = ctypes.c_int()
+    assert lib.ltn_attn_query_sweeps(1, 1, 64, 128, 1, None) == E_NULL
+    assert lib.ltn_attn_query_sweeps(1, 0, 64, 128, 1, ctypes.byref(n)) == E_SHAPE
+    assert lib.ltn_attn_query_sweeps(1, 1, 64, 80, 1, ctypes.byref(n)) == E_UNSUP
+    # the most chains there can be (the sizes in 64 bits: this file also runs under the sanitizers)
+    assert ltn.ltn_attn_query_sweeps(0x3fff, 0x10000, 8, 256, F32) == 0
+
+
 def test_which_chains_run_in_two_parts(lib):
     """As many as there are workgroups more than whole rounds of 256, up to half a round, in two to four rounds of
     chains long enough; whole chains elsewhere."""
