@@ -35,17 +35,14 @@ def test_forward(D, H, N, dv, segs):
     assert torch.equal(o, want[0]) and torch.equal(kv, want[1])
 
 
-@pytest.mark.parametrize("store_o", [False, True])
-@pytest.mark.parametrize("D,H,N,segs", [(128, 192, 137, 1), (96, 192, 190, 1), (64, 192, 300, 1), (64, 192, 1217, 1),
-                                        (128, 200, 705, 1), (96, 200, 769, 1), (128, 16, 5000, 8)])
-def test_gated_forward(D, H, N, segs, store_o):
-    if segs > 1 and store_o:
-        pytest.skip("few chains with o stored run in two steps")
+# without o (with it there are no hints); 64 features with up to four blocks, whose kernel is another, and in segments too
+@pytest.mark.parametrize("D,H,N,segs", [(128, 192, 137, 1), (96, 192, 190, 1), (64, 192, 300, 1), (64, 192, 1217, 1), (64, 210, 250, 1),
+                                        (128, 200, 705, 1), (96, 200, 769, 1), (128, 16, 5000, 8), (64, 16, 9900, 8)])
+def test_gated_forward(D, H, N, segs):
     t, decay = inputs(H, N, D, 4)
 
     def call(*x):
-        o, y, kv = ltn.ltn_attn_fwd_gated(*x, decay, eps=1e-6, return_state=True, store_o=store_o)
-        return (y, kv, o) if store_o else (y, kv)
+        return ltn.ltn_attn_fwd_gated(*x, decay, eps=1e-6, return_state=True, store_o=False)[1:]
 
     with force_plan(segs=segs if segs > 1 else 0):
         got = call(*t)
@@ -60,6 +57,17 @@ def test_backward(D, H, N):
     assert all(torch.equal(a, b) for a, b in zip(ltn.ltn_attn_bwd(*t, decay), want))
     with force_plan(segs=1):
         assert all(torch.equal(a, b) for a, b in zip(ltn.ltn_attn_bwd(*t, decay), want))
+
+
+# in segments of full width: inputs of 241 and 289 MiB
+@pytest.mark.parametrize("D,H,N", [(128, 8, 15400), (64, 8, 37000)])
+def test_backward_in_segments(D, H, N):
+    t, decay = inputs(H, N, D, 4)
+    with force_plan(dv=D, segs=5):
+        assert ltn.ltn_attn_query_plan(2, H, N, D, torch.bfloat16, 1) == (D, 5)
+        got = ltn.ltn_attn_bwd(*t, decay)
+    want = halves(lambda *x: ltn.ltn_attn_bwd(*x, decay), t, D, 5)
+    assert all(torch.equal(a, b) for a, b in zip(got, want))
 
 
 # states of just the size that is written through, and the halves, which are not
