@@ -27,21 +27,21 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0  # MI355X published dense bf16 MFMA rate
 MFMA_FP32_PEAK_TFLOPS = 157.3   # MI355X published fp32 matrix rate
 
 
-def flops_per_token_head(D: int, B: int, plan_fwd=(0, 1), plan_bwd=(0, 1)):
+def flops_per_token_head(D: int, B: int, plan_fwd=(0, 1), plan_bwd=(0, 1), sweeps_bwd: int = 0):
     """FLOP conventions per token-head (one multiply or one add = 1 FLOP), fwd+bwd.
-    plan_* = (value columns per workgroup, segments per chain) the library takes for the call."""
-    def issued(passes, plan):
+    plan_* = (value columns per workgroup, segments per chain) the library takes for the call; sweeps_bwd = the
+    state-only sweeps of its backward."""
+    def issued(passes, plan, sweeps):
         # One decayed pass per token-head: 4 D^2 for the two state products (state update, query times
         # state); per 64-token block 10 of 16 score tiles, recomputed by each of the D/dv value-column
-        # slices of a chain, and 12 of 16 score-times-value tiles; a chain cut into segments also runs the
-        # state-only sweep (one more state update, 2 D^2).
-        dv, segs = plan
-        slices = D // dv if dv else 1
-        return passes * ((1.25 * slices + 1.5) * B * D + 4 * D * D + (2 * D * D if segs > 1 else 0))
+        # slices of a chain, and 12 of 16 score-times-value tiles; a chain cut into segments also runs
+        # state-only sweeps (one more state update each, 2 D^2).
+        slices = D // plan[0] if plan[0] else 1
+        return passes * ((1.25 * slices + 1.5) * B * D + 4 * D * D) + sweeps * 2 * D * D
     return {
         "F_min": 14 * D * D,                               # recurrent form, block independent
         "F_alg": 14 * D * D + 7 * (B + 1) * D,             # blockwise method, causal half of each tile
-        "F_exec": issued(1, plan_fwd) + issued(3, plan_bwd),   # what the kernels issue under the plan taken
+        "F_exec": issued(1, plan_fwd, int(plan_fwd[1] > 1)) + issued(3, plan_bwd, sweeps_bwd),   # what the kernels issue under the plan taken
     }
 
 
@@ -50,13 +50,12 @@ def f32_block(block: int) -> int:
     return min(block, 32)
 
 
-def f32_issued_flops_per_token_head(D: int, block: int, plan, passes: int) -> float:
-    """FLOPs the fp32 kernel issues: per pass, causal 16-token score tiles ((B/16+1)/2 of B/16 a strip,
-    recomputed per value-column slice), the same share of P C, 4 D^2 of state products, and 2 D^2 more in
-    the state-only sweep of chains cut into segments.  plan = (value columns per workgroup, segments)."""
-    dv, segs = plan
+def f32_issued_flops_per_token_head(D: int, block: int, dv: int, passes: int, sweeps: int) -> float:
+    """FLOPs the fp32 kernel issues with dv value columns a workgroup: per pass, causal 16-token score tiles
+    ((B/16+1)/2 of B/16 a strip, recomputed per value-column slice), the same share of P C and 4 D^2 of state
+    products; and 2 D^2 in each state-only sweep of chains cut into segments."""
     causal = (f32_block(block) / 16 + 1) / 2 * 16
-    return passes * (2 * causal * D * (D // dv) + 2 * causal * D + (4 if segs == 1 else 6) * D * D)
+    return passes * (2 * causal * D * (D // dv) + 2 * causal * D + 4 * D * D) + sweeps * 2 * D * D
 
 
 def algorithmic_bytes_per_token_head(D: int, esize: int):
@@ -263,7 +262,8 @@ def main() -> int:
     tokens_per_s = tokens / (ms_per_step * 1e-3)
     plan_f = ltn.ltn_attn_query_plan(w.Bt, w.H, w.N, w.D, w.dtype, 0)
     plan_b = ltn.ltn_attn_query_plan(w.Bt, w.H, w.N, w.D, w.dtype, 1)
-    fl = flops_per_token_head(w.D, block, plan_f, plan_b)
+    sweeps_b = ltn.ltn_attn_query_sweeps(w.Bt, w.H, w.N, w.D, w.dtype)
+    fl = flops_per_token_head(w.D, block, plan_f, plan_b, sweeps_b)
     ab = algorithmic_bytes_per_token_head(w.D, esize)
     tflops = {n: f * token_heads / (ms_per_step * 1e-3) / 1e12 for n, f in fl.items()}
 
@@ -273,7 +273,7 @@ def main() -> int:
     achieved = bwd_bytes / (bwd_ms * 1e-3) / 1e9
     if w.dtype == torch.float32:
         # fp32 tensors: the matrix cores' fp32 rate bounds the launch, not memory
-        bwd_flops = f32_issued_flops_per_token_head(w.D, block, plan_b, 3) * token_heads
+        bwd_flops = f32_issued_flops_per_token_head(w.D, block, plan_b[0], 3, sweeps_b) * token_heads
         ach_t = bwd_flops / (bwd_ms * 1e-3) / 1e12
         roofline = {
             "bound": "mfma", "kernel": bwd_kernel + " (the backward launch: dV, dK and dQ passes of every chain)",
@@ -500,12 +500,13 @@ def extended_report(ltn, synth, torch, dev, sections=""):
             B_ = blk or ltn.ltn_attn_pick_block(Dh, torch.float32)
             pf = ltn.ltn_attn_query_plan(Bt, H, N, Dh, torch.float32, 0)
             pb_ = ltn.ltn_attn_query_plan(Bt, H, N, Dh, torch.float32, 1)
+            sw = ltn.ltn_attn_query_sweeps(Bt, H, N, Dh, torch.float32)
             print(json.dumps({"workload": name, "Bt": Bt, "H": H, "N": N, "D": Dh, "block": B_, "dv_fwd": pf[0], "segs_fwd": pf[1], "dv_bwd": pb_[0], "segs_bwd": pb_[1],
                               "fwd_ms": round(f, 4), "bwd_ms": round(b, 4), "fwd_min_ms": round(fmin, 4), "bwd_min_ms": round(bmin, 4),
                               "fwd_GBs": round(4 * Dh * 4 * th / (f * 1e-3) / 1e9, 1),
                               "bwd_GBs": round(7 * Dh * 4 * th / (b * 1e-3) / 1e9, 1),
-                              "fwd_issued_TFLOPs": round(f32_issued_flops_per_token_head(Dh, B_, pf, 1) * th / (f * 1e-3) / 1e12, 1),
-                              "bwd_issued_TFLOPs": round(f32_issued_flops_per_token_head(Dh, B_, pb_, 3) * th / (b * 1e-3) / 1e12, 1),
+                              "fwd_issued_TFLOPs": round(f32_issued_flops_per_token_head(Dh, B_, pf[0], 1, int(pf[1] > 1)) * th / (f * 1e-3) / 1e12, 1),
+                              "bwd_issued_TFLOPs": round(f32_issued_flops_per_token_head(Dh, B_, pb_[0], 3, sw) * th / (b * 1e-3) / 1e12, 1),
                               "fp32_mfma_peak_TFLOPs": 157.3}), file=sys.stderr, flush=True)
             del q, k, v, g, o, gr
 

@@ -51,7 +51,18 @@ def test_traffic_record_of_launches_with_chains_in_two_parts(tmp_path, monkeypat
 
 def test_fp32_flops_are_those_of_the_tiles_and_launches_that_run():
     # a block of 64 tokens is two tiles of 32: 24 keys a token on average, whatever the block
-    whole = bench.f32_issued_flops_per_token_head(64, 64, (64, 1), 1)
-    assert whole == bench.f32_issued_flops_per_token_head(64, 32, (64, 1), 1) == 2 * 24 * 64 * 2 + 4 * 64 * 64
-    # chains cut into segments: one state update more
-    assert bench.f32_issued_flops_per_token_head(64, 64, (64, 4), 1) == whole + 2 * 64 * 64
+    whole = bench.f32_issued_flops_per_token_head(64, 64, 64, 1, 0)
+    assert whole == bench.f32_issued_flops_per_token_head(64, 32, 64, 1, 0) == 2 * 24 * 64 * 2 + 4 * 64 * 64
+    # chains cut into segments: one state update more for each sweep, of which a backward has two or three
+    assert bench.f32_issued_flops_per_token_head(64, 64, 64, 1, 1) == whole + 2 * 64 * 64
+    assert bench.f32_issued_flops_per_token_head(64, 64, 64, 3, 2) == 3 * whole + 2 * 2 * 64 * 64
+
+
+def test_sweeps_of_a_segmented_backward_count_as_often_as_they_run():
+    def exec_(*plans):
+        return bench.flops_per_token_head(256, 64, *plans)["F_exec"]
+
+    whole = exec_((64, 1), (64, 1))
+    assert exec_((64, 4), (64, 1)) == whole + 2 * 256 * 256
+    assert exec_((64, 1), (64, 4), 2) == whole + 2 * 2 * 256 * 256
+    assert exec_((64, 4), (64, 4), 3) == whole + 4 * 2 * 256 * 256
