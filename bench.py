@@ -63,14 +63,19 @@ def algorithmic_bytes_per_token_head(D: int, esize: int):
     return {"fwd": 4 * D * esize, "bwd": 7 * D * esize}
 
 
+# What the timed calls launch, what that includes, and where it is chosen
+TIMED_SOURCES = ("ltn_pass_bf16.hip", "ltn_pass_f32.hip", "ltn_scan.hip", "ltn_bf16_tiles.h", "ltn_cache.h", "ltn_kernels.h",
+                 "ltn_api.hip")
+
+
 def kernel_source_hash() -> str:
-    """Fingerprint of the sources of the timed kernels: a stored traffic measurement is only
-    quoted while it matches."""
+    """Fingerprint of the timed kernels, their sources and the compiler's flags: a stored traffic measurement
+    is only quoted while it matches."""
     import hashlib
-    h = hashlib.sha256()
-    csrc = os.path.join(ROOT, "paper_2307_14995_amd", "csrc")
-    for name in ("ltn_pass_bf16.hip", "ltn_pass_f32.hip", "ltn_bf16_tiles.h", "ltn_kernels.h", "ltn_api.hip"):
-        with open(os.path.join(csrc, name), "rb") as f:
+    from paper_2307_14995_amd.build import CSRC, HIPCC_FLAGS
+    h = hashlib.sha256(" ".join(HIPCC_FLAGS).encode())
+    for name in TIMED_SOURCES:
+        with open(os.path.join(CSRC, name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()[:16]
 

@@ -1,8 +1,11 @@
 """Host-side arithmetic of bench.py's report (CPU only): traffic records keep the kernel variants of one
 workload apart, and fp32 FLOP counts are those of the tiles and launches that run."""
 import json
+import os
+import re
 
 import bench
+from paper_2307_14995_amd import build
 
 NAME = "void ltn::(anonymous namespace)::pass_f32_kernel<{}>(ltn::PassBatch, int, int)"
 
@@ -66,3 +69,14 @@ def test_sweeps_of_a_segmented_backward_count_as_often_as_they_run():
     assert exec_((64, 4), (64, 1)) == whole + 2 * 256 * 256
     assert exec_((64, 1), (64, 4), 2) == whole + 2 * 2 * 256 * 256
     assert exec_((64, 4), (64, 4), 3) == whole + 4 * 2 * 256 * 256
+
+
+def test_a_traffic_record_goes_stale_with_every_source_it_depends_on(monkeypatch):
+    included = {name for src in bench.TIMED_SOURCES for name in
+                re.findall(r'#include "(\S+)"', open(os.path.join(build.CSRC, src)).read())} - {"ltn_attn.h"}
+    assert included <= set(bench.TIMED_SOURCES)
+    for src in ("ltn_scan.hip", "ltn_cache.h"):
+        assert src in bench.TIMED_SOURCES
+    before = bench.kernel_source_hash()
+    monkeypatch.setattr(build, "HIPCC_FLAGS", build.HIPCC_FLAGS + ["-O2"])
+    assert bench.kernel_source_hash() != before
