@@ -61,8 +61,8 @@ SAN_FLAGS = ["-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize=und
              "-Xarch_host", "-fno-omit-frame-pointer", "-Xarch_host", "-fno-sanitize-recover=undefined"]
 
 
-def _obj_of(src: str, objdir: str = OBJ) -> str:
-    return os.path.join(objdir, os.path.basename(src) + ".o")
+def _obj_of(src: str, objdir=None) -> str:
+    return os.path.join(objdir or OBJ, os.path.basename(src) + ".o")
 
 
 def _stale(target: str, deps) -> bool:
@@ -70,6 +70,19 @@ def _stale(target: str, deps) -> bool:
         return True
     t = os.path.getmtime(target)
     return any(os.path.getmtime(d) > t for d in deps)
+
+
+def _flags_of(extra=()) -> str:
+    return " ".join(HIPCC_FLAGS + list(extra))
+
+
+def _obj_stale(src: str, objdir=None, extra=()) -> bool:
+    """Older than its source or a header, or compiled with other flags."""
+    obj = _obj_of(src, objdir)
+    if _stale(obj, [src] + _headers()) or not os.path.exists(obj + ".flags"):
+        return True
+    with open(obj + ".flags") as f:
+        return f.read() != _flags_of(extra)
 
 
 def marshalling_id() -> str:
@@ -88,7 +101,7 @@ def marshalling_is_stale() -> bool:
 
 
 def is_stale() -> bool:
-    return _stale(LIB, sources() + _headers()) or marshalling_is_stale()
+    return _stale(LIB, sources() + _headers()) or any(_obj_stale(s) for s in sources()) or marshalling_is_stale()
 
 
 def check_resource_report(report: str) -> None:
@@ -107,8 +120,10 @@ def check_resource_report(report: str) -> None:
         raise RuntimeError("kernels with register-resident asynchronous loads must not spill:\n  " + "\n  ".join(bad))
 
 
-def _compile(src: str, hipcc: str, verbose: bool, objdir: str = OBJ, extra=()) -> str:
+def _compile(src: str, hipcc: str, verbose: bool, objdir=None, extra=()) -> str:
     obj = _obj_of(src, objdir)
+    if os.path.exists(obj + ".flags"):                 # (a compilation that fails leaves no record for the old object)
+        os.remove(obj + ".flags")
     cmd = [hipcc] + HIPCC_FLAGS + list(extra) + ["-I", os.path.join(ROOT, "include"), "-c", src, "-o", obj]
     if verbose:
         print(" ".join(cmd), flush=True)
@@ -116,6 +131,8 @@ def _compile(src: str, hipcc: str, verbose: bool, objdir: str = OBJ, extra=()) -
     if res.returncode != 0:
         raise RuntimeError(f"hipcc failed on {src}:\n" + res.stdout + res.stderr)
     check_resource_report(res.stderr)
+    with open(obj + ".flags", "w") as f:
+        f.write(_flags_of(extra))
     with open(obj + ".resources.txt", "w") as f:       # kept beside the object for inspection
         f.write("\n".join(l for l in res.stderr.splitlines() if "remark:" in l and "Function Name" in l or
                           re.search(r"remark:\s+(VGPRs|AGPRs|ScratchSize|Occupancy|VGPRs Spill|SGPRs Spill|LDS Size)", l)))
@@ -151,12 +168,12 @@ def build_marshalling(verbose: bool = False) -> str:
 
 def build_library(force: bool = True, verbose: bool = False, marshalling: bool = True) -> str:
     """Compile every HIP source for gfx950 (all of them when `force`, otherwise only those
-    older than a source or header), link the shared library, and build the marshalling beside it
+    older than a source or header or compiled with other flags), link the shared library, and build the marshalling beside it
     (a failure there is raised once the library is complete)."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     os.makedirs(OBJ, exist_ok=True)
     srcs = sources()
-    todo = [s for s in srcs if force or _stale(_obj_of(s), [s] + _headers())]
+    todo = [s for s in srcs if force or _obj_stale(s)]
     jobs = int(os.environ.get("MAX_JOBS", "8") or 8)
     with ThreadPoolExecutor(max_workers=max(1, min(jobs, 16))) as pool:
         beside = pool.submit(build_marshalling, verbose) if marshalling and (force or marshalling_is_stale()) else None
@@ -191,7 +208,7 @@ def build_sanitized(verbose: bool = False) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     os.makedirs(SAN_OBJ, exist_ok=True)
     srcs = sources()
-    todo = [s for s in srcs if _stale(_obj_of(s, SAN_OBJ), [s] + _headers())]
+    todo = [s for s in srcs if _obj_stale(s, SAN_OBJ, SAN_FLAGS)]
     jobs = int(os.environ.get("MAX_JOBS", "8") or 8)
     with ThreadPoolExecutor(max_workers=max(1, min(jobs, 16))) as pool:
         list(pool.map(lambda s: _compile(s, hipcc, verbose, SAN_OBJ, SAN_FLAGS), todo))
