@@ -508,8 +508,9 @@ Cut pick_cut(int chains, int count, long long N, int D, int DC, int dv, int wide
 //     34.0 and 36.6, 128 x 1000 65.4 and 69.2), and so do 64-column slices (32 x 16301 322 and 334).
 //     With the gradients read next (forward, backward, copies of dQ, dK, dV): 128 features 128 x 2048 269 and 262, 128 x 8192
 //     1017 and 975, 200 x 3000 589 and 576; 96 features 544 x 928 411 and 393; 64 features 320 x 2048 334 and 320, 600 x 2048
-//     (600 MiB) 627 and 621, but from 650 MiB on most lose (512 x 2600 666 and 671, 640 x 2200 699 and 709, 640 x 3000 948
-//     and 966, 1024 x 2048 1011 and 1025; 250 x 8192 982 and 971).  96 features in segments: nothing (16 x 24000 440 and 440)
+//     (600 MiB) 627 and 621, but from 650 MiB on most with 128 chains or more lose (512 x 2600 666 and 671, 640 x 2200 699 and 709,
+//     640 x 3000 948 and 966, 1024 x 2048 1011 and 1025, 2500 x 1024 1146 and 1179; 250 x 8192 982 and 971), not with
+//     fewer (102 x 25568 1385 and 1372, 64 x 25000 925 and 915).  96 features in segments: nothing (16 x 24000 440 and 440)
 //   forward in segments, all once in the pass after the sweep and outputs past the caches, so that K and V of the sweep
 //     stay: 32 x 16301 and its backward 501 and 475; alone 176 and 140, 8 x 65536 179 and 154.  With a gate that reads O, and
 //     the backward: 16 x 16384 (256 MiB) 297 and 307, 16 x 20000 359 and 367, 32 x 12000 (375) 407 and 404, 32 x 13000
@@ -531,7 +532,7 @@ void set_hints(ltn::PassBatch& pb, int D, int DC, int dv, bool segmented) {
     if (D == 256 || D != DC || dv != D) return;
     if (pb.count == 3) {
         const long long bytes = 8LL * D * tokens;
-        const bool pays = D == 64 ? bytes >= 288 * kMiB && (segmented || bytes < 640 * kMiB) : bytes >= 240 * kMiB && !(segmented && D == 96);
+        const bool pays = D == 64 ? bytes >= 288 * kMiB && (segmented || pb.chains < 128 || bytes < 640 * kMiB) : bytes >= 240 * kMiB && !(segmented && D == 96);
         if (pays) pb.hints = ltn::kOnceA | ltn::kPast;
     } else if (pb.p[0].gate) {
         const bool fills = D != 96 || (!segmented && pb.chains >= 192);
