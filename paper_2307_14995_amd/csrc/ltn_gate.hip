@@ -11,15 +11,20 @@
 // neighbours in one wave and reduce with cross-lane shuffles (rows of 96 features take 16 or 32
 // lanes of which 12 or 24 hold data); fp32 arithmetic.
 // ONCE, from kOnceBytes a tensor on: loads that leave the caches first, and a derivative's du stored so, which a projection's
-// gradient reads later.  y and dx are stored plainly: the output projection and the attention's backward read them
-// next.  us, rotating inputs, no hints / loads / loads and du / everything.  Derivative, attention backward, copies of
-// dq, dk, dv, du: 32 chains x 2048 x 128 (16 MiB a tensor) 117.5 / 117.5 / 118.5 / 118.9, 48 x 2048 145.6 / 145.6 /
-// 144.4 / 144.4, 64 x 2048 177.5 / 175.1 / 171.5 / 173.4, 128 x 2048 332 / 332 / 327 / 338, 128 x 8192 1291 / 1294 / 1268
-// / 1275; the copy of du before the attention 96 x 2048 186.8 / 177.0 / 174.0 / 187.0, 128 x 2048 222.7 / 217.5 / 217.7 /
-// 225.7; no copies 128 x 2048 184.0 / 182.5 / 180.1 / 188.3.  Attention forward, gate, copy of y (none / loads / with y):
-// 48 x 2048 64.8 / 63.8 / 64.7, 128 x 2048 121.1 / 122.4 / 121.0, 128 x 4096 247 / 235 / 240, fp32 64 x 2048 184.5 / 186.5 /
-// 187.8.  The kernels alone, 2^18 rows of 128, outputs in other memory each time (in one place): forward 38.5 and 34.3 (34.0 and
-// 34.5), derivative 64.3 and 54.6 (62.8 and 54.7).
+// gradient reads later.  dx is stored plainly, for the attention's backward, which reads it next, and so is y, for the
+// output projection, up to kOnceYBytes.  us, rotating inputs.
+//   no hints / loads / loads and du / everything.  Derivative, attention backward, copies of
+//     dq, dk, dv, du: 32 chains x 2048 x 128 (16 MiB a tensor) 117.5 / 117.5 / 118.5 / 118.9, 48 x 2048 145.6 / 145.6 /
+//     144.4 / 144.4, 64 x 2048 177.5 / 175.1 / 171.5 / 173.4, 128 x 2048 332 / 332 / 327 / 338, 128 x 8192 1291 / 1294 / 1268
+//     / 1275; the copy of du before the attention 96 x 2048 186.8 / 177.0 / 174.0 / 187.0, 128 x 2048 222.7 / 217.5 / 217.7 /
+//     225.7; no copies 128 x 2048 184.0 / 182.5 / 180.1 / 188.3
+//   y plain / once.  Mixer step with copies of what it returns: 96 x 2048 (48 MiB) 329.9 / 331.2, 128 x 2048 (64) 396 / 398 and
+//     400.7 / 401.6, 160 x 2048 492 / 493, 180 x 2500 (110) 709 / 705, 128 x 4096 790 / 778, 96 x 4096 x 256 (192) 1558 / 1545,
+//     102 x 25568 x 64 2163 / 2151; without them 128 x 2048 261 / 253, 128 x 4096 522 / 504, 102 x 25568 x 64 1557 / 1510.
+//     Forward and copy of y: 64 x 3000 (47) 92.8 / 94.4, 96 x 1500 (35) 64.6 / 67.0, 128 x 2048 107.7 / 109.3 (no hints
+//     109.4), 160 x 2048 139 / 142 (144), 64 x 8192 253.5 / 253.6 (266), 128 x 8192 457 / 449 (463)
+//   The kernels alone, 2^18 rows of 128, no hints and so, outputs in other memory each time (in one place): forward 38.5 and 34.3
+//     (34.0 and 34.5), derivative 64.3 and 54.6 (62.8 and 54.7)
 #include "ltn_cache.h"
 #include "ltn_kernels.h"
 
@@ -29,7 +34,7 @@ namespace {
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(8 * sizeof(float)))) float f32x8;
 
-constexpr long long kOnceBytes = 24 << 20;
+constexpr long long kOnceBytes = 24 << 20, kOnceYBytes = 64 << 20;
 
 template <bool ONCE> __device__ __forceinline__ u32x4 load16(const void* p) {
     if constexpr (ONCE) return load16_once(p);
@@ -89,7 +94,7 @@ __device__ __forceinline__ float row_sum(float x) {   // sum over the LPR neighb
 
 constexpr int kThreads = 256;
 
-template <int D, bool BF16, bool BWD, bool ONCE>
+template <int D, bool BF16, bool BWD, bool ONCE, bool ONCE_Y>
 __global__ __launch_bounds__(kThreads)
 void gate_kernel(const char* x, const char* __restrict__ u, const char* __restrict__ dy,
                  char* o0, char* __restrict__ o1, float eps, long long rows) {
@@ -122,7 +127,7 @@ void gate_kernel(const char* x, const char* __restrict__ u, const char* __restri
             V yv;
 #pragma unroll
             for (int i = 0; i < V::N; ++i) yv.v[i] = xv.v[i] * rstd * uv.v[i];
-            if (live) yv.template store<false>(o0 + off);
+            if (live) yv.template store<ONCE_Y>(o0 + off);
         } else {
             V gv;
             gv.template load<ONCE>(dy + off);
@@ -160,8 +165,10 @@ hipError_t launch_gate_t(const void* x, const void* u, const void* dy, void* o0,
         hipLaunchKernelGGL(kernel, dim3((unsigned)wgs), dim3(kThreads), 0, stream,
                            (const char*)x, (const char*)u, (const char*)dy, (char*)o0, (char*)o1, eps, rows);
     };
-    if (rows * ACT * 16 >= kOnceBytes) launch(gate_kernel<D, BF16, BWD, true>);
-    else launch(gate_kernel<D, BF16, BWD, false>);
+    const long long bytes = rows * ACT * 16;
+    if (!BWD && bytes >= kOnceYBytes) launch(gate_kernel<D, BF16, BWD, true, !BWD>);
+    else if (bytes >= kOnceBytes) launch(gate_kernel<D, BF16, BWD, true, false>);
+    else launch(gate_kernel<D, BF16, BWD, false, false>);
     return hipGetLastError();
 }
 
