@@ -36,31 +36,31 @@ __device__ __forceinline__ unsigned short f32_to_bf16_bits(float f) {   // round
 
 // A state is read once and written once, and the next call that wants it comes after every other layer's.  Loads and
 // stores that leave the caches first, or are written through, keep the lines from being written back
-// in the middle of the reads.  us a call, plain / once / read once and written through; states of many layers (1.1 GiB in
-// turn), of few (176 MiB in turn, all of them in the memory-side cache), and one repeated:
-//     128 x 128    512 chains (32 MiB)   15.7 / 11.2 / 11.4     11.1 / 10.8 / 10.5      8.3 /  8.2 / 10.6
-//                  768                   23.6 / 17.2 / 17.7     14.9 / 16.5 / 14.8     13.1 / 12.5 / 14.8
-//                 1024 (64)              29.7 / 22.4 / 23.7     19.5 / 21.8 / 19.6     19.5 / 19.0 / 19.5
-//                 1280 (80)              37.4 / 31.0 / 32.1     24.5 / 30.0 / 27.1     24.5 / 28.0 / 27.1
-//                 1536                   44.6 / 37.8 / 40.0     30.3 / 36.8 / 32.7     30.3 / 35.5 / 32.7
+// in the middle of the reads.  us a call, plain / once / read once and written through; states of many layers (1.2 GiB in
+// turn), of three, and one repeated (in the memory-side cache, below 85 MiB a state):
+//     128 x 128    512 chains (32 MiB)   15.8 / 11.2 / 11.4     11.2 / 10.3 / 10.6      8.4 /  8.3 / 10.5
+//                  640 (40)              21.0 / 14.3 / 15.3     12.6 / 13.2 / 12.5     11.1 / 10.9 / 12.5
+//                  768 (48)              23.5 / 17.3 / 17.7     14.8 / 15.9 / 14.8     12.9 / 12.5 / 14.8
+//                  896 (56)              26.7 / 21.0 / 22.0     16.8 / 20.2 / 17.3     16.8 / 18.1 / 17.2
+//                 1024 (64)              29.4 / 22.3 / 23.6     19.6 / 21.7 / 19.6     19.6 / 18.8 / 19.5
+//                 1280 (80)              37.1 / 30.9 / 31.9     24.6 / 30.4 / 25.3     24.5 / 27.8 / 25.3
 //                 2048 (128)             56.9 / 50.2 / 50.9                            39.8 / 47.8 / 41.3
-//     64 x 64     1024 (16)               8.5 /  6.0 /  6.3      6.8 /  5.9 /  5.7      5.3 /  5.2 /  5.7
-//                 1536 (24)              12.2 /  9.3 /  9.8      8.7 /  8.9 /  8.2      6.4 /  6.0 /  8.2
-//                 2048 (32)              15.1 / 12.3 / 12.4     10.7 / 11.8 / 10.2      8.2 /  9.1 / 10.2
-//     96 x 96     1140 (40)              20.0 / 16.3 / 17.5     12.4 / 15.7 / 14.1     11.7 / 13.1 / 14.0
-//                 1424 (50)              24.1 / 20.1 / 20.9     16.1 / 19.3 / 16.7     16.0 / 17.2 / 16.6
+//     64 x 64     1200 (19)               9.3 /  6.7 /  7.1      7.2 /  6.2 /  6.5      5.6 /  5.4 /  6.5
+//                 1536 (24)              12.1 /  9.3 /  9.8      8.7 /  8.3 /  8.4      6.4 /  6.0 /  8.4
+//                 2048 (32), six sets    15.1 / 12.3 / 12.4     10.7 / 11.8 / 10.2      8.2 /  9.1 / 10.2
+//     96 x 96     1000 (35)              17.7 / 12.8 / 13.2     11.5 / 11.7 / 11.2     10.1 /  9.8 / 11.1
+//                 1140 (40)              19.9 / 16.3 / 17.4     12.4 / 15.4 / 13.4     11.8 / 13.0 / 13.3
 //                 2000 (70)              32.5 / 27.3 / 29.0     22.3 / 26.3 / 23.2     22.3 / 24.8 / 23.2
-//     128 x 64    1280 (40)              20.0 / 14.2 / 15.1     13.1 / 13.3 / 12.9     12.7 / 10.9 / 12.9
-//                 1600 (50)              24.8 / 19.6 / 20.5     15.7 / 19.0 / 16.4     15.7 / 16.3 / 16.4
-//     256 x 128    192 (24)              11.9 /  9.2 /  9.3      9.2 /  8.8 /  8.8      7.6 /  7.7 /  8.8
-//                  256 (32)              16.6 / 12.8 / 13.6     10.7 / 12.4 / 11.0      8.2 /  8.6 / 10.9
+//     128 x 64    1280 (40)              19.5 / 14.1 / 14.9     13.1 / 13.0 / 12.5     12.8 / 10.8 / 12.5
+//                 1600 (50), four sets   24.8 / 19.6 / 20.5     15.7 / 19.0 / 16.4     15.7 / 16.3 / 16.4
+//     256 x 128    192 (24), seven sets  11.9 /  9.2 /  9.3      9.2 /  8.8 /  8.8      7.6 /  7.7 /  8.8
+//                  256 (32), six sets    16.6 / 12.8 / 13.6     10.7 / 12.4 / 11.0      8.2 /  8.6 / 10.9
 //                  512 (64)              29.2 / 25.0 / 26.9     20.8 / 24.4 / 20.8     20.8 / 23.3 / 20.8
-//     256 x 256     96 (24)              12.2 /  9.2 /  9.5      9.4 /  8.9 /  8.8      6.8 /  6.6 /  8.8
-//                  128 (32)              17.6 / 13.5 / 14.4     11.1 / 13.1 / 11.2      8.7 / 10.0 / 11.0
-// Many layers are what a model has and few what a small one has; writing through costs the many up to 8 % and spares the few up
-// to 15 from the line of each width on (through_bytes; 128 x 128 later: below it the many lose 6 %, and the few are within 12 %
-// of plain).  Plain ones are ahead where all states of a program fit the cache (the few and the repeated), by up to 14 %
-// and 30, and cost the many 10 to 30 %.
+//     256 x 256     96 (24)              12.1 /  9.2 /  9.5      9.4 /  8.4 /  8.6      6.8 /  6.5 /  8.6
+//                  160 (40)              21.1 / 16.6 / 17.7     13.3 / 15.9 / 13.3     13.2 / 14.3 / 13.1
+// A model's many layers gain a fifth to a third either way.  Past the line (through_bytes) a program of few layers would lose up
+// to a fifth without writing through, which costs the many up to 8 %; with it the few are within 4 % of plain (96 x 96
+// 8), and a single layer's state, repeated, loses up to a third at the line and nothing from 64 MiB on.
 union Bits { u32x4 u; float4 f; };
 __device__ __forceinline__ float4 load_state(const float4* p) {
     Bits b;
@@ -74,8 +74,8 @@ __device__ __forceinline__ void store_state(float4* p, float4 v) {      // (by r
     if constexpr (THROUGH) store16_through(p, b.u);
     else store16_once(p, b.u);
 }
-constexpr long long through_bytes(int DK, int DV) { return (DK == 256 || DK == 64 ? 24LL : DV == 128 ? 72 : 40) << 20; }
-bool write_through(int chains, int DK, int DV) { return (long long)chains * DK * DV * 4 >= through_bytes(DK, DV); }
+constexpr long long through_bytes(int DK) { return (DK == 256 || DK == 64 ? 24LL : 40) << 20; }
+bool write_through(int chains, int DK, int DV) { return (long long)chains * DK * DV * 4 >= through_bytes(DK); }
 
 // Order of an output's sum, the same in both kernels below, so that a sequence's output does not depend on
 // how many others are in the call: rows in DK / 8 classes (row mod DK / 8) of eight, each summed in the
@@ -272,7 +272,7 @@ template <int DK, int DV, bool BF16, bool THROUGH>
 hipError_t launch_t(const void* q, const void* k, const void* v, void* o, float* kv, const float* decay, int chains, int H,
                     int steps, hipStream_t stream) {
     constexpr int PER = DV / kSliceCols, MOST = split_limit(DK, DV) / PER;      // slices of a chain, chains that are split
-    if constexpr (MOST > 0 && (!THROUGH || 4LL * MOST * DK * DV >= through_bytes(DK, DV))) {
+    if constexpr (MOST > 0 && (!THROUGH || 4LL * MOST * DK * DV >= through_bytes(DK))) {
         if (chains <= MOST) {
             hipLaunchKernelGGL((decode_slice_kernel<DK, DV, BF16, THROUGH>), dim3((unsigned)(chains * PER)), dim3(DK), 0, stream,
                                q, k, v, o, kv, decay, H, steps);

@@ -70,9 +70,9 @@ def test_backward_in_segments(D, H, N):
     assert all(torch.equal(a, b) for a, b in zip(got, want))
 
 
-# states of just the size that is written through, and the halves, which are not
+# states of the size that is written through, and the halves, which are not
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
-@pytest.mark.parametrize("Dk,Dv,chains,steps", [(128, 128, 1152, 1), (128, 128, 1152, 3), (256, 256, 96, 2), (64, 64, 1536, 1),
+@pytest.mark.parametrize("Dk,Dv,chains,steps", [(128, 128, 640, 1), (128, 128, 1152, 1), (128, 128, 1152, 3), (256, 256, 96, 2), (64, 64, 1536, 1),
                                                 (96, 96, 1140, 2), (128, 64, 1280, 1), (256, 128, 192, 1)])
 def test_decode(Dk, Dv, chains, steps, dtype):
     g = torch.Generator(device="cuda").manual_seed(chains)
