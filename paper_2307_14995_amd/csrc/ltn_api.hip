@@ -510,7 +510,9 @@ Cut pick_cut(int chains, int count, long long N, int D, int DC, int dv, int wide
 //     1017 and 975, 200 x 3000 589 and 576; 96 features 544 x 928 411 and 393; 64 features 320 x 2048 334 and 320, 600 x 2048
 //     (600 MiB) 627 and 621, but from 650 MiB on most with 128 chains or more lose (512 x 2600 666 and 671, 640 x 2200 699 and 709,
 //     640 x 3000 948 and 966, 1024 x 2048 1011 and 1025, 2500 x 1024 1146 and 1179; 250 x 8192 982 and 971), not with
-//     fewer (102 x 25568 1385 and 1372, 64 x 25000 925 and 915).  96 features in segments: nothing (16 x 24000 440 and 440)
+//     fewer (102 x 25568 1385 and 1372, 64 x 25000 925 and 915).  Just past the lines, where the last round of workgroups
+//     is partly filled, up to 2 % are lost (100 x 2476 269 and 273, 260 x 1500 x 96 332 and 338; beside them 128 x 2000 254 and 249,
+//     200 x 1300 265 and 258, 256 x 1000 252 and 247).  96 features in segments: nothing (16 x 24000 440 and 440)
 //   forward in segments, all once in the pass after the sweep and outputs past the caches, so that K and V of the sweep
 //     stay: 32 x 16301 and its backward 501 and 475; alone 176 and 140, 8 x 65536 179 and 154.  With a gate that reads O, and
 //     the backward: 16 x 16384 (256 MiB) 297 and 307, 16 x 20000 359 and 367, 32 x 12000 (375) 407 and 404, 32 x 13000

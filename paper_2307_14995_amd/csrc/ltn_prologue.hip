@@ -30,8 +30,12 @@ namespace {
 constexpr int kThreads = 256;
 // From so many bytes of x on, loads leave the caches first and outputs are stored past them.  us, rotating inputs, plain and
 // so: expansion of 64 chains x 2048 x 128 24.9 and 22.9, derivative 30.5 and 28.4; of 32 x 30000 148 and 145, 211 and
-// 198.  The first layer's step, whose attention reads the expansions, 64 chains x 2048 (with the batch entries below)
-// 310 and 295; tensors that stay in the caches in between lose (16 x 1000 114 and 128).
+// 198.  Tensors that stay in the caches in between lose (the first layer's step of 16 x 1000 114 and 128).  The whole step with copies
+// of what it returns, the expansions plain and so: 4 x 16 x 2048 x 128 (32 MiB of x) 343 and 338, 6 x 8 x 2048 (24) 322 and 316, 1 x 16 x
+// 4096 (16) 245 and 245, 8 x 16 x 2048 (64) 566 and 567, 4 x 32 x 4096 1164 and 1155; fp32 4 x 8 x 1024 (16) 415 and 400.
+// The derivatives (dx stored plainly): 2 x 16 x 2048 x 128 221 and 220 (218), 4 x 16 x 2048 349 and 338 (338), 8 x 16 x 2048 583 and 569
+// (576), 1 x 32 x 30000 2629 and 2606 (2630), 4 x 16 x 2048 x 64 185 and 184 (183); fp32 4 x 8 x 2048 x 128 646 and 620 (629).
+// Inference, two expansions and the forward: 6 x 8 x 2048 x 128 111 and 106, 4 x 16 x 2048 111 and 110, but 3 x 16 x 2048 100 and 103.
 constexpr long long kOnceBytes = 16 << 20;
 constexpr int kTok = 64;                 // tokens per workgroup
 
